@@ -99,8 +99,8 @@ int32_t ts_workspace_bytes(const ts_problem* p, int32_t k, size_t* bytes);
 
 /* Clears a fresh workspace (launches a fill kernel on `stream`; safe under graph capture).  Must
  * run once before the first use of a workspace; the kernels leave it ready for the next call.
- * The radix-select histograms inside it must be zero when a selection starts and are zeroed again by the last
- * kernel of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
+ * The radix-select histograms inside it must be zero when a selection starts and are zeroed again by the
+ * kernels of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
  * an error after it has launched part of its kernels, or a stream is torn down between its launches, the
  * workspace is in an undefined state: call ts_workspace_init again before reusing it.  The call zeroes every
  * byte, so the next selection must start with its score pass (which it does anyway). */
@@ -193,7 +193,7 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
  *                      the k largest of those votes are returned exactly as ts_topk returns them (ties to the
  *                      lower token index, ascending token ids, unused slots -1); sel_votes [device] float [B][k],
  *                      if not NULL, receives the vote of idx[b][j] at [b][j] (0 in unused slots).  Must follow
- *                      ts_soft_vote_bounds with the same problem, workspace, q and score_scale.  Two launches.
+ *                      ts_soft_vote_bounds with the same problem, workspace, q and score_scale.  Three launches.
  * codes [device] uint8 [B][max_seq_len][H]; vote_hi, vote_lo [device] float [B][max_seq_len] (vote_lo may be NULL:
  * ts_topk_exact needs the upper bounds only, the lower ones live on in the workspace as a histogram); the other arguments
  * as for the three calls they stand in for.  Sequences with skip[b] != 0 are left untouched.  The cost of

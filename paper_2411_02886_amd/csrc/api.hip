@@ -404,7 +404,8 @@ int32_t ts_topk_exact(const ts_problem* p, const void* q, const float* vote_hi, 
   a.t.head = p->num_initial; a.t.tail = p->num_local;
   a.t.votes = vote_hi; a.t.seq_lens = p->seq_lens; a.t.skip = skip; a.t.idx = idx; a.t.count = count;
   a.t.hist = (uint32_t*)((uint8_t*)ws + w.topk_hist);
-  a.t.bound_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
+  a.t.rep_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
+  a.t.dense = (uint2*)((uint8_t*)ws + w.topk_dense);
   a.t.sel_votes = sel_votes;
   a.t.state = (uint32_t*)((uint8_t*)ws + w.topk_state);
   a.t.blk = (uint32_t*)((uint8_t*)ws + w.topk_blk);
@@ -413,15 +414,15 @@ int32_t ts_topk_exact(const ts_problem* p, const void* q, const float* vote_hi, 
   a.q = (const uint8_t*)q; a.k_pool = (const uint8_t*)p->k_pool;
   a.page_indptr = p->page_indptr; a.page_indices = p->page_indices; a.row_stats = row_stats;
   a.H = p->num_q_heads; a.H_kv = p->num_kv_heads; a.P = p->page_size; a.p_shift = ilog2(p->page_size);
-  a.HB = p->num_kv_heads < 8 ? p->num_kv_heads : 8; a.hb_shift = ilog2(a.HB); a.NU = p->num_kv_heads / a.HB;
   a.scale = score_scale;
-  // few chunks (131072 tokens: 64): several workgroups per chunk, so that the exact re-evaluation of the candidates
-  // is spread over the machine (131072 tokens: 14.1 -> 9.9 us); many chunks fill it anyway
-  a.parts = 256 / (w.topk_nblk * p->batch);
-  if (a.parts > 4) a.parts = 4;
+  // two workgroups per CU in all (one round: their registers allow no more), four candidates each at least (the list usually holds a little more than k)
+  a.parts = 512 / p->batch;
+  if (a.parts > (k + 3) / 4) a.parts = (k + 3) / 4;
+  if (a.parts > 512) a.parts = 512;
   if (a.parts < 1) a.parts = 1;
   const int G = p->num_q_heads / p->num_kv_heads;
-  if (launch_topk_refine(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
+  if (launch_topk_compact(a.t, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
+  if (launch_topk_eval(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   return launch_topk_final_full(a.t, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 

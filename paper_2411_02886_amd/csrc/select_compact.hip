@@ -5,10 +5,10 @@
 // usual per-workgroup softmax statistics.  After the statistics merge (soft_vote.hip):
 //   vote_bounds_kernel   turns the bytes into an upper and a lower bound of every token's vote (they differ
 //                        by 2^(1/4) plus guards) and histograms the lower bounds;
-//   topk_refine_kernel   takes every token whose upper bound reaches the histogram bin of the k-th largest
-//                        lower bound -- a superset of the top-k, usually 1.05-1.5 k tokens -- recomputes its
-//                        scores from K (exact products, double accumulation) and its vote as Eq. 5 defines
-//                        it, and lists (vote key, token) in token order.
+//   topk_compact_kernel  (topk.hip) lists every token whose upper bound reaches the histogram bin of the k-th
+//                        largest lower bound -- a superset of the top-k, usually 1.05-1.5 k tokens;
+//   topk_eval_kernel     recomputes their scores from K (exact products, double accumulation) and their votes as
+//                        Eq. 5 defines them, and lists (vote key, token) in token order.
 // The finishing workgroup of the radix select (topk.hip) then picks the k largest of those votes.  Why the
 // candidates are a superset: k tokens have votes >= their lower bounds >= the k-th largest lower bound L_k,
 // so the k-th largest vote is >= L_k, and a token of the top-k has upper bound >= its vote >= L_k.
@@ -161,82 +161,17 @@ hipError_t launch_vote_bounds(const BoundArgs& a, int B, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// The refine workgroup has 256 threads, or 1024 when a sequence has few chunks: the candidates of a chunk are few,
-// their evaluation is a chain of dependent loads, so every candidate should get a wave step of its own in the
-// first round; with many chunks small workgroups keep every chunk resident at once.
-// exclusive prefix sum over the threads of the refine workgroup; *total receives the sum
-template <int kRefineWaves>
-__device__ __forceinline__ uint32_t refine_block_scan(uint32_t v, uint32_t* total, uint32_t* lds /* >= kRefineWaves words */) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
-  __syncthreads();
-  if (lane == 63) lds[wave] = incl;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kRefineWaves; ++w) {
-    const uint32_t x = lds[w];
-    if (w < wave) base += x;
-    tot += x;
-  }
-  *total = tot;
-  return base + incl - v;
-}
-
-// bin of the k_rem-th largest key in the replicated 2048-bin histogram (kTopkBins if k_rem == 0); all threads get it
-template <int kRefineWaves>
-__device__ __forceinline__ uint32_t refine_find_bin(const uint32_t* gh, uint32_t k_rem, uint32_t* lds /* >= kRefineWaves + 1 words */) {
-  constexpr int kRefineThreads = kRefineWaves * 64;
-  constexpr int PER = kTopkBins / kRefineThreads;
-  uint32_t c[PER];
-  uint32_t sum = 0;
-  // the thread's PER bins are consecutive in memory (descending bin order = ascending address from `lowest`): vector loads
-  const int lowest = kTopkBins - PER - (int)threadIdx.x * PER;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) c[e] = 0u;
-#pragma unroll
-  for (int r = 0; r < kBoundHistCopies; ++r) {
-    uint32_t v[PER];
-    if (PER % 4 == 0) {
-#pragma unroll
-      for (int q4 = 0; q4 < PER / 4; ++q4) {
-        const uint4 w = *reinterpret_cast<const uint4*>(gh + r * kTopkBins + lowest + q4 * 4);
-        v[q4 * 4] = w.x; v[q4 * 4 + 1] = w.y; v[q4 * 4 + 2] = w.z; v[q4 * 4 + 3] = w.w;
-      }
-    } else {
-#pragma unroll
-      for (int q2 = 0; q2 < PER / 2; ++q2) {
-        const uint2 w = *reinterpret_cast<const uint2*>(gh + r * kTopkBins + lowest + q2 * 2);
-        v[q2 * 2] = w.x; v[q2 * 2 + 1] = w.y;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) c[e] += v[PER - 1 - e];     // c[e] is bin kTopkBins - 1 - (threadIdx.x * PER + e)
-  }
-#pragma unroll
-  for (int e = 0; e < PER; ++e) sum += c[e];
-  uint32_t total;
-  uint32_t above = refine_block_scan<kRefineWaves>(sum, &total, lds);
-  __syncthreads();
-  if (threadIdx.x == 0) lds[kRefineWaves] = kTopkBins;
-  __syncthreads();
-  if (k_rem != 0) {
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if (above < k_rem && k_rem <= above + c[e]) lds[kRefineWaves] = kTopkBins - 1 - (threadIdx.x * PER + e);
-      above += c[e];
-    }
-  }
-  __syncthreads();
-  const uint32_t d = lds[kRefineWaves];
-  __syncthreads();
-  return d;
-}
+// The candidates (listed per 2048-token chunk by topk_compact_kernel over the upper bounds) re-evaluated from K.
+//
+// What bounds it: for a batch the double-precision products (D * H per candidate), for one sequence the chain of
+// dependent loads (chunk counts -> token -> page id -> K row).  Hence the split: the candidates of a sequence are
+// numbered through and every workgroup takes an equal share of them, whatever chunk they come from.  (When the
+// workgroup that had compacted a chunk also evaluated it, a short sequence -- all of its tokens candidates, in one
+// or two chunks -- was one workgroup's serial tail: 32 sequences of 1031 to 16001 tokens, H 32/8, k 2048 took 277 us,
+// compaction and this kernel take 54 us.)
+// Eight or sixteen lanes share a K row, so that a wave can keep the query heads of its KV heads as doubles in registers
+// for its whole life (up to 128 of them) instead of converting them again for every candidate.  The scores of up to CB candidates meet in LDS, where the softmax weights
+// are formed with every lane at work.
 
 // exp(c * d) as ts_soft_vote forms it: argument reduced in double, 2^fraction from the float hardware exponential
 __device__ __forceinline__ float refine_vote_exp(double d, double c2) {
@@ -246,9 +181,6 @@ __device__ __forceinline__ float refine_vote_exp(double d, double c2) {
   return ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
-constexpr int ST_KEFF_WORD = 2;   // state word that carries min(k, ranked tokens) to the finishing workgroup
-
-// sum of a double over the 8 lanes of an aligned lane group (both halves through the DPP network)
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   const long long u = __double_as_longlong(v);
@@ -256,247 +188,245 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-__device__ __forceinline__ double group8_sum_f64(double v) {
-  v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_f64<0x141>(v);   // row_half_mirror
-  return v;
-}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128;
 
-// exact products of one 16-byte piece of a K row with the matching piece of a query head, accumulated in double
-template <int DT>
-__device__ __forceinline__ double piece_dot_f64(uint4 k, uint4 q, double acc);
-template <>
-__device__ __forceinline__ double piece_dot_f64<TS_BF16>(uint4 k, uint4 q, double acc) {
-  // a product of two bf16 values is exact in float; the sum runs in double
-  acc += (double)(bf16_lo(k.x) * bf16_lo(q.x)); acc += (double)(bf16_hi(k.x) * bf16_hi(q.x));
-  acc += (double)(bf16_lo(k.y) * bf16_lo(q.y)); acc += (double)(bf16_hi(k.y) * bf16_hi(q.y));
-  acc += (double)(bf16_lo(k.z) * bf16_lo(q.z)); acc += (double)(bf16_hi(k.z) * bf16_hi(q.z));
-  acc += (double)(bf16_lo(k.w) * bf16_lo(q.w)); acc += (double)(bf16_hi(k.w) * bf16_hi(q.w));
-  return acc;
-}
-template <>
-__device__ __forceinline__ double piece_dot_f64<TS_F32>(uint4 k, uint4 q, double acc) {
-  acc = fma((double)__uint_as_float(k.x), (double)__uint_as_float(q.x), acc);
-  acc = fma((double)__uint_as_float(k.y), (double)__uint_as_float(q.y), acc);
-  acc = fma((double)__uint_as_float(k.z), (double)__uint_as_float(q.z), acc);
-  acc = fma((double)__uint_as_float(k.w), (double)__uint_as_float(q.w), acc);
-  return acc;
-}
-
-template <int DT, int D, int G, int kRefineThreads>
-__global__ __launch_bounds__(kRefineThreads) void topk_refine_kernel(RefineArgs a) {
-  constexpr int kRefineWaves = kRefineThreads / 64;
-  constexpr int ES = Elt<DT>::size;
-  constexpr int RB = D * ES;
-  constexpr int L = RB / 128;
-  constexpr int PER = kTopkChunk / kRefineThreads;
-  constexpr int UB = DT == TS_F32 ? 2 : 4;      // wave steps whose K rows are in flight together
-  __shared__ uint32_t lds[kRefineWaves + 2];
-  __shared__ uint32_t scan_lds[kRefineWaves];
-  __shared__ int ctok[kTopkChunk];
-  __shared__ int cpid[kTopkChunk];
-  __shared__ double s_m[128];
-  __shared__ double s_inv[128];
-  extern __shared__ uint4 q_lds[];              // the sequence's query, [H][row bytes]
-  const TopkArgs& ta = a.t;
-  const int b = blockIdx.y;
-  const int skip_flag = ta.skip != nullptr ? (int)ta.skip[b] : 0;
-  const int Nb = min(max(ta.seq_lens[b], 0), ta.max_seq_len);
-  const int indptr = a.page_indptr[b];
-  if (skip_flag != 0) return;
-  const int LO = min(ta.head, Nb), N = max(LO, Nb - ta.tail);      // ranked range [LO, N)
-  const uint32_t k_eff = (uint32_t)min(ta.k, N - LO);
-  const int H = a.H;
-  // a.parts workgroups share a chunk: each finds the threshold and compacts the chunk for itself (cheap, and the same
-  // in all of them), then re-evaluates its share of the candidates -- few chunks then still fill the machine
-  const int chunk = blockIdx.x / a.parts, part = blockIdx.x - chunk * a.parts;
-  const int base = chunk * kTopkChunk;
-  const int t0 = base + threadIdx.x * PER;      // PER consecutive tokens per thread: order is preserved
-  const float* v = ta.votes + (size_t)b * ta.max_seq_len;
-  uint32_t key[PER];
-  bool valid[PER];
-  if (PER % 4 == 0 && ((reinterpret_cast<uintptr_t>(v) & 15) == 0) && base + kTopkChunk <= ta.max_seq_len) {
-    // the usual case: the chunk's upper bounds as 16-byte loads (the row exists up to max_seq_len)
+// Sums v[g] over the LPR lanes of a row and leaves head g = (lane % GP) of the sums in each lane (GP = G rounded up to
+// a power of two; LPR = 8 or 16).  Where two lanes meet, each takes over half of the heads that both still carry, so
+// the number of additions halves from step to step.
+template <int GP, int LPR>
+__device__ __forceinline__ double row_reduce(double (&v)[GP], int lane) {
+  if (GP == 8) {
+    const bool b = (lane & 4) != 0;        // the half mirror flips bits 0 to 2: done first, when all lanes carry all heads
 #pragma unroll
-    for (int q4 = 0; q4 < PER / 4; ++q4) {
-      const float4 w = *reinterpret_cast<const float4*>(v + t0 + q4 * 4);
-      const float x[4] = {w.x, w.y, w.z, w.w};
+    for (int g = 0; g < GP / 2; ++g) {
+      const double keep = b ? v[g + GP / 2] : v[g], give = b ? v[g] : v[g + GP / 2];
+      v[g] = keep + dpp_f64<kDppHalfMirror>(give);
+    }
+  } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = q4 * 4 + i;
-        valid[e] = (t0 + e) >= LO && (t0 + e) < N;
-        key[e] = valid[e] ? float_key(x[i]) : 0u;
+    for (int g = 0; g < GP; ++g) v[g] += (LPR == 16) ? dpp_f64<kDppRor4>(v[g]) : dpp_f64<kDppHalfMirror>(v[g]);
+  }
+  if (GP >= 4) {
+    const bool b = (lane & 2) != 0;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if (g + 2 < GP) {
+        const double keep = b ? v[g + 2] : v[g], give = b ? v[g] : v[g + 2];
+        v[g] = keep + dpp_f64<kDppXor2>(give);
       }
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      valid[e] = (t0 + e) >= LO && (t0 + e) < N;
-      key[e] = valid[e] ? float_key(v[t0 + e]) : 0u;
+    for (int g = 0; g < GP; ++g) v[g] += dpp_f64<kDppXor2>(v[g]);
+  }
+  if (GP >= 2) {
+    const bool b = (lane & 1) != 0;
+    const double keep = b ? v[GP > 1 ? 1 : 0] : v[0], give = b ? v[0] : v[GP > 1 ? 1 : 0];
+    v[0] = keep + dpp_f64<kDppXor1>(give);
+  } else {
+    v[0] += dpp_f64<kDppXor1>(v[0]);
+  }
+  if (LPR == 16) v[0] += dpp_f64<kDppRor8>(v[0]);
+  return v[0];
+}
+
+// the elements of NW 16-byte pieces as doubles
+template <int DT, int NW>
+__device__ __forceinline__ void unpack_f64(const uint4 (&w)[NW], double* f) {
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const uint32_t x[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (DT == TS_BF16) { f[i * 8 + 2 * c] = (double)bf16_lo(x[c]); f[i * 8 + 2 * c + 1] = (double)bf16_hi(x[c]); }
+      else f[i * 4 + c] = (double)__uint_as_float(x[c]);
     }
+  }
+}
+
+constexpr int kEvalThreads = 256;
+constexpr int kEvalMaxBatch = 128;        // candidates whose scores a workgroup holds in LDS at a time, at most
+
+template <int DT, int D, int G>
+__global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a, int cb) {
+  constexpr int ES = Elt<DT>::size;
+  constexpr int RB = D * ES;
+  constexpr int EPL = (D == 128 && G <= 4) ? 16 : 8;   // elements of a row per lane: the query then takes 128 registers at most
+  constexpr int LPR = D / EPL;            // lanes per K row: 8 or 16
+  constexpr int RPS = 64 / LPR;           // rows of a wave step
+  constexpr int NW = ES * EPL / 16;       // 16-byte pieces of a lane's elements, LPR pieces apart
+  constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
+  constexpr int UB = NW == 1 ? 4 : 2;     // wave steps of a round
+  __shared__ uint32_t wave_sum[kEvalThreads / 64];
+  __shared__ int ctok[kEvalMaxBatch];
+  __shared__ long long cslot[kEvalMaxBatch];
+  __shared__ double s_m[128];
+  __shared__ double s_inv[128];
+  extern __shared__ double sc[];          // [cb][H] scores of the batch, then uint32 [nblk + 1] prefix of the chunk counts
+  const TopkArgs& ta = a.t;
+  const int b = blockIdx.y;
+  const int H = a.H;
+  uint32_t* off = reinterpret_cast<uint32_t*>(sc + (size_t)cb * H);
+  const int skip_flag = ta.skip != nullptr ? (int)ta.skip[b] : 0;
+  const int Nb = min(max(ta.seq_lens[b], 0), ta.max_seq_len);
+  const int indptr = a.page_indptr[b];
+  if (skip_flag != 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // a wave owns one slice of the KV heads (every nuw-th, where there are more slices than waves) and every 4 / nuw-th step
+  const int j = lane % LPR, r = lane / LPR;
+  const int HB = min(a.H_kv, RPS);                    // KV heads of a wave step
+  const int hb_shift = 31 - __clz(HB);
+  const int NU = a.H_kv >> hb_shift;                  // slices
+  const int nuw = min(NU, 4);
+  const int kvh_l = r & (HB - 1), tis = r >> hb_shift;
+  const int tps = RPS >> hb_shift;                    // candidates of a wave step
+  const int wsub = wave / nuw, wstep = 4 / nuw;
+  double qd[G][EPL];
+  auto load_q = [&](int u) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      uint4 w[NW];
+      const uint8_t* qp = a.q + ((size_t)b * H + (size_t)(u * HB + kvh_l) * G + g) * RB + j * 16;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) w[i] = *reinterpret_cast<const uint4*>(qp + i * (LPR * 16));
+      unpack_f64<DT, NW>(w, qd[g]);
+    }
+  };
+  load_q(wave % nuw);
+  // the lower bounds' histogram has been consumed by the compaction: leave it zeroed, a share per workgroup
+  {
+    uint4* g0 = reinterpret_cast<uint4*>(ta.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);   // 256-byte aligned section
+    for (int i = (int)(blockIdx.x * kEvalThreads + threadIdx.x); i < kBoundHistCopies * kTopkBins / 4; i += (int)gridDim.x * kEvalThreads)
+      g0[i] = make_uint4(0u, 0u, 0u, 0u);
   }
   if (threadIdx.x < H) {
     const float2 st = *reinterpret_cast<const float2*>(a.row_stats + ((size_t)b * H + threadIdx.x) * 2);
     s_m[threadIdx.x] = (double)st.x; s_inv[threadIdx.x] = 1.0 / (double)st.y;
   }
-  // the sequence's query goes to LDS as floats ([H][D]): a product then costs one conversion and one double fma
-  for (int i = threadIdx.x; i < H * (RB / 16); i += kRefineThreads) {
-    const uint4 w = reinterpret_cast<const uint4*>(a.q + (size_t)b * H * RB)[i];
-    if (DT == TS_BF16) {
-      q_lds[2 * i] = make_uint4(w.x << 16, w.x & 0xffff0000u, w.y << 16, w.y & 0xffff0000u);
-      q_lds[2 * i + 1] = make_uint4(w.z << 16, w.z & 0xffff0000u, w.w << 16, w.w & 0xffff0000u);
-    } else {
-      q_lds[i] = w;
+  // ---- prefix of the chunks' candidate counts
+  constexpr int CPT = 4;                              // consecutive chunks per thread and round: 1024 chunks at a time
+  uint32_t carry = 0;
+  for (int c0 = 0; c0 < ta.nblk; c0 += kEvalThreads * CPT) {
+    const int c = c0 + (int)threadIdx.x * CPT;
+    uint32_t cnt[CPT], sum = 0;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) { cnt[i] = c + i < ta.nblk ? ta.blk[(size_t)b * ta.nblk + c + i] : 0u; sum += cnt[i]; }
+    const uint32_t incl = wave_inclusive_scan(sum);
+    __syncthreads();
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t base = carry + incl - sum;
+#pragma unroll
+    for (int w = 0; w < kEvalThreads / 64; ++w) {
+      const uint32_t x = wave_sum[w];
+      if (w < wave) base += x;
+      carry += x;
     }
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) { if (c + i < ta.nblk) off[c + i] = base; base += cnt[i]; }
   }
-  const uint32_t d0 = refine_find_bin<kRefineWaves>(ta.bound_hist + (size_t)b * kBoundHistCopies * kTopkBins, k_eff, lds);
-
-  if (blockIdx.x == 0 && threadIdx.x == 0) ta.state[b * 8 + ST_KEFF_WORD] = k_eff;
-  uint32_t n = 0;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) n += valid[e] && (key[e] >> 21) >= d0;      // d0 == kTopkBins (empty selection) matches nothing
-  uint32_t total;
-  uint32_t pos = refine_block_scan<kRefineWaves>(n, &total, scan_lds);
-  const int npages = (Nb + a.P - 1) >> a.p_shift;
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (valid[e] && (key[e] >> 21) >= d0) {
-      ctok[pos] = t0 + e;
-      cpid[pos] = a.page_indices[indptr + min((t0 + e) >> a.p_shift, npages - 1)];
-      ++pos;
-    }
-  if (threadIdx.x == 0 && part == 0) ta.blk[(size_t)b * ta.nblk + chunk] = total;
+  if (threadIdx.x == 0) off[ta.nblk] = carry;
+  const uint32_t total = carry;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ta.state[b * 8 + kStTotal] = total;
   __syncthreads();
-  if (total == 0) return;
-
-  // ---- votes of the candidates from exact scores: a wave step covers 8 K rows = HB KV heads of 8 / HB candidates
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = lane & 7, r = lane >> 3;
-  const int HB = a.HB;
-  const int kvh_l = r & (HB - 1);
-  const int tis = r >> a.hb_shift;
-  const int tps_shift = 3 - a.hb_shift;
-  const int ngroups = ((int)total + (1 << tps_shift) - 1) >> tps_shift;
+  const uint32_t c_begin = (uint32_t)((unsigned long long)total * blockIdx.x / gridDim.x);
+  const uint32_t c_end = (uint32_t)((unsigned long long)total * (blockIdx.x + 1) / gridDim.x);
   const double c2d = (double)a.scale * 1.44269504088896340736;
-  uint2* list = ta.list + ((size_t)b * ta.nblk + chunk) * kTopkChunk;
-  const int g_begin = (int)((long)part * ngroups / a.parts), g_end = (int)((long)(part + 1) * ngroups / a.parts);   // this workgroup's groups
-  for (int g0 = g_begin + wave; g0 < g_end; g0 += kRefineWaves * UB) {   // group uu of this round: g0 + uu * kRefineWaves
-    // groups of this round that exist (the same for the whole wave): the others cost neither loads nor arithmetic
-    const int nact = min(UB, (g_end - g0 + kRefineWaves - 1) / kRefineWaves);
-    double vote[UB];
-#pragma unroll
-    for (int uu = 0; uu < UB; ++uu) vote[uu] = 0.0;
-    for (int u = 0; u < a.NU; ++u) {
+  const int npages = (Nb + a.P - 1) >> a.p_shift;
+  uint2* dense = ta.dense + (size_t)b * ta.nblk * kTopkChunk;
+  for (uint32_t c0 = c_begin; c0 < c_end; c0 += cb) {
+    const int n = (int)min((uint32_t)cb, c_end - c0);
+    if ((int)threadIdx.x < n) {                        // one thread per candidate: its token and its row in the pool
+      const uint32_t i = c0 + threadIdx.x;
+      int lo = 0, hi = ta.nblk;                        // off[lo] <= i < off[hi]
+      while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (off[mid] <= i) lo = mid; else hi = mid; }
+      const int t = (int)ta.list[((size_t)b * ta.nblk + lo) * kTopkChunk + (i - off[lo])].y;
+      const int pid = a.page_indices[indptr + min(t >> a.p_shift, npages - 1)];
+      ctok[threadIdx.x] = t;
+      cslot[threadIdx.x] = ((long long)pid << a.p_shift) + (t & (a.P - 1));
+    }
+    __syncthreads();
+    const int nsteps = (n + tps - 1) / tps;
+    for (int u = wave % nuw; u < NU; u += nuw) {
+      if (NU > nuw) load_q(u);
       const int kvh = u * HB + kvh_l;
-      uint4 kr[UB][L];
+      // steps of this wave and slice: wsub, wsub + wstep, ...; the next round's rows are in flight during a round
+      uint4 cur[UB][NW], nxt[UB][NW];
+      auto issue = [&](int s0, uint4 (&kr)[UB][NW]) {
 #pragma unroll
-      for (int uu = 0; uu < UB; ++uu) {
-        if (uu >= nact) continue;
-        const int ci = min(((g0 + uu * kRefineWaves) << tps_shift) + tis, (int)total - 1);
-        const int t = ctok[ci], pid = cpid[ci];
-        const uint8_t* kp = a.k_pool + (((size_t)pid << a.p_shift) + (size_t)(t & (a.P - 1))) * ((size_t)a.H_kv * RB) +
-                            (size_t)kvh * RB + j * 16;
+        for (int uu = 0; uu < UB; ++uu) {
+          const int st = s0 + uu * wstep;
+          if (st >= nsteps) continue;                                   // the same for the whole wave
+          const long long slot = cslot[min(st * tps + tis, n - 1)];
+          const uint8_t* kp = a.k_pool + ((size_t)slot * a.H_kv + kvh) * RB + j * 16;
 #pragma unroll
-        for (int i = 0; i < L; ++i) kr[uu][i] = *reinterpret_cast<const uint4*>(kp + i * 128);
-      }
-      double svv[UB];
-#pragma unroll
-      for (int uu = 0; uu < UB; ++uu) svv[uu] = 0.0;
-      constexpr int EPP = 16 / ES;               // elements per 16-byte piece of K
-#pragma unroll
-      for (int uu = 0; uu < UB; ++uu) {
-        if (uu >= nact) continue;
-        // the candidate's K pieces as doubles, once for all G query heads of the row's KV head
-        double kd[L][EPP];
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-          const uint4 k4 = kr[uu][i];
-          if (DT == TS_BF16) {
-            kd[i][0] = (double)bf16_lo(k4.x); kd[i][1] = (double)bf16_hi(k4.x); kd[i][2] = (double)bf16_lo(k4.y); kd[i][3] = (double)bf16_hi(k4.y);
-            kd[i][4 % EPP] = (double)bf16_lo(k4.z); kd[i][5 % EPP] = (double)bf16_hi(k4.z); kd[i][6 % EPP] = (double)bf16_lo(k4.w); kd[i][7 % EPP] = (double)bf16_hi(k4.w);
-          } else {
-            kd[i][0] = (double)__uint_as_float(k4.x); kd[i][1] = (double)__uint_as_float(k4.y);
-            kd[i][2] = (double)__uint_as_float(k4.z); kd[i][3] = (double)__uint_as_float(k4.w);
-          }
+          for (int i = 0; i < NW; ++i) kr[uu][i] = *reinterpret_cast<const uint4*>(kp + i * (LPR * 16));
         }
-#pragma unroll 1
-        for (int g = 0; g < G; ++g) {           // one query head at a time: its elements come from LDS as floats
-          const float* qf = reinterpret_cast<const float*>(q_lds) + (size_t)(kvh * G + g) * D + j * EPP;
-          double pc[L];                          // independent chains (products of two floats are exact in double)
+      };
+      if (wsub < nsteps) issue(wsub, cur);
+      for (int s0 = wsub; s0 < nsteps; s0 += wstep * UB) {
+        issue(s0 + wstep * UB, nxt);
 #pragma unroll
-          for (int i = 0; i < L; ++i) {
-            double acc = 0.0;
+        for (int uu = 0; uu < UB; ++uu) {
+          const int st = s0 + uu * wstep;
+          if (st >= nsteps) continue;
+          double kd[EPL];
+          unpack_f64<DT, NW>(cur[uu], kd);
+          double v[GP];
 #pragma unroll
-            for (int e4 = 0; e4 < EPP / 4; ++e4) {
-              const float4 q4 = *reinterpret_cast<const float4*>(qf + i * (128 / ES) + e4 * 4);
-              acc = fma(kd[i][e4 * 4], (double)q4.x, acc); acc = fma(kd[i][e4 * 4 + 1], (double)q4.y, acc);
-              acc = fma(kd[i][e4 * 4 + 2], (double)q4.z, acc); acc = fma(kd[i][e4 * 4 + 3], (double)q4.w, acc);
+          for (int g = 0; g < GP; ++g) {
+            v[g] = 0.0;
+            if (g < G) {
+              // products of two floats are exact in double
+#pragma unroll
+              for (int e = 0; e < EPL; ++e) v[g] = fma(kd[e], qd[g < G ? g : 0][e], v[g]);
             }
-            pc[i] = acc;
           }
-          double sc = pc[0];
-#pragma unroll
-          for (int i = 1; i < L; ++i) sc += pc[i];
-          sc = group8_sum_f64(sc);                // the eight lanes of the row
-          svv[uu] = (j == g) ? sc : svv[uu];
+          const double s = row_reduce<GP, LPR>(v, lane);
+          const int ci = st * tps + tis, g = j & (GP - 1);
+          if (ci < n && j < GP && g < G) sc[(size_t)ci * H + kvh * G + g] = s;
         }
-      }
 #pragma unroll
-      for (int uu = 0; uu < UB; ++uu) {
-        if (uu >= nact) continue;
-        const double sv = svv[uu];
-        const int hh = min(kvh * G + j, H - 1);
-        double term = (j < G) ? (double)refine_vote_exp(sv - s_m[hh], c2d) * s_inv[hh] : 0.0;
-        // sum over the lanes of this candidate: the eight lanes of a row, then the HB rows
-        term = group8_sum_f64(term);
-        for (int off = 8; off < (8 << a.hb_shift); off <<= 1) term += __shfl_xor(term, off);
-        vote[uu] += term;
+        for (int uu = 0; uu < UB; ++uu)
+#pragma unroll
+          for (int i = 0; i < NW; ++i) cur[uu][i] = nxt[uu][i];
       }
     }
-#pragma unroll
-    for (int uu = 0; uu < UB; ++uu) {
-      const int ci = ((g0 + uu * kRefineWaves) << tps_shift) + tis;
-      if (uu < nact && ci < (int)total && kvh_l == 0 && j == 0) list[ci] = make_uint2(float_key((float)vote[uu]), (uint32_t)ctok[ci]);
+    __syncthreads();
+    // ---- votes: 16 lanes per candidate
+    for (int ci = (int)threadIdx.x >> 4; ci < ((n + 15) & ~15); ci += kEvalThreads / 16) {
+      const int cc = min(ci, n - 1);
+      double vote = 0.0;
+      for (int h = (int)threadIdx.x & 15; h < H; h += 16)
+        vote += (double)refine_vote_exp(sc[(size_t)cc * H + h] - s_m[h], c2d) * s_inv[h];
+      vote += dpp_f64<kDppXor1>(vote);
+      vote += dpp_f64<kDppXor2>(vote);
+      vote += dpp_f64<kDppHalfMirror>(vote);
+      vote += dpp_f64<kDppRor8>(vote);
+      if (ci < n && (threadIdx.x & 15) == 0) dense[c0 + ci] = make_uint2(float_key((float)vote), (uint32_t)ctok[ci]);
     }
+    __syncthreads();
   }
-}
-
-template <int DT, int D, int GG, int NT>
-static hipError_t refine_launch(const RefineArgs& a, dim3 grid, hipStream_t s) {
-  const size_t lds = (size_t)a.H * D * sizeof(float);     // the query as floats in LDS (next to about 19 KiB of static LDS)
-  if (lds > 40960) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&topk_refine_kernel<DT, D, GG, NT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((topk_refine_kernel<DT, D, GG, NT>), grid, dim3(NT), lds, s, a);
-  return hipGetLastError();
-}
-
-template <int DT, int D, int GG>
-static hipError_t refine_one(const RefineArgs& a, dim3 grid, hipStream_t s) {
-  // few chunks: one fat workgroup per CU at most anyway, so take 16 waves per chunk (bf16; the fp32 form needs the
-  // registers); many chunks: small workgroups, so that all of them are resident at once (a workgroup's run is one
-  // chain of dependent loads, about 10 us, whatever its size)
-  if (DT == TS_BF16 && (long)grid.x * grid.y <= 256) return refine_launch<DT, D, GG, 1024>(a, grid, s);
-  return refine_launch<DT, D, GG, 256>(a, grid, s);
 }
 
 template <int DT, int D>
-static hipError_t refine_g(int G, const RefineArgs& a, dim3 grid, hipStream_t s) {
+static hipError_t eval_g(int G, const RefineArgs& a, dim3 grid, hipStream_t s) {
+  int cb = 3072 / a.H;                                // the scores of a batch and the prefix of 8192 chunks fit 64 KiB
+  if (cb > kEvalMaxBatch) cb = kEvalMaxBatch;
+  const size_t lds = (size_t)cb * a.H * sizeof(double) + (size_t)(a.t.nblk + 1) * sizeof(uint32_t);
   switch (G) {
-#define TS_CASE(GG) case GG: return refine_one<DT, D, GG>(a, grid, s);
+#define TS_CASE(GG) case GG: hipLaunchKernelGGL((topk_eval_kernel<DT, D, GG>), grid, dim3(kEvalThreads), lds, s, a, cb); break;
     TS_CASE(1) TS_CASE(2) TS_CASE(3) TS_CASE(4) TS_CASE(5) TS_CASE(6) TS_CASE(7) TS_CASE(8)
 #undef TS_CASE
+    default: return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
-hipError_t launch_topk_refine(int dtype, int D, int G, const RefineArgs& a, int B, hipStream_t s) {
-  const dim3 grid(a.t.nblk * a.parts, B);
-  if (dtype == TS_F32) return D == 64 ? refine_g<TS_F32, 64>(G, a, grid, s) : refine_g<TS_F32, 128>(G, a, grid, s);
-  return D == 64 ? refine_g<TS_BF16, 64>(G, a, grid, s) : refine_g<TS_BF16, 128>(G, a, grid, s);
+hipError_t launch_topk_eval(int dtype, int D, int G, const RefineArgs& a, int B, hipStream_t s) {
+  const dim3 grid(a.parts, B);
+  if (dtype == TS_F32) return D == 64 ? eval_g<TS_F32, 64>(G, a, grid, s) : eval_g<TS_F32, 128>(G, a, grid, s);
+  return D == 64 ? eval_g<TS_BF16, 64>(G, a, grid, s) : eval_g<TS_BF16, 128>(G, a, grid, s);
 }
 
 }  // namespace ts

@@ -16,12 +16,7 @@ namespace ts {
 // exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* total, uint32_t* lds /* >= 5 words */) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
+  const uint32_t incl = wave_inclusive_scan(v);
   __syncthreads();
   if (lane == 63) lds[wave] = incl;
   __syncthreads();
@@ -341,6 +336,7 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
 constexpr int kFinalThreads = 1024;        // many threads, few entries each: the per-entry chain of a thread is the latency
                                            // that counts (256 threads x 32 entries measured 1.7x slower)
 constexpr int kFinalMaxBlk = 8192;         // chunks per sequence the short path handles (16 Mi tokens)
+constexpr int kTieMax = 256;               // entries of one 2^13-key bin that the finish ranks among themselves
 
 // pass 1 of the short path: fix digit 0, compact the entries with (key >> 21) >= digit 0
 __global__ __launch_bounds__(256) void topk_compact_kernel(TopkArgs a) {
@@ -358,10 +354,25 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(TopkArgs a) {
   // the votes are loaded before the histogram is walked: the two round trips overlap
   uint32_t key[PER];
   bool valid[PER];
+  if (((reinterpret_cast<uintptr_t>(v) & 15) == 0) && base + kTopkChunk <= a.max_seq_len) {
+    // the usual case: 16-byte loads (the row exists up to max_seq_len)
 #pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    valid[e] = (t0 + e) >= LO && (t0 + e) < N;
-    key[e] = valid[e] ? float_key(v[t0 + e]) : 0u;
+    for (int q4 = 0; q4 < PER / 4; ++q4) {
+      const float4 w = *reinterpret_cast<const float4*>(v + t0 + q4 * 4);
+      const float x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int e = q4 * 4 + i;
+        valid[e] = (t0 + e) >= LO && (t0 + e) < N;
+        key[e] = valid[e] ? float_key(x[i]) : 0u;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      valid[e] = (t0 + e) >= LO && (t0 + e) < N;
+      key[e] = valid[e] ? float_key(v[t0 + e]) : 0u;
+    }
   }
   uint32_t d0, krem0;
   if (a.rep_hist != nullptr) find_digit_rep<kTopkBins>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins, k_eff, &d0, &krem0, lds);
@@ -384,12 +395,7 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(TopkArgs a) {
 // exclusive prefix sum over the kFinalThreads threads of the final workgroup
 __device__ __forceinline__ uint32_t final_exclusive_scan(uint32_t v, uint32_t* total, uint32_t* lds /* >= 16 words */) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
+  const uint32_t incl = wave_inclusive_scan(v);
   __syncthreads();
   if (lane == 63) lds[wave] = incl;
   __syncthreads();
@@ -431,12 +437,14 @@ __device__ __forceinline__ void final_find_digit(const uint32_t* h, uint32_t k_r
 }
 
 // passes 2, 3 and the emit of the short path: one workgroup per (virtual) sequence
-// FULL: the list holds exact votes whose top digit has not been fixed yet (compact selection: the entries are
-// the re-evaluated candidates), so digit 0 is found here too, over the entries.
+// FULL: the entries are the re-evaluated candidates of the compact selection, listed without gaps (a.dense); their
+// keys are exact votes, of which only the lower edge of the k-th largest lower bound's bin is known.
 template <int kFinalPer, bool FULL>        // consecutive list entries per thread and batch
 __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
-  __shared__ uint32_t off[kFinalMaxBlk + 1];   // exclusive prefix of the chunks' entry counts
+  __shared__ uint32_t off[FULL ? 1 : kFinalMaxBlk + 1];   // exclusive prefix of the chunks' entry counts
   __shared__ uint32_t h[kTopkBins];
+  __shared__ uint32_t tie[FULL ? kTieMax : 1];            // keys that share the k-th key's bin
+  __shared__ uint32_t n_tie;
   __shared__ uint32_t scan_lds[16];
   __shared__ uint32_t res[2];
   const int b = blockIdx.x;
@@ -456,9 +464,7 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
       for (int i = k_eff + tid; i < a.k; i += kFinalThreads) a.sel_votes[(size_t)b * a.k + i] = 0.f;
     if (tid == 0) a.count[b] = k_eff;
   }
-  if (FULL) {  // the replicated histogram of the lower bounds has been consumed by the refine pass: zero it again
-    uint4* g0 = reinterpret_cast<uint4*>(a.bound_hist + (size_t)b * kBoundHistCopies * kTopkBins);   // 256-byte aligned section
-    for (int i = tid; i < kBoundHistCopies * kTopkBins / 4; i += kFinalThreads) g0[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (FULL) {                  // the lower bounds' histogram was cleared by the re-evaluation
   } else if (a.rep_hist != nullptr) {   // the vote kernel's replicated histogram has been consumed by the compact pass
     uint4* g0 = reinterpret_cast<uint4*>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);
     for (int i = tid; i < kBoundHistCopies * kTopkBins / 4; i += kFinalThreads) g0[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -466,26 +472,43 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
     uint32_t* g0 = a.hist + ((size_t)b * 3 + 0) * kTopkBins;
     for (int i = tid; i < kTopkBins; i += kFinalThreads) g0[i] = 0u;
   }
-  // ---- chunk offsets
-  uint32_t carry = 0;
-  for (int c0 = 0; c0 < a.nblk; c0 += kFinalThreads) {
-    const int c = c0 + tid;
-    const uint32_t n = c < a.nblk ? a.blk[(size_t)b * a.nblk + c] : 0u;
-    uint32_t tot;
-    const uint32_t ex = final_exclusive_scan(n, &tot, scan_lds);
-    if (c < a.nblk) off[c] = carry + ex;
-    carry += tot;
+  uint32_t total;
+  if (FULL) {
+    total = min(a.state[b * 8 + kStTotal], (uint32_t)a.nblk * kTopkChunk);
+  } else {
+    // ---- chunk offsets
+    uint32_t carry = 0;
+    for (int c0 = 0; c0 < a.nblk; c0 += kFinalThreads) {
+      const int c = c0 + tid;
+      const uint32_t n = c < a.nblk ? a.blk[(size_t)b * a.nblk + c] : 0u;
+      uint32_t tot;
+      const uint32_t ex = final_exclusive_scan(n, &tot, scan_lds);
+      if (c < a.nblk) off[c] = carry + ex;
+      carry += tot;
+      __syncthreads();
+    }
+    total = carry;
+    if (tid == 0) off[a.nblk] = total;
     __syncthreads();
   }
-  const uint32_t total = carry;
-  if (tid == 0) off[a.nblk] = total;
-  __syncthreads();
   if (total == 0 || k_eff == 0) return;
   const uint2* list = a.list + (size_t)b * a.nblk * kTopkChunk;
+  const uint2* dense = FULL ? a.dense + (size_t)b * a.nblk * kTopkChunk : nullptr;
 
   // entries of a batch: thread tid owns the kFinalPer consecutive positions from p0
   auto load_batch = [&](uint32_t base, uint2 (&e)[kFinalPer]) {
     const uint32_t p0 = base + (uint32_t)tid * kFinalPer;
+    if (FULL) {
+      // the section holds a multiple of 2048 entries: whole pairs are read, those past the end are masked
+#pragma unroll
+      for (int i = 0; i < kFinalPer; i += 2) {
+        uint4 w = make_uint4(0u, 0xffffffffu, 0u, 0xffffffffu);
+        if (p0 + i < total) w = *reinterpret_cast<const uint4*>(dense + p0 + i);
+        e[i] = make_uint2(w.x, w.y);
+        e[i + 1] = p0 + i + 1 < total ? make_uint2(w.z, w.w) : make_uint2(0u, 0xffffffffu);
+      }
+      return;
+    }
     int c = 0;
     if (p0 < total) {                         // chunk with off[c] <= p0 < off[c + 1]
       int lo = 0, hi = a.nblk;                // invariant: off[lo] <= p0 < off[hi]
@@ -507,52 +530,103 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
   uint2 e[kFinalPer];
   if (single) load_batch(0, e);
 
-  if (FULL) {   // ---- digit 0: bits 31..21 over all entries
+  uint32_t thr, need_eq;
+  bool fixed = false;                         // thr and need_eq are known (the same in all threads)
+  if (FULL) {
+    // The k-th vote lies at or above the lower edge of the bin that the k-th largest lower bound fell into, and
+    // within the width of the bounds above it: 2048 bins of 2^13 keys from that edge on (two octaves) hold it, and a
+    // bin of 2^13 keys (a thousandth of the vote) a few entries, which are ranked among themselves.  One histogram
+    // pass instead of two or three (with the list dense and its scans on the DPP network, 1048576 tokens, k 4096: 14.5 -> 7.6 us).  Votes spread otherwise (the last bin also
+    // takes everything above, or a bin holds more entries than can be ranked at once) go the general way below.
+    const uint32_t edge = a.state[b * 8 + ST_PREFIX0];
+    auto bin_of = [&](uint32_t key) -> uint32_t { return min((key - edge) >> 13, (uint32_t)kTopkBins - 1u); };
+    for (int i = tid; i < kTopkBins; i += kFinalThreads) h[i] = 0u;
+    if (tid == 0) n_tie = 0u;
+    uint32_t above = 0u;
+    __syncthreads();
+    for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
+      if (!single) load_batch(base, e);
+#pragma unroll
+      for (int i = 0; i < kFinalPer; ++i)
+        if (e[i].y != 0xffffffffu && e[i].x >= edge) {
+          const uint32_t d = bin_of(e[i].x);
+          if (d < (uint32_t)kTopkBins - 1u) atomicAdd(&h[d], 1u);
+          else ++above;                        // most entries: one addition per wave below instead of one each
+        }
+    }
+    above = wave_inclusive_scan(above);
+    if ((tid & 63) == 63 && above != 0u) atomicAdd(&h[kTopkBins - 1], above);
+    __syncthreads();
+    uint32_t d, krem;
+    final_find_digit<kTopkBins>(h, (uint32_t)k_eff, &d, &krem, scan_lds, res);
+    if (d < (uint32_t)kTopkBins - 1u && h[d] <= (uint32_t)kTieMax) {
+      const int n = (int)h[d];
+      for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
+        if (!single) load_batch(base, e);
+#pragma unroll
+        for (int i = 0; i < kFinalPer; ++i)
+          if (e[i].y != 0xffffffffu && e[i].x >= edge && bin_of(e[i].x) == d) tie[atomicAdd(&n_tie, 1u)] = e[i].x;
+      }
+      __syncthreads();
+      if (tid < n) {
+        const uint32_t mine = tie[tid];
+        uint32_t gt = 0, eq = 0;
+        for (int i = 0; i < n; ++i) { gt += tie[i] > mine; eq += tie[i] == mine; }
+        if (gt < krem && krem <= gt + eq) { res[0] = mine; res[1] = krem - gt; }   // equal keys write equal values
+      }
+      __syncthreads();
+      thr = res[0]; need_eq = res[1];
+      fixed = true;
+    }
+    __syncthreads();
+  }
+  if (!fixed) {
+    if (FULL) {   // ---- digit 0: bits 31..21 over all entries
+      for (int i = tid; i < kTopkBins; i += kFinalThreads) h[i] = 0u;
+      __syncthreads();
+      for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
+        if (!single) load_batch(base, e);
+#pragma unroll
+        for (int i = 0; i < kFinalPer; ++i)
+          if (e[i].y != 0xffffffffu) atomicAdd(&h[e[i].x >> 21], 1u);
+      }
+      __syncthreads();
+      final_find_digit<kTopkBins>(h, (uint32_t)k_eff, &d0, &krem0, scan_lds, res);
+    }
+    // ---- digit 1: bits 20..10 of the candidates (entries of bin d0)
     for (int i = tid; i < kTopkBins; i += kFinalThreads) h[i] = 0u;
     __syncthreads();
     for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
       if (!single) load_batch(base, e);
 #pragma unroll
       for (int i = 0; i < kFinalPer; ++i)
-        if (e[i].y != 0xffffffffu) atomicAdd(&h[e[i].x >> 21], 1u);
+        if (e[i].y != 0xffffffffu && (e[i].x >> 21) == d0) atomicAdd(&h[(e[i].x >> 10) & 2047u], 1u);
     }
     __syncthreads();
-    final_find_digit<kTopkBins>(h, (uint32_t)k_eff, &d0, &krem0, scan_lds, res);
-  }
-  // ---- digit 1: bits 20..10 of the candidates (entries of bin d0)
-  for (int i = tid; i < kTopkBins; i += kFinalThreads) h[i] = 0u;
-  __syncthreads();
-  for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
-    if (!single) load_batch(base, e);
+    uint32_t d1, krem1;
+    final_find_digit<kTopkBins>(h, krem0, &d1, &krem1, scan_lds, res);
+    const uint32_t prefix1 = (d0 << 21) | ((d1 & 2047u) << 10);
+    // ---- digit 2: the last 10 bits -- unless every entry that shares the threshold's 22-bit prefix is a winner (the
+    // usual case: a few thousand entries over 2^22 prefixes leave the threshold's bin with one or two), when the
+    // prefix alone decides
+    const uint32_t cnt1 = d1 < (uint32_t)kTopkBins ? h[d1] : 0xffffffffu;
+    if (krem1 == cnt1 && prefix1 != 0u) {
+      thr = prefix1 - 1u; need_eq = 0u;          // "above thr" = "prefix at least prefix1"; nothing equals thr among the winners
+    } else {
+      __syncthreads();                            // every thread has read cnt1 before the histogram is cleared
+      for (int i = tid; i < 1024; i += kFinalThreads) h[i] = 0u;
+      __syncthreads();
+      for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
+        if (!single) load_batch(base, e);
 #pragma unroll
-    for (int i = 0; i < kFinalPer; ++i)
-      if (e[i].y != 0xffffffffu && (e[i].x >> 21) == d0) atomicAdd(&h[(e[i].x >> 10) & 2047u], 1u);
-  }
-  __syncthreads();
-  uint32_t d1, krem1;
-  final_find_digit<kTopkBins>(h, krem0, &d1, &krem1, scan_lds, res);
-  const uint32_t prefix1 = (d0 << 21) | ((d1 & 2047u) << 10);
-  // ---- digit 2: the last 10 bits -- unless every entry that shares the threshold's 22-bit prefix is a winner (the
-  // usual case: a few thousand entries over 2^22 prefixes leave the threshold's bin with one or two), when the
-  // prefix alone decides
-  uint32_t thr, need_eq;
-  const uint32_t cnt1 = d1 < (uint32_t)kTopkBins ? h[d1] : 0xffffffffu;
-  if (krem1 == cnt1 && prefix1 != 0u) {
-    thr = prefix1 - 1u; need_eq = 0u;          // "above thr" = "prefix at least prefix1"; nothing equals thr among the winners
-  } else {
-    __syncthreads();                            // every thread has read cnt1 before the histogram is cleared
-    for (int i = tid; i < 1024; i += kFinalThreads) h[i] = 0u;
-    __syncthreads();
-    for (uint32_t base = 0; base < total; base += kFinalThreads * kFinalPer) {
-      if (!single) load_batch(base, e);
-#pragma unroll
-      for (int i = 0; i < kFinalPer; ++i)
-        if (e[i].y != 0xffffffffu && (e[i].x >> 10) == (prefix1 >> 10)) atomicAdd(&h[e[i].x & 1023u], 1u);
+        for (int i = 0; i < kFinalPer; ++i)
+          if (e[i].y != 0xffffffffu && (e[i].x >> 10) == (prefix1 >> 10)) atomicAdd(&h[e[i].x & 1023u], 1u);
+      }
+      __syncthreads();
+      uint32_t d2;
+      final_find_digit<1024>(h, krem1, &d2, &need_eq, scan_lds, res);
+      thr = prefix1 | (d2 & 1023u);
     }
-    __syncthreads();
-    uint32_t d2;
-    final_find_digit<1024>(h, krem1, &d2, &need_eq, scan_lds, res);
-    thr = prefix1 | (d2 & 1023u);
   }
   // ---- emit in token order: every key above the threshold, and the first need_eq keys equal to it
   uint32_t gt_done = 0, eq_done = 0;
@@ -617,9 +691,19 @@ hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
   return hipGetLastError();
 }
 
+// the candidates of the compact selection: votes = upper bounds, rep_hist = the lower bounds' histogram
+hipError_t launch_topk_compact(const TopkArgs& a, int B, hipStream_t s) {
+  hipLaunchKernelGGL(topk_compact_kernel, dim3(a.nblk, B), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 // finishing workgroup over a list of exact votes (compact selection)
 hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s) {
-  if (a.k <= 2048) hipLaunchKernelGGL((topk_final_kernel<4, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  // entries per thread: a list of up to 5/4 k sits in registers (the candidates are usually 1.03 to 1.2 k)
+  const int per = (int)(((long)a.k * 5 / 4 + kFinalThreads - 1) / kFinalThreads);
+  if (per <= 2) hipLaunchKernelGGL((topk_final_kernel<2, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  else if (per <= 4) hipLaunchKernelGGL((topk_final_kernel<4, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  else if (per <= 6) hipLaunchKernelGGL((topk_final_kernel<6, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
   else hipLaunchKernelGGL((topk_final_kernel<8, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
   return hipGetLastError();
 }

@@ -28,6 +28,7 @@ struct WsLayout {
   size_t score_partials;   // float [B][kScoreMaxWg][H][2]
   size_t topk_blk;         // uint32 [B][nblk] : per-chunk counts
   size_t topk_list;        // uint2 [B][nblk][kTopkChunk] : compacted (key, token) entries of the short top-k path
+  size_t topk_dense;       // uint2 [B][nblk * kTopkChunk] : compact selection, (vote key, token) of the candidates without gaps (decode only)
   size_t blk_max;          // float [B][score_nblk][H] : compact score pass, per-block head maxima (decode only)
   int score_nblk;          // ceil(max_seq_len / kScoreTileTokens)
   size_t attn_out;         // float [B][H][nsplit][D]
@@ -78,6 +79,7 @@ inline WsLayout ws_layout(const ts_problem* p, int k) {
   w.topk_list = take(B * (size_t)w.topk_nblk * kTopkChunk * 8);
   w.score_nblk = (p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens;
   if (p->chunk == 1) {
+    w.topk_dense = take(B * (size_t)w.topk_nblk * kTopkChunk * 8);
     w.blk_max = take(B * (size_t)w.score_nblk * H * 4);
   }
   if (p->chunk > 1) {
@@ -139,6 +141,22 @@ __device__ __forceinline__ float group8_max(float v) {
   v = fmaxf(v, dpp_f32<0xB1>(v));
   v = fmaxf(v, dpp_f32<0x4E>(v));
   v = fmaxf(v, dpp_f32<0x141>(v));
+  return v;
+}
+
+// inclusive prefix sum over the 64 lanes of a wave, on the DPP network (row shifts, then the rows' last lanes broadcast):
+// six dependent additions instead of six trips through the LDS permute unit
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_add_u32(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+  v = dpp_add_u32<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_add_u32<0x112, 0xf>(v);   // row_shr:2
+  v = dpp_add_u32<0x114, 0xf>(v);   // row_shr:4
+  v = dpp_add_u32<0x118, 0xf>(v);   // row_shr:8
+  v = dpp_add_u32<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add_u32<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
   return v;
 }
 

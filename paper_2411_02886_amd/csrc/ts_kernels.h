@@ -85,22 +85,22 @@ struct TopkArgs {
   int heads;            // virtual sequences per real one (Eq. 4: one per head over transposed scores); 1 = plain
   float* vote_acc;      // Eq. 4: the emit pass adds 1 to vote_acc[real sequence][t] for every winner instead of writing idx
   float* sel_votes;     // compact selection: [B][k] votes of the selected tokens in idx order, or nullptr
-  uint32_t* bound_hist; // compact selection: [B][kBoundHistCopies][kTopkBins] histogram of the vote lower bounds (else nullptr)
-  uint32_t* rep_hist;   // the first histogram was left by the vote kernel, replicated like bound_hist (else nullptr: pass 0 builds it)
+  uint2* dense;         // compact selection: [B][nblk * kTopkChunk] (vote key, token) of the candidates, in token order without gaps
+  uint32_t* rep_hist;   // [B][kBoundHistCopies][kTopkBins] first histogram left by the vote kernel (compact selection: by the bounds
+                        // kernel, of the lower bounds); nullptr = pass 0 builds it
 };
 
 // exact votes of the candidates (tokens whose upper bound reaches the bin of the k-th largest lower bound)
 struct RefineArgs {
-  TopkArgs t;             // votes = the upper bounds; hist / state / blk / list as in the short top-k path
+  TopkArgs t;             // votes = the upper bounds; state / blk / list as in the short top-k path
   const uint8_t* q;
   const uint8_t* k_pool;
   const int32_t* page_indptr;
   const int32_t* page_indices;
   const float* row_stats;
   int H, H_kv, P, p_shift;
-  int HB, hb_shift, NU;
   float scale;
-  int parts;              // workgroups per 2048-token chunk: each re-evaluates its share of the chunk's candidates
+  int parts;              // workgroups per sequence: each re-evaluates an equal share of its candidates
 };
 
 struct SelcacheArgs {
@@ -184,7 +184,9 @@ hipError_t launch_soft_vote(const VoteArgs& a, int B, hipStream_t s);
 hipError_t launch_soft_vote_ranked(const VoteArgs& a, int B, hipStream_t s);
 hipError_t launch_stats_merge(const VoteArgs& a, int B, hipStream_t s);
 hipError_t launch_vote_bounds(const BoundArgs& a, int B, hipStream_t s);
-hipError_t launch_topk_refine(int dtype, int D, int G, const RefineArgs& a, int B, hipStream_t s);
+hipError_t launch_topk_compact(const TopkArgs& a, int B, hipStream_t s);
+hipError_t launch_topk_eval(int dtype, int D, int G, const RefineArgs& a, int B, hipStream_t s);
+constexpr int kStTotal = 5;   // state word that carries the number of candidates from topk_eval_kernel to the finish
 hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s);
 hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s);
 constexpr int kTopkFinalMaxBlk = 8192;   // chunks per sequence the finishing workgroup can index (16 Mi tokens)
