@@ -661,14 +661,13 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
     ChunkAttnArgs c{};
     c.q = (const uint8_t*)q; c.k_pool = (const uint8_t*)p->k_pool; c.v_pool = (const uint8_t*)p->v_pool;
     c.page_indptr = p->page_indptr; c.page_indices = p->page_indices; c.seq_lens = p->seq_lens;
-    c.idx = idx; c.count = count; c.slots = (int32_t*)((uint8_t*)ws + w.attn_slots);
+    c.idx = idx; c.count = count;
     c.out = (uint8_t*)out; c.lse = lse;
     c.C = p->chunk; c.H = p->num_q_heads; c.H_kv = p->num_kv_heads; c.G = p->num_q_heads / p->num_kv_heads;
     c.D = p->head_dim; c.P = p->page_size; c.p_shift = ilog2(p->page_size); c.idx_stride = idx_stride;
     c.max_seq_len = p->max_seq_len; c.sm_scale = sm_scale;
     c.nsplit = w.attn_chunk_nsplit;
     c.n_init = p->num_initial; c.n_local = p->num_local;
-    c.slot_stride = idx_stride + p->num_initial + p->num_local + p->chunk;
     c.part_o = (float*)((uint8_t*)ws + w.attn_chunk_o); c.part_ml = (float*)((uint8_t*)ws + w.attn_chunk_ml);
     return launch_sparse_attn_chunk(c, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
   }

@@ -2,78 +2,81 @@
 // over the shared selected tokens plus the chunk's own tokens up to and including itself, in one
 // joint softmax ([K_select, K_current] of Eq. 2 with a causal mask inside the chunk).
 //
-// Matrix-core flash attention over a gathered key list.  A small kernel first resolves the key list
-// of a sequence (selected tokens, then the chunk's tokens) to physical slots.  In the main kernel a
-// workgroup owns 128 rows (query x head pairs of one KV head; 32 per wave, fragments pinned in
-// registers) and walks the key list in tiles of 32: K rows and V rows of the tile are gathered once
-// into LDS (row-major both; the V operand of P V is read as eight 2-byte pieces down a column), S = Q K^T and O += P V run
-// on v_mfma_f32_32x32x16_bf16, P goes through a wave-private LDS tile to change from the result
-// layout to the operand layout.  The softmax uses a per-row reference exponent that is raised only
-// when a logit would exceed it by 2^16, so the common tile needs no cross-lane traffic; row sums
-// are merged once at the end.  The next tile's rows are in flight while the current one is used.
+// Matrix-core flash attention over a gathered key list.  The G query heads x C queries of one KV head are rows that
+// all meet the same keys.  A workgroup of eight waves owns 128 rows: four waves of 32 rows take the even 64-key tiles
+// of its share of the list, four the odd ones, and the two halves meet in LDS at the end, so that half as many
+// partials have to travel through memory.
+//
+// What bounds it: per 64-key tile a wave issues 32 MFMAs (32 cycles of matrix core each, 8 of the issue port) and
+// 32 x (fma, exp2, half a conversion, half a dot) on the vector ALU, and its phases (scores, weights, output) follow
+// each other; the two waves of a SIMD fill each other's gaps only in part (the matrix core is busy a third of the time;
+// row loads alone take 33 us, arithmetic alone 50 us of the 60).  What was taken out of the loop:
+//   * Scores are formed transposed (K as A operand, Q as B): a lane then holds 32 keys of ONE row, so the running
+//     softmax is two registers per lane, and the weights, rounded to bf16, are the B operand of O^T += V^T P^T
+//     as they stand -- which key sits at which k of the product is free as long as V^T is read the same way.
+//   * V^T is read from the row-major V tile by the transposing LDS read (16 columns x 4 keys per 16 lanes).
+//   * K and V rows go from memory to LDS directly, 16 bytes per lane, each lane fetching the piece that belongs at its
+//     place: pieces are exchanged inside a row (piece ^ swz(key)) so that both reads are free of bank conflicts.
+//   * No maximum over the scores: weights are formed against the row's reference exponent; only if a tile's sum
+//     comes out above 2^30 (or not a number) the reference is raised and the tile's weights are formed again.
+//   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows.
+// 512 queries, H 32/8, D 128, 4096 selected + 512 own keys: 155 + 12 + 5 us (one tile of 32 keys per
+// barrier, weights and V^T through 2-byte LDS accesses, four splits, a slot list built first) -> 61 + 6 us.  Tried
+// without gain: the next block's scores and the previous one's output interleaved with the weights (241 to 256
+// registers, 67 us), fragments read ahead of their use, one 32-key block at a time (62 us).
 #include "ts_kernels.h"
 
 namespace ts {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-constexpr int kCaRows = 128;   // rows per workgroup
-constexpr int kCaTile = 32;    // keys per tile
+constexpr int kCaRows = 128;     // rows per workgroup (four waves of 32)
+constexpr int kCaGroups = 2;     // key groups per workgroup
+constexpr int kCaTile = 64;      // keys per tile
+constexpr float kCaUnset = -1e30f;   // reference exponent of a row that has seen no key
+constexpr float kCaRaise = 1073741824.f;   // a tile sum above this raises the reference
 
-// slots[b][j]: physical slot of the j-th key of sequence b: the count[b] selected tokens, then the
-// chunk's C tokens (logical positions N_b - C ...); with forced tokens the selected ones are preceded by the initial
-// block and followed by the cached tokens just before the chunk
-__global__ __launch_bounds__(256) void chunk_slots_kernel(ChunkAttnArgs a) {
-  const int b = blockIdx.y;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  const int cnt = min(max(a.count[b], 0), a.idx_stride);
-  const int N = min(max(a.seq_lens[b], 0), a.max_seq_len);
-  if (N < a.C) return;                                          // shorter than a chunk: holds none, nothing is attended
-  const int Nc = max(N - a.C, 0);                               // cached tokens before the chunk
-  const int f_lo = min(a.n_init, Nc), f_hi = max(f_lo, Nc - a.n_local);   // forced blocks [0, f_lo) and [f_hi, Nc)
-  const int nsel = f_lo + cnt + (Nc - f_hi);                    // keys every query of the chunk sees
-  if (j >= nsel + a.C) return;
-  int t;
-  if (j < f_lo) t = j;
-  else if (j < f_lo + cnt) t = a.idx[(size_t)b * a.idx_stride + (j - f_lo)];
-  else if (j < nsel) t = f_hi + (j - f_lo - cnt);
-  else t = N - a.C + (j - nsel);
-  t = min(max(t, 0), max(N, 1) - 1);             // a stale or corrupt index must not leave the page table
-  const int page = a.page_indices[a.page_indptr[b] + (t >> a.p_shift)];
-  a.slots[(size_t)b * a.slot_stride + j] = (page << a.p_shift) + (t & (a.P - 1));
+// place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 4 rows x 4 pieces (V^T) each
+// fall on all banks
+template <int D> __device__ __forceinline__ int ca_swz(int key) {
+  return D == 128 ? (((key & 3) << 2) | ((key >> 2) & 3)) : ((((key >> 1) & 1) << 2) | ((key >> 2) & 3));
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void chunk_attn_kernel(ChunkAttnArgs a) {
+__global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
   constexpr int KS = D / 16;                     // k-steps of Q K^T
-  constexpr int NBO = D / 32;                    // 32-column blocks of the output
+  constexpr int NBO = D / 32;                    // 32-row blocks of the transposed output
   constexpr int RBYTES = D * 2;
   constexpr int PPR = RBYTES / 16;               // 16-byte pieces per K/V row
-  constexpr int NLD = kCaTile * PPR / 256;       // gather loads per thread per tile and per pool (2 for D = 128)
-  constexpr int LROW = RBYTES + 16;              // padded K row in LDS
-  constexpr int VROW = kCaTile * 2 + 16;         // padded V^T row in LDS: 32 keys of bf16
-  constexpr float TH = 16.f;
-  static_assert(NLD >= 1, "tile too small for the workgroup");
-  __shared__ __attribute__((aligned(16))) uint8_t s_k[2][kCaTile * LROW];
-  __shared__ __attribute__((aligned(16))) uint8_t s_v[2][kCaTile * LROW];    // V rows as gathered ([key][d]); transposed on the way out
-  __shared__ __attribute__((aligned(16))) uint8_t s_p[4][32 * VROW];
+  constexpr int KPI = 64 / PPR;                  // keys per wave load
+  constexpr int NLD = 16 / KPI;                  // loads per wave, tile and pool: a wave stages 16 keys
+  constexpr int TILE_B = kCaTile * RBYTES;
+  // [buffer][key group][K tile, V tile]
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wave >> 2, rg = wave & 3;       // key group, row group
   const int half = lane >> 5, col = lane & 31;
-  const int rb = blockIdx.x / a.nsplit, split = blockIdx.x % a.nsplit, kvh = blockIdx.y, b = blockIdx.z;
+  // Workgroups that gather the same rows (sequence, KV head, split) sit on one XCD, next to each other in launch order,
+  // so that its L2 fetches the rows once (workgroup L runs on XCD L % 8); the row blocks of a group are dealt to
+  // a.xsplit XCDs where the groups alone would leave some of them idle.
+  const int nrb = (a.C * a.G + kCaRows - 1) / kCaRows, rbs = (nrb + a.xsplit - 1) / a.xsplit;
+  const int vg = ((int)(blockIdx.x >> 3) / rbs) * 8 + (int)(blockIdx.x & 7);
+  const int rb = (vg % a.xsplit) * rbs + (int)(blockIdx.x >> 3) % rbs, group = vg / a.xsplit;
+  if (rb >= nrb) return;
+  const int split = group % a.nsplit, kvh = group / a.nsplit % a.H_kv, b = group / a.nsplit / a.H_kv;
   const int C = a.C, G = a.G, H = a.H;
   const int nrows = C * G;
-  // keys every query sees: forced initial block, selected tokens, forced block before the chunk (see chunk_slots_kernel)
-  const int Nc_ = max(min(max(a.seq_lens[b], 0), a.max_seq_len) - C, 0);
-  const int f_lo_ = min(a.n_init, Nc_), f_hi_ = max(f_lo_, Nc_ - a.n_local);
-  const int cnt = f_lo_ + min(max(a.count[b], 0), a.idx_stride) + (Nc_ - f_hi_);
+  const int N = min(max(a.seq_lens[b], 0), a.max_seq_len);
   const int r0 = rb * kCaRows;
-  if (r0 >= nrows) return;
-  if (min(max(a.seq_lens[b], 0), a.max_seq_len) < C) {
+  if (N < C) {
     // a sequence shorter than the chunk holds no chunk (an idle slot of the batch): its rows are zero, and nothing is
     // read through its page table, which may be empty
-    for (int i = threadIdx.x; i < kCaRows * D; i += 256) {
+    for (int i = threadIdx.x; i < kCaRows * D; i += 512) {
       const int row = r0 + i / D, d = i % D;
       if (row >= nrows) break;
       const size_t hb = ((size_t)b * C + row / G) * H + kvh * G + row % G;
@@ -87,22 +90,34 @@ __global__ __launch_bounds__(256) void chunk_attn_kernel(ChunkAttnArgs a) {
     }
     return;
   }
-  const int c_last = min(C - 1, (r0 + kCaRows - 1) / G);      // last query of this row block
-  const int nkeys = cnt + c_last + 1;                          // keys any row of the block may see
+  // key list: forced initial block, selected tokens, forced block before the chunk (seen by every query), then the
+  // chunk's own tokens
+  const int Nc = N - C;                                         // cached tokens before the chunk
+  const int f_lo = min(a.n_init, Nc), f_hi = max(f_lo, Nc - a.n_local);
+  const int csel = min(max(a.count[b], 0), a.idx_stride);
+  const int cnt = f_lo + csel + (Nc - f_hi);
+  const int c_last = min(C - 1, (r0 + kCaRows - 1) / G);       // last query of this row block
+  const int nkeys = cnt + c_last + 1;                           // keys any row of the block may see
   const int ntile_all = (nkeys + kCaTile - 1) / kCaTile;
   // this workgroup's share of the key list (tiles [tile0, tile0 + ntile)); may be empty
   const int tps = (ntile_all + a.nsplit - 1) / a.nsplit;
   const int tile0 = min(split * tps, ntile_all);
   const int ntile = min(tps, ntile_all - tile0);
-  const int* slots = a.slots + (size_t)b * a.slot_stride;
-  const float c2 = a.sm_scale * 1.44269504088896340736f;
+  const int niter = (ntile + kCaGroups - 1) / kCaGroups;
+  const int32_t* sel = a.idx + (size_t)b * a.idx_stride;
+  const int32_t* pages = a.page_indices + a.page_indptr[b];
+  float c2 = a.sm_scale * 1.44269504088896340736f;
+  if (c2 == 0.f) c2 = 1e-37f;                                   // the same weights (all 1), and a hidden key still gets 0
+  const float hidden = c2 > 0.f ? -INFINITY : INFINITY;         // c2 * hidden = -inf
 
-  // ---- query fragments (A operand of Q K^T): lane holds row = col, k = 16 * ks + 8 * half .. + 8
+  // ---- query fragments (B operand of K Q^T): lane holds row = col, k = 16 * ks + 8 * half .. + 8
+  const int row = r0 + rg * 32 + col;
+  const int qc = row / G;                                       // query of this lane's row
+  const int vis = min(qc, c_last);                              // last token of the chunk that it sees
   bf16x8_t qfrag[KS];
   {
-    const int row = r0 + wave * 32 + col;
     const bool valid = row < nrows;
-    const int c = valid ? row / G : 0, g = valid ? row % G : 0;
+    const int c = valid ? qc : 0, g = valid ? row % G : 0;
     const uint8_t* qp = a.q + ((((size_t)b * C + c) * H + (size_t)kvh * G + g) * D + 8 * half) * 2;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -111,205 +126,258 @@ __global__ __launch_bounds__(256) void chunk_attn_kernel(ChunkAttnArgs a) {
       qfrag[ks] = __builtin_bit_cast(bf16x8_t, v);
     }
   }
-  // rows of the result layout held by this lane: 8 * i + 4 * half + j; the query index decides causality
-  int qidx[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int row = r0 + wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-    qidx[e] = row / G;
-  }
-  float ref[16], lsum[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) { ref[e] = -INFINITY; lsum[e] = 0.f; }
-  f32x16_t oacc[NBO];
+  float ref = kCaUnset, lsum = 0.f;                             // the row's reference exponent; this lane's keys' sum
+  f32x16_t oacc[NBO];                                           // O^T: d = 32 * nb + 8 * (e / 4) + 4 * half + e % 4
 #pragma unroll
   for (int nb = 0; nb < NBO; ++nb)
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[nb][e] = 0.f;
 
-  // ---- gather staging: thread -> (key within pass, 16-byte piece)
-  const int st_key = threadIdx.x / PPR, st_piece = threadIdx.x % PPR;
-  constexpr int KPP = 256 / PPR;                 // keys per pass
-  struct Rows { uint4 k[NLD]; uint4 v[NLD]; };
-  struct Slots { int v[NLD]; };
-  // the slots of a tile are read one tile earlier than its rows: the slot list and the pools are two dependent
-  // round trips, and a tile's arithmetic is too short to hide both
-  auto fetch_slots = [&](int tile) -> Slots {
-    Slots r;
+  // ---- staging: this wave's 16 keys of its group's tile, load i covering keys 16 * rg + i * KPI + lane / PPR.  A list
+  // entry becomes a row in three steps, one iteration apart: token id (raw_*), page id (page_*), rows.  What an
+  // iteration consumes was loaded in the one before and has been waited for at its top, so nothing waits behind the rows.
+  const int st_key = lane / PPR, st_pos = lane % PPR;
+  int raw_id[NLD], page_id[NLD], page_off[NLD];
+  auto key_of = [&](int it, int i) { return min((tile0 + it * kCaGroups + kg) * kCaTile + rg * 16 + i * KPI + st_key, nkeys - 1); };   // past the end: the last key
+  auto fetch_ids = [&](int it) {
 #pragma unroll
-    for (int it = 0; it < NLD; ++it) r.v[it] = slots[min((tile0 + tile) * kCaTile + st_key + it * KPP, nkeys - 1)];   // ragged last tile: shadow the last key
-    return r;
+    for (int i = 0; i < NLD; ++i) raw_id[i] = sel[min(max(key_of(it, i) - f_lo, 0), a.idx_stride - 1)];
   };
-  auto fetch = [&](const Slots& sl) -> Rows {
-    Rows r;
-#pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      const size_t o = ((size_t)sl.v[it] * a.H_kv + kvh) * RBYTES + st_piece * 16;
-      r.k[it] = *reinterpret_cast<const uint4*>(a.k_pool + o);
-      r.v[it] = *reinterpret_cast<const uint4*>(a.v_pool + o);
-    }
-    return r;
+  auto token_of = [&](int it, int i) -> int {
+    const int j = key_of(it, i);
+    int t = (j < f_lo) ? j : raw_id[i];
+    t = (j < f_lo + csel) ? t : f_hi + (j - f_lo - csel);
+    t = (j < cnt) ? t : Nc + (j - cnt);
+    return min(max(t, 0), N - 1);                               // a stale or corrupt index must not leave the page table
   };
-  auto stage = [&](int buf, const Rows& r) {
+  auto fetch_pages = [&](const int (&t)[NLD]) {
 #pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      const int key = st_key + it * KPP;
-      *reinterpret_cast<uint4*>(&s_k[buf][key * LROW + st_piece * 16]) = r.k[it];
-      *reinterpret_cast<uint4*>(&s_v[buf][key * LROW + st_piece * 16]) = r.v[it];
+    for (int i = 0; i < NLD; ++i) { page_id[i] = pages[t[i] >> a.p_shift]; page_off[i] = t[i] & (a.P - 1); }
+  };
+  // Memory to LDS, 16 bytes per lane: the wave's 64 lanes fill 1 KiB from the (uniform) LDS address.  Written in
+  // assembly because the compiler, which cannot tell the two buffers apart, makes every later LDS read wait for the
+  // builtin form; completion is awaited by the vmcnt(0) before the barrier at the top of the loop.
+  auto load_rows = [&](int buf) {
+    const uint32_t kt = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem +
+                        (uint32_t)((buf * kCaGroups + kg) * 2 * TILE_B + rg * 16 * RBYTES);
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int key = i * KPI + st_key;                         // the swizzle looks at the low four bits only
+      const size_t slot = ((size_t)page_id[i] << a.p_shift) + page_off[i];
+      const size_t o = (slot * a.H_kv + kvh) * RBYTES + (size_t)((st_pos ^ ca_swz<D>(key)) * 16);
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(kt + i * KPI * RBYTES);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(a.k_pool + o) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst + TILE_B), "v"(a.v_pool + o) : "memory", "m0");
     }
   };
 
-  Rows pre;
+  if (niter > 0) {
+    int t[NLD];
+    fetch_ids(0);
 #pragma unroll
-  for (int it = 0; it < NLD; ++it) { pre.k[it] = make_uint4(0, 0, 0, 0); pre.v[it] = make_uint4(0, 0, 0, 0); }
-  Slots spre;
+    for (int i = 0; i < NLD; ++i) t[i] = token_of(0, i);
+    fetch_pages(t);
+    fetch_ids(1);
+    load_rows(0);
 #pragma unroll
-  for (int it = 0; it < NLD; ++it) spre.v[it] = 0;
-  stage(0, fetch(fetch_slots(0)));
-  if (ntile > 1) pre = fetch(fetch_slots(1));
-  if (ntile > 2) spre = fetch_slots(2);
-  __syncthreads();
-
-  for (int tile = 0; tile < ntile; ++tile) {
-    const int buf = tile & 1;
-    if (tile + 1 < ntile) stage(buf ^ 1, pre);
-    if (tile + 2 < ntile) pre = fetch(spre);
-    if (tile + 3 < ntile) spre = fetch_slots(tile + 3);
-
-    // ---- S = Q K^T for 32 rows x 32 keys
-    f32x16_t sacc;
+    for (int i = 0; i < NLD; ++i) t[i] = token_of(1, i);
+    fetch_pages(t);
+    fetch_ids(2);
+  }
+  const int ka_swz = ca_swz<D>(col);                            // K fragment: key 32 * kb + col
+  // V^T: 16 lanes read 4 keys x 16 columns; lane i of them reads key i / 4, columns 4 * (i % 4) ..
+  const int vt_key = 4 * half + ((lane & 15) >> 2), vt_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  for (int it = 0; it < niter; ++it) {
+    const int buf = it & 1;
+    __builtin_amdgcn_s_waitcnt(0x0f70);                         // vmcnt(0): this wave's rows of the tile (and the ids behind them) are there
+    __syncthreads();                                            // ... everybody's; and the other buffer has been read
+    if (it + 1 < niter) {
+      int t[NLD];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const uint4 bv = *reinterpret_cast<const uint4*>(&s_k[buf][col * LROW + (ks * 2 + half) * 16]);
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfrag[ks], __builtin_bit_cast(bf16x8_t, bv), sacc, 0, 0, 0);
+      for (int i = 0; i < NLD; ++i) t[i] = token_of(it + 2, i);
+      load_rows(buf ^ 1);
+      fetch_pages(t);
+      fetch_ids(it + 3);
     }
-    // ---- mask and exponent arguments; key j of this lane's column
-    const int j = (tile0 + tile) * kCaTile + col;
-    const int cq = j - cnt;                                    // >= 0: the chunk's token cq
-    float raw[16], ar[16];
-    float amax = -INFINITY;
+    const int tile = tile0 + it * kCaGroups + kg;
+    if (it * kCaGroups + kg >= ntile) continue;                 // the last round of the odd group may be empty
+    const uint8_t* kt = smem + (size_t)((buf * kCaGroups + kg) * 2) * TILE_B;
+    const uint8_t* vt = kt + TILE_B;
+    // ---- S^T for 64 keys x 32 rows, two independent chains
+    f32x16_t s[2];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const bool vis = (j < cnt) || (j < nkeys && cq <= qidx[e]);
-      raw[e] = vis ? c2 * sacc[e] : -INFINITY;
-      ar[e] = raw[e] - ref[e];                                 // +inf while the reference is unset and the key visible
-      ar[e] = (raw[e] == -INFINITY) ? -INFINITY : ar[e];
-      amax = fmaxf(amax, ar[e]);
-    }
-    if (__builtin_amdgcn_ballot_w64(amax > TH) != 0) {         // first visible key of a row, or a logit far above the reference
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float rmax = raw[e];
+      for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
 #pragma unroll
-        for (int o = 1; o < 32; o <<= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, o));   // over the row's 32 columns
-        if (rmax - ref[e] > TH) {                              // same decision in all lanes of the row
-          const float f = (ref[e] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ref[e] - rmax);
-          lsum[e] *= f;
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-          for (int nb = 0; nb < NBO; ++nb) oacc[nb][e] *= f;
-          ref[e] = rmax;
-          ar[e] = (raw[e] == -INFINITY) ? -INFINITY : raw[e] - rmax;
-        }
+      for (int kb = 0; kb < 2; ++kb) {
+        const uint4 av = *reinterpret_cast<const uint4*>(kt + (kb * 32 + col) * RBYTES + (((ks * 2 + half) ^ ka_swz) * 16));
+        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av), qfrag[ks], s[kb], 0, 0, 0);
       }
-    }
-    // ---- P (bf16) into the wave's LDS tile, row-major [row][key], and the row sums
-    uint8_t* pw = s_p[wave];
+    // ---- weights against the reference; keys the row may not see get none
+    const int j0 = tile * kCaTile;
+    if (j0 + kCaTile > cnt) {                                   // the same for the whole wave
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float p = __builtin_amdgcn_exp2f(ar[e]);           // exp2(-inf) = 0 for masked keys
-      const uint32_t pb = f32_to_bf16_bits(p);
-      lsum[e] += __uint_as_float(pb << 16);                    // the sum uses the rounded weights that multiply V
-      const int row = 8 * (e >> 2) + 4 * half + (e & 3);
-      *reinterpret_cast<uint16_t*>(&pw[row * VROW + col * 2]) = (uint16_t)pb;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // ---- O += P V: A = P[row = col][keys 16 * ks + 8 * half ..], B = V^T[d = 32 * nb + col][same keys]
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int ks = 0; ks < kCaTile / 16; ++ks) {
-      const uint4 pa = *reinterpret_cast<const uint4*>(&pw[col * VROW + (ks * 16 + 8 * half) * 2]);
+        for (int e = 0; e < 16; ++e) {
+          const int cq = j0 + kb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) - cnt;   // >= 0: the chunk's token cq
+          s[kb][e] = cq <= vis ? s[kb][e] : hidden;
+        }
+    }
+    uint32_t pk[2][8];
+    float sum;
+    for (int tries = 0; tries < 2; ++tries) {
+      float part[2] = {0.f, 0.f};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const bf16x2_t p = {(__bf16)__builtin_amdgcn_exp2f(fmaf(c2, s[kb][e], -ref)), (__bf16)__builtin_amdgcn_exp2f(fmaf(c2, s[kb][e + 1], -ref))};
+          const bf16x2_t one = {(__bf16)1.f, (__bf16)1.f};
+          pk[kb][e >> 1] = __builtin_bit_cast(uint32_t, p);
+          part[kb] = __builtin_amdgcn_fdot2_f32_bf16(p, one, part[kb], false);    // the sum of the rounded weights that multiply V
+        }
+      sum = part[0] + part[1];
+      if (__builtin_amdgcn_ballot_w64(!(sum <= kCaRaise)) == 0) break;
+      // first visible key of a row, or a logit far above the reference.  Straight-line code: a branch per lane here
+      // makes the compiler copy the accumulators on the common path too.
+      float m = ref;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) m = fmaxf(m, c2 * s[kb][e]);
+      m = fmaxf(m, __shfl_xor(m, 32));                          // both halves of a row raise its reference together
+      const float f = __builtin_amdgcn_exp2f(ref - m);          // 1 where nothing changes, 0 while the reference is unset
+      lsum *= f;
+#pragma unroll
+      for (int nb = 0; nb < NBO; ++nb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[nb][e] *= f;
+      ref = m;
+    }
+    lsum += sum;
+    // ---- O^T += V^T P^T: k-step ks2 of a block takes keys 16 * ks2 + 4 * half + {0..3, 8..11}, the keys of s[8 * ks2 ..]
+#pragma unroll
+    for (int k4 = 0; k4 < 4; ++k4) {
+      const uint32_t (&pw)[8] = pk[k4 >> 1];
+      const int o = 4 * (k4 & 1);
+      const uint4 pb = make_uint4(pw[o], pw[o + 1], pw[o + 2], pw[o + 3]);
 #pragma unroll
       for (int nb = 0; nb < NBO; ++nb) {
-        // B operand: column d = 32 * nb + col of eight consecutive keys -- eight 2-byte reads down a column of the
-        // row-major V tile (a wave's 32 columns of one key are 64 contiguous bytes: no bank conflicts; writing V
-        // transposed instead cost 16-way conflicts on 2-byte stores)
-        const uint8_t* vcol = &s_v[buf][(ks * 16 + 8 * half) * LROW + (nb * 32 + col) * 2];
-        uint32_t vw[4];
+        s16x4_t v[2];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const uint32_t lo16 = *reinterpret_cast<const uint16_t*>(vcol + (2 * jj) * LROW);
-          const uint32_t hi16 = *reinterpret_cast<const uint16_t*>(vcol + (2 * jj + 1) * LROW);
-          vw[jj] = lo16 | (hi16 << 16);
+        for (int h8 = 0; h8 < 2; ++h8) {
+          const int key = k4 * 16 + h8 * 8 + vt_key, c = nb * 32 + vt_col;
+          const uint8_t* p = vt + key * RBYTES + (((c >> 3) ^ ca_swz<D>(key)) * 16) + (c & 7) * 2;
+          v[h8] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)p);
         }
-        const uint4 vb = make_uint4(vw[0], vw[1], vw[2], vw[3]);
-        oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pa), __builtin_bit_cast(bf16x8_t, vb),
-                                                            oacc[nb], 0, 0, 0);
+        const uint2 v0 = __builtin_bit_cast(uint2, v[0]), v1 = __builtin_bit_cast(uint2, v[1]);
+        oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(v0.x, v0.y, v1.x, v1.y)),
+                                                            __builtin_bit_cast(bf16x8_t, pb), oacc[nb], 0, 0, 0);
       }
     }
-    __syncthreads();
   }
 
-  // ---- finish: row sums over the 32 columns; normalise and write, or hand the partial to the merge kernel
+  // ---- the two key groups meet: the odd group's rows through LDS
+  lsum += __shfl_xor(lsum, 32);
+  __syncthreads();
+  float* xo = reinterpret_cast<float*>(smem) + (size_t)rg * (NBO * 16 + 2) * 64 + lane;   // [row group][register][lane]
+  if (kg == 1) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    float l = lsum[e];
+    for (int nb = 0; nb < NBO; ++nb)
 #pragma unroll
-    for (int o = 1; o < 32; o <<= 1) l += __shfl_xor(l, o);
-    const int row = r0 + wave * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-    if (row < nrows) {
-      const int c = row / G, g = row % G;
-      const size_t hb = ((size_t)b * C + c) * H + kvh * G + g;
-      if (a.nsplit == 1) {
-        const float inv = l > 0.f ? 1.f / l : 0.f;
+      for (int e = 0; e < 16; ++e) xo[(nb * 16 + e) * 64] = oacc[nb][e];
+    xo[(NBO * 16) * 64] = ref; xo[(NBO * 16 + 1) * 64] = lsum;
+  }
+  __syncthreads();
+  if (kg == 1 || row >= nrows) return;
+  const float ref1 = xo[(NBO * 16) * 64], l1 = xo[(NBO * 16 + 1) * 64];
+  const float m = fmaxf(ref, ref1);
+  const float w0 = __builtin_amdgcn_exp2f(ref - m), w1 = __builtin_amdgcn_exp2f(ref1 - m);
+  const float l = fmaf(w1, l1, w0 * lsum);
+  const size_t hb = ((size_t)b * C + qc) * H + kvh * G + row % G;
+  auto merged = [&](int nb, int q4) -> float4 {                 // O[row][d .. d + 3], d = 32 * nb + 8 * q4 + 4 * half
+    float o[4];
 #pragma unroll
-        for (int nb = 0; nb < NBO; ++nb)
-          reinterpret_cast<uint16_t*>(a.out)[hb * D + nb * 32 + col] = (uint16_t)f32_to_bf16_bits(oacc[nb][e] * inv);
-        if (a.lse != nullptr && col == 0) a.lse[hb] = l > 0.f ? (ref[e] + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f : -INFINITY;
-      } else {
-        float* po = a.part_o + (hb * a.nsplit + split) * D;
+    for (int e = 0; e < 4; ++e) o[e] = fmaf(w1, xo[(nb * 16 + q4 * 4 + e) * 64], w0 * oacc[nb][q4 * 4 + e]);
+    return make_float4(o[0], o[1], o[2], o[3]);
+  };
+  if (a.nsplit == 1) {
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    uint8_t* po = a.out + (hb * D + half * 4) * 2;
 #pragma unroll
-        for (int nb = 0; nb < NBO; ++nb) po[nb * 32 + col] = oacc[nb][e];
-        if (col == 0) { float* pm = a.part_ml + (hb * a.nsplit + split) * 2; pm[0] = ref[e]; pm[1] = l; }
+    for (int nb = 0; nb < NBO; ++nb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 o = merged(nb, q4);
+        *reinterpret_cast<uint2*>(po + (nb * 32 + q4 * 8) * 2) =
+            make_uint2(f32_to_bf16_bits(o.x * inv) | (f32_to_bf16_bits(o.y * inv) << 16), f32_to_bf16_bits(o.z * inv) | (f32_to_bf16_bits(o.w * inv) << 16));
       }
+    if (half == 0 && a.lse != nullptr) a.lse[hb] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f : -INFINITY;
+  } else {
+    float* po = a.part_o + (hb * a.nsplit + split) * D + half * 4;
+#pragma unroll
+    for (int nb = 0; nb < NBO; ++nb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) *reinterpret_cast<float4*>(po + nb * 32 + q4 * 8) = merged(nb, q4);
+    if (half == 0) {
+      float* pm = a.part_ml + (hb * a.nsplit + split) * 2;
+      pm[0] = l > 0.f ? m : -INFINITY; pm[1] = l;
     }
   }
 }
 
 // Merges the key-list splits of one row: with M = max_s ref_s (base-2 exponents),
-// out = sum_s 2^(ref_s - M) O_s / sum_s 2^(ref_s - M) l_s.  One workgroup of D threads per row.
+// out = sum_s 2^(ref_s - M) O_s / sum_s 2^(ref_s - M) l_s.  D / 4 lanes per row, 16 bytes of every split's partial each.
 template <int D>
-__global__ __launch_bounds__(D) void chunk_attn_merge_kernel(ChunkAttnArgs a) {
-  const size_t hb = blockIdx.x;
-  const int d = threadIdx.x;
-  const float* pm = a.part_ml + hb * a.nsplit * 2;
+__global__ __launch_bounds__(256) void chunk_attn_merge_kernel(ChunkAttnArgs a, int nrow) {
+  constexpr int LPR = D / 4;
+  const int hb = blockIdx.x * (256 / LPR) + (int)threadIdx.x / LPR, d = ((int)threadIdx.x % LPR) * 4;
+  if (hb >= nrow) return;
+  const float* pm = a.part_ml + (size_t)hb * a.nsplit * 2;
   float M = -INFINITY;
   for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, pm[2 * s]);
-  float L = 0.f, o = 0.f;
+  float L = 0.f;
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s = 0; s < a.nsplit; ++s) {
     const float r = pm[2 * s];
     const float w = (r == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(r - M);
+    const float4 x = *reinterpret_cast<const float4*>(a.part_o + ((size_t)hb * a.nsplit + s) * D + d);
     L = fmaf(w, pm[2 * s + 1], L);
-    o = fmaf(w, a.part_o[(hb * a.nsplit + s) * D + d], o);
+    o.x = fmaf(w, x.x, o.x); o.y = fmaf(w, x.y, o.y); o.z = fmaf(w, x.z, o.z); o.w = fmaf(w, x.w, o.w);
   }
-  reinterpret_cast<uint16_t*>(a.out)[hb * D + d] = (uint16_t)f32_to_bf16_bits(L > 0.f ? o / L : 0.f);
-  if (a.lse != nullptr && d == 0) a.lse[hb] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994530942f : -INFINITY;
+  const bool any = L > 0.f;
+  const uint2 w = make_uint2(f32_to_bf16_bits(any ? o.x / L : 0.f) | (f32_to_bf16_bits(any ? o.y / L : 0.f) << 16),
+                             f32_to_bf16_bits(any ? o.z / L : 0.f) | (f32_to_bf16_bits(any ? o.w / L : 0.f) << 16));
+  *reinterpret_cast<uint2*>(a.out + ((size_t)hb * D + d) * 2) = w;
+  if (a.lse != nullptr && d == 0) a.lse[hb] = any ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994530942f : -INFINITY;
+}
+
+template <int D>
+static hipError_t chunk_attn_launch(ChunkAttnArgs a, int B, hipStream_t s) {
+  const int nrb = (a.C * a.G + kCaRows - 1) / kCaRows;
+  const size_t lds = (size_t)2 * kCaGroups * 2 * kCaTile * D * 2;      // 128 KiB for D = 128: one workgroup per CU
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chunk_attn_kernel<D>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const int groups = B * a.H_kv * a.nsplit;                            // times xsplit: a multiple of 8
+  a.xsplit = groups % 8 == 0 ? 1 : groups % 4 == 0 ? 2 : groups % 2 == 0 ? 4 : 8;
+  const int rbs = (nrb + a.xsplit - 1) / a.xsplit;
+  hipLaunchKernelGGL(chunk_attn_kernel<D>, dim3((unsigned)(groups * a.xsplit * rbs)), dim3(512), lds, s, a);
+  if (a.nsplit > 1) {
+    const int rows = B * a.C * a.H, rpw = 256 / (D / 4);
+    hipLaunchKernelGGL(chunk_attn_merge_kernel<D>, dim3((rows + rpw - 1) / rpw), dim3(256), 0, s, a, rows);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_sparse_attn_chunk(const ChunkAttnArgs& a, int B, hipStream_t s) {
-  hipLaunchKernelGGL(chunk_slots_kernel, dim3((a.slot_stride + 255) / 256, B), dim3(256), 0, s, a);
-  const int nrb = (a.C * a.G + kCaRows - 1) / kCaRows;
-  const dim3 grid(nrb * a.nsplit, a.H_kv, B);
-  if (a.D == 128) hipLaunchKernelGGL(chunk_attn_kernel<128>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(chunk_attn_kernel<64>, grid, dim3(256), 0, s, a);
-  if (a.nsplit > 1) {
-    const int rows = B * a.C * a.H;
-    if (a.D == 128) hipLaunchKernelGGL(chunk_attn_merge_kernel<128>, dim3(rows), dim3(128), 0, s, a);
-    else hipLaunchKernelGGL(chunk_attn_merge_kernel<64>, dim3(rows), dim3(64), 0, s, a);
-  }
-  return hipGetLastError();
+  return a.D == 128 ? chunk_attn_launch<128>(a, B, s) : chunk_attn_launch<64>(a, B, s);
 }
 
 }  // namespace ts

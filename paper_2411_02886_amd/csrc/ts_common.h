@@ -35,7 +35,6 @@ struct WsLayout {
   size_t attn_ml;          // float [B][H][nsplit][2]
   size_t pf_stat_part;     // float [B][TS][C][H][2]            (chunk > 1 only)
   size_t pf_vote_part;     // float [B][RB * H_kv][max_seq_len] (chunk > 1 only)
-  size_t attn_slots;       // int32 [B][k + C]                  (chunk > 1 only)
   size_t attn_chunk_o;     // float [B][C][H][nsplit][D]        (chunk > 1 with key-list splits)
   size_t attn_chunk_ml;    // float [B][C][H][nsplit][2]
   int attn_chunk_nsplit;
@@ -47,13 +46,13 @@ struct WsLayout {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Key-list splits of the chunk-form attention: its rows alone give few waves (config 5: 512 on 1024 SIMDs), so the
-// key list is split until about two waves per SIMD are in flight; every split keeps at least four 32-key tiles.
+// Key-list splits of the chunk-form attention: a workgroup of eight waves owns 128 rows and fills a CU, so the key list
+// is split until there is about one workgroup per CU; every split keeps at least four 64-key tiles (two per key group).
 inline int chunk_attn_splits(const ts_problem* p, int k) {
   const int G = p->num_q_heads / p->num_kv_heads;
-  const long waves = (long)((p->chunk * G + 127) / 128) * 4 * p->num_kv_heads * p->batch;
-  const int ntile = (k + p->num_initial + p->num_local + p->chunk + 31) / 32;
-  int s = (int)((2048 + waves - 1) / waves);
+  const long wgs = (long)((p->chunk * G + 127) / 128) * p->num_kv_heads * p->batch;
+  const int ntile = (k + p->num_initial + p->num_local + p->chunk + 63) / 64;
+  int s = (int)((256 + wgs / 2) / wgs);
   if (s > 8) s = 8;
   if (s > ntile / 4) s = ntile / 4;
   if (s < 1) s = 1;
@@ -98,7 +97,6 @@ inline WsLayout ws_layout(const ts_problem* p, int k) {
   w.attn_out = take(B * H * (size_t)w.attn_nsplit * D * 4);
   w.attn_ml = take(B * H * (size_t)w.attn_nsplit * 2 * 4);
   if (p->chunk > 1) {
-    w.attn_slots = take(B * ((size_t)k + p->num_initial + p->num_local + p->chunk) * 4);
     w.attn_chunk_nsplit = chunk_attn_splits(p, k);
     if (w.attn_chunk_nsplit > 1) {
       w.attn_chunk_o = take(B * p->chunk * H * (size_t)w.attn_chunk_nsplit * D * 4);

@@ -164,13 +164,12 @@ struct ChunkAttnArgs {
   const int32_t* seq_lens;
   const int32_t* idx;
   const int32_t* count;
-  int32_t* slots;            // [B][idx_stride + C] physical slots of the key list
   uint8_t* out;              // [B][C][H][D] bf16
   float* lse;                // [B][C][H] or null
   int C, H, H_kv, G, D, P, p_shift, idx_stride, max_seq_len;
   int nsplit;                // key-list splits per row block (1 = the kernel writes the result itself)
+  int xsplit;                // XCDs that the row blocks of one (sequence, KV head, split) are dealt to (set by the launch)
   int n_init, n_local;       // forced cached tokens attended before / after the selected ones
-  int slot_stride;           // row stride of slots: idx_stride + n_init + n_local + C
   float* part_o;             // [B][C][H][nsplit][D] un-normalised partial outputs (nsplit > 1)
   float* part_ml;            // [B][C][H][nsplit][2] (reference exponent, row sum) of each partial
   float sm_scale;
