@@ -25,6 +25,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 constexpr int kPfRowsPerWg = 256;
 constexpr int kPfTile = 64;            // tokens per tile
 constexpr float kRefHead = 32.f;       // head room (log2 units) a raised reference exponent gets in sweep 1
+constexpr float kRaiseAt = 1.8446744e19f;   // 2^64: a lane's sum over a block above this raises the reference
 
 // XCD-aware decode of the linear workgroup id: (row block, group) with group = (sequence, KV head, split)
 __device__ __forceinline__ bool pf_decode_block(const PrefillArgs& a, int* rb, int* b, int* kvh, int* split) {
@@ -91,8 +92,8 @@ __global__ __launch_bounds__(256, 2) void prefill_qk_kernel(PrefillArgs a) {
   // Sweep 1 multiplies the same fragments the other way round (K tile as A, Q as B: the same products summed in the same
   // order, S transposed): a lane then holds 16 tokens of ONE query row per block, so the row's running statistics are two
   // registers per block instead of 32 -- a reference exponent `off1` (log2 units) and the sum of exp2(c2 * s - off1) over
-  // the lane's tokens.  The reference is raised only when an argument would exceed 2^64 (rare: a raised reference gets
-  // 2^32 of head room), so the common path is one fma, one exp2 and one add per score plus half a max.
+  // the lane's tokens.  The reference is raised only when a block's sum comes out above 2^64 (rare: a raised reference
+  // gets 2^32 of head room), so the common path is one fma, one exp2 and one add per score.
   float off[2][16], aux[2][16];                  // sweep 2 only
   float off1[2] = {-INFINITY, -INFINITY}, aux1[2] = {0.f, 0.f};   // sweep 1 only (see below)
   if (SWEEP == 2) {
@@ -182,48 +183,22 @@ __global__ __launch_bounds__(256, 2) void prefill_qk_kernel(PrefillArgs a) {
     }
   };
   using K0 = std::integral_constant<int, 0>;
-  using KH = std::integral_constant<int, KS / 2>;
   using KE = std::integral_constant<int, KS>;
   auto mfma_block = [&](int buf, int nb, f32x16_t (&acc)[2]) { mfma_part(buf, nb, acc, K0{}, KE{}); };
 
   // Softmax arithmetic of one block on the vector ALU, overlapped with the MFMAs of the next block `nacc`.
-  // Sweep 1 has a (rare) branch in the middle -- a reference has to be raised -- and the scheduler cannot move MFMAs
-  // across it, so half of the next block's k-steps are issued before it and half after it.  RAGGED: the tile holds
+  // RAGGED: the tile holds
   // columns outside the ranked range; they get weight 0 in the sum (a full tile needs neither mask nor weight).
   auto step = [&](auto ragged, const f32x16_t (&acc)[2], int tile, int nb, int cbuf, int nbuf, int nnb, f32x16_t (&nacc)[2]) __attribute__((always_inline)) {
     constexpr bool RAGGED = decltype(ragged)::value;
     if (SWEEP == 1) {
       // acc[mb][e]: token 8 * (e / 4) + 4 * half + e % 4 of the block, query row mb * 32 + col
-      mfma_part(nbuf, nnb, nacc, K0{}, KH{});
-      float mraw[2], xm[2];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        float m = acc[mb][0];
-#pragma unroll
-        for (int e = 1; e < 16; ++e) m = fmaxf(m, acc[mb][e]);
-        mraw[mb] = m;
-        xm[mb] = fmaf(c2, m, -off1[mb]);          // the largest argument (c2 >= 0); +inf while off1 is unset
-      }
-      // first block of a lane, or a score far above the reference (tokens outside the ranked range shadow a real
-      // token or are real tokens: a reference they raise is as good as any other)
-      if (__builtin_amdgcn_ballot_w64(fmaxf(xm[0], xm[1]) > 64.f) != 0) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-          if (xm[mb] > 64.f) {
-            // the new reference sits kRefHead above the value that forced it: without head room the next larger
-            // score would raise it again
-            const float noff = c2 * mraw[mb] + kRefHead;
-            aux1[mb] = (off1[mb] == -INFINITY) ? 0.f : aux1[mb] * __builtin_amdgcn_exp2f(off1[mb] - noff);
-            off1[mb] = noff;
-          }
-      }
-      mfma_part(nbuf, nnb, nacc, KH{}, KE{});
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
+      mfma_part(nbuf, nnb, nacc, K0{}, KE{});
+      auto sum_of = [&](int mb) __attribute__((always_inline)) -> float {
         float s0 = 0.f, s1 = 0.f;
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
-          float e0 = __builtin_amdgcn_exp2f(fmaf(c2, acc[mb][e], -off1[mb]));        // arguments are <= 64: finite
+          float e0 = __builtin_amdgcn_exp2f(fmaf(c2, acc[mb][e], -off1[mb]));
           float e1 = __builtin_amdgcn_exp2f(fmaf(c2, acc[mb][e + 1], -off1[mb]));
           if (RAGGED) {
             const int t0 = tile * kPfTile + nb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
@@ -232,8 +207,30 @@ __global__ __launch_bounds__(256, 2) void prefill_qk_kernel(PrefillArgs a) {
           }
           s0 += e0; s1 += e1;
         }
-        aux1[mb] += s0 + s1;
+        return s0 + s1;
+      };
+      float p0 = sum_of(0), p1 = sum_of(1);
+      // first ranked block of a lane, or a score far above the reference: the reference is raised and the sums are
+      // formed again (tokens outside the ranked range shadow a real token or are real tokens: a reference they raise
+      // is as good as any other).  Looking at the sums instead of the largest score first saves a max per two scores
+      // and leaves all of the next block's MFMAs in one piece of straight-line code with the exponentials.
+      if (__builtin_amdgcn_ballot_w64(!(p0 <= kRaiseAt) || !(p1 <= kRaiseAt)) != 0) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          if (!((mb == 0 ? p0 : p1) <= kRaiseAt)) {
+            float m = acc[mb][0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) m = fmaxf(m, acc[mb][e]);
+            // the new reference sits kRefHead above the value that forced it: without head room the next larger
+            // score would raise it again
+            const float noff = c2 * m + kRefHead;
+            aux1[mb] = (off1[mb] == -INFINITY) ? 0.f : aux1[mb] * __builtin_amdgcn_exp2f(off1[mb] - noff);
+            off1[mb] = noff;
+          }
+        }
+        p0 = sum_of(0); p1 = sum_of(1);
       }
+      aux1[0] += p0; aux1[1] += p1;
     } else {
       mfma_part(nbuf, nnb, nacc, K0{}, KE{});
       float cs = 0.f;

@@ -59,6 +59,27 @@ inline int chunk_attn_splits(const ts_problem* p, int k) {
   return s;
 }
 
+// Token splits of the chunked-prefill sweeps.  The chip holds 512 workgroups at a time (two per CU), so the splits are
+// those whose workgroups fill whole rounds: a workgroup costs its tiles plus about 2.5 tiles of start (query fragments,
+// row statistics, first loads), and a single round leaves the chip waiting for its slowest workgroup -- the more so when
+// the sequences of a batch have different lengths.  (2 x 300 queries of H 28/4 over 12007 and 30011 tokens: 28 splits in
+// four rounds 121 + 140 us, 14 in two 114 + 129, 7 in one 129 + 141; 512 queries of H 32/8 over 262144: 16 and 32 the same.)
+inline int prefill_token_splits(const ts_problem* p, int row_blocks) {
+  const int ntile = (p->max_seq_len + 63) / 64;
+  const long pairs = (long)p->batch * p->num_kv_heads;
+  const double uneven = p->batch > 1 ? 0.15 : 0.03;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int t = 1; t <= 64 && t <= ntile; ++t) {
+    const long n = (pairs * t + 7) / 8 * 8 * row_blocks;
+    if (t > 1 && n > 2048) break;
+    const long rounds = (n + 511) / 512;
+    const double cost = (double)rounds * ((ntile + t - 1) / t + 2.5) * (1.0 + uneven / (double)rounds);
+    if (t == 1 || cost < best_cost) { best = t; best_cost = cost; }
+  }
+  return best;
+}
+
 inline WsLayout ws_layout(const ts_problem* p, int k) {
   WsLayout w{};
   const size_t B = (size_t)p->batch, H = (size_t)p->num_q_heads, D = (size_t)p->head_dim;
@@ -84,12 +105,8 @@ inline WsLayout ws_layout(const ts_problem* p, int k) {
   if (p->chunk > 1) {
     const int G = p->num_q_heads / p->num_kv_heads;
     w.pf_rb = (p->chunk * G + 255) / 256;
-    const int ntile = (p->max_seq_len + 63) / 64;
-    int ts = 2048 / (p->batch * p->num_kv_heads * w.pf_rb);
-    if (ts > 64) ts = 64;
-    if (ts > ntile) ts = ntile;
-    if (ts < 1) ts = 1;
-    w.pf_ts = ts;
+    w.pf_ts = prefill_token_splits(p, w.pf_rb);
+    const int ts = w.pf_ts;
     w.pf_stat_part = take(B * (size_t)ts * p->chunk * H * 2 * 4);
     w.pf_vote_part = take(B * (size_t)w.pf_rb * p->num_kv_heads * (size_t)p->max_seq_len * 4);
   }
