@@ -680,18 +680,27 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
   a.part_ml = (float*)((uint8_t*)ws + w.attn_ml);
   a.H = p->num_q_heads; a.H_kv = p->num_kv_heads; a.P = p->page_size; a.p_shift = ilog2(p->page_size);
   a.idx_stride = idx_stride; a.max_seq_len = p->max_seq_len; a.sm_scale = sm_scale;
-  // chunks per workgroup: one while the chunks alone are few workgroups (a latency problem), four when there are many
-  // thousands (a throughput problem: the next chunk's rows are in flight while a chunk is worked on).  Measured
-  // with 2048 tokens per sequence, H 32/8: 32 sequences 63.8 -> 59.1 us, 64 sequences 142.3 -> 134.7 us; 8 sequences
-  // (2048 chunk workgroups) 20.4 us with one chunk, 20.8 / 21.6 us with two / four.
+  a.n_init = p->num_initial; a.n_local = p->num_local;
+  const int G = p->num_q_heads / p->num_kv_heads;
   const long chunk_wgs = (long)w.attn_nsplit * p->num_kv_heads * p->batch;
+  if (p->dtype == TS_BF16 && chunk_wgs >= kAttnStreamFrom) {
+    // a throughput problem: long runs, as few splits as still give every CU a workgroup
+    const long pairs = (long)p->num_kv_heads * p->batch;
+    const int total = idx_stride + p->num_initial + p->num_local;
+    int ns = (int)((256 + pairs - 1) / pairs);
+    if (ns < (total + kStreamMaxSpan - 1) / kStreamMaxSpan) ns = (total + kStreamMaxSpan - 1) / kStreamMaxSpan;
+    a.span = ((total + ns - 1) / ns + kStreamTile - 1) / kStreamTile * kStreamTile;
+    a.nsplit = (total + a.span - 1) / a.span;
+    return launch_sparse_attn_stream(p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
+  }
+  // chunks per workgroup: one while the chunks alone are few workgroups (a latency problem), four when there are many
+  // thousands (fp32; the next chunk's rows are in flight while a chunk is worked on)
   a.nch = chunk_wgs >= 8192 ? kAttnMaxRun : 1;
   if (a.nch > w.attn_nsplit) a.nch = w.attn_nsplit;
   if (a.nch < 1) a.nch = 1;
   if (a.nch > kAttnMaxRun) a.nch = kAttnMaxRun;
   a.nsplit = (w.attn_nsplit + a.nch - 1) / a.nch;
-  a.n_init = p->num_initial; a.n_local = p->num_local;
-  const int G = p->num_q_heads / p->num_kv_heads;
+  a.span = kAttnChunk * a.nch;
   return launch_sparse_attn_decode(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 

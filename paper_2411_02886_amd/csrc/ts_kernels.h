@@ -128,6 +128,7 @@ struct AttnArgs {
   float* part_ml;      // [B][H][nsplit][2]
   int H, H_kv, P, p_shift, idx_stride, nsplit, max_seq_len;
   int n_init, n_local;  // forced tokens attended before / after the selected ones
+  int span;             // list entries per split
   int nch;              // chunks of kAttnChunk tokens per workgroup (1 .. kAttnMaxRun); nsplit counts workgroups
   float sm_scale;
 };
@@ -191,6 +192,10 @@ hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s);
 constexpr int kTopkFinalMaxBlk = 8192;   // chunks per sequence the finishing workgroup can index (16 Mi tokens)
 hipError_t launch_selcache(const SelcacheArgs& a, int B, hipStream_t s);
 hipError_t launch_sparse_attn_decode(int dtype, int D, int G, const AttnArgs& a, int B, hipStream_t s);
+// the streaming form (bf16): a.span list entries per split, a multiple of kStreamTile
+constexpr int kStreamTile = 32;        // keys per wave tile
+constexpr int kStreamMaxSpan = 3584;   // the run's rows in LDS beside the tiles, two workgroups per CU
+hipError_t launch_sparse_attn_stream(int D, int G, const AttnArgs& a, int B, hipStream_t s);
 hipError_t launch_chunk_mean_query(const void* q, void* out, int B, int C, int n, hipStream_t s);
 hipError_t launch_sum_vote(const VoteArgs& a, int B, hipStream_t s);
 hipError_t launch_transpose_scores(const VoteArgs& a, float* st, int B, hipStream_t s);

@@ -1,0 +1,72 @@
+"""The streaming form of the decode attention (bf16 batches) against plain float64 attention: runs of one key, of less
+and more than a tile, of several splits; every group size; scales that are zero, negative or make the logits outgrow the
+first reference; empty sequences beside full ones."""
+import math
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, H, H_kv, D, P, longest sequence, k, n_init, n_local, scale (None = 1/sqrt(D))
+    (256, 8, 8, 64, 16, 90, 64, 0, 0, None),
+    (300, 14, 2, 128, 16, 400, 257, 3, 5, None),
+    (64, 32, 16, 128, 1, 300, 129, 0, 0, 0.0),
+    (40, 24, 8, 64, 16, 700, 500, 4, 61, -0.3),
+    (12, 32, 8, 128, 16, 3000, 2048, 128, 512, None),
+    (10, 40, 8, 128, 32, 2000, 1777, 0, 0, 2.0),
+    (33, 12, 2, 128, 16, 2300, 2100, 0, 0, 1.0),
+    (3, 32, 4, 128, 16, 12000, 11000, 0, 0, None),
+    (9, 64, 8, 64, 16, 1900, 1800, 0, 0, 0.5),
+]
+
+
+@pytest.mark.parametrize("B,H,H_kv,D,P,longest,k,ni,nl,scale", CASES)
+def test_batch_attention(B, H, H_kv, D, P, longest, k, ni, nl, scale):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_02886_amd.runtime import DecodeLayer, to_device, to_host
+    print("batch attention", B, H, H_kv, D, P, longest, k, ni, nl, scale, flush=True)
+    rng = np.random.default_rng(B + k)
+    lens = rng.integers(1, longest + 1, size=B)
+    lens[0], lens[-1] = longest, (0 if B > 3 else 1)
+    w = W.make_workload("batch", dtype=W.BF16, B=B, H=H, H_kv=H_kv, D=D, P=P, seq_lens=lens, k=k, seed=3 * B + D + k)
+    layer = DecodeLayer.from_workload(w, num_initial=ni, num_local=nl)
+    idx = np.full((B, k), -1, np.int32)
+    count = np.zeros(B, np.int32)
+    for b, n in enumerate(int(x) for x in lens):
+        lo = min(ni, n)
+        hi = max(lo, n - nl)
+        count[b] = min(k, hi - lo)
+        idx[b, :count[b]] = np.sort(lo + rng.permutation(hi - lo)[:count[b]])
+    layer.idx = to_device(idx); layer.count = to_device(count)
+    sm = 1.0 / math.sqrt(D) if scale is None else scale
+    layer.attend(to_device(w.q), sm)
+    torch.cuda.synchronize()
+    out = W.as_f32(to_host(layer.out, bits16=True), W.BF16).astype(np.float64)
+    lse = to_host(layer.lse).astype(np.float64)
+    G = H // H_kv
+    q = W.as_f32(w.q, W.BF16).astype(np.float64)
+    for b in sorted(set([0, B - 1, B - 2] + list(rng.integers(0, B, size=5)))):
+        n = int(lens[b])
+        if n == 0:
+            assert not out[b].any() and np.all(np.isneginf(lse[b])), b
+            continue
+        lo = min(ni, n)
+        tok = np.concatenate([np.arange(lo), idx[b, :count[b]], np.arange(max(lo, n - nl), n)])
+        slots = w.slots_of(b)[tok]
+        K = W.as_f32(w.k_pool.reshape(-1, H_kv, D)[slots], W.BF16).astype(np.float64)
+        V = W.as_f32(w.v_pool.reshape(-1, H_kv, D)[slots], W.BF16).astype(np.float64)
+        for h in range(H):
+            s = K[:, h // G] @ q[b, 0, h] * float(np.float32(sm))
+            p = np.exp(s - s.max())
+            ref = p @ V[:, h // G] / p.sum()
+            # the weights are float (the output's rounding to bf16 is 2^-9 of it); logits carry float rounding of up to
+            # |s| * 2^-22, which acts on a weight as a factor
+            err = np.abs(s).max() * 2.0 ** -21 + 2.0 ** -20
+            assert np.all(np.abs(out[b, 0, h] - ref) <= 2.0 ** -8 * np.abs(ref) + err * np.abs(V[:, h // G]).max()), (b, h)
+            assert abs(lse[b, 0, h] - (s.max() + math.log(p.sum()))) <= err + np.abs(s).max() * 2.0 ** -22, (b, h)
