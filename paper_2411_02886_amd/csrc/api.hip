@@ -258,6 +258,20 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, ScoreArgs*
   *wg_out = wgl;
 }
 
+// Partials per sequence that a score launch of this shape leaves (workgroups it runs with): what the statistics merge
+// loads before it has seen the count in the workspace.
+static int expected_parts(const ts_problem* p, bool dense) {
+  const int G = p->num_q_heads / p->num_kv_heads;
+  if ((dense ? g_score_variant == 2 : true) && g_codes_mfma && (p->num_q_heads % 4) == 0 &&
+      score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
+    ScoreArgs a{};
+    long wgl = 0;
+    mfma_launch_shape(p, G, dense, &a, &wgl);
+    return (int)wgl;
+  }
+  return score_workgroups(p);
+}
+
 // Algorithm 1's state for the score launches that run the test themselves
 static int32_t fill_selcache(const ts_problem* p, const void* q, const ts_selcache* sc, ScoreArgs* a) {
   if (sc == nullptr || sc->cached_q == nullptr || sc->cached_q_next == nullptr || sc->first == nullptr ||
@@ -382,7 +396,7 @@ int32_t ts_soft_vote_bounds(const ts_problem* p, const uint8_t* codes, float sco
   a.scale = score_scale;
   VoteArgs m{};
   m.partials = (const float*)((uint8_t*)ws + w.score_partials); m.hdr = a.hdr;
-  m.row_stats_out = row_stats; m.skip = skip; m.H = p->num_q_heads; m.scale = score_scale;
+  m.row_stats_out = row_stats; m.skip = skip; m.parts_hint = expected_parts(p, false); m.H = p->num_q_heads; m.scale = score_scale;
   if (launch_stats_merge(m, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   return launch_vote_bounds(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
@@ -439,7 +453,7 @@ int32_t ts_soft_vote(const ts_problem* p, const float* scores, float score_scale
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local;
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true);
   return launch_soft_vote(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -456,7 +470,7 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local;
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true);
   a.rank_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_soft_vote_ranked(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
@@ -482,8 +496,8 @@ int32_t ts_topk(const ts_problem* p, const float* votes, int32_t k, int32_t* idx
   // so chunk problems (and callers that say so) take the five-pass form, whose cost does not depend on the
   // distribution.
   a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)((uint8_t*)ws + w.topk_list);
-  a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = w.topk_nblk; a.heads = 1;
-  if ((flags & TS_TOPK_VOTE_HIST) != 0) a.rep_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
+  a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = w.topk_nblk; a.heads = 1; a.one_wg = !g_topk_five_pass;
+  if ((flags & TS_TOPK_VOTE_HIST) != 0 && p->max_seq_len > kTopkOneWg) a.rep_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_topk(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -506,7 +520,7 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
   a.state = (uint32_t*)(base + kNoAllocState);
   a.blk = (uint32_t*)(base + kNoAllocBlk);
   a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)(base + kNoAllocList);
-  a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = nblk; a.heads = 1;
+  a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = nblk; a.heads = 1; a.one_wg = !g_topk_five_pass;
   // the array keeps whatever the last call on this GPU left: the histograms must start at zero (a fill kernel,
   // not a memset node: callers may be under graph capture)
   hipLaunchKernelGGL(fill_zero_kernel, dim3(24), dim3(256), 0, (hipStream_t)stream, a.hist, (size_t)p->batch * 3 * kTopkBins);
@@ -579,7 +593,7 @@ int32_t ts_head_vote(const ts_problem* p, const float* scores, int32_t k_head, f
   a.votes = (const float*)(base + l.st); a.seq_lens = p->seq_lens; a.skip = skip;
   a.hist = (uint32_t*)(base + l.hist); a.state = (uint32_t*)(base + l.state); a.blk = (uint32_t*)(base + l.blk);
   a.list = g_topk_five_pass ? nullptr : (uint2*)(base + l.list);
-  a.k = k_head; a.max_seq_len = p->max_seq_len; a.nblk = l.nblk; a.heads = p->num_q_heads; a.vote_acc = votes;
+  a.k = k_head; a.max_seq_len = p->max_seq_len; a.nblk = l.nblk; a.heads = p->num_q_heads; a.vote_acc = votes; a.one_wg = !g_topk_five_pass;
   return launch_topk(a, p->batch * p->num_q_heads, s) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 

@@ -18,21 +18,31 @@ __global__ __launch_bounds__(256) void score_stats_merge_kernel(VoteArgs a) {
   __shared__ double s_l[4];
   const int h = blockIdx.x, b = blockIdx.y;
   const int skip_flag = a.skip != nullptr ? (int)a.skip[b] : 0;   // checked after the partials' loads have been issued
-  // the partial count is what the score launch recorded in the workspace, whatever the host believes now; every
-  // slot is loaded at once (one memory round trip, the slots all exist) and the unused ones are masked afterwards
+  // The partial count is what the score launch recorded in the workspace, whatever the host believes now; the slots that
+  // the host expects are loaded at once (one memory round trip, the slots all exist), unused ones are masked afterwards,
+  // and in the rare case that there are more (a tuning knob changed in between) the rest follows.  (Always loading all
+  // 1024 slots, a batch of 32 sequences of 16001 tokens took 12.1 us instead of 5.1.)
   const int nparts = min((int)a.hdr[b * 8 + 0], kScoreMaxWg);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int PER = kScoreMaxWg / 256;
   float mp[PER], lp[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
+  auto load_slot = [&](int i) {
     const int p = threadIdx.x + 256 * i;
     const float2 v = *reinterpret_cast<const float2*>(a.partials + (((size_t)b * kScoreMaxWg + p) * a.H + h) * 2);
     mp[i] = v.x; lp[i] = v.y;
+  };
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    mp[i] = -INFINITY; lp[i] = 0.f;
+    if (256 * i < a.parts_hint) load_slot(i);
+  }
+  if (nparts > a.parts_hint) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) load_slot(i);
   }
 #pragma unroll
   for (int i = 0; i < PER; ++i)
-    if (threadIdx.x + 256 * i >= nparts) { mp[i] = -INFINITY; lp[i] = 0.f; }
+    if ((int)threadIdx.x + 256 * i >= nparts) { mp[i] = -INFINITY; lp[i] = 0.f; }
   if (skip_flag != 0) return;
   float m = mp[0];
 #pragma unroll
@@ -134,9 +144,14 @@ __global__ __launch_bounds__(256) void soft_vote_kernel(VoteArgs a, int lpt_shif
 // same-address atomics stay few.  (Measured and dropped: merging the score pass's statistics partials inside this
 // kernel as well, every workgroup for itself.  At 128K tokens that is 128 KiB of partials per workgroup, 32 MiB of
 // L2 reads per launch, and costs the kernel 4.7 us -- what the merge launch costs.)
+// MERGE: a sequence whose score launch leaves few partials (kMergeInVote pairs at most: short sequences) has them merged
+// here after all, by every workgroup for itself -- the partials' loads go out with the scores', the same sums otherwise --
+// and the merge launch disappears.  (4096 tokens, 8 heads, 32 partials: 3.3 + 4.2 -> 5.4 us.)
+constexpr int kMergeInVote = 4096;   // partials x heads
+constexpr int kMergeParts = 256;     // partials per head that the 32 threads of a head hold in registers
 constexpr int kRankTokens = 512;     // per workgroup: one round of four passes for H = 32, and a workgroup for every CU at 128K tokens
 
-template <int CPL, bool VEC>
+template <int CPL, bool VEC, bool MERGE>
 __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int lpt_shift) {
   __shared__ double s_m[128];
   __shared__ double s_inv[128];
@@ -147,7 +162,12 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
   const int N = min(max(a.seq_lens[b], 0), a.max_seq_len);
   if (skip_flag != 0) return;
   const int tok0 = blockIdx.x * kRankTokens;
-  if (tok0 >= N) return;
+  if (tok0 >= N) {
+    // an empty sequence has statistics too: those of no score
+    if (MERGE && tok0 == 0 && (int)threadIdx.x < a.H)
+      *reinterpret_cast<float2*>(a.row_stats_out + ((size_t)b * a.H + threadIdx.x) * 2) = make_float2(-INFINITY, 0.f);
+    return;
+  }
   const int H = a.H;
   const double c2 = (double)a.scale * 1.44269504088896340736;
   const int LPT = 1 << lpt_shift;
@@ -175,8 +195,60 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
     }
   };
   load_round(0);
-  for (int i = threadIdx.x; i < kTopkBins; i += 1024) hist[i] = 0u;
-  if (threadIdx.x < H) {
+  const bool counts = a.max_seq_len > kTopkOneWg;      // shorter sequences are ranked without a histogram
+  if (counts) for (int i = threadIdx.x; i < kTopkBins; i += 1024) hist[i] = 0u;
+  if (MERGE) {
+    // 32 threads per head, 32 heads per round.  Thread pl stands in for the threads pl + 32 * i of the merge kernel and adds
+    // in that kernel's order, so that the statistics are the same bit for bit.
+    constexpr int PER = kMergeParts / 32;
+    const int nparts = min((int)a.hdr[b * 8 + 0], kScoreMaxWg);
+    const int pl = threadIdx.x & 31;
+    const double sc = (double)a.scale;
+    for (int h0 = 0; h0 < H; h0 += 32) {
+      const int h = h0 + (int)(threadIdx.x >> 5), hc = min(h, H - 1);
+      auto slot = [&](int p) { return *reinterpret_cast<const float2*>(a.partials + (((size_t)b * kScoreMaxWg + p) * H + hc) * 2); };
+      float mp[PER], lp[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        mp[i] = -INFINITY; lp[i] = 0.f;
+        if (32 * i < a.parts_hint) { const float2 v = slot(pl + 32 * i); mp[i] = v.x; lp[i] = v.y; }   // the slots the host expects; all slots exist
+      }
+      if (nparts > a.parts_hint) {                     // more than that (a tuning knob changed in between)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) { const float2 v = slot(pl + 32 * i); mp[i] = v.x; lp[i] = v.y; }
+      }
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (pl + 32 * i >= nparts) { mp[i] = -INFINITY; lp[i] = 0.f; }
+      float m = mp[0];
+#pragma unroll
+      for (int i = 1; i < PER; ++i) m = fmaxf(m, mp[i]);
+      for (int p = pl + kMergeParts; p < nparts; p += 32) m = fmaxf(m, slot(p).x);
+#pragma unroll
+      for (int o = 1; o < 32; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+      auto term = [&](float pm, float pv) { return pm != -INFINITY ? (double)pv * exp_f64(sc * ((double)pm - (double)m)) : 0.0; };
+      double l = 0.0;
+#pragma unroll
+      for (int w = 0; w < PER / 2; ++w) {              // the merge kernel's wave w
+        if (64 * w >= a.parts_hint && 64 * w >= nparts) break;
+        double t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          t[i] = term(mp[2 * w + i], lp[2 * w + i]);
+          for (int p = pl + 32 * (2 * w + i) + kMergeParts; p < nparts; p += kMergeParts) { const float2 v = slot(p); t[i] += term(v.x, v.y); }
+        }
+        double tw = t[0] + t[1];
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) tw += __shfl_xor(tw, o);
+        l += tw;
+      }
+      if (pl == 0 && h < H) {
+        const float lf = (float)l;
+        s_m[h] = (double)m; s_inv[h] = 1.0 / (double)lf;
+        if (blockIdx.x == 0) { a.row_stats_out[((size_t)b * H + h) * 2] = m; a.row_stats_out[((size_t)b * H + h) * 2 + 1] = lf; }
+      }
+    }
+  } else if (threadIdx.x < H) {
     const float2 stv = *reinterpret_cast<const float2*>(a.row_stats + ((size_t)b * H + threadIdx.x) * 2);
     s_m[threadIdx.x] = (double)stv.x; s_inv[threadIdx.x] = 1.0 / (double)stv.y;
   }
@@ -203,10 +275,11 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
         const bool ranked = t >= r_lo && t < r_hi;
         const float vf = ranked ? (float)vote : 0.f;
         a.votes[(size_t)b * a.max_seq_len + t] = vf;
-        if (ranked) atomicAdd(&hist[float_key(vf) >> 21], 1u);
+        if (ranked && counts) atomicAdd(&hist[float_key(vf) >> 21], 1u);
       }
     }
   }
+  if (!counts) return;
   __syncthreads();
   uint32_t* gh = a.rank_hist + ((size_t)b * kBoundHistCopies + (blockIdx.x & (kBoundHistCopies - 1))) * kTopkBins;
   for (int i = threadIdx.x; i < kTopkBins; i += 1024)
@@ -219,9 +292,11 @@ hipError_t launch_soft_vote_ranked(const VoteArgs& a, int B, hipStream_t s) {
   while ((1 << lpt_shift) < hq && lpt_shift < 3) ++lpt_shift;
   const int cpl = (hq + (1 << lpt_shift) - 1) >> lpt_shift;   // 1, 2 or 4 for H <= 128
   const bool vec = (a.H % 4 == 0) && (((uintptr_t)a.scores & 15) == 0);
-  hipLaunchKernelGGL(score_stats_merge_kernel, dim3(a.H, B), dim3(256), 0, s, a);
+  const bool merge_in_vote = a.parts_hint <= kMergeParts && a.parts_hint * a.H <= kMergeInVote;
+  if (!merge_in_vote) hipLaunchKernelGGL(score_stats_merge_kernel, dim3(a.H, B), dim3(256), 0, s, a);
   dim3 grid((a.max_seq_len + kRankTokens - 1) / kRankTokens, B);
-#define TS_RV(C, V) hipLaunchKernelGGL((soft_vote_ranked_kernel<C, V>), grid, dim3(1024), 0, s, a, lpt_shift)
+#define TS_RV(C, V) do { if (merge_in_vote) hipLaunchKernelGGL((soft_vote_ranked_kernel<C, V, true>), grid, dim3(1024), 0, s, a, lpt_shift); \
+    else hipLaunchKernelGGL((soft_vote_ranked_kernel<C, V, false>), grid, dim3(1024), 0, s, a, lpt_shift); } while (0)
   if (cpl <= 1) { if (vec) TS_RV(1, true); else TS_RV(1, false); }
   else if (cpl <= 2) { if (vec) TS_RV(2, true); else TS_RV(2, false); }
   else { if (vec) TS_RV(4, true); else TS_RV(4, false); }

@@ -439,9 +439,13 @@ __device__ __forceinline__ void final_find_digit(const uint32_t* h, uint32_t k_r
 // passes 2, 3 and the emit of the short path: one workgroup per (virtual) sequence
 // FULL: the entries are the re-evaluated candidates of the compact selection, listed without gaps (a.dense); their
 // keys are exact votes, of which only the lower edge of the k-th largest lower bound's bin is known.
-template <int kFinalPer, bool FULL>        // consecutive list entries per thread and batch
+// SHORT: no list at all: a sequence of at most kFinalThreads * kFinalPer tokens whose votes this workgroup reads itself;
+// digit 0 is counted here.
+enum { FINAL_LIST = 0, FINAL_FULL = 1, FINAL_SHORT = 2 };
+template <int kFinalPer, int MODE>         // consecutive entries per thread and batch
 __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
-  __shared__ uint32_t off[FULL ? 1 : kFinalMaxBlk + 1];   // exclusive prefix of the chunks' entry counts
+  constexpr bool FULL = MODE == FINAL_FULL, SHORT = MODE == FINAL_SHORT;
+  __shared__ uint32_t off[MODE != FINAL_LIST ? 1 : kFinalMaxBlk + 1];   // exclusive prefix of the chunks' entry counts
   __shared__ uint32_t h[kTopkBins];
   __shared__ uint32_t tie[FULL ? kTieMax : 1];            // keys that share the k-th key's bin
   __shared__ uint32_t n_tie;
@@ -450,9 +454,40 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
   const int b = blockIdx.x;
   const int skip_flag = a.skip != nullptr ? (int)a.skip[b / a.heads] : 0;   // issued together with the state words
   const int tid = threadIdx.x;
-  uint32_t d0 = FULL ? 0u : a.state[b * 8 + ST_PREFIX0] >> 21, krem0 = FULL ? 0u : a.state[b * 8 + ST_KREM0];
-  const int k_eff = (int)a.state[b * 8 + ST_KEFF];
+  const int LO = SHORT ? ranked_lo(a, b) : 0, N = SHORT ? ranked_hi(a, b, LO) : 0;
+  uint32_t d0 = MODE != FINAL_LIST ? 0u : a.state[b * 8 + ST_PREFIX0] >> 21, krem0 = MODE != FINAL_LIST ? 0u : a.state[b * 8 + ST_KREM0];
+  const int k_eff = SHORT ? min(a.k, N - LO) : (int)a.state[b * 8 + ST_KEFF];
   if (skip_flag != 0) return;
+  uint2 e[kFinalPer];
+  if (SHORT) {                               // the votes' loads go out first
+    const float* v = a.votes + (size_t)b * a.max_seq_len;
+    const int t0 = tid * kFinalPer;
+    if ((reinterpret_cast<uintptr_t>(v) & 15) == 0 && t0 + kFinalPer <= a.max_seq_len) {     // 16-byte loads (the row exists up to max_seq_len)
+#pragma unroll
+      for (int q4 = 0; q4 < kFinalPer / 4; ++q4) {
+        const float4 w = *reinterpret_cast<const float4*>(v + t0 + q4 * 4);
+        const float x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int t = t0 + q4 * 4 + i;
+          e[q4 * 4 + i] = (t >= LO && t < N) ? make_uint2(float_key(x[i]), (uint32_t)t) : make_uint2(0u, 0xffffffffu);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < kFinalPer; ++i) {
+        const int t = t0 + i;
+        e[i] = (t >= LO && t < N) ? make_uint2(float_key(v[t]), (uint32_t)t) : make_uint2(0u, 0xffffffffu);
+      }
+    }
+    for (int i = tid; i < kTopkBins; i += kFinalThreads) h[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kFinalPer; ++i)
+      if (e[i].y != 0xffffffffu) atomicAdd(&h[e[i].x >> 21], 1u);
+    __syncthreads();
+    final_find_digit<kTopkBins>(h, (uint32_t)k_eff, &d0, &krem0, scan_lds, res);
+  }
   const bool as_votes = a.vote_acc != nullptr;
   int32_t* out = as_votes ? nullptr : a.idx + (size_t)b * a.k;
   float* acc = as_votes ? a.vote_acc + (size_t)(b / a.heads) * a.max_seq_len : nullptr;
@@ -464,7 +499,7 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
       for (int i = k_eff + tid; i < a.k; i += kFinalThreads) a.sel_votes[(size_t)b * a.k + i] = 0.f;
     if (tid == 0) a.count[b] = k_eff;
   }
-  if (FULL) {                  // the lower bounds' histogram was cleared by the re-evaluation
+  if (FULL || SHORT) {         // the lower bounds' histogram was cleared by the re-evaluation; short sequences have none
   } else if (a.rep_hist != nullptr) {   // the vote kernel's replicated histogram has been consumed by the compact pass
     uint4* g0 = reinterpret_cast<uint4*>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);
     for (int i = tid; i < kBoundHistCopies * kTopkBins / 4; i += kFinalThreads) g0[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -473,7 +508,9 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
     for (int i = tid; i < kTopkBins; i += kFinalThreads) g0[i] = 0u;
   }
   uint32_t total;
-  if (FULL) {
+  if (SHORT) {
+    total = (uint32_t)N;
+  } else if (FULL) {
     total = min(a.state[b * 8 + kStTotal], (uint32_t)a.nblk * kTopkChunk);
   } else {
     // ---- chunk offsets
@@ -492,7 +529,7 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
     __syncthreads();
   }
   if (total == 0 || k_eff == 0) return;
-  const uint2* list = a.list + (size_t)b * a.nblk * kTopkChunk;
+  const uint2* list = SHORT ? nullptr : a.list + (size_t)b * a.nblk * kTopkChunk;
   const uint2* dense = FULL ? a.dense + (size_t)b * a.nblk * kTopkChunk : nullptr;
 
   // entries of a batch: thread tid owns the kFinalPer consecutive positions from p0
@@ -526,9 +563,8 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
       }
     }
   };
-  const bool single = total <= (uint32_t)kFinalThreads * kFinalPer;   // the usual case: the list sits in registers
-  uint2 e[kFinalPer];
-  if (single) load_batch(0, e);
+  const bool single = SHORT || total <= (uint32_t)kFinalThreads * kFinalPer;   // the usual case: the list sits in registers
+  if (!SHORT && single) load_batch(0, e);
 
   uint32_t thr, need_eq;
   bool fixed = false;                         // thr and need_eq are known (the same in all threads)
@@ -672,6 +708,16 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
 hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
   dim3 grid(a.nblk, B);
   const bool short_path = a.list != nullptr && a.nblk <= kFinalMaxBlk;
+  static_assert(kTopkOneWg == kFinalThreads * 16, "16 votes per thread");
+  if (a.one_wg && a.max_seq_len <= kTopkOneWg) {
+    // the whole sequence fits one workgroup's registers: one launch instead of two, three or (flat votes) five, whatever
+    // the distribution.  4096 tokens, k 256: 4.6 + 5.1 -> 5.5 us (and no histogram in the vote kernel); the line lies where 16 votes per
+    // thread end: more would leave the registers
+    if (a.max_seq_len <= kFinalThreads * 4) hipLaunchKernelGGL((topk_final_kernel<4, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    else if (a.max_seq_len <= kFinalThreads * 8) hipLaunchKernelGGL((topk_final_kernel<8, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    else hipLaunchKernelGGL((topk_final_kernel<16, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    return hipGetLastError();
+  }
   if (a.rep_hist == nullptr) {
     hipLaunchKernelGGL(topk_hist0_kernel, dim3(a.nblk < 128 ? a.nblk : 128, B), dim3(256), 0, s, a);
   } else if (!short_path) {
@@ -680,8 +726,8 @@ hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
   if (short_path) {
     hipLaunchKernelGGL(topk_compact_kernel, grid, dim3(256), 0, s, a);
     // the list holds about k entries plus the few that share the k-th key's bin: one batch in the usual case
-    if (a.k <= 3072) hipLaunchKernelGGL((topk_final_kernel<4, false>), dim3(B), dim3(kFinalThreads), 0, s, a);
-    else hipLaunchKernelGGL((topk_final_kernel<8, false>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    if (a.k <= 3072) hipLaunchKernelGGL((topk_final_kernel<4, FINAL_LIST>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    else hipLaunchKernelGGL((topk_final_kernel<8, FINAL_LIST>), dim3(B), dim3(kFinalThreads), 0, s, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(topk_hist1_kernel, grid, dim3(256), 0, s, a);
@@ -701,10 +747,10 @@ hipError_t launch_topk_compact(const TopkArgs& a, int B, hipStream_t s) {
 hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s) {
   // entries per thread: a list of up to 5/4 k sits in registers (the candidates are usually 1.03 to 1.2 k)
   const int per = (int)(((long)a.k * 5 / 4 + kFinalThreads - 1) / kFinalThreads);
-  if (per <= 2) hipLaunchKernelGGL((topk_final_kernel<2, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
-  else if (per <= 4) hipLaunchKernelGGL((topk_final_kernel<4, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
-  else if (per <= 6) hipLaunchKernelGGL((topk_final_kernel<6, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
-  else hipLaunchKernelGGL((topk_final_kernel<8, true>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  if (per <= 2) hipLaunchKernelGGL((topk_final_kernel<2, FINAL_FULL>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  else if (per <= 4) hipLaunchKernelGGL((topk_final_kernel<4, FINAL_FULL>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  else if (per <= 6) hipLaunchKernelGGL((topk_final_kernel<6, FINAL_FULL>), dim3(B), dim3(kFinalThreads), 0, s, a);
+  else hipLaunchKernelGGL((topk_final_kernel<8, FINAL_FULL>), dim3(B), dim3(kFinalThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -66,6 +66,7 @@ struct VoteArgs {
   int H, max_seq_len;
   int n_init, n_local;    // forced tokens: votes outside [min(n_init, N), max(that, N - n_local)) are 0
   float scale;
+  int parts_hint;         // partials the score launch of this shape leaves, as the host reckons; the header has the last word
   uint32_t* rank_hist;    // ranked vote only: [B][kBoundHistCopies][kTopkBins], top 11 key bits of the votes it writes
 };
 
@@ -82,6 +83,7 @@ struct TopkArgs {
   uint32_t* blk;        // [B][nblk]
   uint2* list;          // [B][nblk][kTopkChunk] (key, token) entries of the short path; nullptr = five-pass form
   int k, max_seq_len, nblk;
+  int one_wg;           // sequences that fit one workgroup's registers may be ranked by it alone (0: a tuning knob asks for the passes)
   int heads;            // virtual sequences per real one (Eq. 4: one per head over transposed scores); 1 = plain
   float* vote_acc;      // Eq. 4: the emit pass adds 1 to vote_acc[real sequence][t] for every winner instead of writing idx
   float* sel_votes;     // compact selection: [B][k] votes of the selected tokens in idx order, or nullptr
@@ -189,6 +191,9 @@ hipError_t launch_topk_eval(int dtype, int D, int G, const RefineArgs& a, int B,
 constexpr int kStTotal = 5;   // state word that carries the number of candidates from topk_eval_kernel to the finish
 hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s);
 hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s);
+// sequences of up to this many tokens are ranked by one workgroup that reads their votes itself: the vote kernel then
+// counts no histogram for the TopK, and the TopK expects none
+constexpr int kTopkOneWg = 16384;
 constexpr int kTopkFinalMaxBlk = 8192;   // chunks per sequence the finishing workgroup can index (16 Mi tokens)
 hipError_t launch_selcache(const SelcacheArgs& a, int B, hipStream_t s);
 hipError_t launch_sparse_attn_decode(int dtype, int D, int G, const AttnArgs& a, int B, hipStream_t s);
