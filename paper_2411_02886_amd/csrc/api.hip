@@ -249,6 +249,11 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, ScoreArgs*
       const double fill = (double)n / (double)(rounds * slots);
       if (fill > best + 0.05) { best = fill; rr = r; }
     }
+    // A batch of shorter sequences fills the machine with runs of four tiles too, and the compact form's bytes then leave
+    // in fewer, longer bursts (score pass alone: 8 sequences of 16384 to 65536 tokens, H 32/8, 82.1 -> 71.8 us; 32 of 1031 to
+    // 16001, 111.7 -> 107.8; 16 of 4000 to 16000, H 28/4, 37.5 -> 34.1).  The score matrix's rows, four times as many bytes,
+    // lose that way (118.8 -> 147.5 us with the 32).
+    if (!dense && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
   }
   if (rr > 8) rr = 8;
   while (rr > 1 && score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) > 163840) --rr;
