@@ -144,11 +144,12 @@ __global__ __launch_bounds__(256) void soft_vote_kernel(VoteArgs a, int lpt_shif
 // same-address atomics stay few.  (Measured and dropped: merging the score pass's statistics partials inside this
 // kernel as well, every workgroup for itself.  At 128K tokens that is 128 KiB of partials per workgroup, 32 MiB of
 // L2 reads per launch, and costs the kernel 4.7 us -- what the merge launch costs.)
-// MERGE: a sequence whose score launch leaves few partials (kMergeInVote pairs at most: short sequences) has them merged
+// MERGE: a sequence whose score launch leaves few partials (kMergeParts a head, kMergeInVote in all: short sequences) has them merged
 // here after all, by every workgroup for itself -- the partials' loads go out with the scores', the same sums otherwise --
 // and the merge launch disappears.  (4096 tokens, 8 heads, 32 partials: 3.3 + 4.2 -> 5.4 us.)
-constexpr int kMergeInVote = 4096;   // partials x heads
-constexpr int kMergeParts = 256;     // partials per head that the 32 threads of a head hold in registers
+// The line: with up to 256 partials a head (30000 tokens of 12 heads, five sequences) the step took 62 us instead of 55.
+constexpr int kMergeInVote = 1024;   // partials x heads
+constexpr int kMergeParts = 64;      // partials per head: two per thread
 constexpr int kRankTokens = 512;     // per workgroup: one round of four passes for H = 32, and a workgroup for every CU at 128K tokens
 
 template <int CPL, bool VEC, bool MERGE>
@@ -200,42 +201,31 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
   if (MERGE) {
     // 32 threads per head, 32 heads per round.  Thread pl stands in for the threads pl + 32 * i of the merge kernel and adds
     // in that kernel's order, so that the statistics are the same bit for bit.
-    constexpr int PER = kMergeParts / 32;
     const int nparts = min((int)a.hdr[b * 8 + 0], kScoreMaxWg);
     const int pl = threadIdx.x & 31;
     const double sc = (double)a.scale;
     for (int h0 = 0; h0 < H; h0 += 32) {
       const int h = h0 + (int)(threadIdx.x >> 5), hc = min(h, H - 1);
       auto slot = [&](int p) { return *reinterpret_cast<const float2*>(a.partials + (((size_t)b * kScoreMaxWg + p) * H + hc) * 2); };
-      float mp[PER], lp[PER];
+      float2 v[2];                                     // all slots exist; unused ones are masked
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        mp[i] = -INFINITY; lp[i] = 0.f;
-        if (32 * i < a.parts_hint) { const float2 v = slot(pl + 32 * i); mp[i] = v.x; lp[i] = v.y; }   // the slots the host expects; all slots exist
-      }
-      if (nparts > a.parts_hint) {                     // more than that (a tuning knob changed in between)
+      for (int i = 0; i < 2; ++i) v[i] = slot(pl + 32 * i);
 #pragma unroll
-        for (int i = 0; i < PER; ++i) { const float2 v = slot(pl + 32 * i); mp[i] = v.x; lp[i] = v.y; }
-      }
-#pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (pl + 32 * i >= nparts) { mp[i] = -INFINITY; lp[i] = 0.f; }
-      float m = mp[0];
-#pragma unroll
-      for (int i = 1; i < PER; ++i) m = fmaxf(m, mp[i]);
-      for (int p = pl + kMergeParts; p < nparts; p += 32) m = fmaxf(m, slot(p).x);
+      for (int i = 0; i < 2; ++i)
+        if (pl + 32 * i >= nparts) v[i] = make_float2(-INFINITY, 0.f);
+      float m = fmaxf(v[0].x, v[1].x);
+      for (int p = pl + kMergeParts; p < nparts; p += 32) m = fmaxf(m, slot(p).x);   // more than expected: a tuning knob changed in between
 #pragma unroll
       for (int o = 1; o < 32; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-      auto term = [&](float pm, float pv) { return pm != -INFINITY ? (double)pv * exp_f64(sc * ((double)pm - (double)m)) : 0.0; };
+      auto term = [&](float2 x) { return x.x != -INFINITY ? (double)x.y * exp_f64(sc * ((double)x.x - (double)m)) : 0.0; };
       double l = 0.0;
-#pragma unroll
-      for (int w = 0; w < PER / 2; ++w) {              // the merge kernel's wave w
-        if (64 * w >= a.parts_hint && 64 * w >= nparts) break;
+      for (int w = 0; w == 0 || (w < 4 && 64 * w < nparts); ++w) {                   // the merge kernel's wave w
         double t[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          t[i] = term(mp[2 * w + i], lp[2 * w + i]);
-          for (int p = pl + 32 * (2 * w + i) + kMergeParts; p < nparts; p += kMergeParts) { const float2 v = slot(p); t[i] += term(v.x, v.y); }
+          const int p0 = pl + 64 * w + 32 * i;
+          t[i] = w == 0 ? term(v[i]) : p0 < nparts ? term(slot(p0)) : 0.0;
+          for (int p = p0 + 256; p < nparts; p += 256) t[i] += term(slot(p));
         }
         double tw = t[0] + t[1];
 #pragma unroll

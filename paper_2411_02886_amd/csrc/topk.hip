@@ -708,14 +708,14 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
 hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
   dim3 grid(a.nblk, B);
   const bool short_path = a.list != nullptr && a.nblk <= kFinalMaxBlk;
-  static_assert(kTopkOneWg == kFinalThreads * 16, "16 votes per thread");
+  static_assert(kTopkOneWg == kFinalThreads * 8, "8 votes per thread");
   if (a.one_wg && a.max_seq_len <= kTopkOneWg) {
     // the whole sequence fits one workgroup's registers: one launch instead of two, three or (flat votes) five, whatever
-    // the distribution.  4096 tokens, k 256: 4.6 + 5.1 -> 5.5 us (and no histogram in the vote kernel); the line lies where 16 votes per
-    // thread end: more would leave the registers
+    // the distribution.  4096 tokens, k 256: 4.6 + 5.1 -> 5.5 us (and no histogram in the vote kernel).  The line lies at
+    // 8 votes per thread: a decode step of 8000 tokens 42 -> 37 us; with 16 votes per thread 16000 tokens took 45 us
+    // instead of 43, and five sequences of them 72 instead of 68
     if (a.max_seq_len <= kFinalThreads * 4) hipLaunchKernelGGL((topk_final_kernel<4, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
-    else if (a.max_seq_len <= kFinalThreads * 8) hipLaunchKernelGGL((topk_final_kernel<8, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
-    else hipLaunchKernelGGL((topk_final_kernel<16, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
+    else hipLaunchKernelGGL((topk_final_kernel<8, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
     return hipGetLastError();
   }
   if (a.rep_hist == nullptr) {

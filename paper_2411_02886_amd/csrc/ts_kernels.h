@@ -193,7 +193,7 @@ hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s);
 hipError_t launch_topk_final_full(const TopkArgs& a, int B, hipStream_t s);
 // sequences of up to this many tokens are ranked by one workgroup that reads their votes itself: the vote kernel then
 // counts no histogram for the TopK, and the TopK expects none
-constexpr int kTopkOneWg = 16384;
+constexpr int kTopkOneWg = 8192;
 constexpr int kTopkFinalMaxBlk = 8192;   // chunks per sequence the finishing workgroup can index (16 Mi tokens)
 hipError_t launch_selcache(const SelcacheArgs& a, int B, hipStream_t s);
 hipError_t launch_sparse_attn_decode(int dtype, int D, int G, const AttnArgs& a, int B, hipStream_t s);

@@ -19,7 +19,7 @@ def gpu():
     return ts
 
 
-@pytest.mark.parametrize("longest", [1, 63, 4095, 4096, 4097, 8192, 8193, 16383, 16384, 16385])
+@pytest.mark.parametrize("longest", [1, 63, 4095, 4096, 4097, 8191, 8192, 8193, 16385])
 @pytest.mark.parametrize("kind", ["spread", "flat", "ties", "signed"])
 def test_topk(gpu, longest, kind):
     from paper_2411_02886_amd import binding as ts
