@@ -702,7 +702,7 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
   a.n_init = p->num_initial; a.n_local = p->num_local;
   const int G = p->num_q_heads / p->num_kv_heads;
   const long chunk_wgs = (long)w.attn_nsplit * p->num_kv_heads * p->batch;
-  if (p->dtype == TS_BF16 && chunk_wgs >= kAttnStreamFrom) {
+  if (p->dtype == TS_BF16 && chunk_wgs >= attn_stream_from(G)) {
     // a throughput problem: long runs, as few splits as still give every CU a workgroup
     const long pairs = (long)p->num_kv_heads * p->batch;
     const int total = idx_stride + p->num_initial + p->num_local;

@@ -16,10 +16,11 @@ constexpr int kTopkChunk = 2048;       // keys per workgroup in the top-k passes
 constexpr int kBoundHistCopies = 8;    // replicas of the lower-bound histogram (same-address atomics are what its flush costs)
 constexpr int kAttnChunk = 64;         // selected tokens per workgroup in sparse attention
 constexpr int kAttnMaxRun = 4;        // chunks one attention workgroup folds into its partial, at most (256 list entries: one per thread)
-// bf16: from this many 64-token chunk workgroups on the attention streams long runs (sparse_attn_stream.hip).  Measured,
-// kernel alone: 1344 of them (4 x 2688 tokens, H 64/8) 19.6 us in chunks, 12.1 streamed; 2048 (8 x 2048, H 32/8) 16.2 and
-// 16.0; 256 (one sequence of 2048) 6.4 in chunks, where every workgroup would stream a single tile per wave
-constexpr long kAttnStreamFrom = 1024;
+// bf16: from this many 64-token chunk workgroups on the attention streams long runs (sparse_attn_stream.hip).  The more
+// query heads a KV head has, the more the vector kernel has to do per row, and the earlier the line.  Measured, kernel
+// alone: 1344 of them (4 x 2688 tokens, H 64/8) 19.6 us in chunks, 12.1 streamed; 2048 (8 x 2048, H 32/8) 16.2 and 16.0; whole
+// steps: 1280 (5 x 2048, H 32/8) 98 us in chunks, 101 streamed; 2560 (5 x 2048, H 16/16, D 64) 89 and 92
+inline long attn_stream_from(int G) { return G >= 5 ? 1024 : G >= 3 ? 2048 : 4096; }
 constexpr int kAttnMaxSplit = 512;     // splits the merge kernel can stage (k <= 32768)
 
 // ---------------------------------------------------------------- workspace layout (host + device)

@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # B, H, H_kv, D, P, longest sequence, k, n_init, n_local, scale (None = 1/sqrt(D))
-    (256, 8, 8, 64, 16, 90, 64, 0, 0, None),
+    (256, 8, 8, 64, 16, 200, 129, 0, 0, None),
     (300, 14, 2, 128, 16, 400, 257, 3, 5, None),
-    (64, 32, 16, 128, 1, 300, 129, 0, 0, 0.0),
+    (96, 32, 16, 128, 1, 300, 129, 0, 0, 0.0),
     (40, 24, 8, 64, 16, 700, 500, 4, 61, -0.3),
     (12, 32, 8, 128, 16, 3000, 2048, 128, 512, None),
     (10, 40, 8, 128, 32, 2000, 1777, 0, 0, 2.0),
