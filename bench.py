@@ -202,7 +202,7 @@ def selection_cache_run(args):
            "selection_form": "compact (no score matrix in memory)" if compact else "five calls (fp32 score matrix)",
            "selection_cache_check": "inside the score launch" if args.check == "fused" else "ts_selcache_check before the score launch",
            "note": ("%d library launches + 1 torch launch (the append of the step's K/V rows) per step; " %
-                    ((8 if compact else (8 if args.vote == "ranked" else 9)) - (1 if args.check == "fused" else 0))) +
+                    ((9 if compact else (8 if args.vote == "ranked" else 9)) - (1 if args.check == "fused" else 0))) +
                    "'graph' = the whole 64-step run captured once as a HIP graph "
                    "and replayed (replays checked against the eager run), 'eager' = host-driven loop"}
     if args.theta_sweep:

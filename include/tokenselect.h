@@ -144,6 +144,7 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
  * order of increasing token index, written as ascending logical token ids.
  * idx [device] int32 [B][k] (slots past the count are set to -1); count [device] int32 [B].
  * -0.0 compares equal to +0.0.
+ * Sequences of up to 8192 tokens (max_seq_len) are ranked by one workgroup each, in one launch whatever the flags.
  * flags: 0, or TS_TOPK_FLAT_VOTES.  By default (decode) the radix select runs as three launches whose last one
  * finishes each sequence on one workgroup: fast when few votes lie within a quarter octave of the k-th vote, as
  * with the peaked votes of Eq. 5, and slow (still exact) when most do.  TS_TOPK_FLAT_VOTES selects the five-launch
