@@ -38,7 +38,7 @@ struct WsLayout {
   int score_nblk;          // ceil(max_seq_len / kScoreTileTokens)
   size_t attn_out;         // float [B][H][nsplit][D]
   size_t attn_ml;          // float [B][H][nsplit][2]
-  size_t pf_stat_part;     // float [B][TS][C][H][2]            (chunk > 1 only)
+  size_t pf_stat_part;     // float [B][TS][C][H][2]            (chunk > 1 only; sized for prefill_max_token_splits)
   size_t pf_vote_part;     // float [B][RB * H_kv][max_seq_len] (chunk > 1 only)
   size_t attn_chunk_o;     // float [B][C][H][nsplit][D]        (chunk > 1 with key-list splits)
   size_t attn_chunk_ml;    // float [B][C][H][nsplit][2]
@@ -64,21 +64,30 @@ inline int chunk_attn_splits(const ts_problem* p, int k) {
   return s;
 }
 
+// workgroups of a chunked-prefill sweep whose token range is split t ways
+inline long prefill_sweep_workgroups(const ts_problem* p, int row_blocks, int t) {
+  return ((long)p->batch * p->num_kv_heads * t + 7) / 8 * 8 * row_blocks;
+}
+// The most token splits that may be chosen: grows with max_seq_len, as the choice below does not.  The workspace is sized by
+// this one, so that a workspace for the longest prompt serves every shorter one.
+inline int prefill_max_token_splits(const ts_problem* p, int row_blocks) {
+  const int ntile = (p->max_seq_len + 63) / 64;
+  int t = 1;
+  while (t < 64 && t < ntile && prefill_sweep_workgroups(p, row_blocks, t + 1) <= 2048) ++t;
+  return t;
+}
 // Token splits of the chunked-prefill sweeps.  The chip holds 512 workgroups at a time (two per CU), so the splits are
 // those whose workgroups fill whole rounds: a workgroup costs its tiles plus about 2.5 tiles of start (query fragments,
 // row statistics, first loads), and a single round leaves the chip waiting for its slowest workgroup -- the more so when
 // the sequences of a batch have different lengths.  (2 x 300 queries of H 28/4 over 12007 and 30011 tokens: 28 splits in
 // four rounds 121 + 140 us, 14 in two 114 + 129, 7 in one 129 + 141; 512 queries of H 32/8 over 262144: 16 and 32 the same.)
 inline int prefill_token_splits(const ts_problem* p, int row_blocks) {
-  const int ntile = (p->max_seq_len + 63) / 64;
-  const long pairs = (long)p->batch * p->num_kv_heads;
+  const int ntile = (p->max_seq_len + 63) / 64, most = prefill_max_token_splits(p, row_blocks);
   const double uneven = p->batch > 1 ? 0.15 : 0.03;
   int best = 1;
   double best_cost = 0.0;
-  for (int t = 1; t <= 64 && t <= ntile; ++t) {
-    const long n = (pairs * t + 7) / 8 * 8 * row_blocks;
-    if (t > 1 && n > 2048) break;
-    const long rounds = (n + 511) / 512;
+  for (int t = 1; t <= most; ++t) {
+    const long rounds = (prefill_sweep_workgroups(p, row_blocks, t) + 511) / 512;
     const double cost = (double)rounds * ((ntile + t - 1) / t + 2.5) * (1.0 + uneven / (double)rounds);
     if (t == 1 || cost < best_cost) { best = t; best_cost = cost; }
   }
@@ -111,8 +120,7 @@ inline WsLayout ws_layout(const ts_problem* p, int k) {
     const int G = p->num_q_heads / p->num_kv_heads;
     w.pf_rb = (p->chunk * G + 255) / 256;
     w.pf_ts = prefill_token_splits(p, w.pf_rb);
-    const int ts = w.pf_ts;
-    w.pf_stat_part = take(B * (size_t)ts * p->chunk * H * 2 * 4);
+    w.pf_stat_part = take(B * (size_t)prefill_max_token_splits(p, w.pf_rb) * p->chunk * H * 2 * 4);
     w.pf_vote_part = take(B * (size_t)w.pf_rb * p->num_kv_heads * (size_t)p->max_seq_len * 4);
   }
   // the sections that depend on k come last, so that every other offset is the same for any k

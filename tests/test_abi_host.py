@@ -47,6 +47,20 @@ def test_workspace_bytes_and_shape_validation():
     assert L.ts_workspace_bytes(None, 4, ctypes.byref(out)) == -1
 
 
+@pytest.mark.parametrize("B,C,H,H_kv,D,k", [(1, 512, 32, 8, 128, 2048), (2, 300, 28, 4, 128, 2048), (1, 64, 8, 2, 64, 256),
+                                            (3, 777, 64, 8, 128, 4096), (1, 128, 1, 1, 64, 16), (5, 2, 32, 32, 64, 512)])
+def test_a_workspace_for_the_longest_prompt_serves_every_shorter_one(B, C, H, H_kv, D, k):
+    L = ts.load()
+    out = ctypes.c_size_t(0)
+    last = 0
+    lens = sorted(set(range(64, 262145, 64)) | set(range(1, 700)) | {x + d for x in range(4096, 262144, 4096) for d in (-1, 1)})
+    for n in lens:
+        p = cproblem(batch=B, chunk=C, num_q_heads=H, num_kv_heads=H_kv, head_dim=D, dtype=ts.TS_BF16, max_seq_len=n)
+        assert L.ts_workspace_bytes(ctypes.byref(p), k, ctypes.byref(out)) == 0
+        assert out.value >= last, n
+        last = out.value
+
+
 def test_calls_reject_bad_arguments_without_launching():
     L = ts.load()
     p = ctypes.byref(cproblem())
