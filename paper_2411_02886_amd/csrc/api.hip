@@ -701,14 +701,11 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
   a.idx_stride = idx_stride; a.max_seq_len = p->max_seq_len; a.sm_scale = sm_scale;
   a.n_init = p->num_initial; a.n_local = p->num_local;
   const int G = p->num_q_heads / p->num_kv_heads;
-  const long chunk_wgs = (long)w.attn_nsplit * p->num_kv_heads * p->batch;
+  const int total = idx_stride + p->num_initial + p->num_local;
+  const long pairs = (long)p->num_kv_heads * p->batch;
+  const long chunk_wgs = w.attn_nsplit * pairs;
   if (p->dtype == TS_BF16 && chunk_wgs >= attn_stream_from(G)) {
-    // a throughput problem: long runs, as few splits as still give every CU a workgroup
-    const long pairs = (long)p->num_kv_heads * p->batch;
-    const int total = idx_stride + p->num_initial + p->num_local;
-    int ns = (int)((256 + pairs - 1) / pairs);
-    if (ns < (total + kStreamMaxSpan - 1) / kStreamMaxSpan) ns = (total + kStreamMaxSpan - 1) / kStreamMaxSpan;
-    a.span = ((total + ns - 1) / ns + kStreamTile - 1) / kStreamTile * kStreamTile;
+    a.span = stream_span(pairs, total);
     a.nsplit = (total + a.span - 1) / a.span;
     return launch_sparse_attn_stream(p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
   }

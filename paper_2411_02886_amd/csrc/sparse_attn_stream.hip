@@ -245,15 +245,31 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(AttnArgs a, int nrow)
   const int ns = min(a.nsplit, (total + a.span - 1) / a.span);   // splits that hold tokens
   const float* ml = a.part_ml + (size_t)hb * a.nsplit * 2;
   const float* po = a.part_out + (size_t)hb * a.nsplit * D + d;
-  float M = -INFINITY;
-  for (int s = 0; s < ns; ++s) M = fmaxf(M, ml[2 * s]);
-  float L = 0.f;
+  constexpr int US = 8;                       // splits whose partials are in flight together
+  float M = -INFINITY, L = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < ns; ++s) {
-    const float w = expf(ml[2 * s] - M);
-    const float4 x = *reinterpret_cast<const float4*>(po + (size_t)s * D);
-    L = fmaf(w, ml[2 * s + 1], L);
-    o.x = fmaf(w, x.x, o.x); o.y = fmaf(w, x.y, o.y); o.z = fmaf(w, x.z, o.z); o.w = fmaf(w, x.w, o.w);
+  for (int s0 = 0; s0 < ns; s0 += US) {
+    float2 v[US];
+    float4 x[US];
+#pragma unroll
+    for (int u = 0; u < US; ++u) {
+      const int s = min(s0 + u, ns - 1);
+      v[u] = *reinterpret_cast<const float2*>(ml + 2 * s);
+      x[u] = *reinterpret_cast<const float4*>(po + (size_t)s * D);
+    }
+    float m = M;
+#pragma unroll
+    for (int u = 0; u < US; ++u) m = fmaxf(m, v[u].x);
+    if (m == -INFINITY) continue;             // nothing but empty splits so far
+    const float f = expf(M - m);
+    L *= f; o.x *= f; o.y *= f; o.z *= f; o.w *= f;
+#pragma unroll
+    for (int u = 0; u < US; ++u) {
+      const float w = s0 + u < ns ? expf(v[u].x - m) : 0.f;
+      L = fmaf(w, v[u].y, L);
+      o.x = fmaf(w, x[u].x, o.x); o.y = fmaf(w, x[u].y, o.y); o.z = fmaf(w, x[u].z, o.z); o.w = fmaf(w, x[u].w, o.w);
+    }
+    M = m;
   }
   const bool any = L > 0.f;
   *reinterpret_cast<uint2*>(a.out + ((size_t)hb * D + d) * 2) =

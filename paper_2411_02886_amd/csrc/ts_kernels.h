@@ -198,8 +198,6 @@ constexpr int kTopkFinalMaxBlk = 8192;   // chunks per sequence the finishing wo
 hipError_t launch_selcache(const SelcacheArgs& a, int B, hipStream_t s);
 hipError_t launch_sparse_attn_decode(int dtype, int D, int G, const AttnArgs& a, int B, hipStream_t s);
 // the streaming form (bf16): a.span list entries per split, a multiple of kStreamTile
-constexpr int kStreamTile = 32;        // keys per wave tile
-constexpr int kStreamMaxSpan = 3584;   // the run's rows in LDS beside the tiles, two workgroups per CU
 hipError_t launch_sparse_attn_stream(int D, int G, const AttnArgs& a, int B, hipStream_t s);
 hipError_t launch_chunk_mean_query(const void* q, void* out, int B, int C, int n, hipStream_t s);
 hipError_t launch_sum_vote(const VoteArgs& a, int B, hipStream_t s);

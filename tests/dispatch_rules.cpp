@@ -1,0 +1,6 @@
+/* The host rules of csrc/ts_common.h behind C names, compiled by tests/rules_util.py: what a launch would be, without a GPU. */
+#include "ts_common.h"
+
+extern "C" {
+int rule_stream_span(long pairs, int total) { return ts::stream_span(pairs, total); }
+}
