@@ -703,15 +703,14 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
   const int G = p->num_q_heads / p->num_kv_heads;
   const int total = idx_stride + p->num_initial + p->num_local;
   const long pairs = (long)p->num_kv_heads * p->batch;
-  const long chunk_wgs = w.attn_nsplit * pairs;
-  if (p->dtype == TS_BF16 && chunk_wgs >= attn_stream_from(G)) {
+  if (p->dtype == TS_BF16 && attn_streams(G, p->head_dim, pairs, total)) {
     a.span = stream_span(pairs, total);
     a.nsplit = (total + a.span - 1) / a.span;
     return launch_sparse_attn_stream(p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
   // chunks per workgroup: one while the chunks alone are few workgroups (a latency problem), four when there are many
-  // thousands (fp32; the next chunk's rows are in flight while a chunk is worked on)
-  a.nch = chunk_wgs >= 8192 ? kAttnMaxRun : 1;
+  // thousands (the next chunk's rows are in flight while a chunk is worked on)
+  a.nch = w.attn_nsplit * pairs >= 8192 ? kAttnMaxRun : 1;
   if (a.nch > w.attn_nsplit) a.nch = w.attn_nsplit;
   if (a.nch < 1) a.nch = 1;
   if (a.nch > kAttnMaxRun) a.nch = kAttnMaxRun;

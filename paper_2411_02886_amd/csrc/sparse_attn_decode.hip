@@ -6,8 +6,8 @@
 // the gathered K and V rows).  For one sequence memory latency, not bandwidth, bounds this step (a few MiB are
 // gathered), so every K and V load of a wave is issued before the first multiply; logits use eight
 // lanes per K row, a local softmax sits in LDS, the P.V product uses 16-byte V pieces per lane.  With
-// thousands of such workgroups (large batches) a workgroup takes several chunks in a row instead (MULTI; fp32 only,
-// bf16 batches take sparse_attn_stream.hip).  A
+// thousands of such workgroups (large batches) a workgroup takes several chunks in a row instead (MULTI); most bf16
+// batches take sparse_attn_stream.hip (attn_streams).  A
 // second small kernel merges the (max, sum, partial output) triples of the splits.
 #include "ts_kernels.h"
 #include "ts_score_math.h"
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(D * kMergeGroups) void sparse_attn_merge_kernel(Att
 
 template <int DT, int D>
 static hipError_t attn_launch_g(int G, const AttnArgs& a, dim3 grid, hipStream_t s) {
-#define TS_CASE(g) case g: if (DT == TS_F32 && a.nch > 1) hipLaunchKernelGGL((sparse_attn_decode_kernel<TS_F32, D, g, true>), grid, dim3(256), 0, s, a); \
+#define TS_CASE(g) case g: if (a.nch > 1) hipLaunchKernelGGL((sparse_attn_decode_kernel<DT, D, g, true>), grid, dim3(256), 0, s, a); \
                    else hipLaunchKernelGGL((sparse_attn_decode_kernel<DT, D, g, false>), grid, dim3(256), 0, s, a); break;
   switch (G) {
     TS_CASE(1) TS_CASE(2) TS_CASE(3) TS_CASE(4) TS_CASE(5) TS_CASE(6) TS_CASE(7) TS_CASE(8)
@@ -317,7 +317,7 @@ static hipError_t attn_launch_g(int G, const AttnArgs& a, dim3 grid, hipStream_t
 }
 
 hipError_t launch_sparse_attn_decode(int dtype, int D, int G, const AttnArgs& a, int B, hipStream_t s) {
-  if (a.nch < 1 || a.nch > (dtype == TS_F32 ? kAttnMaxRun : 1)) return hipErrorInvalidValue;
+  if (a.nch < 1 || a.nch > kAttnMaxRun) return hipErrorInvalidValue;
   dim3 grid(a.nsplit, a.H_kv, B);
   if (dtype == TS_F32) return D == 64 ? attn_launch_g<TS_F32, 64>(G, a, grid, s) : attn_launch_g<TS_F32, 128>(G, a, grid, s);
   return D == 64 ? attn_launch_g<TS_BF16, 64>(G, a, grid, s) : attn_launch_g<TS_BF16, 128>(G, a, grid, s);

@@ -16,11 +16,6 @@ constexpr int kTopkChunk = 2048;       // keys per workgroup in the top-k passes
 constexpr int kBoundHistCopies = 8;    // replicas of the lower-bound histogram (same-address atomics are what its flush costs)
 constexpr int kAttnChunk = 64;         // selected tokens per workgroup in sparse attention
 constexpr int kAttnMaxRun = 4;        // chunks one attention workgroup folds into its partial, at most (256 list entries: one per thread)
-// bf16: from this many 64-token chunk workgroups on the attention streams long runs (sparse_attn_stream.hip).  The more
-// query heads a KV head has, the more the vector kernel has to do per row, and the earlier the line.  Measured, kernel
-// alone: 1344 of them (4 x 2688 tokens, H 64/8) 19.6 us in chunks, 12.1 streamed; 2048 (8 x 2048, H 32/8) 16.2 and 16.0; whole
-// steps: 1280 (5 x 2048, H 32/8) 98 us in chunks, 101 streamed; 2560 (5 x 2048, H 16/16, D 64) 89 and 92
-inline long attn_stream_from(int G) { return G >= 5 ? 1024 : G >= 3 ? 2048 : 4096; }
 constexpr int kAttnMaxSplit = 512;     // splits the merge kernel can stage (k <= 32768)
 
 constexpr int kStreamTile = 32;        // keys per wave tile
@@ -42,6 +37,23 @@ inline int stream_span(long pairs, int total) {
     if (best == 0 || cost < best_cost) { best = span; best_cost = cost; }
   }
   return best;
+}
+
+// bf16: whether the attention streams long runs (sparse_attn_stream.hip) instead of taking 64-token chunks, `wgs` of them
+// (sparse_attn_decode.hip).  The more query heads a KV head has, the more the vector kernel has to do per row, and the
+// earlier the line.  Three heads and more, at or just above it (us, chunks and streamed): H 64/8, D 128, 8 x 1000 tokens
+// 20.9 and 13.2; H 32/8, D 128, 8 x 2048 21.8 and 18.1, 1 x 16384 24.4 and 20.8; H 24/8, D 64, 16 x 1000 15.1 and 13.2.
+// With one or two heads the vector kernel keeps up with the memory until its partials are many (2048 tokens of H 16/8:
+// D 128 with 9216 workgroups 61 and 60, with 10496 74 and 66; D 64 with 18432 63 and 68, with 23040 83 and 74).  Before
+// that streaming pays for short lists that need no splits (H 16/8, D 128, 47 x 700 tokens 33 and 29), with one head if they
+// also fill the rounds (H 16/16, D 128, 700 tokens: 480 pairs 35 and 33, 528 pairs in their three rounds 39 and 44).
+inline bool attn_streams(int G, int D, long pairs, int total) {
+  const long wgs = (total + kAttnChunk - 1) / kAttnChunk * pairs;
+  if (G >= 3) return wgs >= (G >= 5 ? 1024 : 2048);
+  if (wgs < 4096) return false;
+  if (wgs >= (D == 128 ? 10240 : 22528)) return true;
+  if (total > (G == 2 ? 1536 : 1024) || stream_span(pairs, total) < total) return false;
+  return G == 2 || 5 * pairs >= 4 * ((pairs + 255) / 256 * 256);
 }
 
 // ---------------------------------------------------------------- workspace layout (host + device)

@@ -2,5 +2,6 @@
 #include "ts_common.h"
 
 extern "C" {
+int rule_attn_streams(int G, int D, long pairs, int total) { return ts::attn_streams(G, D, pairs, total) ? 1 : 0; }
 int rule_stream_span(long pairs, int total) { return ts::stream_span(pairs, total); }
 }

@@ -23,5 +23,17 @@ def rules():
                                "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2411_02886_amd", "csrc"),
                                os.path.join(ROOT, "tests", "dispatch_rules.cpp"), "-o", so])
         L = ctypes.CDLL(so)
+    L.rule_attn_streams.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     L.rule_stream_span.argtypes = [ctypes.c_long, ctypes.c_int]
     return L
+
+
+def decode_attention(B, H, H_kv, D, total):
+    """(streamed, splits) of a bf16 decode attention over lists of `total` entries."""
+    L, chunks = rules(), (total + 63) // 64
+    if not L.rule_attn_streams(H // H_kv, D, H_kv * B, total):
+        wgs = chunks * H_kv * B
+        nch = min(4 if wgs >= 8192 else 1, chunks)
+        return False, (chunks + nch - 1) // nch
+    span = L.rule_stream_span(H_kv * B, total)
+    return True, (total + span - 1) // span

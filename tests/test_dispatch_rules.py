@@ -30,3 +30,16 @@ def test_streaming_attention_splits_fill_the_rounds(total):
         whole = pairs * total / 256                    # keys per CU if nothing were left over
         # 1.5: 171 pairs in one run each, a third of the CUs without work, where two runs and their merge cost more
         assert rounds * span <= 1.5 * whole + 160, (pairs, runs)
+
+
+@pytest.mark.parametrize("G,D,pairs,total,streamed", [
+    # measured, us in 64-token chunks and streamed
+    (1, 64, 144, 2048, 0), (1, 64, 288, 2048, 0), (1, 64, 384, 2048, 0),       # 20.2 / 22.4, 35.2 / 37.5, 43 / 44
+    (1, 128, 144, 2048, 0), (1, 128, 112, 4096, 0),                            # 30.1 / 33.7, 42 / 47
+    (2, 64, 288, 2048, 0), (2, 64, 384, 2048, 0), (2, 128, 136, 4000, 0),      # 35.6 / 36.9, 43 / 45, 53 / 55
+    (1, 64, 720, 2048, 1), (1, 128, 368, 2048, 1), (2, 128, 368, 2048, 1),     # 80 / 75, 81 / 71, 85 / 72
+    (1, 64, 832, 300, 1), (1, 128, 480, 700, 1), (1, 128, 528, 700, 0),        # 20 / 16, 35 / 33, 39 / 44
+    (2, 64, 648, 700, 1), (2, 128, 424, 700, 1),                               # 31 / 27, 36 / 30
+    (4, 128, 64, 2048, 1), (3, 64, 128, 1000, 1), (8, 128, 64, 1000, 1)])      # 21.8 / 18.1, 15.1 / 13.2, 20.9 / 13.2
+def test_streaming_attention_only_where_it_is_the_faster_form(G, D, pairs, total, streamed):
+    assert rules().rule_attn_streams(G, D, pairs, total) == streamed

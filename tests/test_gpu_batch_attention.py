@@ -1,12 +1,14 @@
-"""The streaming form of the decode attention (bf16 batches) against plain float64 attention: runs of one key, of less
+"""Both batch forms of the decode attention against plain float64 attention.  Streaming (bf16): runs of one key, of less
 and more than a tile, of several splits; every group size; scales that are zero, negative or make the logits outgrow the
-first reference; empty sequences beside full ones."""
+first reference; empty sequences beside full ones.  Several 64-token chunks per workgroup (fp32, and bf16 with one or two
+heads per KV head): a last workgroup of one to four chunks, empty splits, forced tokens, up to eight heads."""
 import math
 
 import numpy as np
 import pytest
 
 import workloads as W
+from rules_util import decode_attention
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -25,16 +27,40 @@ CASES = [
 ]
 
 
+CHUNKED = [
+    # dtype, then as above: 8192 chunk workgroups and more, counted over lists of k entries
+    (W.F32, 33, 16, 8, 128, 16, 700, 2000, 0, 0, None),
+    (W.F32, 35, 16, 8, 128, 16, 600, 1900, 10, 50, None),
+    (W.F32, 70, 20, 4, 64, 4, 450, 1870, 3, 61, 1.0),
+    (W.F32, 66, 32, 4, 128, 16, 330, 2000, 0, 0, -0.3),
+    (W.F32, 9, 16, 16, 64, 1, 1500, 4096, 4, 0, None),
+    (W.BF16, 33, 16, 8, 64, 16, 700, 2000, 10, 50, None),
+    (W.BF16, 18, 16, 16, 128, 16, 900, 2048, 0, 0, None),
+]
+
+
 @pytest.mark.parametrize("B,H,H_kv,D,P,longest,k,ni,nl,scale", CASES)
 def test_batch_attention(B, H, H_kv, D, P, longest, k, ni, nl, scale):
+    assert decode_attention(B, H, H_kv, D, k + ni + nl)[0], "not streamed"
+    check_batch(W.BF16, B, H, H_kv, D, P, longest, k, ni, nl, scale)
+
+
+@pytest.mark.parametrize("dtype,B,H,H_kv,D,P,longest,k,ni,nl,scale", CHUNKED)
+def test_batch_attention_in_chunks(dtype, B, H, H_kv, D, P, longest, k, ni, nl, scale):
+    assert (k + ni + nl + 63) // 64 * H_kv * B >= 8192
+    assert dtype == W.F32 or not decode_attention(B, H, H_kv, D, k + ni + nl)[0], "streamed"
+    check_batch(dtype, B, H, H_kv, D, P, longest, k, ni, nl, scale)
+
+
+def check_batch(dtype, B, H, H_kv, D, P, longest, k, ni, nl, scale):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2411_02886_amd.runtime import DecodeLayer, to_device, to_host
-    print("batch attention", B, H, H_kv, D, P, longest, k, ni, nl, scale, flush=True)
+    print("batch attention", dtype, B, H, H_kv, D, P, longest, k, ni, nl, scale, flush=True)
     rng = np.random.default_rng(B + k)
     lens = rng.integers(1, longest + 1, size=B)
     lens[0], lens[-1] = longest, (0 if B > 3 else 1)
-    w = W.make_workload("batch", dtype=W.BF16, B=B, H=H, H_kv=H_kv, D=D, P=P, seq_lens=lens, k=k, seed=3 * B + D + k)
+    w = W.make_workload("batch", dtype=dtype, B=B, H=H, H_kv=H_kv, D=D, P=P, seq_lens=lens, k=k, seed=3 * B + D + k)
     layer = DecodeLayer.from_workload(w, num_initial=ni, num_local=nl)
     idx = np.full((B, k), -1, np.int32)
     count = np.zeros(B, np.int32)
@@ -47,10 +73,10 @@ def test_batch_attention(B, H, H_kv, D, P, longest, k, ni, nl, scale):
     sm = 1.0 / math.sqrt(D) if scale is None else scale
     layer.attend(to_device(w.q), sm)
     torch.cuda.synchronize()
-    out = W.as_f32(to_host(layer.out, bits16=True), W.BF16).astype(np.float64)
+    out = W.as_f32(to_host(layer.out, bits16=dtype == W.BF16), dtype).astype(np.float64)
     lse = to_host(layer.lse).astype(np.float64)
     G = H // H_kv
-    q = W.as_f32(w.q, W.BF16).astype(np.float64)
+    q = W.as_f32(w.q, dtype).astype(np.float64)
     for b in sorted(set([0, B - 1, B - 2] + list(rng.integers(0, B, size=5)))):
         n = int(lens[b])
         if n == 0:
@@ -59,8 +85,8 @@ def test_batch_attention(B, H, H_kv, D, P, longest, k, ni, nl, scale):
         lo = min(ni, n)
         tok = np.concatenate([np.arange(lo), idx[b, :count[b]], np.arange(max(lo, n - nl), n)])
         slots = w.slots_of(b)[tok]
-        K = W.as_f32(w.k_pool.reshape(-1, H_kv, D)[slots], W.BF16).astype(np.float64)
-        V = W.as_f32(w.v_pool.reshape(-1, H_kv, D)[slots], W.BF16).astype(np.float64)
+        K = W.as_f32(w.k_pool.reshape(-1, H_kv, D)[slots], dtype).astype(np.float64)
+        V = W.as_f32(w.v_pool.reshape(-1, H_kv, D)[slots], dtype).astype(np.float64)
         for h in range(H):
             s = K[:, h // G] @ q[b, 0, h] * float(np.float32(sm))
             p = np.exp(s - s.max())
@@ -68,5 +94,8 @@ def test_batch_attention(B, H, H_kv, D, P, longest, k, ni, nl, scale):
             # the weights are float (the output's rounding to bf16 is 2^-9 of it); logits carry float rounding of up to
             # |s| * 2^-22, which acts on a weight as a factor
             err = np.abs(s).max() * 2.0 ** -21 + 2.0 ** -20
-            assert np.all(np.abs(out[b, 0, h] - ref) <= 2.0 ** -8 * np.abs(ref) + err * np.abs(V[:, h // G]).max()), (b, h)
+            if dtype == W.F32:
+                err += 2.0 ** -19            # the float sums over V: chains of up to 32 additions, 2^-24 each
+            own = 2.0 ** (-8 if dtype == W.BF16 else -22)
+            assert np.all(np.abs(out[b, 0, h] - ref) <= own * np.abs(ref) + err * np.abs(V[:, h // G]).max()), (b, h)
             assert abs(lse[b, 0, h] - (s.max() + math.log(p.sum()))) <= err + np.abs(s).max() * 2.0 ** -22, (b, h)
