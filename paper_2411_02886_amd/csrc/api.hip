@@ -434,11 +434,7 @@ int32_t ts_topk_exact(const ts_problem* p, const void* q, const float* vote_hi, 
   a.page_indptr = p->page_indptr; a.page_indices = p->page_indices; a.row_stats = row_stats;
   a.H = p->num_q_heads; a.H_kv = p->num_kv_heads; a.P = p->page_size; a.p_shift = ilog2(p->page_size);
   a.scale = score_scale;
-  // two workgroups per CU in all (one round: their registers allow no more), four candidates each at least (the list usually holds a little more than k)
-  a.parts = 512 / p->batch;
-  if (a.parts > (k + 3) / 4) a.parts = (k + 3) / 4;
-  if (a.parts > 512) a.parts = 512;
-  if (a.parts < 1) a.parts = 1;
+  a.parts = eval_workgroups(p->batch, p->max_seq_len);
   const int G = p->num_q_heads / p->num_kv_heads;
   if (launch_topk_compact(a.t, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   if (launch_topk_eval(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;

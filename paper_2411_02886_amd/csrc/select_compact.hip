@@ -329,8 +329,10 @@ __global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a
   const uint32_t total = carry;
   if (blockIdx.x == 0 && threadIdx.x == 0) ta.state[b * 8 + kStTotal] = total;
   __syncthreads();
-  const uint32_t c_begin = (uint32_t)((unsigned long long)total * blockIdx.x / gridDim.x);
-  const uint32_t c_end = (uint32_t)((unsigned long long)total * (blockIdx.x + 1) / gridDim.x);
+  const uint32_t groups = min((uint32_t)gridDim.x, (total + kEvalMinShare - 1) / kEvalMinShare);   // that have work
+  if (blockIdx.x >= groups) return;
+  const uint32_t c_begin = (uint32_t)((unsigned long long)total * blockIdx.x / groups);
+  const uint32_t c_end = (uint32_t)((unsigned long long)total * (blockIdx.x + 1) / groups);
   const double c2d = (double)a.scale * 1.44269504088896340736;
   const int npages = (Nb + a.P - 1) >> a.p_shift;
   uint2* dense = ta.dense + (size_t)b * ta.nblk * kTopkChunk;

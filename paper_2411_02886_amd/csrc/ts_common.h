@@ -56,6 +56,17 @@ inline bool attn_streams(int G, int D, long pairs, int total) {
   return G == 2 || 5 * pairs >= 4 * ((pairs + 255) / 256 * 256);
 }
 
+// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (one round:
+// their registers allow no more).  How many candidates there are is known on the device only -- a little more than k when
+// votes are peaked, every token when they are flat, whatever k is -- so k has no say here (k 64 of 1048576 flat votes: 12.9 ms
+// with k / 4 workgroups, 1.7 ms with 512); those that would get fewer than kEvalMinShare candidates leave at once.
+constexpr int kEvalMinShare = 4;
+inline int eval_workgroups(int batch, int max_seq_len) {
+  int n = 512 / batch;
+  if (n > (max_seq_len + kEvalMinShare - 1) / kEvalMinShare) n = (max_seq_len + kEvalMinShare - 1) / kEvalMinShare;
+  return n < 1 ? 1 : n;
+}
+
 // ---------------------------------------------------------------- workspace layout (host + device)
 struct WsLayout {
   size_t topk_hist;        // uint32 [B][3][kTopkBins] : one histogram per radix pass (must start zeroed)

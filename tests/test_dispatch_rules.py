@@ -43,3 +43,15 @@ def test_streaming_attention_splits_fill_the_rounds(total):
     (4, 128, 64, 2048, 1), (3, 64, 128, 1000, 1), (8, 128, 64, 1000, 1)])      # 21.8 / 18.1, 15.1 / 13.2, 20.9 / 13.2
 def test_streaming_attention_only_where_it_is_the_faster_form(G, D, pairs, total, streamed):
     assert rules().rule_attn_streams(G, D, pairs, total) == streamed
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 8, 100, 511, 600])
+def test_candidates_are_evaluated_by_a_full_chip_whatever_k(batch):
+    """With flat votes every token is a candidate: the workgroups are counted by what a sequence can hold, not by k."""
+    for n in (1, 4, 5, 1000, 2048, 131072, 1 << 20):
+        parts = rules().rule_eval_workgroups(batch, n)
+        assert 1 <= parts <= 512
+        if n >= 2048:
+            assert batch * parts >= 256, (batch, n)       # a workgroup for every CU
+        assert parts == 1 or batch * parts <= 512         # one round at two per CU
+        assert parts <= (n + 3) // 4                      # four candidates each, at least

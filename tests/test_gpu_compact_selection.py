@@ -226,18 +226,19 @@ def test_matrix_core_score_pass_run_lengths_and_grids(gpu, rr, wg, heads):
         gpu.ts_debug_set_codes_path(1, 0); gpu.ts_debug_set_score_variant(2, 0, 0)
 
 
-@pytest.mark.parametrize("lens,parts", [([70000, 66000, 41000], 2), ([150000, 9000], 1), ([30000], 4), ([70000, 70000, 70000, 3000], 1)],
-                         ids=["2-per-chunk", "1-per-chunk", "4-per-chunk", "1-per-chunk-batch4"])
-def test_refine_with_several_workgroups_per_chunk(gpu, lens, parts):
-    """The exact re-evaluation runs 256 / (chunks x batch) workgroups per 2048-token chunk, four at most: every split
-    gives the oracle's selection."""
-    w = W.make_workload("parts", dtype=W.BF16, H=8, H_kv=2, D=64, P=16, B=len(lens), seq_lens=lens, k=700, beta=2.5,
+@pytest.mark.parametrize("lens,parts", [([70000, 66000, 41000], 170), ([150000, 9000], 256), ([30000], 512), ([70000, 70000, 70000, 3000], 128)],
+                         ids=["batch3", "batch2", "batch1", "batch4"])
+@pytest.mark.parametrize("k,scale", [(700, 1.0), (40, 0.01)], ids=["peaked", "flat"])
+def test_candidates_split_over_many_workgroups(gpu, lens, parts, k, scale):
+    """The exact re-evaluation numbers a sequence's candidates through and gives its workgroups equal shares of them: a
+    few candidates each, or (flat votes, every token a candidate) hundreds in several batches, whatever k is."""
+    from rules_util import rules
+    w = W.make_workload("parts", dtype=W.BF16, H=8, H_kv=2, D=64, P=16, B=len(lens), seq_lens=lens, k=k, beta=2.5,
                         planted_per_head=2, seed=sum(lens) % 977)
     layer, q = make_layer(w)
-    nblk = (max(lens) + 2047) // 2048
-    assert max(1, min(4, 256 // (nblk * len(lens)))) == parts
-    print("compact refine parts", parts, lens, flush=True)
-    check_compact(w, layer, q, score_scale=1.0, label="parts%d" % parts)
+    assert rules().rule_eval_workgroups(len(lens), max(lens)) == parts
+    print("compact candidates", parts, lens, k, scale, flush=True)
+    check_compact(w, layer, q, score_scale=scale, label="parts%d k%d" % (parts, k))
 
 
 def test_batch_ragged_and_forced(gpu):
