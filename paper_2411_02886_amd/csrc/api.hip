@@ -221,8 +221,8 @@ static size_t score_lds_bytes(const ScoreArgs& a, int G) {
 // Launch shape of the matrix-core score kernel (both forms): fills the wave-tile fields and a.RR, returns the
 // workgroups per sequence.  A wave owns one run of consecutive tiles where the sequence is short enough, so that
 // its output leaves in one burst at the end of its life; about 2048 waves per sequence (measured on MI355X:
-// 131072 tokens 49 us with one tile per wave, 45.7 us with two).
-static void mfma_launch_shape(const ts_problem* p, int G, bool dense, ScoreArgs* a, long* wg_out) {
+// 131072 tokens 49 us with one tile per wave, 45.7 us with two).  whole_batch: no sequence can be skipped.
+static void mfma_launch_shape(const ts_problem* p, int G, bool dense, bool whole_batch, ScoreArgs* a, long* wg_out) {
   a->HB = G <= 4 ? 8 : 4; a->hb_shift = ilog2(a->HB); a->NU = p->num_kv_heads / a->HB;
   a->uniform_page = p->page_size >= (8 / a->HB);
   const long ntt = (p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens;
@@ -250,10 +250,11 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, ScoreArgs*
       if (fill > best + 0.05) { best = fill; rr = r; }
     }
     // A batch of shorter sequences fills the machine with runs of four tiles too, and the compact form's bytes then leave
-    // in fewer, longer bursts (score pass alone: 8 sequences of 16384 to 65536 tokens, H 32/8, 82.1 -> 71.8 us; 32 of 1031 to
-    // 16001, 111.7 -> 107.8; 16 of 4000 to 16000, H 28/4, 37.5 -> 34.1).  The score matrix's rows, four times as many bytes,
-    // lose that way (118.8 -> 147.5 us with the 32).
-    if (!dense && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
+    // in fewer, longer bursts (score pass alone: 32 sequences of 1031 to 16001 tokens, H 32/8, 117 -> 114 us; 16 of 4000
+    // to 16000, H 28/4, 40 -> 37; 8 of 65536, H 32/8, 190 -> 188).  Not where a skip mask or the Selection Cache's test may leave
+    // one or two of them to fill it (one of the 32: 15 us with runs of one tile, 38 of four; one of the 8: 28 and 43), and not
+    // for the score matrix's rows, four times as many bytes (the 32: 118.8 -> 147.5).
+    if (!dense && whole_batch && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
   }
   if (rr > 8) rr = 8;
   while (rr > 1 && score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) > 163840) --rr;
@@ -265,13 +266,13 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, ScoreArgs*
 
 // Partials per sequence that a score launch of this shape leaves (workgroups it runs with): what the statistics merge
 // loads before it has seen the count in the workspace.
-static int expected_parts(const ts_problem* p, bool dense) {
+static int expected_parts(const ts_problem* p, bool dense, bool whole_batch) {
   const int G = p->num_q_heads / p->num_kv_heads;
   if ((dense ? g_score_variant == 2 : true) && g_codes_mfma && (p->num_q_heads % 4) == 0 &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     ScoreArgs a{};
     long wgl = 0;
-    mfma_launch_shape(p, G, dense, &a, &wgl);
+    mfma_launch_shape(p, G, dense, whole_batch, &a, &wgl);
     return (int)wgl;
   }
   return score_workgroups(p);
@@ -311,7 +312,7 @@ static int32_t paged_qk_scores_impl(const ts_problem* p, const void* q, const ts
   if (g_score_variant == 2 && g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)scores & 3) == 0) &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, true, &a, &wgl);
+    mfma_launch_shape(p, G, true, false, &a, &wgl);
     const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, dim3((unsigned)wgl, p->batch),
                                                  score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, true), (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
@@ -352,7 +353,7 @@ static int32_t paged_qk_codes_impl(const ts_problem* p, const void* q, const ts_
   if (g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)codes & 3) == 0) &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, false, &a, &wgl);
+    mfma_launch_shape(p, G, false, skip == nullptr && sc == nullptr, &a, &wgl);
     // Bytes and block maxima that fit the chip's L2 (eight XCDs x 4 MiB) with room to spare stay there as dirty lines
     // until the kernel ends and cost the read stream nothing; more than that thrashes it, and streaming them past the
     // L2 is the cheaper way (measured, H 28/4: 524288 tokens 89.2 us cached / 90.2 streamed, 786432 tokens 142.0 / 135.7,
@@ -401,7 +402,7 @@ int32_t ts_soft_vote_bounds(const ts_problem* p, const uint8_t* codes, float sco
   a.scale = score_scale;
   VoteArgs m{};
   m.partials = (const float*)((uint8_t*)ws + w.score_partials); m.hdr = a.hdr;
-  m.row_stats_out = row_stats; m.skip = skip; m.parts_hint = expected_parts(p, false); m.H = p->num_q_heads; m.scale = score_scale;
+  m.row_stats_out = row_stats; m.skip = skip; m.parts_hint = expected_parts(p, false, skip == nullptr); m.H = p->num_q_heads; m.scale = score_scale;
   if (launch_stats_merge(m, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   return launch_vote_bounds(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
@@ -454,7 +455,7 @@ int32_t ts_soft_vote(const ts_problem* p, const float* scores, float score_scale
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, false);
   return launch_soft_vote(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -471,7 +472,7 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, false);
   a.rank_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_soft_vote_ranked(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }

@@ -241,6 +241,38 @@ def test_candidates_split_over_many_workgroups(gpu, lens, parts, k, scale):
     check_compact(w, layer, q, score_scale=scale, label="parts%d k%d" % (parts, k))
 
 
+@pytest.mark.parametrize("check", [False, True], ids=["skip-mask", "cache-test"])
+def test_a_sequence_scanned_among_skipped_ones_runs_as_it_would_alone(gpu, check):
+    """The score pass of a call that may skip sequences is shaped for each of them, whatever the batch: the one that is
+    scanned fills the machine, and its statistics are those of its own call bit for bit."""
+    from paper_2411_02886_amd.runtime import to_host
+    w = W.make_workload("one_of_16", dtype=W.BF16, H=32, H_kv=8, D=128, P=16, B=16, seq_lens=[50] * 11 + [20000] + [50] * 4,
+                        k=128, beta=2.5, planted_per_head=2, seed=63)
+    layer, q = make_layer(w)
+    print("one of sixteen", check, flush=True)
+    if check:
+        layer.cached_q.copy_(q.view(layer.cached_q.shape)); layer.first.zero_(); layer.first[11] = 1
+        layer.select_compact(q, 1.0, None, check_theta=0.9)
+        assert to_host(layer.reuse).tolist() == [1] * 11 + [0] + [1] * 4
+    else:
+        skip = torch.ones(16, dtype=torch.uint8, device=q.device); skip[11] = 0
+        layer.select_compact(q, 1.0, skip)
+    torch.cuda.synchronize()
+    stats, idx = to_host(layer.row_stats)[11].copy(), to_host(layer.idx)[11].copy()
+    alone = gpu_layer_of_one(w, 11)
+    alone.select_compact(q[11:12].contiguous(), 1.0, None)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(alone.row_stats)[0], stats)
+    assert np.array_equal(to_host(alone.idx)[0], idx)
+
+
+def gpu_layer_of_one(w, b):
+    from paper_2411_02886_amd.runtime import DecodeLayer
+    return DecodeLayer(dtype=w.dtype, H=w.H, H_kv=w.H_kv, D=w.D, P=w.P, k=w.k, k_pool=w.k_pool, v_pool=w.v_pool,
+                       page_indptr=np.array([0, len(w.pages_of(b))], np.int32), page_indices=w.pages_of(b), seq_lens=[int(w.seq_lens[b])],
+                       max_seq_len=int(max(w.seq_lens)))
+
+
 def test_batch_ragged_and_forced(gpu):
     w = W.make_workload("ragged", dtype=W.BF16, H=32, H_kv=8, D=128, P=16, B=6, seq_lens=[4100, 0, 37, 2048, 9999, 1],
                         k=256, beta=2.5, planted_per_head=0, seed=11)
