@@ -21,8 +21,10 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-constexpr float kStUnset = -1e30f;            // reference exponent before the first key
+constexpr float kStUnset = -3.40282347e38f;   // reference logit before the first key: no finite logit lies below it
 constexpr float kStRaise = 1073741824.f;      // a sum above this raises the reference
+constexpr float kStBig = 1048576.f;           // references beyond this: the logits are rounded before it is taken off them
+constexpr float kLog2e = 1.44269504088896340736f;
 
 // place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 8 rows x 2 pieces (V^T) each fall on
 // all banks
@@ -92,8 +94,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
     if (col < G) v = *reinterpret_cast<const uint4*>(a.q + (hb0 + col) * RB + ks * 64 + kgrp * 16);
     qf[ks] = __builtin_bit_cast(bf16x8_t, v);
   }
-  float c2 = a.sm_scale * 1.44269504088896340736f;
-  if (c2 == 0.f) c2 = 1e-37f;                 // the same weights (all 1)
+  const float sm = a.sm_scale;
   __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0): from here on only the row loads are outstanding
   __syncthreads();
 
@@ -116,7 +117,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
     for (int i = 0; i < NLD; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" :: "s"(dst + i * 1024), "v"(pool + off[i]) : "memory", "m0");
   };
-  float ref = kStUnset, lsum = 0.f;           // of head `col`: reference exponent (the same in its four lanes), this lane's keys' sum
+  float ref = kStUnset, lsum = 0.f;           // of head `col`: reference logit (the same in its four lanes), this lane's keys' sum
+  bool big = false;                           // some head's reference is large (the same for the whole wave)
   f32x4_t o[DB];                              // O^T: row d = 16 * db + 4 * kgrp + r, column = head
 #pragma unroll
   for (int db = 0; db < DB; ++db) o[db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
@@ -139,7 +141,9 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                     // the K tile has been read
     if (more) { rows_of(tile + 4); load_rows(a.k_pool, lds_k); }
-    // ---- weights against the reference
+    // ---- weights against the reference: exp(logit - reference).  One fma forms the difference, which loses least; its
+    // exact product differs from the rounded one that the reference came from by up to 2^-24 of the logit, though, and with
+    // logits of 2^31 that alone would over- or underflow the exponential
     const int left = nj - tile * kStreamTile;                              // keys of this tile that exist
     float p[8];
     float sum;
@@ -147,17 +151,19 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
       sum = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        p[e] = __builtin_amdgcn_exp2f(fmaf(c2, s[e >> 2][e & 3], -ref));
+        const float x = s[e >> 2][e & 3];
+        p[e] = __builtin_amdgcn_exp2f((big ? x * sm - ref : fmaf(x, sm, -ref)) * kLog2e);
         if (16 * (e >> 2) + 4 * kgrp + (e & 3) >= left) p[e] = 0.f;
         sum += p[e];
       }
       if (__builtin_amdgcn_ballot_w64(!(sum <= kStRaise)) == 0) break;
       float m = ref;                                                       // first keys, or a logit far above the reference
 #pragma unroll
-      for (int e = 0; e < 8; ++e) m = fmaxf(m, c2 * s[e >> 2][e & 3]);     // (a repeated key past the end is a real one)
+      for (int e = 0; e < 8; ++e) m = fmaxf(m, s[e >> 2][e & 3] * sm);     // (a repeated key past the end is a real one)
       m = fmaxf(m, __shfl_xor(m, 16));
       m = fmaxf(m, __shfl_xor(m, 32));
-      const float f = __builtin_amdgcn_exp2f(ref - m);                     // 0 while the reference is unset
+      big = __builtin_amdgcn_ballot_w64(fabsf(m) > kStBig) != 0;
+      const float f = __builtin_amdgcn_exp2f((ref - m) * kLog2e);          // 0 while the reference is unset
       lsum *= f;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -216,17 +222,16 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
     float x = 0.f, l = 0.f;
 #pragma unroll
     for (int w4 = 0; w4 < 4; ++w4) {
-      const float f = __builtin_amdgcn_exp2f(s_ml[w4][g][0] - m);          // a wave without keys: 2^-huge = 0
+      const float f = __builtin_amdgcn_exp2f((s_ml[w4][g][0] - m) * kLog2e);   // a wave without keys: 0
       x = fmaf(f, so[(w4 * G + g) * (D + 4) + d], x);
       l = fmaf(f, s_ml[w4][g][1], l);
     }
-    const float ln_m = m * 0.69314718055994530942f;
     if (a.nsplit > 1) {
       a.part_out[((hb0 + g) * a.nsplit + split) * D + d] = x;
-      if (d == 0) { float* ml = a.part_ml + ((hb0 + g) * a.nsplit + split) * 2; ml[0] = ln_m; ml[1] = l; }
+      if (d == 0) { float* ml = a.part_ml + ((hb0 + g) * a.nsplit + split) * 2; ml[0] = m; ml[1] = l; }
     } else {
       reinterpret_cast<uint16_t*>(a.out)[(hb0 + g) * D + d] = (uint16_t)f32_to_bf16_bits(l > 0.f ? x / l : 0.f);
-      if (d == 0 && a.lse != nullptr) a.lse[hb0 + g] = l > 0.f ? ln_m + logf(l) : -INFINITY;
+      if (d == 0 && a.lse != nullptr) a.lse[hb0 + g] = l > 0.f ? m + logf(l) : -INFINITY;
     }
   }
 }

@@ -1,0 +1,96 @@
+"""The attention kernels at the ends of the number range, against plain float64: logits of any finite size, values up to
+what a sum of them can hold, and the log-sum-exp of the streaming form against that of the form it stands in for."""
+import math
+
+import numpy as np
+import pytest
+
+import workloads as W
+from rules_util import decode_attention
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# form: B, C, H, H_kv, D, tokens before the chunk (all of them selected)
+FORMS = {
+    "chunks": (1, 1, 8, 2, 64, 300),
+    "streamed": (26, 1, 40, 8, 64, 300),
+    "streamed-splits": (2, 1, 64, 8, 128, 4096),
+    "chunk-form": (1, 24, 8, 2, 128, 100),
+    "chunk-form-splits": (1, 48, 8, 2, 64, 1000),
+}
+STREAMED = {"chunks": (False, 5), "streamed": (True, 1), "streamed-splits": (True, 16)}
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_02886_amd as ts
+    ts.load()
+    return ts
+
+
+def attend(form, K, q, V, sm):
+    """Attention of every head over all tokens, with the same key rows K [n][D], query row q [D] and value rows V [n][D]
+    everywhere.  Returns (out, lse) of the last sequence as float64 [C][H][D], [C][H] and the references [C][D], [C]."""
+    from paper_2411_02886_amd.runtime import ChunkSelector, DecodeLayer, to_device, to_host
+    B, C, H, H_kv, D, cached = FORMS[form]
+    n = cached + (C if C > 1 else 0)
+    if C == 1:
+        assert decode_attention(B, H, H_kv, D, cached) == STREAMED[form]
+    w = W.make_workload("range", dtype=W.BF16, B=B, C=C, H=H, H_kv=H_kv, D=D, P=16, seq_lens=[n] * B, k=cached, seed=5)
+    bits = lambda x: W.store(np.asarray(x, np.float32), W.BF16)
+    for x in (K, q, V):
+        fin = np.isfinite(x)
+        assert np.array_equal(W.as_f32(bits(x), W.BF16)[fin], np.asarray(x, np.float32)[fin])     # bf16 numbers as they are
+    for b in range(B):
+        w.k_pool.reshape(-1, H_kv, D)[w.slots_of(b)] = bits(K)[:, None]
+        w.v_pool.reshape(-1, H_kv, D)[w.slots_of(b)] = bits(V)[:, None]
+    w.q[:] = bits(q)
+    layer = (DecodeLayer if C == 1 else ChunkSelector).from_workload(w)
+    layer.idx = to_device(np.tile(np.arange(cached, dtype=np.int32), (B, 1)))
+    layer.count = to_device(np.full(B, cached, np.int32))
+    layer.attend(to_device(w.q), sm)
+    torch.cuda.synchronize()
+    out = W.as_f32(to_host(layer.out, bits16=True), W.BF16).astype(np.float64)[-1]
+    lse = to_host(layer.lse).astype(np.float64)[-1]
+    s = (K.astype(np.float64) @ q.astype(np.float64)) * float(np.float32(sm))
+    ref, ref_lse = [], []
+    for c in range(C):
+        m = n if C == 1 else cached + c + 1
+        p = np.exp(s[:m] - s[:m].max())
+        with np.errstate(invalid="ignore"):
+            ref.append((p[:, None] * V[:m].astype(np.float64)).sum(axis=0) / p.sum())
+        ref_lse.append(s[:m].max() + math.log(p.sum()))
+    return out, lse, np.array(ref), np.array(ref_lse)
+
+
+def rows(form):
+    _, C, _, _, D, cached = FORMS[form]
+    return cached + (C if C > 1 else 0), D
+
+
+def bf16_values(rng, shape):
+    return W.as_f32(W.store(rng.standard_normal(shape).astype(np.float32), W.BF16), W.BF16)
+
+
+LARGE_LOGITS = ["chunks", "streamed", "streamed-splits"]
+
+
+@pytest.mark.parametrize("form", LARGE_LOGITS)
+@pytest.mark.parametrize("exponent", [20, 28, 36, 105, 124])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_large_logits(gpu, form, exponent, sign):
+    """Logits of about 2^exponent, all of one sign, in 61 classes of equal ones a 64th apart: far apart beside their own
+    rounding, so that the weights are those of the largest class alone."""
+    n, D = rows(form)
+    print("large logits", form, exponent, sign, flush=True)
+    K, q = np.zeros((n, D), np.float32), np.zeros(D, np.float32)
+    q[0] = 2.0 ** (exponent // 2)
+    K[:, 0] = sign * 2.0 ** (exponent - exponent // 2) * (1 + (np.arange(n) * 7 % 61) / 64)
+    V = bf16_values(np.random.default_rng(exponent), (n, D))
+    out, lse, ref, ref_lse = attend(form, K, q, V, 0.3)
+    # weights of 0 and 1 (exact in bf16 too), sums of up to 100 values, the result's rounding to bf16
+    assert np.abs(out - ref[:, None]).max() <= 2.0 ** -8 * np.abs(ref).max() + 2.0 ** -16
+    assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -22 * np.abs(ref_lse).max()
