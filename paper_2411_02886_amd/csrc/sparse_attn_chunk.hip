@@ -25,6 +25,7 @@
 // without gain: the next block's scores and the previous one's output interleaved with the weights (241 to 256
 // registers, 67 us), fragments read ahead of their use, one 32-key block at a time (62 us).
 #include "ts_kernels.h"
+#include <limits.h>
 
 namespace ts {
 
@@ -36,8 +37,9 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 constexpr int kCaRows = 128;     // rows per workgroup (four waves of 32)
 constexpr int kCaGroups = 2;     // key groups per workgroup
 constexpr int kCaTile = 64;      // keys per tile
-constexpr float kCaUnset = -1e30f;   // reference exponent of a row that has seen no key
+constexpr float kCaUnset = -3.40282347e38f;   // reference exponent of a row that has seen no key: no finite logit lies below it
 constexpr float kCaRaise = 1073741824.f;   // a tile sum above this raises the reference
+constexpr float kCaBig = 1048576.f;  // references beyond this: the logits are rounded before it is taken off them
 
 // place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 4 rows x 4 pieces (V^T) each
 // fall on all banks
@@ -127,6 +129,12 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
     }
   }
   float ref = kCaUnset, lsum = 0.f;                             // the row's reference exponent; this lane's keys' sum
+  // The weights' exponents are one fma, c2 * score - reference.  Its exact product differs from the rounded one that the
+  // reference came from by up to 2^-24 of the logit, and with logits of 2^31 that alone would over- or underflow the
+  // exponential.  A wave that meets such a reference rounds the logits first from then on: `factor` is 1 and every tile takes
+  // the way of the masked ones, where the scores are multiplied (a test of its own in the loop cost 0.6 us of 60, this 0.4).
+  float factor = c2;
+  int plain_below = cnt - kCaTile + 1;                          // tiles that begin below this need no look at their scores
   f32x16_t oacc[NBO];                                           // O^T: d = 32 * nb + 8 * (e / 4) + 4 * half + e % 4
 #pragma unroll
   for (int nb = 0; nb < NBO; ++nb)
@@ -218,7 +226,13 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
       }
     // ---- weights against the reference; keys the row may not see get none
     const int j0 = tile * kCaTile;
-    if (j0 + kCaTile > cnt) {                                   // the same for the whole wave
+    auto round_logits = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[kb][e] *= c2;
+    };
+    if (j0 >= plain_below) {                                    // the same for the whole wave
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -226,6 +240,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
           const int cq = j0 + kb * 32 + 8 * (e >> 2) + 4 * half + (e & 3) - cnt;   // >= 0: the chunk's token cq
           s[kb][e] = cq <= vis ? s[kb][e] : hidden;
         }
+      if (__builtin_expect(plain_below == INT_MIN, 0)) round_logits();
     }
     uint32_t pk[2][8];
     float sum;
@@ -235,7 +250,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
-          const bf16x2_t p = {(__bf16)__builtin_amdgcn_exp2f(fmaf(c2, s[kb][e], -ref)), (__bf16)__builtin_amdgcn_exp2f(fmaf(c2, s[kb][e + 1], -ref))};
+          const bf16x2_t p = {(__bf16)__builtin_amdgcn_exp2f(fmaf(factor, s[kb][e], -ref)), (__bf16)__builtin_amdgcn_exp2f(fmaf(factor, s[kb][e + 1], -ref))};
           const bf16x2_t one = {(__bf16)1.f, (__bf16)1.f};
           pk[kb][e >> 1] = __builtin_bit_cast(uint32_t, p);
           part[kb] = __builtin_amdgcn_fdot2_f32_bf16(p, one, part[kb], false);    // the sum of the rounded weights that multiply V
@@ -248,7 +263,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) m = fmaxf(m, c2 * s[kb][e]);
+        for (int e = 0; e < 16; ++e) m = fmaxf(m, factor * s[kb][e]);
       m = fmaxf(m, __shfl_xor(m, 32));                          // both halves of a row raise its reference together
       const float f = __builtin_amdgcn_exp2f(ref - m);          // 1 where nothing changes, 0 while the reference is unset
       lsum *= f;
@@ -257,6 +272,10 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[nb][e] *= f;
       ref = m;
+      if (__builtin_expect(plain_below != INT_MIN && __builtin_amdgcn_ballot_w64(fabsf(m) > kCaBig && m != kCaUnset) != 0, 0)) {
+        factor = 1.f; plain_below = INT_MIN;
+        round_logits();
+      }
     }
     lsum += sum;
     // ---- O^T += V^T P^T: k-step ks2 of a block takes keys 16 * ks2 + 4 * half + {0..3, 8..11}, the keys of s[8 * ks2 ..]

@@ -75,10 +75,7 @@ def bf16_values(rng, shape):
     return W.as_f32(W.store(rng.standard_normal(shape).astype(np.float32), W.BF16), W.BF16)
 
 
-LARGE_LOGITS = ["chunks", "streamed", "streamed-splits"]
-
-
-@pytest.mark.parametrize("form", LARGE_LOGITS)
+@pytest.mark.parametrize("form", list(FORMS))
 @pytest.mark.parametrize("exponent", [20, 28, 36, 105, 124])
 @pytest.mark.parametrize("sign", [1, -1])
 def test_large_logits(gpu, form, exponent, sign):
