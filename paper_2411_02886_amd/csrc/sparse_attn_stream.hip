@@ -22,7 +22,8 @@ typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 constexpr float kStUnset = -3.40282347e38f;   // reference logit before the first key: no finite logit lies below it
-constexpr float kStRaise = 1073741824.f;      // a sum above this raises the reference
+constexpr float kStHead = 4.f;                // a raised reference lies this far above the largest logit so far ...
+constexpr float kStRaise = 1.f;               // ... and is raised again when a lane's eight weights exceed this: no weight is above 1
 constexpr float kStBig = 1048576.f;           // references beyond this: the logits are rounded before it is taken off them
 constexpr float kLog2e = 1.44269504088896340736f;
 
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
       if (__builtin_amdgcn_ballot_w64(!(sum <= kStRaise)) == 0) break;
       float m = ref;                                                       // first keys, or a logit far above the reference
 #pragma unroll
-      for (int e = 0; e < 8; ++e) m = fmaxf(m, s[e >> 2][e & 3] * sm);     // (a repeated key past the end is a real one)
+      for (int e = 0; e < 8; ++e) m = fmaxf(m, s[e >> 2][e & 3] * sm + kStHead);   // (a repeated key past the end is a real one)
       m = fmaxf(m, __shfl_xor(m, 16));
       m = fmaxf(m, __shfl_xor(m, 32));
       big = __builtin_amdgcn_ballot_w64(fabsf(m) > kStBig) != 0;

@@ -91,3 +91,26 @@ def test_large_logits(gpu, form, exponent, sign):
     # weights of 0 and 1 (exact in bf16 too), sums of up to 100 values, the result's rounding to bf16
     assert np.abs(out - ref[:, None]).max() <= 2.0 ** -8 * np.abs(ref).max() + 2.0 ** -16
     assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -22 * np.abs(ref_lse).max()
+
+
+# the largest exponent of V's elements at which the sums of each form fit a float: weights of up to 1 over 300 to 512 keys,
+# in the chunk form of up to 2^16 over 24 to 1048
+LARGE_VALUES = {"chunks": 118, "streamed": 118, "streamed-splits": 115, "chunk-form": 103, "chunk-form-splits": 101}
+
+
+@pytest.mark.parametrize("form", ["chunks", "streamed", "streamed-splits"])
+def test_large_values_under_rising_logits(gpu, form):
+    """Every other stretch of 128 keys has logits 19 octaves above the rest: less than a float holds, so that a kernel may
+    leave its reference where it was, but then its weights must not outgrow the room above the values."""
+    n, D = rows(form)
+    print("large values", form, flush=True)
+    K, q = np.zeros((n, D), np.float32), np.zeros(D, np.float32)
+    q[0] = 1.0
+    K[:, 0] = np.where(np.arange(n) // 128 % 2 == 1, 13.25, 0.0)
+    V = np.ldexp(1 + np.abs(bf16_values(np.random.default_rng(3), (n, D))) % 1.0, LARGE_VALUES[form] - 1)
+    V = W.as_f32(W.store(V.astype(np.float32), W.BF16), W.BF16)
+    out, lse, ref, ref_lse = attend(form, K, q, V, 1.0)
+    assert np.isfinite(out).all()
+    # all of V's elements have one sign: the weights' rounding to bf16 (chunk form) and the result's own
+    assert np.abs(out / ref[:, None] - 1).max() <= 2.0 ** -7
+    assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -8
