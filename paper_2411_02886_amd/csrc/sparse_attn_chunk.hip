@@ -18,7 +18,7 @@
 //   * K and V rows go from memory to LDS directly, 16 bytes per lane, each lane fetching the piece that belongs at its
 //     place: pieces are exchanged inside a row (piece ^ swz(key)) so that both reads are free of bank conflicts.
 //   * No maximum over the scores: weights are formed against the row's reference exponent; only if a tile's sum
-//     comes out above 2^30 (or not a number) the reference is raised and the tile's weights are formed again.
+//     comes out above 2^16 (or not a number) the reference is raised and the tile's weights are formed again.
 //   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows.
 // 512 queries, H 32/8, D 128, 4096 selected + 512 own keys: 155 + 12 + 5 us (one tile of 32 keys per
 // barrier, weights and V^T through 2-byte LDS accesses, four splits, a slot list built first) -> 61 + 6 us.  Tried
@@ -38,7 +38,7 @@ constexpr int kCaRows = 128;     // rows per workgroup (four waves of 32)
 constexpr int kCaGroups = 2;     // key groups per workgroup
 constexpr int kCaTile = 64;      // keys per tile
 constexpr float kCaUnset = -3.40282347e38f;   // reference exponent of a row that has seen no key: no finite logit lies below it
-constexpr float kCaRaise = 1073741824.f;   // a tile sum above this raises the reference
+constexpr float kCaRaise = 65536.f;  // a tile sum above this raises the reference
 constexpr float kCaBig = 1048576.f;  // references beyond this: the logits are rounded before it is taken off them
 
 // place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 4 rows x 4 pieces (V^T) each

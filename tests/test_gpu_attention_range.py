@@ -16,7 +16,7 @@ FORMS = {
     "chunks": (1, 1, 8, 2, 64, 300),
     "streamed": (26, 1, 40, 8, 64, 300),
     "streamed-splits": (2, 1, 64, 8, 128, 4096),
-    "chunk-form": (1, 24, 8, 2, 128, 100),
+    "chunk-form": (1, 24, 8, 2, 128, 250),
     "chunk-form-splits": (1, 48, 8, 2, 64, 1000),
 }
 STREAMED = {"chunks": (False, 5), "streamed": (True, 1), "streamed-splits": (True, 16)}
@@ -93,12 +93,12 @@ def test_large_logits(gpu, form, exponent, sign):
     assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -22 * np.abs(ref_lse).max()
 
 
-# the largest exponent of V's elements at which the sums of each form fit a float: weights of up to 1 over 300 to 512 keys,
-# in the chunk form of up to 2^16 over 24 to 1048
-LARGE_VALUES = {"chunks": 118, "streamed": 118, "streamed-splits": 115, "chunk-form": 103, "chunk-form-splits": 101}
+# exponent of V's elements: weights of at most 1 over 300 to 4096 keys fit a float.  The chunk form lets a weight grow to 2^16
+# before it raises its reference, so the 2^19 of the test do not stand, and neither do the values come closer than that
+LARGE_VALUES = {"chunks": 118, "streamed": 118, "streamed-splits": 115, "chunk-form": 108, "chunk-form-splits": 108}
 
 
-@pytest.mark.parametrize("form", ["chunks", "streamed", "streamed-splits"])
+@pytest.mark.parametrize("form", list(FORMS))
 def test_large_values_under_rising_logits(gpu, form):
     """Every other stretch of 128 keys has logits 19 octaves above the rest: less than a float holds, so that a kernel may
     leave its reference where it was, but then its weights must not outgrow the room above the values."""
