@@ -17,7 +17,6 @@
 namespace ts {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
@@ -173,16 +172,21 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
       ref = m;
     }
     lsum += sum;
-    // each weight as three bf16 numbers whose sum is the weight; k-slot 8 * kgrp + e of the product is p[e]'s key
+    // each weight as three bf16 numbers whose sum is the weight; k-slot 8 * kgrp + e of the product is p[e]'s key.  The
+    // parts are cut off, not rounded, and the lower two are kept above 2^-30 of the weight: all three have its sign and none
+    // is zero beside it, so that an infinite V row comes out infinite (inf - inf and 0 * inf would make it NaN).
     uint32_t w[3][4];
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
+      const float q0 = p[e] * 9.3132257e-10f, q1 = p[e + 1] * 9.3132257e-10f;
       float x0 = p[e], x1 = p[e + 1];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const bf16x2_t h = {(__bf16)x0, (__bf16)x1};
-        w[c][e >> 1] = __builtin_bit_cast(uint32_t, h);
-        x0 -= bf16_lo(w[c][e >> 1]); x1 -= bf16_hi(w[c][e >> 1]);          // exact
+        w[c][e >> 1] = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);   // the high halves
+        if (c < 2) {
+          x0 = fmaxf(x0 - bf16_lo(w[c][e >> 1]), q0);                      // the differences are exact
+          x1 = fmaxf(x1 - bf16_hi(w[c][e >> 1]), q1);
+        }
       }
     }
     // ---- O^T += V^T P^T

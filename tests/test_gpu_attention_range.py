@@ -114,3 +114,22 @@ def test_large_values_under_rising_logits(gpu, form):
     # all of V's elements have one sign: the weights' rounding to bf16 (chunk form) and the result's own
     assert np.abs(out / ref[:, None] - 1).max() <= 2.0 ** -7
     assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+def test_infinite_values(gpu, form):
+    """A value row with infinite elements under a weight that is not zero: those elements of the output are infinite, the
+    others what they are without it."""
+    n, D = rows(form)
+    print("infinite values", form, flush=True)
+    rng = np.random.default_rng(4)
+    K, q, V = bf16_values(rng, (n, D)), bf16_values(rng, D), bf16_values(rng, (n, D))
+    for t, d, x in ((37, 3, np.inf), (70, 5, -np.inf), (71, D - 1, np.inf), (222, 3, np.inf)):
+        V[t, d] = x
+    out, lse, ref, ref_lse = attend(form, K, q, V, 1.0 / math.sqrt(D))
+    assert np.array_equal(np.isinf(out[:, 0]), np.isinf(ref)) and np.array_equal(np.isnan(out), np.zeros(out.shape, bool))
+    inf = np.isinf(ref)
+    for h in range(out.shape[1]):
+        assert np.array_equal(out[:, h][inf], ref[inf])
+        # weights rounded to bf16 in the chunk form, the result's own rounding
+        assert np.abs(out[:, h][~inf] - ref[~inf]).max() <= 2.0 ** -7 * np.abs(V[np.isfinite(V)]).max()
