@@ -128,16 +128,23 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_stream_kernel(AttnArgs a) 
   for (int tile = wave; tile < ntile; tile += 4) {
     const bool more = tile + 4 < ntile;
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLD) : "memory");            // this tile's K rows (its V rows follow them)
-    // ---- scores: two blocks of 16 keys, element r is key 16 * kb + 4 * kgrp + r
-    f32x4_t s[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) s[kb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    // ---- scores: two blocks of 16 keys, element r is key 16 * kb + 4 * kgrp + r.  The products of each MFMA are added up on
+    // their own: handed from one to the next the sums lose more than the vector form's (root mean square error of the
+    // log-sum-exp, 1500 keys at four times 1 / sqrt(D): 5.8e-7 against 4.6e-7 of the vector form; this way 4.4e-7)
+    f32x4_t part[KS][2], s[2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         const uint4 av = *reinterpret_cast<const uint4*>(kt + (kb * 16 + col) * RB + (((ks * 4 + kgrp) ^ st_swz<D>(col)) * 16));
-        s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av), qf[ks], s[kb], 0, 0, 0);
+        part[ks][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av), qf[ks], (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[kb][r] = part[0][kb][r] + part[1][kb][r];
+        if (KS == 4) s[kb][r] += part[KS - 2][kb][r] + part[KS - 1][kb][r];
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                     // the K tile has been read
     if (more) { rows_of(tile + 4); load_rows(a.k_pool, lds_k); }

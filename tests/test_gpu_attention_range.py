@@ -133,3 +133,37 @@ def test_infinite_values(gpu, form):
         assert np.array_equal(out[:, h][inf], ref[inf])
         # weights rounded to bf16 in the chunk form, the result's own rounding
         assert np.abs(out[:, h][~inf] - ref[~inf]).max() <= 2.0 ** -7 * np.abs(V[np.isfinite(V)]).max()
+
+
+@pytest.mark.parametrize("H,H_kv,D,k,scale", [(32, 8, 128, 2048, 1.0), (28, 4, 128, 1500, 4.0), (24, 8, 64, 1000, 4.0), (64, 8, 64, 600, 1.0)])
+def test_log_sum_exp_of_the_streaming_form_is_as_close_as_that_of_the_chunks(gpu, H, H_kv, D, k, scale):
+    """The same sequences attended as a batch (streamed) and one by one (64-token chunks): the root mean square of the
+    log-sum-exp's distance from float64 over all heads may not be larger, but for what 10 % of chance in it leaves."""
+    from paper_2411_02886_amd.runtime import DecodeLayer, to_device, to_host
+    B = max(1, 2600 // ((k + 63) // 64 * H_kv)) + 1
+    assert decode_attention(B, H, H_kv, D, k)[0] and not decode_attention(1, H, H_kv, D, k)[0]
+    print("lse", H, H_kv, D, k, scale, B, flush=True)
+    w = W.make_workload("lse", dtype=W.BF16, B=B, H=H, H_kv=H_kv, D=D, P=16, seq_lens=[k] * B, k=k, seed=9)
+    sm = float(np.float32(scale / math.sqrt(D)))
+    layer = DecodeLayer.from_workload(w)
+    idx = to_device(np.tile(np.arange(k, dtype=np.int32), (B, 1)))
+    layer.idx, layer.count = idx, to_device(np.full(B, k, np.int32))
+    q = to_device(w.q)
+    layer.attend(q, sm)
+    torch.cuda.synchronize()
+    got = {"streamed": to_host(layer.lse).astype(np.float64)[:, 0], "chunks": np.empty((B, H))}
+    want = np.empty((B, H))
+    for b in range(B):
+        one = DecodeLayer(dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=16, k=k, k_pool=layer.k_pool, v_pool=layer.v_pool,
+                          page_indptr=[0, len(w.pages_of(b))], page_indices=w.pages_of(b), seq_lens=[k])
+        one.idx, one.count = idx[:1].contiguous(), to_device(np.array([k], np.int32))
+        one.attend(q[b:b + 1].contiguous(), sm)
+        got["chunks"][b] = to_host(one.lse).astype(np.float64)[0, 0]
+        K = W.as_f32(w.k_pool.reshape(-1, H_kv, D)[w.slots_of(b)], W.BF16).astype(np.float64)
+        qb = W.as_f32(w.q[b, 0], W.BF16).astype(np.float64)
+        for h in range(H):
+            s = K[:, h // (H // H_kv)] @ qb[h] * sm
+            want[b, h] = s.max() + math.log(np.exp(s - s.max()).sum())
+    rms = {f: float(np.sqrt(((got[f] - want) ** 2).mean())) for f in got}
+    print("rms error of the log-sum-exp: streamed %.3e, chunks %.3e" % (rms["streamed"], rms["chunks"]), flush=True)
+    assert rms["streamed"] <= 1.1 * rms["chunks"]
