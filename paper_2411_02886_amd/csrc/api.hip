@@ -435,7 +435,7 @@ int32_t ts_topk_exact(const ts_problem* p, const void* q, const float* vote_hi, 
   a.page_indptr = p->page_indptr; a.page_indices = p->page_indices; a.row_stats = row_stats;
   a.H = p->num_q_heads; a.H_kv = p->num_kv_heads; a.P = p->page_size; a.p_shift = ilog2(p->page_size);
   a.scale = score_scale;
-  a.parts = eval_workgroups(p->batch, p->max_seq_len);
+  a.parts = eval_workgroups(p->batch, p->max_seq_len, k);
   const int G = p->num_q_heads / p->num_kv_heads;
   if (launch_topk_compact(a.t, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   if (launch_topk_eval(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;

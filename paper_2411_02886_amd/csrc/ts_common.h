@@ -56,15 +56,25 @@ inline bool attn_streams(int G, int D, long pairs, int total) {
   return G == 2 || 5 * pairs >= 4 * ((pairs + 255) / 256 * 256);
 }
 
-// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (one round:
-// their registers allow no more).  How many candidates there are is known on the device only -- a little more than k when
-// votes are peaked, every token when they are flat, whatever k is -- so k has no say here (k 64 of 1048576 flat votes: 12.9 ms
-// with k / 4 workgroups, 1.7 ms with 512); those that would get fewer than kEvalMinShare candidates leave at once.
+// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (their
+// registers allow no more).  How many candidates there are is known on the device only -- a little more than k when votes
+// are peaked, every token when they are flat, whatever k is -- so the number does not fall with k (k 64 of 1048576 flat
+// votes: 12.9 ms with k / 4 workgroups, 1.7 ms with 512); those that would get fewer than kEvalMinShare candidates leave at once.
+// Large batches: 512 / batch may leave a good part of the round empty; more rounds of smaller shares do not, and a round
+// more costs about 0.08 of a sequence, with a small k more (300 sequences of up to 4000 tokens, H 8/2, k 256: peaked votes
+// 45 -> 43 us, flat 205 -> 123).
 constexpr int kEvalMinShare = 4;
-inline int eval_workgroups(int batch, int max_seq_len) {
-  int n = 512 / batch;
-  if (n > (max_seq_len + kEvalMinShare - 1) / kEvalMinShare) n = (max_seq_len + kEvalMinShare - 1) / kEvalMinShare;
-  return n < 1 ? 1 : n;
+inline int eval_workgroups(int batch, int max_seq_len, int k) {
+  const int most = (max_seq_len + kEvalMinShare - 1) / kEvalMinShare;
+  int best = 512 / batch;
+  if (best < 4) {
+    double best_cost = 0.0;
+    for (int n = 1; n <= 8; ++n) {
+      const double cost = (double)((n * (long)batch + 511) / 512) * (1.0 / n + 0.08 + 4.0 / (k > 32 ? k : 32));
+      if (n == 1 || cost < best_cost) { best = n; best_cost = cost; }
+    }
+  }
+  return best < most ? best : most;
 }
 
 // ---------------------------------------------------------------- workspace layout (host + device)

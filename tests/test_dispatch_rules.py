@@ -45,13 +45,13 @@ def test_streaming_attention_only_where_it_is_the_faster_form(G, D, pairs, total
     assert rules().rule_attn_streams(G, D, pairs, total) == streamed
 
 
-@pytest.mark.parametrize("batch", [1, 2, 3, 8, 100, 511, 600])
-def test_candidates_are_evaluated_by_a_full_chip_whatever_k(batch):
+@pytest.mark.parametrize("batch", [1, 2, 3, 8, 100, 171, 200, 300, 511, 600])
+@pytest.mark.parametrize("k", [1, 64, 4096])
+def test_candidates_are_evaluated_by_a_full_chip_whatever_k(batch, k):
     """With flat votes every token is a candidate: the workgroups are counted by what a sequence can hold, not by k."""
     for n in (1, 4, 5, 1000, 2048, 131072, 1 << 20):
-        parts = rules().rule_eval_workgroups(batch, n)
+        parts = rules().rule_eval_workgroups(batch, n, k)
         assert 1 <= parts <= 512
-        if n >= 2048:
-            assert batch * parts >= 256, (batch, n)       # a workgroup for every CU
-        assert parts == 1 or batch * parts <= 512         # one round at two per CU
         assert parts <= (n + 3) // 4                      # four candidates each, at least
+        if n >= 2048:                                     # 512 workgroups a round, the rounds at least two thirds full
+            assert batch * parts >= 341 * ((batch * parts + 511) // 512), (batch, n)

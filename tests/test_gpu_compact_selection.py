@@ -236,7 +236,7 @@ def test_candidates_split_over_many_workgroups(gpu, lens, parts, k, scale):
     w = W.make_workload("parts", dtype=W.BF16, H=8, H_kv=2, D=64, P=16, B=len(lens), seq_lens=lens, k=k, beta=2.5,
                         planted_per_head=2, seed=sum(lens) % 977)
     layer, q = make_layer(w)
-    assert rules().rule_eval_workgroups(len(lens), max(lens)) == parts
+    assert rules().rule_eval_workgroups(len(lens), max(lens), k) == parts
     print("compact candidates", parts, lens, k, scale, flush=True)
     check_compact(w, layer, q, score_scale=scale, label="parts%d k%d" % (parts, k))
 
