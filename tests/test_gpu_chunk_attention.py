@@ -71,3 +71,38 @@ def test_chunk_attention(C, H, H_kv, D, P, cached, k, ni, nl, scale):
             tol = (2.0 ** -8 + np.abs(s[~hidden]).max() * 2.0 ** -21) * np.abs(V[:, h // G]).max()
             assert np.abs(out[b, :, h] - ref).max() <= tol, (b, h)
             assert np.abs(lse[b, :, h] - ref_lse).max() <= 2.0 ** -8 + np.abs(s[~hidden]).max() * 2.0 ** -20, (b, h)
+
+
+@pytest.mark.parametrize("k", [60, 700], ids=["one-split", "splits"])
+def test_stale_and_corrupt_selection_state(k):
+    """Token ids outside the sequence are clamped into it, counts into [0, k]; a sequence shorter than the chunk holds none."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_02886_amd.runtime import ChunkSelector, to_device, to_host
+    C, H, H_kv, D = 20, 8, 2, 128
+    cached = [k + 11, k, 5, -20]                            # the last one is empty
+    w = W.make_workload("stale_chunk", dtype=W.BF16, B=4, C=C, H=H, H_kv=H_kv, D=D, P=16, seq_lens=[n + C for n in cached], k=k, seed=8)
+    layer = ChunkSelector.from_workload(w)
+    rng = np.random.default_rng(k)
+    idx = rng.integers(0, k, size=(4, k)).astype(np.int32)
+    count = np.array([k, k + 500, -4, k], np.int32)
+    idx[0, 3] = -12; idx[0, 5] = 10 ** 9; idx[1, 7] = -2 ** 31; idx[1, k - 1] = 2 ** 31 - 1
+    layer.idx = to_device(idx); layer.count = to_device(count)
+    print("stale chunk selection", k, flush=True)
+    sm = 1.0 / math.sqrt(D)
+    layer.out.fill_(3)
+    layer.attend(to_device(w.q), sm)
+    torch.cuda.synchronize()
+    out = W.as_f32(to_host(layer.out, bits16=True), W.BF16).astype(np.float64)
+    assert not out[3].any()
+    for b, n in enumerate(cached[:3]):
+        att = np.clip(idx[b, :min(max(int(count[b]), 0), k)], 0, n + C - 1)
+        slots = w.slots_of(b)
+        for c in (0, C - 1):
+            tok = slots[np.concatenate([att, np.arange(n, n + c + 1)])]
+            K = W.as_f32(w.k_pool.reshape(-1, H_kv, D)[tok], W.BF16).astype(np.float64)
+            V = W.as_f32(w.v_pool.reshape(-1, H_kv, D)[tok], W.BF16).astype(np.float64)
+            for h in range(H):
+                s = K[:, h // 4] @ W.as_f32(w.q[b, c, h], W.BF16).astype(np.float64) * sm
+                p = np.exp(s - s.max())
+                assert np.abs(out[b, c, h] - p @ V[:, h // 4] / p.sum()).max() <= 2.0 ** -7 * np.abs(V).max(), (b, c, h)

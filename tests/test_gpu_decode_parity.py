@@ -213,9 +213,9 @@ def test_attention_bounds_stale_and_corrupt_selection_state(gpu):
 
 
 def test_attention_with_several_chunks_per_workgroup(gpu):
-    # 8192 and more chunk workgroups: a workgroup folds four chunks of 64 tokens into its partial with a running
-    # maximum and sum; ragged ends (a last workgroup with one, two or three chunks, a last chunk of a few tokens),
-    # empty sequences and forced tokens included
+    # 8192 and more chunk workgroups.  fp32: a workgroup folds four chunks of 64 tokens into its partial with a running
+    # maximum and sum.  bf16, two heads per KV head and short lists: the streaming form, with ragged ends (tiles of a few
+    # tokens), empty sequences and forced tokens.  test_gpu_batch_attention.py has both forms at more shapes
     rng = np.random.Generator(np.random.PCG64(75))
     lens = [int(x) for x in rng.integers(1100, 1500, size=70)]
     lens[3] = 0; lens[10] = 5; lens[20] = 129; lens[30] = 64 * 4 + 1; lens[40] = 64 * 7; lens[69] = 0
@@ -293,7 +293,9 @@ def test_five_pass_topk_path_gives_the_same_result(gpu):
     from paper_2411_02886_amd.runtime import to_host
     gpu.ts_debug_set_topk_path(1)
     try:
-        for shape in [(W.BF16, 32, 8, 128, 16, [5000], 300), (W.F32, 8, 2, 64, 4, [0, 1, 31, 2049, 700, 4100], 33)]:
+        # (with the default, sequences of up to 8192 tokens are ranked by one workgroup: the last two are longer)
+        for shape in [(W.BF16, 32, 8, 128, 16, [5000], 300), (W.F32, 8, 2, 64, 4, [0, 1, 31, 2049, 700, 4100], 33),
+                      (W.BF16, 32, 8, 128, 16, [9000, 777], 300), (W.F32, 8, 2, 64, 4, [20000, 0, 8193], 33)]:
             dtype, H, H_kv, D, P, lens, k = shape
             print("five-pass", shape, flush=True)
             w = W.make_workload("fp", dtype=dtype, B=len(lens), H=H, H_kv=H_kv, D=D, P=P, seq_lens=lens, k=k, seed=sum(lens))
@@ -306,16 +308,17 @@ def test_five_pass_topk_path_gives_the_same_result(gpu):
         assert to_host(layer.idx)[0].tolist() == list(range(10))
     finally:
         gpu.ts_debug_set_topk_path(0)
-    # the same form chosen per call
-    w = W.make_workload("flat", dtype=W.BF16, B=2, H=8, H_kv=2, D=128, P=16, seq_lens=[5000, 2100], k=100, seed=37)
-    layer, q = make_layer(w)
-    layer.select(q, 0.01, None)                      # a small scale: nearly uniform votes
-    torch.cuda.synchronize()
-    idx_a, cnt_a = to_host(layer.idx).copy(), to_host(layer.count).copy()
-    layer.idx.fill_(-7); layer.count.fill_(-7)
-    gpu.ts_topk(layer.problem, layer.votes, layer.k, layer.idx, layer.count, None, layer.ws, flags=gpu.TS_TOPK_FLAT_VOTES)
-    torch.cuda.synchronize()
-    assert np.array_equal(to_host(layer.idx), idx_a) and np.array_equal(to_host(layer.count), cnt_a)
+    # the same form chosen per call (20000 tokens; up to 8192 both calls are the one-workgroup form)
+    for lens in ([5000, 2100], [20000, 2100]):
+        w = W.make_workload("flat", dtype=W.BF16, B=2, H=8, H_kv=2, D=128, P=16, seq_lens=lens, k=100, seed=37)
+        layer, q = make_layer(w)
+        layer.select(q, 0.01, None)                      # a small scale: nearly uniform votes
+        torch.cuda.synchronize()
+        idx_a, cnt_a = to_host(layer.idx).copy(), to_host(layer.count).copy()
+        layer.idx.fill_(-7); layer.count.fill_(-7)
+        gpu.ts_topk(layer.problem, layer.votes, layer.k, layer.idx, layer.count, None, layer.ws, flags=gpu.TS_TOPK_FLAT_VOTES)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(layer.idx), idx_a) and np.array_equal(to_host(layer.count), cnt_a)
 
 
 def test_k_larger_than_n_equals_full_attention(gpu):

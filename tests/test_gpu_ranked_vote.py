@@ -65,3 +65,29 @@ def test_ranked_pair_agrees_with_the_plain_pair_and_restores_the_workspace(gpu, 
     layer.idx.fill_(-9)
     layer.select_compact(q, 1.0, None); torch.cuda.synchronize()
     assert np.array_equal(to_host(layer.idx), idx_c)
+
+
+@pytest.mark.parametrize("lens", [[9000, 3333, 0, 17], [30000]], ids=["9000-ragged", "30000"])
+@pytest.mark.parametrize("scale", [1.0, 0.01], ids=["peaked", "flat"])
+def test_the_vote_launch_histogram_in_the_five_launch_form(gpu, lens, scale):
+    """TS_TOPK_VOTE_HIST with TS_TOPK_FLAT_VOTES: the replicas of the vote launch's histogram are folded into the five-launch
+    form's first one and left zeroed.  Twice in a row, against the plain pair; then the compact form, which shares the section."""
+    from paper_2411_02886_amd.runtime import to_host
+    w = W.make_workload("rvflat", dtype=W.BF16, B=len(lens), H=32, H_kv=8, D=128, P=16, seq_lens=lens, k=200, beta=2.5,
+                        planted_per_head=2, seed=sum(lens))
+    layer, q = make_layer(w)
+    print("ranked, five launches", lens, scale, flush=True)
+    layer.select_compact(q, scale, None); torch.cuda.synchronize()
+    idx_c = to_host(layer.idx).copy()
+    layer.select(q, scale, None); torch.cuda.synchronize()
+    idx_p, cnt_p = to_host(layer.idx).copy(), to_host(layer.count).copy()
+    for rep in range(2):
+        layer.idx.fill_(-9); layer.count.fill_(-9)
+        gpu.ts_soft_vote_ranked(layer.problem, layer.scores, scale, layer.row_stats, layer.votes, None, layer.ws)
+        gpu.ts_topk(layer.problem, layer.votes, layer.k, layer.idx, layer.count, None, layer.ws,
+                    flags=gpu.TS_TOPK_VOTE_HIST | gpu.TS_TOPK_FLAT_VOTES)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(layer.idx), idx_p) and np.array_equal(to_host(layer.count), cnt_p), rep
+    layer.idx.fill_(-9)
+    layer.select_compact(q, scale, None); torch.cuda.synchronize()
+    assert np.array_equal(to_host(layer.idx), idx_c)
