@@ -133,7 +133,8 @@ int32_t ts_soft_vote(const ts_problem* p, const float* scores, float score_scale
 
 /* Eq. 5 and the start of the TopK in one launch: ts_soft_vote that also counts, while the votes are in registers,
  * the histogram of their top 11 key bits -- the first pass of ts_topk's radix select (one launch less per decode
- * step).  Same arguments, same row_stats and votes as ts_soft_vote, bit for bit.
+ * step; for max_seq_len up to 8192, which ts_topk ranks without one, no histogram is counted, and the calls pair all the
+ * same).  Same arguments, same row_stats and votes as ts_soft_vote, bit for bit.
  * Contract: the histogram lives in ws until a ts_topk call with TS_TOPK_VOTE_HIST, the same votes, skip mask and ws
  * consumes and clears it; that call must be the next selection call on ws (ts_soft_vote_bounds / ts_topk_exact share
  * the section).  After a call that was not followed that way, ts_workspace_init restores the workspace. */
@@ -144,11 +145,11 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
  * order of increasing token index, written as ascending logical token ids.
  * idx [device] int32 [B][k] (slots past the count are set to -1); count [device] int32 [B].
  * -0.0 compares equal to +0.0.
- * Sequences of up to 8192 tokens (max_seq_len) are ranked by one workgroup each, in one launch whatever the flags.
- * flags: 0, or TS_TOPK_FLAT_VOTES.  By default (decode) the radix select runs as three launches whose last one
+ * max_seq_len up to 8192: each sequence is ranked by one workgroup, in one launch, whatever the flags and the chunk.
+ * Longer ones, flags: 0, or TS_TOPK_FLAT_VOTES.  By default (decode) the radix select runs as three launches whose last one
  * finishes each sequence on one workgroup: fast when few votes lie within a quarter octave of the k-th vote, as
  * with the peaked votes of Eq. 5, and slow (still exact) when most do.  TS_TOPK_FLAT_VOTES selects the five-launch
- * form whose time does not depend on the distribution; chunk problems (chunk > 1) always use it.
+ * form whose time does not depend on the distribution; longer chunk problems (chunk > 1) always use it.
  * TS_TOPK_VOTE_HIST: the votes were written by ts_soft_vote_ranked, which left the radix select's first histogram in
  * ws (see there): the pass that builds it is skipped (decode only; not for ts_topk_noalloc). */
 #define TS_TOPK_FLAT_VOTES 1
@@ -268,10 +269,11 @@ int32_t ts_paged_qk_codes_checked(const ts_problem* p, const void* q, const ts_s
  * out = 0 and lse = -inf.  idx and count are read defensively (they may be a cached selection of an earlier step):
  * token ids are clamped into [0, N_b), count[b] into [0, k], and a sequence with N_b == 0 attends nothing whatever its
  * count says.  The page table itself is trusted: every page id of a sequence must lie inside the pools.
+ * Logits may have any finite size; sums of up to 32768 values, each under a weight of at most 1, have to fit a float.
  * Chunk form (chunk = C > 1, bf16): query c of the chunk (logical token N_b - C + c) attends over the
  * count[b] selected tokens and the chunk's own tokens 0..c in one joint softmax (Eq. 2's
  * [K_select, K_current] with a causal mask inside the chunk); the weights that multiply V are rounded
- * to bf16 (matrix-core operand).  A sequence with N_b < C holds no chunk (an idle slot of the batch): its rows of
+ * to bf16 (matrix-core operand) and may reach 2^16 before they are normalised.  A sequence with N_b < C holds no chunk (an idle slot of the batch): its rows of
  * out are zero, its lse -inf, and nothing is read through its page table (the selection calls give it count 0). */
 int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* idx, int32_t idx_stride,
                              const int32_t* count, float sm_scale, void* out, float* lse, void* ws,
@@ -327,9 +329,9 @@ int32_t ts_debug_set_score_variant(int32_t variant, int32_t wg, int32_t run_tile
 int32_t ts_debug_set_codes_path(int32_t mfma, int32_t run_tiles);
 
 /* Tuning knob (process-wide, tests and benchmarks): five_pass = 1 makes ts_topk / ts_head_vote use the
- * five-pass radix select (three global histogram passes, count, emit) that otherwise only serves sequences
- * beyond 16 Mi tokens; 0 (default) = histogram pass, compaction of the candidates, one finishing workgroup
- * per sequence.  Both give the same result.  Host only. */
+ * five-pass radix select (three global histogram passes, count, emit) that otherwise serves flat votes and sequences
+ * beyond 16 Mi tokens; 0 (default) = up to 8192 tokens one workgroup per sequence, beyond that histogram pass, compaction
+ * of the candidates, one finishing workgroup per sequence.  All give the same result.  Host only. */
 int32_t ts_debug_set_topk_path(int32_t five_pass);
 
 /* Benchmark helpers (host only; process-wide, not thread-safe).  ts_debug_set_score_timing_events(start, stop)

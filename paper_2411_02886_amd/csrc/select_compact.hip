@@ -163,8 +163,10 @@ hipError_t launch_vote_bounds(const BoundArgs& a, int B, hipStream_t s) {
 // ------------------------------------------------------------------------------------------------
 // The candidates (listed per 2048-token chunk by topk_compact_kernel over the upper bounds) re-evaluated from K.
 //
-// What bounds it: for a batch the double-precision products (D * H per candidate), for one sequence the chain of
-// dependent loads (chunk counts -> token -> page id -> K row).  Hence the split: the candidates of a sequence are
+// What bounds it: for one sequence the chain of dependent loads (chunk counts -> token -> page id -> K row).  For a batch
+// no single thing: 32 sequences of 1031 to 16001 tokens, H 32/8, are about 70 thousand candidates and 140 MB of gathered K
+// rows in 47 us; by count the double-precision products need about 10 of them, and conversions, reduction and row loads
+// follow one after another at two waves per SIMD.  Hence the split: the candidates of a sequence are
 // numbered through and every workgroup takes an equal share of them, whatever chunk they come from.  (When the
 // workgroup that had compacted a chunk also evaluated it, a short sequence -- all of its tokens candidates, in one
 // or two chunks -- was one workgroup's serial tail: 32 sequences of 1031 to 16001 tokens, H 32/8, k 2048 took 277 us,

@@ -9,8 +9,8 @@
 //
 // What bounds it: per 64-key tile a wave issues 32 MFMAs (32 cycles of matrix core each, 8 of the issue port) and
 // 32 x (fma, exp2, half a conversion, half a dot) on the vector ALU, and its phases (scores, weights, output) follow
-// each other; the two waves of a SIMD fill each other's gaps only in part (the matrix core is busy a third of the time;
-// row loads alone take 33 us, arithmetic alone 50 us of the 60).  What was taken out of the loop:
+// each other; the two waves of a SIMD fill each other's gaps only in part (of all cycles, start and end included, the matrix
+// core is busy 23 %, the vector ALU 34 %, neither 44 %; row loads alone take 33 us, arithmetic alone 50 us of the 60).  What was taken out of the loop:
 //   * Scores are formed transposed (K as A operand, Q as B): a lane then holds 32 keys of ONE row, so the running
 //     softmax is two registers per lane, and the weights, rounded to bf16, are the B operand of O^T += V^T P^T
 //     as they stand -- which key sits at which k of the product is free as long as V^T is read the same way.
@@ -21,7 +21,7 @@
 //     comes out above 2^16 (or not a number) the reference is raised and the tile's weights are formed again.
 //   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows.
 // 512 queries, H 32/8, D 128, 4096 selected + 512 own keys: 155 + 12 + 5 us (one tile of 32 keys per
-// barrier, weights and V^T through 2-byte LDS accesses, four splits, a slot list built first) -> 61 + 6 us.  Tried
+// barrier, weights and V^T through 2-byte LDS accesses, four splits, a slot list built first) -> 62 + 6 us.  Tried
 // without gain: the next block's scores and the previous one's output interleaved with the weights (241 to 256
 // registers, 67 us), fragments read ahead of their use, one 32-key block at a time (62 us).
 #include "ts_kernels.h"
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
   // The weights' exponents are one fma, c2 * score - reference.  Its exact product differs from the rounded one that the
   // reference came from by up to 2^-24 of the logit, and with logits of 2^31 that alone would over- or underflow the
   // exponential.  A wave that meets such a reference rounds the logits first from then on: `factor` is 1 and every tile takes
-  // the way of the masked ones, where the scores are multiplied (a test of its own in the loop cost 0.6 us of 60, this 0.4).
+  // the way of the masked ones, where the scores are multiplied (0.5 to 1.1 of 60 us; a test of its own in the loop 0.7 to 1.2).
   float factor = c2;
   int plain_below = cnt - kCaTile + 1;                          // tiles that begin below this need no look at their scores
   f32x16_t oacc[NBO];                                           // O^T: d = 32 * nb + 8 * (e / 4) + 4 * half + e % 4

@@ -11,7 +11,7 @@
 // left one or two waves per SIMD.  The weights keep their 24 bits: each is the sum of three bf16 numbers, and V is
 // multiplied with each of them.
 // Measured (H 32/8, D 128, 2048 of each): 64 sequences 113 + 15 (merge) -> 90 us;
-// H 28/4, 48 sequences, 4736 of each: 134 + 12 -> 87 + 5 us.
+// H 28/4, 48 sequences, 4736 of each: 134 + 12 -> 80 + 5 us.
 #include "ts_kernels.h"
 
 namespace ts {
