@@ -142,9 +142,10 @@ class DecodeLayer:
         ts.ts_sparse_paged_attn(self.problem, q, self.idx, self.k, self.count, sm_scale, self.out, self.lse, self.ws)
 
     def compact_form_pays(self) -> bool:
-        """Which form of the Eq. 5 selection is the faster step here (measured on MI355X): while the fp32 score matrix
-        fits the L2 with room to spare (131072 tokens of 32 heads: 16 MiB) the five-call form is, beyond that the
-        compact form, which never writes it (crossover between 128K and 256K tokens of 32 heads)."""
+        """Which form of the Eq. 5 selection to take.  With one sequence (measured on MI355X) the five-call form is the faster
+        step while the fp32 score matrix fits the L2 with room to spare (131072 tokens of 32 heads: 16 MiB), beyond that the
+        compact form, which never writes it (crossover between 128K and 256K tokens of 32 heads).  A batch counts by the sum of
+        its matrices; on three batches tried the five-call form would have been 5 to 8 % faster above the line."""
         return self.B * self.max_seq_len * self.H * 4 > 24 * 2**20
 
     def step(self, q, *, theta=None, score_scale=1.0, sm_scale=None, compact=False, fused_check=False, ranked_vote=False):
