@@ -15,12 +15,17 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtokenselect.so")
-SOURCES = ["api.hip", "score_decode.hip", "soft_vote.hip", "topk.hip", "selcache.hip", "sparse_attn_decode.hip", "sparse_attn_stream.hip", "prefill_select.hip", "sparse_attn_chunk.hip",
+SOURCES = ["api.hip", "score_decode.hip", "soft_vote.hip", "topk.hip", "selcache.hip", "sparse_attn_decode.hip", "sparse_attn_stream.hip", "prefill_select.hip", "sparse_attn_chunk.hip", "sparse_attn_chunk_wide.hip",
            "chunk_mean_query.hip", "select_variants.hip", "select_compact.hip", "score_codes_mfma.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"] + os.environ.get("TS_EXTRA_FLAGS", "").split()
+
+# Flags of single files.  sparse_attn_chunk_wide: its kernel runs one wave per SIMD and needs both halves of the register file; the
+# results of its matrix products are read by vector instructions, which see the first half only, and without this option the
+# compiler keeps all of them in the second half and moves every score over (2113 moves in the kernel, with it 182).
+FILE_FLAGS = {"sparse_attn_chunk_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _deps():
@@ -34,7 +39,7 @@ def _compile(src: str, force: bool) -> str:
     srcp = os.path.join(CSRC, src)
     newest = max(os.path.getmtime(p) for p in [srcp] + _deps())
     if force or not os.path.exists(obj) or os.path.getmtime(obj) < newest:
-        subprocess.check_call([HIPCC, *FLAGS, "-c", srcp, "-o", obj])
+        subprocess.check_call([HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), "-c", srcp, "-o", obj])
     return obj
 
 

@@ -2,15 +2,17 @@
 // over the shared selected tokens plus the chunk's own tokens up to and including itself, in one
 // joint softmax ([K_select, K_current] of Eq. 2 with a causal mask inside the chunk).
 //
+// The kernel here serves head size 64; head size 128 takes sparse_attn_chunk_wide.hip (whose four waves of 64 rows were 0.76 to
+// 0.99 of this kernel's speed at head size 64, over 12 shapes: there two workgroups fit a CU, and four waves a SIMD fill each
+// other's gaps).  The merge of the splits serves both.
+//
 // Matrix-core flash attention over a gathered key list.  The G query heads x C queries of one KV head are rows that
 // all meet the same keys.  A workgroup of eight waves owns 128 rows: four waves of 32 rows take the even 64-key tiles
 // of its share of the list, four the odd ones, and the two halves meet in LDS at the end, so that half as many
 // partials have to travel through memory.
 //
-// What bounds it: per 64-key tile a wave issues 32 MFMAs (32 cycles of matrix core each, 8 of the issue port) and
-// 32 x (fma, exp2, half a conversion, half a dot) on the vector ALU, and its phases (scores, weights, output) follow
-// each other; the two waves of a SIMD fill each other's gaps only in part (of all cycles, start and end included, the matrix
-// core is busy 23 %, the vector ALU 34 %, neither 44 %; row loads alone take 33 us, arithmetic alone 50 us of the 60).  What was taken out of the loop:
+// What bounds it: phases of a wave (scores, weights, output) that follow each other, and the LDS, where eight waves read every
+// fragment for 32 rows only.  What was taken out of the loop:
 //   * Scores are formed transposed (K as A operand, Q as B): a lane then holds 32 keys of ONE row, so the running
 //     softmax is two registers per lane, and the weights, rounded to bf16, are the B operand of O^T += V^T P^T
 //     as they stand -- which key sits at which k of the product is free as long as V^T is read the same way.
@@ -20,10 +22,6 @@
 //   * No maximum over the scores: weights are formed against the row's reference exponent; only if a tile's sum
 //     comes out above 2^16 (or not a number) the reference is raised and the tile's weights are formed again.
 //   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows.
-// 512 queries, H 32/8, D 128, 4096 selected + 512 own keys: 155 + 12 + 5 us (one tile of 32 keys per
-// barrier, weights and V^T through 2-byte LDS accesses, four splits, a slot list built first) -> 62 + 6 us.  Tried
-// without gain: the next block's scores and the previous one's output interleaved with the weights (241 to 256
-// registers, 67 us), fragments read ahead of their use, one 32-key block at a time (62 us).
 #include "ts_kernels.h"
 #include <limits.h>
 
@@ -43,12 +41,10 @@ constexpr float kCaBig = 1048576.f;  // references beyond this: the logits are r
 
 // place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 4 rows x 4 pieces (V^T) each
 // fall on all banks
-template <int D> __device__ __forceinline__ int ca_swz(int key) {
-  return D == 128 ? (((key & 3) << 2) | ((key >> 2) & 3)) : ((((key >> 1) & 1) << 2) | ((key >> 2) & 3));
-}
+__device__ __forceinline__ int ca_swz(int key) { return (((key >> 1) & 1) << 2) | ((key >> 2) & 3); }
 
-template <int D>
 __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
+  constexpr int D = 64;
   constexpr int KS = D / 16;                     // k-steps of Q K^T
   constexpr int NBO = D / 32;                    // 32-row blocks of the transposed output
   constexpr int RBYTES = D * 2;
@@ -172,7 +168,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
     for (int i = 0; i < NLD; ++i) {
       const int key = i * KPI + st_key;                         // the swizzle looks at the low four bits only
       const size_t slot = ((size_t)page_id[i] << a.p_shift) + page_off[i];
-      const size_t o = (slot * a.H_kv + kvh) * RBYTES + (size_t)((st_pos ^ ca_swz<D>(key)) * 16);
+      const size_t o = (slot * a.H_kv + kvh) * RBYTES + (size_t)((st_pos ^ ca_swz(key)) * 16);
       const uint32_t dst = __builtin_amdgcn_readfirstlane(kt + i * KPI * RBYTES);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(a.k_pool + o) : "memory", "m0");
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst + TILE_B), "v"(a.v_pool + o) : "memory", "m0");
@@ -192,7 +188,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
     fetch_pages(t);
     fetch_ids(2);
   }
-  const int ka_swz = ca_swz<D>(col);                            // K fragment: key 32 * kb + col
+  const int ka_swz = ca_swz(col);                            // K fragment: key 32 * kb + col
   // V^T: 16 lanes read 4 keys x 16 columns; lane i of them reads key i / 4, columns 4 * (i % 4) ..
   const int vt_key = 4 * half + ((lane & 15) >> 2), vt_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   for (int it = 0; it < niter; ++it) {
@@ -290,7 +286,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
 #pragma unroll
         for (int h8 = 0; h8 < 2; ++h8) {
           const int key = k4 * 16 + h8 * 8 + vt_key, c = nb * 32 + vt_col;
-          const uint8_t* p = vt + key * RBYTES + (((c >> 3) ^ ca_swz<D>(key)) * 16) + (c & 7) * 2;
+          const uint8_t* p = vt + key * RBYTES + (((c >> 3) ^ ca_swz(key)) * 16) + (c & 7) * 2;
           v[h8] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)p);
         }
         const uint2 v0 = __builtin_bit_cast(uint2, v[0]), v1 = __builtin_bit_cast(uint2, v[1]);
@@ -375,28 +371,26 @@ __global__ __launch_bounds__(256) void chunk_attn_merge_kernel(ChunkAttnArgs a, 
   if (a.lse != nullptr && d == 0) a.lse[hb] = any ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994530942f : -INFINITY;
 }
 
-template <int D>
-static hipError_t chunk_attn_launch(ChunkAttnArgs a, int B, hipStream_t s) {
-  const int nrb = (a.C * a.G + kCaRows - 1) / kCaRows;
-  const size_t lds = (size_t)2 * kCaGroups * 2 * kCaTile * D * 2;      // 128 KiB for D = 128: one workgroup per CU
-  if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chunk_attn_kernel<D>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+hipError_t launch_sparse_attn_chunk(const ChunkAttnArgs& args, int B, hipStream_t s) {
+  ChunkAttnArgs a = args;
+  const int nrb = (a.C * a.G + kCaRows - 1) / kCaRows;                 // both kernels own 128 rows a workgroup
   const int groups = B * a.H_kv * a.nsplit;                            // times xsplit: a multiple of 8
   a.xsplit = groups % 8 == 0 ? 1 : groups % 4 == 0 ? 2 : groups % 2 == 0 ? 4 : 8;
   const int rbs = (nrb + a.xsplit - 1) / a.xsplit;
-  hipLaunchKernelGGL(chunk_attn_kernel<D>, dim3((unsigned)(groups * a.xsplit * rbs)), dim3(512), lds, s, a);
+  const unsigned grid = (unsigned)(groups * a.xsplit * rbs);
+  if (a.D == 128) {
+    const hipError_t e = launch_chunk_attn_wide(a, grid, s);
+    if (e != hipSuccess) return e;
+  } else {
+    const size_t lds = (size_t)2 * kCaGroups * 2 * kCaTile * 64 * 2;   // 64 KiB: two workgroups per CU
+    hipLaunchKernelGGL(chunk_attn_kernel, dim3(grid), dim3(512), lds, s, a);
+  }
   if (a.nsplit > 1) {
-    const int rows = B * a.C * a.H, rpw = 256 / (D / 4);
-    hipLaunchKernelGGL(chunk_attn_merge_kernel<D>, dim3((rows + rpw - 1) / rpw), dim3(256), 0, s, a, rows);
+    const int rows = B * a.C * a.H, rpw = 256 / (a.D / 4);
+    if (a.D == 128) hipLaunchKernelGGL(chunk_attn_merge_kernel<128>, dim3((rows + rpw - 1) / rpw), dim3(256), 0, s, a, rows);
+    else hipLaunchKernelGGL(chunk_attn_merge_kernel<64>, dim3((rows + rpw - 1) / rpw), dim3(256), 0, s, a, rows);
   }
   return hipGetLastError();
-}
-
-hipError_t launch_sparse_attn_chunk(const ChunkAttnArgs& a, int B, hipStream_t s) {
-  return a.D == 128 ? chunk_attn_launch<128>(a, B, s) : chunk_attn_launch<64>(a, B, s);
 }
 
 }  // namespace ts

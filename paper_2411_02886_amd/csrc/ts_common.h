@@ -105,7 +105,7 @@ struct WsLayout {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Key-list splits of the chunk-form attention: a workgroup of eight waves owns 128 rows and fills a CU, so the key list
+// Key-list splits of the chunk-form attention: a workgroup owns 128 rows and fills a CU, so the key list
 // is split until there is about one workgroup per CU; every split keeps at least four 64-key tiles (two per key group).
 inline int chunk_attn_splits(const ts_problem* p, int k) {
   const int G = p->num_q_heads / p->num_kv_heads;

@@ -178,6 +178,7 @@ struct ChunkAttnArgs {
   float sm_scale;
 };
 hipError_t launch_sparse_attn_chunk(const ChunkAttnArgs& a, int B, hipStream_t s);
+hipError_t launch_chunk_attn_wide(const ChunkAttnArgs& a, unsigned grid, hipStream_t s);   // head size 128, the same grid of 128-row blocks
 
 // variant: 0 = fma arithmetic, 1 = packed bf16 dot2 (bf16 only)
 hipError_t launch_score_decode(int dtype, int D, int G, int variant, const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s);
