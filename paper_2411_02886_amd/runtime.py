@@ -142,11 +142,17 @@ class DecodeLayer:
         ts.ts_sparse_paged_attn(self.problem, q, self.idx, self.k, self.count, sm_scale, self.out, self.lse, self.ws)
 
     def compact_form_pays(self) -> bool:
-        """Which form of the Eq. 5 selection to take.  With one sequence (measured on MI355X) the five-call form is the faster
-        step while the fp32 score matrix fits the L2 with room to spare (131072 tokens of 32 heads: 16 MiB), beyond that the
-        compact form, which never writes it (crossover between 128K and 256K tokens of 32 heads).  A batch counts by the sum of
-        its matrices; on three batches tried the five-call form would have been 5 to 8 % faster above the line."""
-        return self.B * self.max_seq_len * self.H * 4 > 24 * 2**20
+        """Which form of the Eq. 5 selection to take.  The compact form saves the write of the fp32 score matrix and part of its
+        reading, which goes with the matrix' size; it pays with a launch and with the candidates' products in double precision,
+        which go with batch * k * heads * head size.  A sequence that is long by itself takes it always: its share of the small
+        launches is small.  Over 220 steps and cached runs (1 to 64 sequences of 1 to 1048576 tokens, on MI355X) this line is
+        0.4 % above the faster form on average, 13 % at most; by the matrices' size alone, with the line at 24 MiB, 2.6 % and 37 %.
+        One sequence of 131072 tokens of 32 heads, 16 MiB: 81.8 us five-call, 84.0 compact; one of 163711 of 28 heads, 17.5 MiB: 75.5
+        and 69.3; one of 1048576, k 4096, 112 MiB: 254.6 and 228.9; 32 of up to 16001 tokens of 32 heads, k 2048, 61 MiB:
+        206.5 and 221.8; 32 of up to 8180 of 64 heads, k 2154, 64 MiB: 194.5 and 259.3."""
+        matrix = self.max_seq_len * self.H * 4 / 2**20
+        products = self.B * min(self.k, self.max_seq_len) * self.H * self.D / 1e6
+        return matrix > 16.5 or self.B * matrix > 22.0 + 0.25 * products
 
     def step(self, q, *, theta=None, score_scale=1.0, sm_scale=None, compact=False, fused_check=False, ranked_vote=False):
         """One decode step: Selection Cache check (when theta is given), selection on a miss, sparse
