@@ -333,6 +333,17 @@ __global__ __launch_bounds__(kCwThreads, 1) void chunk_attn_wide_kernel(ChunkAtt
         float m = ref[rb2];
 #pragma unroll
         for (int e = 0; e < 16; ++e) m = fmaxf(m, factor * x[rb2][e] + kCwHead);
+        // the first block: the second one's scores are there too, and a reference from all keys of the tile leaves more rows
+        // with a largest weight that is a power of two, exact in bf16 (error of `out` against 64 bits, 256 to 2048 keys: 1 to
+        // 2 % more without)
+        if (CUR == 0 && !OUT) {
+          const int see = lt < ntile ? vis[rb2] : INT_MIN;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int cq = j0 + 32 + 8 * (e >> 2) + 4 * half + (e & 3) - cnt;
+            m = fmaxf(m, factor * (cq <= see ? s[NXT][rb2][e] : hidden) + kCwHead);
+          }
+        }
         m = fmaxf(m, __shfl_xor(m, 32));                        // both halves of a row raise its reference together
         const float f = __builtin_amdgcn_exp2f(ref[rb2] - m);   // 1 where nothing changes, 0 while the reference is unset
         const float fo = __shfl(f, (lane & 15) + 16);
