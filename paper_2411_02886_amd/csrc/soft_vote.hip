@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void soft_vote_kernel(VoteArgs a, int lpt_shif
   }
 }
 
-// Eq. 5 and the start of the TopK in one launch.  A workgroup of 1024 threads owns kRankTokens consecutive tokens:
+// Eq. 5 and the start of the TopK in one launch.  A workgroup of T threads owns T / 2 consecutive tokens:
 // it computes their votes as soft_vote_kernel does (same arithmetic, LPT lanes per token row, four passes of loads in
 // flight), counts the top 11 key bits of the ranked tokens' votes in an LDS histogram and adds the non-empty bins to
 // one of the replicated global histograms -- one flush per workgroup, spread over kBoundHistCopies copies, so the
@@ -150,14 +150,19 @@ __global__ __launch_bounds__(256) void soft_vote_kernel(VoteArgs a, int lpt_shif
 // The line: with up to 256 partials a head (30000 tokens of 12 heads, five sequences) the step took 62 us instead of 55.
 constexpr int kMergeInVote = 1024;   // partials x heads
 constexpr int kMergeParts = 64;      // partials per head: two per thread
-constexpr int kRankTokens = 512;     // per workgroup: one round of four passes for H = 32, and a workgroup for every CU at 128K tokens
+// T: 512 where eight lanes share a token (from 17 heads on: a round of four passes), 1024 for narrower rows.  Smaller workgroups
+// fill the rounds of the machine better and start and end beside each other; each flushes a histogram of its own, though, which is
+// what counts for narrow rows (statistics merge and vote, 1024 and 512 threads: 4 x 20011 to 40009 tokens of 64 heads 18.6 and 14.7
+// us, 32 x 1031 to 16001 of 32 heads 20.7 and 19.6, 30000 of 28 heads 9.1 and 8.4, 131072 of 32 heads 10.5 and 10.5; 5 x
+// 20000 to 60000 of 12 heads 9.4 and 9.8).  Up to 32 heads, one large workgroup for each of most CUs is as fast, and its 256
+// histograms take the compaction less (a step of 131072 tokens 81.2 and 81.7).
 
-template <int CPL, bool VEC, bool MERGE>
-__global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int lpt_shift) {
+template <int T, int CPL, bool VEC, bool MERGE>
+__global__ __launch_bounds__(T) void soft_vote_ranked_kernel(VoteArgs a, int lpt_shift) {
   __shared__ double s_m[128];
   __shared__ double s_inv[128];
   __shared__ uint32_t hist[kTopkBins];
-  constexpr int NP = 4;
+  constexpr int NP = 4, kRankTokens = T / 2;
   const int b = blockIdx.y;
   const int skip_flag = a.skip != nullptr ? (int)a.skip[b] : 0;   // issued together with the length
   const int N = min(max(a.seq_lens[b], 0), a.max_seq_len);
@@ -172,7 +177,7 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
   const int H = a.H;
   const double c2 = (double)a.scale * 1.44269504088896340736;
   const int LPT = 1 << lpt_shift;
-  const int tpp = 1024 >> lpt_shift;                 // tokens per pass
+  const int tpp = T >> lpt_shift;                 // tokens per pass
   const int jv = threadIdx.x & (LPT - 1);
   const int npass = (kRankTokens + tpp - 1) / tpp;   // LPT / 2 passes, one for the narrowest rows
   float s[NP][CPL][4];
@@ -197,14 +202,14 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
   };
   load_round(0);
   const bool counts = a.max_seq_len > kTopkOneWg;      // shorter sequences are ranked without a histogram
-  if (counts) for (int i = threadIdx.x; i < kTopkBins; i += 1024) hist[i] = 0u;
+  if (counts) for (int i = threadIdx.x; i < kTopkBins; i += T) hist[i] = 0u;
   if (MERGE) {
-    // 32 threads per head, 32 heads per round.  Thread pl stands in for the threads pl + 32 * i of the merge kernel and adds
+    // 32 threads per head, T / 32 heads per round.  Thread pl stands in for the threads pl + 32 * i of the merge kernel and adds
     // in that kernel's order, so that the statistics are the same bit for bit.
     const int nparts = min((int)a.hdr[b * 8 + 0], kScoreMaxWg);
     const int pl = threadIdx.x & 31;
     const double sc = (double)a.scale;
-    for (int h0 = 0; h0 < H; h0 += 32) {
+    for (int h0 = 0; h0 < H; h0 += T / 32) {
       const int h = h0 + (int)(threadIdx.x >> 5), hc = min(h, H - 1);
       auto slot = [&](int p) { return *reinterpret_cast<const float2*>(a.partials + (((size_t)b * kScoreMaxWg + p) * H + hc) * 2); };
       float2 v[2];                                     // all slots exist; unused ones are masked
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(1024) void soft_vote_ranked_kernel(VoteArgs a, int 
   if (!counts) return;
   __syncthreads();
   uint32_t* gh = a.rank_hist + ((size_t)b * kBoundHistCopies + (blockIdx.x & (kBoundHistCopies - 1))) * kTopkBins;
-  for (int i = threadIdx.x; i < kTopkBins; i += 1024)
+  for (int i = threadIdx.x; i < kTopkBins; i += T)
     if (hist[i] != 0u) atomicAdd(&gh[i], hist[i]);
 }
 
@@ -284,12 +289,15 @@ hipError_t launch_soft_vote_ranked(const VoteArgs& a, int B, hipStream_t s) {
   const bool vec = (a.H % 4 == 0) && (((uintptr_t)a.scores & 15) == 0);
   const bool merge_in_vote = a.parts_hint <= kMergeParts && a.parts_hint * a.H <= kMergeInVote;
   if (!merge_in_vote) hipLaunchKernelGGL(score_stats_merge_kernel, dim3(a.H, B), dim3(256), 0, s, a);
-  dim3 grid((a.max_seq_len + kRankTokens - 1) / kRankTokens, B);
-#define TS_RV(C, V) do { if (merge_in_vote) hipLaunchKernelGGL((soft_vote_ranked_kernel<C, V, true>), grid, dim3(1024), 0, s, a, lpt_shift); \
-    else hipLaunchKernelGGL((soft_vote_ranked_kernel<C, V, false>), grid, dim3(1024), 0, s, a, lpt_shift); } while (0)
-  if (cpl <= 1) { if (vec) TS_RV(1, true); else TS_RV(1, false); }
-  else if (cpl <= 2) { if (vec) TS_RV(2, true); else TS_RV(2, false); }
-  else { if (vec) TS_RV(4, true); else TS_RV(4, false); }
+  const long wgs = ((long)a.max_seq_len + 511) / 512 * B;
+  const int threads = lpt_shift < 3 || (cpl == 1 && wgs > 128 && wgs <= 256) ? 1024 : 512, tokens = threads / 2;
+  dim3 grid((a.max_seq_len + tokens - 1) / tokens, B);
+#define TS_RV(T, C, V) do { if (merge_in_vote) hipLaunchKernelGGL((soft_vote_ranked_kernel<T, C, V, true>), grid, dim3(T), 0, s, a, lpt_shift); \
+    else hipLaunchKernelGGL((soft_vote_ranked_kernel<T, C, V, false>), grid, dim3(T), 0, s, a, lpt_shift); } while (0)
+  if (threads == 1024) { if (vec) TS_RV(1024, 1, true); else TS_RV(1024, 1, false); }
+  else if (cpl <= 1) { if (vec) TS_RV(512, 1, true); else TS_RV(512, 1, false); }
+  else if (cpl <= 2) { if (vec) TS_RV(512, 2, true); else TS_RV(512, 2, false); }
+  else { if (vec) TS_RV(512, 4, true); else TS_RV(512, 4, false); }
 #undef TS_RV
   return hipGetLastError();
 }
