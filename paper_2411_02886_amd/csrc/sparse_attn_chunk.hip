@@ -2,9 +2,9 @@
 // over the shared selected tokens plus the chunk's own tokens up to and including itself, in one
 // joint softmax ([K_select, K_current] of Eq. 2 with a causal mask inside the chunk).
 //
-// The kernel here serves head size 64; head size 128 takes sparse_attn_chunk_wide.hip (whose four waves of 64 rows were 0.76 to
-// 0.99 of this kernel's speed at head size 64, over 12 shapes: there two workgroups fit a CU, and four waves a SIMD fill each
-// other's gaps).  The merge of the splits serves both.
+// The kernel here serves head size 64; head size 128 takes sparse_attn_chunk_wide.hip, whose four waves of 64 rows were 0.76 to
+// 0.94 of this kernel's speed at head size 64 (12 shapes): with half the products per weight the vector ALU is the bound, and two
+// waves a SIMD fill it better than one.  The merge of the splits serves both.
 //
 // Matrix-core flash attention over a gathered key list.  The G query heads x C queries of one KV head are rows that
 // all meet the same keys.  A workgroup of eight waves owns 128 rows: four waves of 32 rows take the even 64-key tiles
@@ -19,24 +19,32 @@
 //   * V^T is read from the row-major V tile by the transposing LDS read (16 columns x 4 keys per 16 lanes).
 //   * K and V rows go from memory to LDS directly, 16 bytes per lane, each lane fetching the piece that belongs at its
 //     place: pieces are exchanged inside a row (piece ^ swz(key)) so that both reads are free of bank conflicts.
-//   * No maximum over the scores: weights are formed against the row's reference exponent; only if a tile's sum
-//     comes out above 2^16 (or not a number) the reference is raised and the tile's weights are formed again.
-//   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows.
+//   * No maximum over the scores: weights are formed against the row's reference exponent, 2^8 above the largest when it was
+//     set; only if a weight comes out as 2 or more (or not a number) the reference is raised and the tile's weights are formed again.
+//   * The weights' sums come from the matrix cores: v_dot2_f32_bf16 with a pair of ones runs on their multipliers (6 cycles
+//     alone, 22 beside another wave's products).
+//   * The key list is resolved in the loop, a step per tile ahead: token id, page id, rows; a lane resolves one key, and the
+//     lanes that stage its row take it from there on the DPP network.
+// (The last two: 1 to 4 % of a call, 12 shapes of 497 to 2687 selected keys: 2 x 512 queries of H 16/16 23.1 -> 22.2 us, 300 of
+// H 32/8 20.0 -> 19.6.  A register limit for four waves a SIMD: 0.83 to 1.03 of that, with scratch.)
 #include "ts_kernels.h"
 #include <limits.h>
+#include <type_traits>
 
 namespace ts {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int kCaRows = 128;     // rows per workgroup (four waves of 32)
 constexpr int kCaGroups = 2;     // key groups per workgroup
 constexpr int kCaTile = 64;      // keys per tile
 constexpr float kCaUnset = -3.40282347e38f;   // reference exponent of a row that has seen no key: no finite logit lies below it
-constexpr float kCaRaise = 65536.f;  // a tile sum above this raises the reference
+constexpr uint32_t kCaTwo = 0x40004000u;      // bits that only bf16 numbers of 2 and more have (and infinities and NaN): such a weight raises the reference ...
+constexpr float kCaHead = 8.f;                // ... to this far above the largest exponent so far
 constexpr float kCaBig = 1048576.f;  // references beyond this: the logits are rounded before it is taken off them
 
 // place of a row's 16-byte pieces in LDS: 16 rows x one piece (K fragments) and 4 rows x 4 pieces (V^T) each
@@ -124,7 +132,15 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
       qfrag[ks] = __builtin_bit_cast(bf16x8_t, v);
     }
   }
-  float ref = kCaUnset, lsum = 0.f;                             // the row's reference exponent; this lane's keys' sum
+  float ref = kCaUnset;                                         // the row's reference exponent
+  // Sums of the rounded weights, by the matrix cores: rows 0 and 1 of the result are the sums of the weights' rows col and
+  // 16 + col (col = lane % 16), the lanes of the operand that hold them picked out by ones
+  f32x4_t lacc = {0.f, 0.f, 0.f, 0.f};
+  bf16x8_t pick;
+  {
+    const uint32_t one = (lane & 15) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
+    pick = __builtin_bit_cast(bf16x8_t, make_uint4(one, one, one, one));
+  }
   // The weights' exponents are one fma, c2 * score - reference.  Its exact product differs from the rounded one that the
   // reference came from by up to 2^-24 of the logit, and with logits of 2^31 that alone would over- or underflow the
   // exponential.  A wave that meets such a reference rounds the logits first from then on: `factor` is 1 and every tile takes
@@ -140,52 +156,57 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
   // ---- staging: this wave's 16 keys of its group's tile, load i covering keys 16 * rg + i * KPI + lane / PPR.  A list
   // entry becomes a row in three steps, one iteration apart: token id (raw_*), page id (page_*), rows.  What an
   // iteration consumes was loaded in the one before and has been waited for at its top, so nothing waits behind the rows.
+  // A lane looks one key up, the m-th (m = lane % 4) of those that the 16 lanes of its row stage; a load's lanes take its row from
+  // there on the DPP network (the look-ups and addresses of every lane for itself were a third of the loop's vector instructions).
   const int st_key = lane / PPR, st_pos = lane % PPR;
-  int raw_id[NLD], page_id[NLD], page_off[NLD];
-  auto key_of = [&](int it, int i) { return min((tile0 + it * kCaGroups + kg) * kCaTile + rg * 16 + i * KPI + st_key, nkeys - 1); };   // past the end: the last key
-  auto fetch_ids = [&](int it) {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) raw_id[i] = sel[min(max(key_of(it, i) - f_lo, 0), a.idx_stride - 1)];
-  };
-  auto token_of = [&](int it, int i) -> int {
-    const int j = key_of(it, i);
-    int t = (j < f_lo) ? j : raw_id[i];
+  const int my_key = rg * 16 + ((lane & 2) >> 1) * KPI + (lane >> 4) * 2 + (lane & 1);
+  int raw_id = 0, page_id = 0, page_off = 0;
+  auto key_of = [&](int it) { return min((tile0 + it * kCaGroups + kg) * kCaTile + my_key, nkeys - 1); };   // past the end: the last key
+  auto fetch_ids = [&](int it) { raw_id = sel[min(max(key_of(it) - f_lo, 0), a.idx_stride - 1)]; };
+  auto token_of = [&](int it) -> int {
+    const int j = key_of(it);
+    int t = (j < f_lo) ? j : raw_id;
     t = (j < f_lo + csel) ? t : f_hi + (j - f_lo - csel);
     t = (j < cnt) ? t : Nc + (j - cnt);
     return min(max(t, 0), N - 1);                               // a stale or corrupt index must not leave the page table
   };
-  auto fetch_pages = [&](const int (&t)[NLD]) {
+  auto fetch_pages = [&](int t) { page_id = pages[t >> a.p_shift]; page_off = t & (a.P - 1); };
+  const int row_shift = 31 - __builtin_clz((uint32_t)(a.H_kv * RBYTES));   // H_kv is a power of two
+  uint32_t piece[NLD];                                          // this lane's piece of load i's rows
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) { page_id[i] = pages[t[i] >> a.p_shift]; page_off[i] = t[i] & (a.P - 1); }
-  };
+  for (int i = 0; i < NLD; ++i) piece[i] = (uint32_t)kvh * RBYTES + (uint32_t)((st_pos ^ ca_swz(i * KPI + st_key)) * 16);   // the swizzle looks at the low four bits only
   // Memory to LDS, 16 bytes per lane: the wave's 64 lanes fill 1 KiB from the (uniform) LDS address.  Written in
   // assembly because the compiler, which cannot tell the two buffers apart, makes every later LDS read wait for the
   // builtin form; completion is awaited by the vmcnt(0) before the barrier at the top of the loop.
   auto load_rows = [&](int buf) {
     const uint32_t kt = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem +
                         (uint32_t)((buf * kCaGroups + kg) * 2 * TILE_B + rg * 16 * RBYTES);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int key = i * KPI + st_key;                         // the swizzle looks at the low four bits only
-      const size_t slot = ((size_t)page_id[i] << a.p_shift) + page_off[i];
-      const size_t o = (slot * a.H_kv + kvh) * RBYTES + (size_t)((st_pos ^ ca_swz(key)) * 16);
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(kt + i * KPI * RBYTES);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(a.k_pool + o) : "memory", "m0");
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst + TILE_B), "v"(a.v_pool + o) : "memory", "m0");
-    }
+    const uint32_t row = ((uint32_t)page_id << a.p_shift) + (uint32_t)page_off;
+    const uint32_t lo = row << row_shift, hi = row >> (32 - row_shift);
+    auto load = [&](auto i_c) __attribute__((always_inline)) {
+      constexpr int I = decltype(i_c)::value;
+      auto of = [&](uint32_t v) __attribute__((always_inline)) -> uint32_t {      // row_newbcast: lanes 2 I and 2 I + 1 of each 16
+        const uint32_t v0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + 2 * I, 0xf, 0xf, true);
+        const uint32_t v1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x151 + 2 * I, 0xf, 0xf, true);
+        return (lane & 8) != 0 ? v1 : v0;
+      };
+      const uint64_t o = ((uint64_t)of(hi) << 32) | (of(lo) | piece[I]);
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(kt + I * KPI * RBYTES), dst_v = dst + TILE_B;
+      const uint8_t *k_row = a.k_pool + o, *v_row = a.v_pool + o;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(k_row) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst_v), "v"(v_row) : "memory", "m0");
+    };
+    static_assert(NLD == 2, "the loads are written out");
+    load(std::integral_constant<int, 0>{});
+    load(std::integral_constant<int, 1>{});
   };
 
   if (niter > 0) {
-    int t[NLD];
     fetch_ids(0);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) t[i] = token_of(0, i);
-    fetch_pages(t);
+    fetch_pages(token_of(0));
     fetch_ids(1);
     load_rows(0);
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) t[i] = token_of(1, i);
-    fetch_pages(t);
+    fetch_pages(token_of(1));
     fetch_ids(2);
   }
   const int ka_swz = ca_swz(col);                            // K fragment: key 32 * kb + col
@@ -196,9 +217,7 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0f70);                         // vmcnt(0): this wave's rows of the tile (and the ids behind them) are there
     __syncthreads();                                            // ... everybody's; and the other buffer has been read
     if (it + 1 < niter) {
-      int t[NLD];
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) t[i] = token_of(it + 2, i);
+      const int t = token_of(it + 2);
       load_rows(buf ^ 1);
       fetch_pages(t);
       fetch_ids(it + 3);
@@ -239,30 +258,28 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
       if (__builtin_expect(plain_below == INT_MIN, 0)) round_logits();
     }
     uint32_t pk[2][8];
-    float sum;
     for (int tries = 0; tries < 2; ++tries) {
-      float part[2] = {0.f, 0.f};
+      uint32_t any = 0u;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
           const bf16x2_t p = {(__bf16)__builtin_amdgcn_exp2f(fmaf(factor, s[kb][e], -ref)), (__bf16)__builtin_amdgcn_exp2f(fmaf(factor, s[kb][e + 1], -ref))};
-          const bf16x2_t one = {(__bf16)1.f, (__bf16)1.f};
           pk[kb][e >> 1] = __builtin_bit_cast(uint32_t, p);
-          part[kb] = __builtin_amdgcn_fdot2_f32_bf16(p, one, part[kb], false);    // the sum of the rounded weights that multiply V
+          any |= pk[kb][e >> 1];
         }
-      sum = part[0] + part[1];
-      if (__builtin_amdgcn_ballot_w64(!(sum <= kCaRaise)) == 0) break;
+      if (__builtin_amdgcn_ballot_w64((any & kCaTwo) != 0u) == 0) break;
       // first visible key of a row, or a logit far above the reference.  Straight-line code: a branch per lane here
       // makes the compiler copy the accumulators on the common path too.
       float m = ref;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) m = fmaxf(m, factor * s[kb][e]);
+        for (int e = 0; e < 16; ++e) m = fmaxf(m, factor * s[kb][e] + kCaHead);
       m = fmaxf(m, __shfl_xor(m, 32));                          // both halves of a row raise its reference together
       const float f = __builtin_amdgcn_exp2f(ref - m);          // 1 where nothing changes, 0 while the reference is unset
-      lsum *= f;
+      const float fo = __shfl(f, (lane & 15) + 16);
+      lacc[0] *= f; lacc[1] *= fo;                              // lanes 0 to 15 hold them
 #pragma unroll
       for (int nb = 0; nb < NBO; ++nb)
 #pragma unroll
@@ -273,13 +290,13 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
         round_logits();
       }
     }
-    lsum += sum;
     // ---- O^T += V^T P^T: k-step ks2 of a block takes keys 16 * ks2 + 4 * half + {0..3, 8..11}, the keys of s[8 * ks2 ..]
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) {
       const uint32_t (&pw)[8] = pk[k4 >> 1];
       const int o = 4 * (k4 & 1);
       const uint4 pb = make_uint4(pw[o], pw[o + 1], pw[o + 2], pw[o + 3]);
+      lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick, __builtin_bit_cast(bf16x8_t, pb), lacc, 0, 0, 0);
 #pragma unroll
       for (int nb = 0; nb < NBO; ++nb) {
         s16x4_t v[2];
@@ -297,7 +314,8 @@ __global__ __launch_bounds__(512, 2) void chunk_attn_kernel(ChunkAttnArgs a) {
   }
 
   // ---- the two key groups meet: the odd group's rows through LDS
-  lsum += __shfl_xor(lsum, 32);
+  const float sum_lo = __shfl(lacc[0], lane & 15), sum_hi = __shfl(lacc[1], lane & 15);
+  const float lsum = (lane & 16) != 0 ? sum_hi : sum_lo;
   __syncthreads();
   float* xo = reinterpret_cast<float*>(smem) + (size_t)rg * (NBO * 16 + 2) * 64 + lane;   // [row group][register][lane]
   if (kg == 1) {

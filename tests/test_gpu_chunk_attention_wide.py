@@ -1,4 +1,4 @@
-"""The chunk attention of head size 128 (four waves of 64 rows, two key groups) where its pipeline changes shape: key lists that
+"""The chunk attention (head size 128: four waves of 64 rows; 64: eight of 32; two key groups) where its pipeline changes shape: key lists that
 end at, before and after a tile of either key group, and logits that jump up in a chosen tile -- a raised reference in an
 even or odd tile, in its first or second half, and one so large that the loop without masks ends there."""
 import math
@@ -12,10 +12,10 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def _attend(C, H, H_kv, cached, n_init, spikes):
+def _attend(C, H, H_kv, D, cached, n_init, spikes):
     """One sequence whose `cached` tokens are all selected (or forced); spikes: {list position: logit of every query with that key}."""
     from paper_2411_02886_amd.runtime import ChunkSelector, to_device, to_host
-    D, k = 128, max(1, cached - n_init)
+    k = max(1, cached - n_init)
     w = W.make_workload("wide", dtype=W.BF16, B=1, C=C, H=H, H_kv=H_kv, D=D, P=16, seq_lens=[cached + C], k=k, seed=3 * cached + C)
     sm = 1.0 / math.sqrt(D)
     slots = w.slots_of(0)
@@ -58,12 +58,12 @@ def _attend(C, H, H_kv, cached, n_init, spikes):
 
 
 @pytest.mark.parametrize("cached", [1, 31, 62, 63, 64, 94, 126, 127, 128, 190, 191, 254, 255, 319, 383, 447, 1151])
-@pytest.mark.parametrize("C,H,H_kv", [(2, 3, 1), (33, 8, 2)])
-def test_key_lists_around_the_tiles(cached, C, H, H_kv):
+@pytest.mark.parametrize("C,H,H_kv,D", [(2, 3, 1, 128), (33, 8, 2, 128), (33, 8, 2, 64)])
+def test_key_lists_around_the_tiles(cached, C, H, H_kv, D):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    print("wide chunk attention", cached, C, H, H_kv, flush=True)
-    _attend(C, H, H_kv, cached, 0, {})
+    print("wide chunk attention", cached, C, H, H_kv, D, flush=True)
+    _attend(C, H, H_kv, D, cached, 0, {})
 
 
 # one split of 12 tiles; logits of the spikes against ordinary ones of a few units.  The last spike's is the largest by far,
@@ -73,9 +73,9 @@ SPIKES = [{70: 30.0}, {200: 40.0}, {64 * 4 + 3: 60.0, 64 * 5 + 40: 90.0}, {0: 25
 
 
 @pytest.mark.parametrize("spikes", SPIKES, ids=range(len(SPIKES)))
-@pytest.mark.parametrize("n_init", [0, 37])
-def test_references_raised_in_either_group_and_half(spikes, n_init):
+@pytest.mark.parametrize("n_init,D", [(0, 128), (37, 128), (0, 64)])
+def test_references_raised_in_either_group_and_half(spikes, n_init, D):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    print("wide chunk attention, spikes", spikes, n_init, flush=True)
-    _attend(160, 2, 1, 700, n_init, spikes)
+    print("wide chunk attention, spikes", spikes, n_init, D, flush=True)
+    _attend(160, 2, 1, D, 700, n_init, spikes)
