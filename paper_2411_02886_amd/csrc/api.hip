@@ -497,7 +497,8 @@ int32_t ts_topk(const ts_problem* p, const float* votes, int32_t k, int32_t* idx
   // quarter-octave (decode votes are peaked), slow when most do.  Votes summed over a chunk's queries are flat,
   // so chunk problems (and callers that say so) take the five-pass form, whose cost does not depend on the
   // distribution.
-  a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)((uint8_t*)ws + w.topk_list);
+  a.table = (uint16_t*)((uint8_t*)ws + w.topk_list);
+  a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)a.table;
   a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = w.topk_nblk; a.heads = 1; a.one_wg = !g_topk_five_pass;
   if ((flags & TS_TOPK_VOTE_HIST) != 0 && p->max_seq_len > kTopkOneWg) a.rep_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_topk(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
@@ -521,7 +522,8 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
   a.hist = (uint32_t*)(base + kNoAllocHist);
   a.state = (uint32_t*)(base + kNoAllocState);
   a.blk = (uint32_t*)(base + kNoAllocBlk);
-  a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)(base + kNoAllocList);
+  a.table = (uint16_t*)(base + kNoAllocList);
+  a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)a.table;
   a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = nblk; a.heads = 1; a.one_wg = !g_topk_five_pass;
   // the array keeps whatever the last call on this GPU left: the histograms must start at zero (a fill kernel,
   // not a memset node: callers may be under graph capture)
@@ -594,7 +596,8 @@ int32_t ts_head_vote(const ts_problem* p, const float* scores, int32_t k_head, f
   a.head = p->num_initial; a.tail = p->num_local;
   a.votes = (const float*)(base + l.st); a.seq_lens = p->seq_lens; a.skip = skip;
   a.hist = (uint32_t*)(base + l.hist); a.state = (uint32_t*)(base + l.state); a.blk = (uint32_t*)(base + l.blk);
-  a.list = g_topk_five_pass ? nullptr : (uint2*)(base + l.list);
+  a.table = (uint16_t*)(base + l.list);
+  a.list = g_topk_five_pass ? nullptr : (uint2*)a.table;
   a.k = k_head; a.max_seq_len = p->max_seq_len; a.nblk = l.nblk; a.heads = p->num_q_heads; a.vote_acc = votes; a.one_wg = !g_topk_five_pass;
   return launch_topk(a, p->batch * p->num_q_heads, s) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }

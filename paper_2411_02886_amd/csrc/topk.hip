@@ -4,9 +4,10 @@
 // workgroup histograms its 2048-key chunk in LDS and adds the non-empty bins to a global histogram;
 // the next kernel's workgroups each walk that (8 KiB, cache-resident) histogram from the top and fix
 // the digit for themselves, so no kernel waits on another workgroup and nothing but the kernel
-// boundary orders the passes.  A counting pass then records per chunk the number of keys above /
-// equal to the threshold key, and the emit pass writes the winners in token order: all keys above
-// the threshold plus the first (k - #above) keys equal to it.  That is the "lower token index wins ties" rule and yields
+// boundary orders the passes.  The emit pass writes the winners in token order: all keys above
+// the threshold plus the first (k - #above) keys equal to it.  How many of both the earlier chunks hold it reads from a
+// table that the third pass leaves, a chunk's number of keys at or above every value of the last digit (kTableChunks); for
+// longer sequences a counting pass in between records them per chunk.  That is the "lower token index wins ties" rule and yields
 // ascending indices without a sort.
 #include "ts_kernels.h"
 
@@ -115,8 +116,13 @@ __global__ __launch_bounds__(256) void topk_fold_rep_hist_kernel(TopkArgs a) {
   a.hist[((size_t)b * 3 + 0) * kTopkBins + i] = sum;
 }
 
+// The counting pass read all votes once more for a launch's latency.  ts_topk on flat votes, five launches and four: 20000 tokens 21.0
+// and 18.4 us, 131072 22.3 and 19.4, 8 x 262144 33.1 and 30.0, 1048576, the last length with the table, 39.0 and 36.5.  Beyond, the
+// emit pass' reads, a piece of the table for every pair of chunks, grow with the square of their number.
+constexpr int kTableChunks = 512;
+
 // state words per sequence
-enum { ST_PREFIX0 = 0, ST_KREM0 = 1, ST_KEFF = 2, ST_PREFIX1 = 3, ST_KREM1 = 4, ST_THR = 5, ST_NEED_EQ = 6, ST_NONE = 7 };
+enum { ST_PREFIX0 = 0, ST_KREM0 = 1, ST_KEFF = 2, ST_PREFIX1 = 3, ST_KREM1 = 4, ST_THR = 5, ST_NEED_EQ = 6 };
 
 // tokens [LO, N) of a sequence take part: forced initial tokens, the chunk's own tokens and forced recent
 // tokens do not
@@ -164,7 +170,8 @@ __global__ __launch_bounds__(256) void topk_hist0_kernel(TopkArgs a) {
   flush_hist(h, a.hist + ((size_t)b * 3 + 0) * kTopkBins, kTopkBins);
 }
 
-// pass 1: fix digit 0 from histogram 0, histogram the next 11 bits of the keys that carry it
+// pass 1: fix digit 0 from histogram 0, histogram the next 11 bits of the keys that carry it; histogram 2, which every
+// workgroup of the last call's emit may have read, is cleared for pass 2
 __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   __shared__ uint32_t h[kTopkBins];
   __shared__ uint32_t lds[8];
@@ -183,6 +190,10 @@ __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.state[b * 8 + ST_PREFIX0] = d0 << 21; a.state[b * 8 + ST_KREM0] = krem0; a.state[b * 8 + ST_KEFF] = k_eff;
   }
+  if (blockIdx.x == 0) {
+    uint32_t* g2 = a.hist + ((size_t)b * 3 + 2) * kTopkBins;
+    for (int i = threadIdx.x; i < 1024; i += 256) g2[i] = 0u;
+  }
 #pragma unroll
   for (int i = 0; i < kTopkChunk / 256; ++i)
     if (valid[i] && (key[i] >> 21) == d0) atomicAdd(&h[(key[i] >> 10) & 2047u], 1u);
@@ -190,9 +201,12 @@ __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   flush_hist(h, a.hist + ((size_t)b * 3 + 1) * kTopkBins, kTopkBins);
 }
 
-// pass 2: fix digit 1, histogram the last 10 bits; histogram 0 is no longer needed and is cleared
+// pass 2: fix digit 1, histogram the last 10 bits; histogram 0 is no longer needed and is cleared.  TABLE: also the chunk's
+// row of the table, for every value of the last digit the number of its keys there or above (at most 2048), and apart the
+// number above all of them.
+template <bool TABLE>
 __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
-  __shared__ uint32_t h[1024];
+  __shared__ __attribute__((aligned(16))) uint32_t h[1024];
   __shared__ uint32_t lds[8];
   const int b = blockIdx.y;
   const int skip_flag = a.skip != nullptr ? (int)a.skip[b / a.heads] : 0;   // issued together with the length
@@ -219,6 +233,19 @@ __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
     if (valid[i] && !none && (key[i] >> 10) == (prefix1 >> 10)) atomicAdd(&h[key[i] & 1023u], 1u);
   __syncthreads();
   flush_hist(h, a.hist + ((size_t)b * 3 + 2) * kTopkBins, 1024);
+  if (TABLE) {
+    uint32_t gt = 0;
+#pragma unroll
+    for (int i = 0; i < kTopkChunk / 256; ++i) gt += valid[i] && !none && (key[i] >> 10) > (prefix1 >> 10);
+    const int lowest = 1020 - 4 * (int)threadIdx.x;             // thread 0 owns the top four values
+    const uint4 c = *reinterpret_cast<const uint4*>(&h[lowest]);
+    uint32_t total;
+    const uint32_t ex = block_exclusive_scan((c.x + c.y + c.z + c.w) | (gt << 16), &total, lds);
+    const uint32_t w3 = (total >> 16) + (ex & 0xffffu) + c.w, w2 = w3 + c.z, w1 = w2 + c.y, w0 = w1 + c.x;
+    const size_t chunk = (size_t)b * a.nblk + blockIdx.x;
+    *reinterpret_cast<uint2*>(a.table + chunk * 1024 + lowest) = make_uint2(w0 | (w1 << 16), w2 | (w3 << 16));
+    if (threadIdx.x == 0) a.blk[chunk] = total >> 16;
+  }
 }
 
 // fix the last digit (the threshold key is now exact) and count, per chunk, the keys above / equal to it
@@ -240,7 +267,7 @@ __global__ __launch_bounds__(256) void topk_count_kernel(TopkArgs a) {
   if (none) need_eq = 0;
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) {
-      a.state[b * 8 + ST_THR] = thr; a.state[b * 8 + ST_NEED_EQ] = need_eq; a.state[b * 8 + ST_NONE] = none;
+      a.state[b * 8 + ST_THR] = thr; a.state[b * 8 + ST_NEED_EQ] = need_eq;
     }
     uint32_t* g1 = a.hist + ((size_t)b * 3 + 1) * kTopkBins;
     for (int i = threadIdx.x; i < kTopkBins; i += 256) g1[i] = 0u;
@@ -259,7 +286,9 @@ __global__ __launch_bounds__(256) void topk_count_kernel(TopkArgs a) {
   if (threadIdx.x == 0) a.blk[(size_t)b * a.nblk + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// winners of a chunk, in token order; every workgroup sums the counts of the chunks before it
+// winners of a chunk, in token order; every workgroup sums the counts of the chunks before it.  TABLE: it fixes the last
+// digit for itself and looks the counts up in the table of pass 2.
+template <bool TABLE>
 __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
   __shared__ uint32_t scan_lds[8];
   __shared__ uint32_t red[2][4];
@@ -267,9 +296,10 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
   const int skip_flag = a.skip != nullptr ? (int)a.skip[b / a.heads] : 0;   // issued together with the length
   const int LO = ranked_lo(a, b), N = ranked_hi(a, b, LO);
   if (skip_flag != 0) return;
-  const uint32_t thr = a.state[b * 8 + ST_THR];
-  const uint32_t need_eq = a.state[b * 8 + ST_NEED_EQ];
-  const bool none = a.state[b * 8 + ST_NONE] != 0;
+  uint32_t thr = a.state[b * 8 + (TABLE ? ST_PREFIX1 : ST_THR)];
+  uint32_t need_eq = TABLE ? 0u : a.state[b * 8 + ST_NEED_EQ];
+  const uint32_t krem1 = a.state[b * 8 + ST_KREM1];
+  const bool none = krem1 == 0;
   const int k_eff = (int)a.state[b * 8 + ST_KEFF];
   const bool as_votes = a.vote_acc != nullptr;      // Eq. 4: winners are counted per token, not listed
   int32_t* out = as_votes ? nullptr : a.idx + (size_t)b * a.k;
@@ -279,8 +309,10 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
       for (int i = k_eff + threadIdx.x; i < a.k; i += 256) out[i] = -1;
       if (threadIdx.x == 0) a.count[b] = k_eff;
     }
-    uint32_t* g2 = a.hist + ((size_t)b * 3 + 2) * kTopkBins;
-    for (int i = threadIdx.x; i < 1024; i += 256) g2[i] = 0u;
+    if (TABLE) {
+      uint32_t* g1 = a.hist + ((size_t)b * 3 + 1) * kTopkBins;
+      for (int i = threadIdx.x; i < kTopkBins; i += 256) g1[i] = 0u;
+    }
   }
   const int base = blockIdx.x * kTopkChunk;
   if (base >= N || none) return;
@@ -290,10 +322,22 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
   uint32_t key[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) key[e] = ((t0 + e) >= LO && (t0 + e) < N) ? float_key(v[t0 + e]) : 0u;
-  // counts of all earlier chunks (gt in the low half is too narrow for a sum: add the halves apart)
+  // counts of all earlier chunks
   uint32_t pg = 0, pe = 0;
   const uint32_t* blk = a.blk + (size_t)b * a.nblk;
-  for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) { const uint32_t x = blk[i]; pg += x & 0xffffu; pe += x >> 16; }
+  if (TABLE) {
+    uint32_t d2;
+    find_digit<1024>(a.hist + ((size_t)b * 3 + 2) * kTopkBins, krem1, &d2, &need_eq, scan_lds);
+    d2 &= 1023u;
+    thr |= d2;
+    const uint16_t* row = a.table + (size_t)b * a.nblk * 1024 + d2;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) {
+      const uint32_t ge = row[(size_t)i * 1024], g = d2 == 1023u ? blk[i] : (uint32_t)row[(size_t)i * 1024 + 1];
+      pg += g; pe += ge - g;
+    }
+  } else {       // gt in the low half is too narrow for a sum: add the halves apart
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) { const uint32_t x = blk[i]; pg += x & 0xffffu; pe += x >> 16; }
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) { pg += __shfl_xor(pg, off); pe += __shfl_xor(pe, off); }
   if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = pg; red[1][threadIdx.x >> 6] = pe; }
@@ -731,9 +775,14 @@ hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
     return hipGetLastError();
   }
   hipLaunchKernelGGL(topk_hist1_kernel, grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(topk_hist2_kernel, grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(topk_count_kernel, grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(topk_emit_kernel, grid, dim3(256), 0, s, a);
+  if (a.nblk <= kTableChunks) {
+    hipLaunchKernelGGL(topk_hist2_kernel<true>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(topk_emit_kernel<true>, grid, dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(topk_hist2_kernel<false>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(topk_count_kernel, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(topk_emit_kernel<false>, grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 
