@@ -99,8 +99,8 @@ int32_t ts_workspace_bytes(const ts_problem* p, int32_t k, size_t* bytes);
 
 /* Clears a fresh workspace (launches a fill kernel on `stream`; safe under graph capture).  Must
  * run once before the first use of a workspace; the kernels leave it ready for the next call.
- * The radix-select histograms inside it must be zero when a selection starts and are zeroed again by the
- * kernels of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
+ * The radix-select histograms inside it must be zero when a selection starts (the third pass' one is cleared by the
+ * call that uses it) and are zeroed again by the kernels of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
  * an error after it has launched part of its kernels, or a stream is torn down between its launches, the
  * workspace is in an undefined state: call ts_workspace_init again before reusing it.  The call zeroes every
  * byte, so the next selection must start with its score pass (which it does anyway). */
@@ -148,8 +148,9 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
  * max_seq_len up to 8192: each sequence is ranked by one workgroup, in one launch, whatever the flags and the chunk.
  * Longer ones, flags: 0, or TS_TOPK_FLAT_VOTES.  By default (decode) the radix select runs as three launches whose last one
  * finishes each sequence on one workgroup: fast when few votes lie within a quarter octave of the k-th vote, as
- * with the peaked votes of Eq. 5, and slow (still exact) when most do.  TS_TOPK_FLAT_VOTES selects the five-launch
- * form whose time does not depend on the distribution; longer chunk problems (chunk > 1) always use it.
+ * with the peaked votes of Eq. 5, and slow (still exact) when most do.  TS_TOPK_FLAT_VOTES selects a form
+ * of four launches (five beyond 1048576 tokens) whose time does not depend on the distribution; longer chunk problems
+ * (chunk > 1) always use it.
  * TS_TOPK_VOTE_HIST: the votes were written by ts_soft_vote_ranked, which left the radix select's first histogram in
  * ws (see there): the pass that builds it is skipped (decode only; not for ts_topk_noalloc). */
 #define TS_TOPK_FLAT_VOTES 1
@@ -331,7 +332,7 @@ int32_t ts_debug_set_score_variant(int32_t variant, int32_t wg, int32_t run_tile
 int32_t ts_debug_set_codes_path(int32_t mfma, int32_t run_tiles);
 
 /* Tuning knob (process-wide, tests and benchmarks): five_pass = 1 makes ts_topk / ts_head_vote use the
- * five-pass radix select (three global histogram passes, count, emit) that otherwise serves flat votes and sequences
+ * radix select by passes over all votes (three global histogram passes, beyond 1048576 tokens a count, emit) that otherwise serves flat votes and sequences
  * beyond 16 Mi tokens; 0 (default) = up to 8192 tokens one workgroup per sequence, beyond that histogram pass, compaction
  * of the candidates, one finishing workgroup per sequence.  All give the same result.  Host only. */
 int32_t ts_debug_set_topk_path(int32_t five_pass);

@@ -104,18 +104,6 @@ __device__ __forceinline__ void find_digit_rep(const uint32_t* gh, uint32_t k_re
   __syncthreads();
 }
 
-// the replicated first histogram folded into histogram 0 and cleared: the five-pass form reads one copy
-__global__ __launch_bounds__(256) void topk_fold_rep_hist_kernel(TopkArgs a) {
-  const int b = blockIdx.y;
-  if (a.skip != nullptr && a.skip[b / a.heads] != 0) return;
-  const int i = blockIdx.x * 256 + threadIdx.x;         // gridDim.x * 256 == kTopkBins
-  uint32_t* rep = a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins;
-  uint32_t sum = 0;
-#pragma unroll
-  for (int r = 0; r < kBoundHistCopies; ++r) { sum += rep[r * kTopkBins + i]; rep[r * kTopkBins + i] = 0u; }
-  a.hist[((size_t)b * 3 + 0) * kTopkBins + i] = sum;
-}
-
 // The counting pass read all votes once more for a launch's latency.  ts_topk on flat votes, five launches and four: 20000 tokens 21.0
 // and 18.4 us, 131072 22.3 and 19.4, 8 x 262144 33.1 and 30.0, 1048576, the last length with the table, 39.0 and 36.5.  Beyond, the
 // emit pass' reads, a piece of the table for every pair of chunks, grow with the square of their number.
@@ -170,8 +158,9 @@ __global__ __launch_bounds__(256) void topk_hist0_kernel(TopkArgs a) {
   flush_hist(h, a.hist + ((size_t)b * 3 + 0) * kTopkBins, kTopkBins);
 }
 
-// pass 1: fix digit 0 from histogram 0, histogram the next 11 bits of the keys that carry it; histogram 2, which every
-// workgroup of the last call's emit may have read, is cleared for pass 2
+// pass 1: fix digit 0 from histogram 0 (or the vote kernel's copies of it, whose fold into one took a launch more), histogram
+// the next 11 bits of the keys that carry it; histogram 2, which every workgroup of the last call's emit may have read, is
+// cleared for pass 2
 __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   __shared__ uint32_t h[kTopkBins];
   __shared__ uint32_t lds[8];
@@ -186,7 +175,8 @@ __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   for (int i = threadIdx.x; i < kTopkBins; i += 256) h[i] = 0;
   const uint32_t k_eff = (uint32_t)min(a.k, N - LO);
   uint32_t d0, krem0;
-  find_digit<kTopkBins>(a.hist + ((size_t)b * 3 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
+  if (a.rep_hist != nullptr) find_digit_rep<kTopkBins>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins, k_eff, &d0, &krem0, lds);
+  else find_digit<kTopkBins>(a.hist + ((size_t)b * 3 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.state[b * 8 + ST_PREFIX0] = d0 << 21; a.state[b * 8 + ST_KREM0] = krem0; a.state[b * 8 + ST_KEFF] = k_eff;
   }
@@ -225,8 +215,13 @@ __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
   const uint32_t prefix1 = prefix0 | ((d1 & 2047u) << 10);
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) { a.state[b * 8 + ST_PREFIX1] = prefix1; a.state[b * 8 + ST_KREM1] = none ? 0u : krem1; }
-    uint32_t* g0 = a.hist + ((size_t)b * 3 + 0) * kTopkBins;
-    for (int i = threadIdx.x; i < kTopkBins; i += 256) g0[i] = 0u;
+    if (a.rep_hist != nullptr) {
+      uint4* g0 = reinterpret_cast<uint4*>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);
+      for (int i = threadIdx.x; i < kBoundHistCopies * kTopkBins / 4; i += 256) g0[i] = make_uint4(0u, 0u, 0u, 0u);
+    } else {
+      uint32_t* g0 = a.hist + ((size_t)b * 3 + 0) * kTopkBins;
+      for (int i = threadIdx.x; i < kTopkBins; i += 256) g0[i] = 0u;
+    }
   }
 #pragma unroll
   for (int i = 0; i < kTopkChunk / 256; ++i)
@@ -762,11 +757,8 @@ hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
     else hipLaunchKernelGGL((topk_final_kernel<8, FINAL_SHORT>), dim3(B), dim3(kFinalThreads), 0, s, a);
     return hipGetLastError();
   }
-  if (a.rep_hist == nullptr) {
+  if (a.rep_hist == nullptr)
     hipLaunchKernelGGL(topk_hist0_kernel, dim3(a.nblk < 128 ? a.nblk : 128, B), dim3(256), 0, s, a);
-  } else if (!short_path) {
-    hipLaunchKernelGGL(topk_fold_rep_hist_kernel, dim3(kTopkBins / 256, B), dim3(256), 0, s, a);
-  }
   if (short_path) {
     hipLaunchKernelGGL(topk_compact_kernel, grid, dim3(256), 0, s, a);
     // the list holds about k entries plus the few that share the k-th key's bin: one batch in the usual case

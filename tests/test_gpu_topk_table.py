@@ -82,3 +82,30 @@ def test_lengths_on_both_sides_of_the_line_share_a_workspace():
         for layer, n in ((long, 1048577), (short, 30000), (short, 30000), (long, 1048577)):
             print("shared workspace", kind, n, flush=True)
             _check(layer, [n], 500, [_votes(kind, n, rng)])
+
+
+@pytest.mark.parametrize("n,H,H_kv", [(8256, 32, 8), (8257, 32, 8), (8257, 16, 8), (20001, 28, 4)])
+def test_mean_query_selection_with_and_without_the_vote_launch_histogram(n, H, H_kv):
+    """select_mean_query on either side of its line, twice in a row, against the plain pair of calls on the same scores."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_02886_amd as ts
+    import workloads as W
+    from paper_2411_02886_amd.runtime import ChunkSelector, to_device
+    print("mean query", n, H, flush=True)
+    w = W.make_workload("mq", dtype=W.BF16, B=2, C=64, H=H, H_kv=H_kv, D=64, P=16, seq_lens=[n, 5000], k=300, seed=n + H)
+    sel = ChunkSelector.from_workload(w)
+    q = to_device(w.q)
+    got = []
+    for _ in range(2):
+        sel.idx.fill_(-7); sel.votes.fill_(-1.0)
+        sel.select_mean_query(q, 1.0)
+        got.append((sel.idx.clone(), sel.votes.clone(), sel.count.clone()))
+    m = sel._mq
+    ts.ts_paged_qk_scores(m["problem"], m["q_mean"], m["scores"], 1.0, None, m["ws"])
+    sel.votes.fill_(-1.0)
+    ts.ts_soft_vote(m["problem"], m["scores"], 1.0, m["row_stats"], sel.votes, None, m["ws"])
+    ts.ts_topk(m["problem"], sel.votes, sel.k, sel.idx, sel.count, None, m["ws"])
+    torch.cuda.synchronize()
+    for idx, votes, count in got:
+        assert torch.equal(idx, sel.idx) and torch.equal(votes, sel.votes) and torch.equal(count, sel.count)
