@@ -142,8 +142,8 @@ __global__ __launch_bounds__(kCwThreads, 1) void chunk_attn_wide_kernel(ChunkAtt
   }
   // The weights' exponents are one fma, c2 * score - reference.  Its exact product differs from the rounded one that the
   // reference came from by up to 2^-24 of the logit, and with logits of 2^31 that alone would over- or underflow the
-  // exponential.  A wave that meets such a reference rounds the logits first from then on: `factor` is 1 and every block takes
-  // the way of the masked ones, where the scores are multiplied.
+  // exponential.  A wave that meets such a reference rounds the logits first from then on: `factor` is 1, and the loop without masks
+  // ends after the second block of its pair; every later block takes the way of the masked ones, where the scores are multiplied.
   float factor = c2;
   int plain_below = cnt - kCwTile + 1;                          // tiles that begin below this need no look at their scores
   f32x16_t oacc[2][NBO];                                        // O^T: d = 32 * nb + 8 * (e / 4) + 4 * half + e % 4
@@ -358,6 +358,8 @@ __global__ __launch_bounds__(kCwThreads, 1) void chunk_attn_wide_kernel(ChunkAtt
       if (__builtin_expect(plain_below != INT_MIN && __builtin_amdgcn_ballot_w64(big) != 0, 0)) {
         factor = 1.f; plain_below = INT_MIN;
         round_logits(x);
+        // the loop without masks takes one more block as it is, whose scores are there already; a masked block rounds its own
+        if (CUR == 1 && SC && !decltype(masked)::value) round_logits(s[NXT]);
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) { exponent(i); power(i); pack(i); }

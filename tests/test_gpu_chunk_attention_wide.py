@@ -7,17 +7,19 @@ import numpy as np
 import pytest
 
 import workloads as W
+from rules_util import rules
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def _attend(C, H, H_kv, D, cached, n_init, spikes):
-    """One sequence whose `cached` tokens are all selected (or forced); spikes: {list position: logit of every query with that key}."""
+def _attend(C, H, H_kv, D, cached, n_init, spikes, sign=1.0):
+    """One sequence whose `cached` tokens are all selected (or forced); spikes: {list position: logit of every query with that key};
+    sign: of the softmax scale."""
     from paper_2411_02886_amd.runtime import ChunkSelector, to_device, to_host
     k = max(1, cached - n_init)
     w = W.make_workload("wide", dtype=W.BF16, B=1, C=C, H=H, H_kv=H_kv, D=D, P=16, seq_lens=[cached + C], k=k, seed=3 * cached + C)
-    sm = 1.0 / math.sqrt(D)
+    sm = sign / math.sqrt(D)
     slots = w.slots_of(0)
     if spikes:
         # query = a common direction plus a little noise across it: the spikes' logits are the same for all queries and exact
@@ -66,8 +68,9 @@ def test_key_lists_around_the_tiles(cached, C, H, H_kv, D):
     _attend(C, H, H_kv, D, cached, 0, {})
 
 
-# one split of 12 tiles; logits of the spikes against ordinary ones of a few units.  The last spike's is the largest by far,
-# so that one key decides where the logits are so large that their float rounding is not small
+# Logits of the spikes against ordinary ones of a few units.  160 queries of two heads are three row blocks, whose lists of 700 +
+# 64, 128 or 160 keys are cut into three splits of four, five and five tiles; a key group has every other one of them.  The last
+# spike's is the largest by far, so that one key decides where the logits are so large that their float rounding is not small.
 SPIKES = [{70: 30.0}, {200: 40.0}, {64 * 4 + 3: 60.0, 64 * 5 + 40: 90.0}, {0: 25.0, 64 * 7 + 33: 80.0}, {64 * 3 + 35: 2.0 ** 22},
           {64 * 2: 2.0 ** 21, 64 * 6 + 1: 2.0 ** 23}, {64 * 10 + 63: 50.0}]
 
@@ -77,5 +80,25 @@ SPIKES = [{70: 30.0}, {200: 40.0}, {64 * 4 + 3: 60.0, 64 * 5 + 40: 90.0}, {0: 25
 def test_references_raised_in_either_group_and_half(spikes, n_init, D):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    assert rules().rule_chunk_splits(160, 2, 1, D, 700 - n_init, n_init) == 3
     print("wide chunk attention, spikes", spikes, n_init, D, flush=True)
     _attend(160, 2, 1, D, 700, n_init, spikes)
+
+
+# The line from which logits are rounded (2^20, base two) is passed in the second half of a tile in the loop without masks, and
+# the next block, the first half of the key group's next tile, whose scores are there by then, holds a large one too: a smaller,
+# an equal, a larger one.  A key group's first tile is left out (its two halves are looked at together).  700 keys, as above: the even
+# group of the first split has tiles 0, 2, 4, of the second 5, 7, 9; 3100 keys, eight splits of seven tiles: the odd one 1, 3, 5.
+LARGE = [(700, {64 * 2 + 37: 2.0 ** 22, 64 * 4 + 1: 2.0 ** 21}), (700, {64 * 2 + 37: 2.0 ** 22, 64 * 4 + 1: 2.0 ** 22}),
+         (700, {64 * 2 + 63: 2.0 ** 21, 64 * 4 + 31: 2.0 ** 22}), (700, {64 * 7 + 32: 2.0 ** 23, 64 * 9: 2.0 ** 22}),
+         (3100, {64 * 3 + 35: 2.0 ** 21, 64 * 5 + 3: 2.0 ** 20 * 1.5}), (3100, {64 * 3 + 32: 2.0 ** 22, 64 * 5 + 31: 2.0 ** 22})]
+
+
+@pytest.mark.parametrize("cached,spikes", LARGE, ids=range(len(LARGE)))
+@pytest.mark.parametrize("D,sign", [(128, 1.0), (128, -1.0), (64, 1.0)])
+def test_logits_are_rounded_from_the_block_on_that_passes_the_line(cached, spikes, D, sign):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    assert rules().rule_chunk_splits(160, 2, 1, D, cached, 0) == (3 if cached == 700 else 8)
+    print("wide chunk attention, large logits", cached, spikes, D, sign, flush=True)
+    _attend(160, 2, 1, D, cached, 0, spikes, sign=sign)
