@@ -142,22 +142,19 @@ class DecodeLayer:
         ts.ts_sparse_paged_attn(self.problem, q, self.idx, self.k, self.count, sm_scale, self.out, self.lse, self.ws)
 
     def compact_form_pays(self) -> bool:
-        """Which form of the Eq. 5 selection to take.  The compact form saves the write of the fp32 score matrix and part of its
-        reading, which goes with the matrix' size; it pays with a launch and with the candidates' products in double precision,
-        which go with batch * k * heads * head size.  A sequence that is long by itself takes it always: its share of the small
-        launches is small.  Over 220 steps and cached runs (1 to 64 sequences of 1 to 1048576 tokens, on MI355X) this line is
-        0.4 % above the faster form on average, 13 % at most; by the matrices' size alone, with the line at 24 MiB, 2.6 % and 37 %.
-        One sequence of 131072 tokens of 32 heads, 16 MiB: 81.8 us five-call, 84.0 compact; one of 163711 of 28 heads, 17.5 MiB: 75.5
-        and 69.3; one of 1048576, k 4096, 112 MiB: 254.6 and 228.9; 32 of up to 16001 tokens of 32 heads, k 2048, 61 MiB:
-        206.5 and 221.8; 32 of up to 8180 of 64 heads, k 2154, 64 MiB: 194.5 and 259.3."""
-        matrix = self.max_seq_len * self.H * 4 / 2**20
-        products = self.B * min(self.k, self.max_seq_len) * self.H * self.D / 1e6
-        return matrix > 16.5 or self.B * matrix > 22.0 + 0.25 * products
+        """Which form of the Eq. 5 selection compact=None takes: compact, which never writes the fp32 score matrix, where the
+        matrices of the batch are larger than 24 MiB together.  One sequence, k 2048 (us on MI355X, five-call, five-call with the
+        ranked vote, compact): 32 heads of 128, 16 MiB 89, 85, 88; 18 MiB 96, 93, 102; 20 MiB 114, 111, 106; 23.9 MiB 123, 119, 113; 28
+        heads, 17 MiB 75, 72, 72; 23.9 MiB 90, 87, 86; 64 heads, 17 MiB 76, 75, 82; 23.9 MiB 81, 80, 85.  The line does not follow the
+        faster form of each shape: above it the candidates are ranked by votes of double-precision products, below it by votes of
+        float scores, and no call is to lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k
+        2048: 206.5 five-call, 221.8 compact).  A caller who prefers the time passes compact=False."""
+        return self.B * self.max_seq_len * self.H * 4 > 24 * 2**20
 
     def step(self, q, *, theta=None, score_scale=1.0, sm_scale=None, compact=False, fused_check=False, ranked_vote=False):
         """One decode step: Selection Cache check (when theta is given), selection on a miss, sparse
-        attention.  No host synchronisation.  compact: the form of the selection (None = whichever is the faster one
-        at this size, see compact_form_pays).  fused_check: the check runs inside the score launch (one launch
+        attention.  No host synchronisation.  compact: the form of the selection (None = by the size of the score
+        matrices, see compact_form_pays).  fused_check: the check runs inside the score launch (one launch
         less; self.cached_q / self.first are swapped with their second copies after the step)."""
         sm = sm_scale if sm_scale is not None else 1.0 / float(np.sqrt(self.D))
         if compact is None:

@@ -1,4 +1,6 @@
-"""Which form of the selection a decode step takes (host rule): the sides of both lines, and the sizes it was measured at."""
+"""Which form of the selection a decode step takes (host rule): by the bytes of the batch's score matrices and nothing else.  Above
+the line the candidates are ranked by votes of double-precision products; a call that has them keeps them whatever k and the
+heads are."""
 from types import SimpleNamespace
 
 import pytest
@@ -9,13 +11,19 @@ from paper_2411_02886_amd.runtime import DecodeLayer
 
 @pytest.mark.parametrize("B,n,H,D,k,compact", [
     (1, 131072, 32, 128, 2048, False),      # 16 MiB
-    (1, 163711, 28, 128, 903, True),        # 17.5 MiB in one sequence
+    (1, 139264, 32, 128, 2048, False),      # 17 MiB: 93 us, compact 101
+    (1, 69632, 64, 128, 2048, False),       # 17 MiB: 76 us, compact 82
+    (1, 196608, 32, 128, 2048, False),      # 24 MiB, the line itself
+    (1, 196609, 32, 128, 2048, True),
     (1, 1048576, 28, 128, 4096, True),
     (1, 4096, 8, 64, 256, False),
-    (32, 16001, 32, 128, 2048, False),      # 62.5 MiB, 268 million products
-    (32, 16001, 32, 128, 256, True),        # the same with 34 million
+    (32, 16001, 32, 128, 2048, True),       # 62.5 MiB: short sequences with a large k, too
+    (32, 16001, 32, 128, 256, True),
+    (32, 8180, 64, 128, 2154, True),
+    (4, 40009, 64, 128, 2048, True),
+    (8, 65536, 32, 128, 2048, True),
     (4, 198163, 32, 64, 2195, True),
-    (16, 500, 128, 128, 1 << 20, False),    # k beyond the sequence counts as the sequence
+    (16, 500, 128, 128, 1 << 20, False),
 ])
 def test_form(B, n, H, D, k, compact):
     assert DecodeLayer.compact_form_pays(SimpleNamespace(B=B, max_seq_len=n, H=H, D=D, k=k)) is compact
