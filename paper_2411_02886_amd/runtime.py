@@ -143,13 +143,16 @@ class DecodeLayer:
 
     def compact_form_pays(self) -> bool:
         """Which form of the Eq. 5 selection compact=None takes: compact, which never writes the fp32 score matrix, where the
-        matrices of the batch are larger than 24 MiB together.  One sequence, k 2048 (us on MI355X, five-call, five-call with the
-        ranked vote, compact): 32 heads of 128, 16 MiB 89, 85, 88; 18 MiB 96, 93, 102; 20 MiB 114, 111, 106; 23.9 MiB 123, 119, 113; 28
-        heads, 17 MiB 75, 72, 72; 23.9 MiB 90, 87, 86; 64 heads, 17 MiB 76, 75, 82; 23.9 MiB 81, 80, 85.  The line does not follow the
-        faster form of each shape: above it the candidates are ranked by votes of double-precision products, below it by votes of
-        float scores, and no call is to lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k
-        2048: 206.5 five-call, 221.8 compact).  A caller who prefers the time passes compact=False."""
-        return self.B * self.max_seq_len * self.H * 4 > 24 * 2**20
+        matrices of the batch are larger than 24 MiB together, and for one sequence of up to 32 heads from 20 MiB on (us on MI355X,
+        five-call, five-call with the ranked vote, compact, k 2048 but for the last: 32 heads over 8, head size 128, 18 MiB 96, 93,
+        102; 19.5 MiB 103, 100, 104; 20 MiB 113, 110, 108; 23 MiB 120, 116, 111; 32 over 4, 18 MiB 72, 69, 71; 20 MiB 79, 77, 73;
+        12 over 2, 18 MiB 83, 79, 85; 20 MiB 89, 85, 87; 64 over 8, 17 MiB 76, 75, 82; 23.9 MiB 81, 80, 85; 40 over 8, k 1024, 20 MiB
+        91, 89, 95; 23.9 MiB 102, 100, 100).  Above 24 MiB the line does not follow the faster form of each shape: the compact form
+        ranks the candidates by votes of double-precision products, the five-call form by votes of float scores, and no call is to
+        lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k 2048: 206.5 five-call, 221.8
+        compact).  A caller who prefers the time passes compact=False."""
+        mib = self.B * self.max_seq_len * self.H * 4 / 2**20
+        return mib > 24 or (self.B == 1 and self.H <= 32 and mib > 19.75)
 
     def step(self, q, *, theta=None, score_scale=1.0, sm_scale=None, compact=False, fused_check=False, ranked_vote=False):
         """One decode step: Selection Cache check (when theta is given), selection on a miss, sparse

@@ -1,6 +1,5 @@
-"""Which form of the selection a decode step takes (host rule): by the bytes of the batch's score matrices and nothing else.  Above
-the line the candidates are ranked by votes of double-precision products; a call that has them keeps them whatever k and the
-heads are."""
+"""Which form of the selection a decode step takes (host rule).  Above 24 MiB of score matrices the candidates are ranked by votes
+of double-precision products whatever k, the heads and the batch are; below, one sequence is from where that is the faster form."""
 from types import SimpleNamespace
 
 import pytest
@@ -13,8 +12,12 @@ from paper_2411_02886_amd.runtime import DecodeLayer
     (1, 131072, 32, 128, 2048, False),      # 16 MiB
     (1, 139264, 32, 128, 2048, False),      # 17 MiB: 93 us, compact 101
     (1, 69632, 64, 128, 2048, False),       # 17 MiB: 76 us, compact 82
-    (1, 196608, 32, 128, 2048, False),      # 24 MiB, the line itself
-    (1, 196609, 32, 128, 2048, True),
+    (1, 159744, 32, 128, 2048, False),      # 19.5 MiB: 103 us, compact 104
+    (1, 163840, 32, 128, 2048, True),       # 20 MiB: 113 us, compact 108
+    (1, 97894, 64, 128, 2048, False),       # 23.9 MiB: 81 us, compact 85
+    (2, 98304, 32, 128, 2048, False),       # 24 MiB, the line of a batch itself
+    (2, 98305, 32, 128, 2048, True),
+    (1, 98305, 64, 128, 2048, True),
     (1, 1048576, 28, 128, 4096, True),
     (1, 4096, 8, 64, 256, False),
     (32, 16001, 32, 128, 2048, True),       # 62.5 MiB: short sequences with a large k, too
