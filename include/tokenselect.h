@@ -99,8 +99,8 @@ int32_t ts_workspace_bytes(const ts_problem* p, int32_t k, size_t* bytes);
 
 /* Clears a fresh workspace (launches a fill kernel on `stream`; safe under graph capture).  Must
  * run once before the first use of a workspace; the kernels leave it ready for the next call.
- * The radix-select histograms inside it must be zero when a selection starts (the third pass' one is cleared by the
- * call that uses it) and are zeroed again by the kernels of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
+ * The radix-select histograms inside it must be zero when a selection starts and are
+ * zeroed again by the kernels of every ts_topk / ts_topk_exact / ts_head_vote call.  If one of those calls (or ts_soft_vote_bounds) returns
  * an error after it has launched part of its kernels, or a stream is torn down between its launches, the
  * workspace is in an undefined state: call ts_workspace_init again before reusing it.  The call zeroes every
  * byte, so the next selection must start with its score pass (which it does anyway). */

@@ -84,8 +84,8 @@ static int32_t check_problem(const ts_problem* p) {
 // process ends; the name below is a host-side stand-in, the device address comes from hipGetSymbolAddress
 constexpr int kNoAllocMaxBatch = 16;
 constexpr int kNoAllocMaxChunks = 256;                       // 2048-token chunks over the whole batch: 524288 tokens
-constexpr size_t kNoAllocHist = 0;                           // uint32 [16][3][2048]
-constexpr size_t kNoAllocState = kNoAllocHist + (size_t)kNoAllocMaxBatch * 3 * kTopkBins * 4;
+constexpr size_t kNoAllocHist = 0;                           // uint32 [16][2][2048]
+constexpr size_t kNoAllocState = kNoAllocHist + (size_t)kNoAllocMaxBatch * 2 * kTopkBins * 4;
 constexpr size_t kNoAllocBlk = kNoAllocState + 1024;         // uint32 [256]
 constexpr size_t kNoAllocList = kNoAllocBlk + 1024;          // uint2 [256][2048]
 constexpr size_t kNoAllocBytes = kNoAllocList + (size_t)kNoAllocMaxChunks * kTopkChunk * 8;
@@ -527,7 +527,7 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
   a.k = k; a.max_seq_len = p->max_seq_len; a.nblk = nblk; a.heads = 1; a.one_wg = !g_topk_five_pass;
   // the array keeps whatever the last call on this GPU left: the histograms must start at zero (a fill kernel,
   // not a memset node: callers may be under graph capture)
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(24), dim3(256), 0, (hipStream_t)stream, a.hist, (size_t)p->batch * 3 * kTopkBins);
+  hipLaunchKernelGGL(fill_zero_kernel, dim3(24), dim3(256), 0, (hipStream_t)stream, a.hist, (size_t)p->batch * 2 * kTopkBins);
   if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
   return launch_topk(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
@@ -554,7 +554,7 @@ static HeadVoteLayout head_vote_layout(const ts_problem* p) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   l.st = take(V * (size_t)p->max_seq_len * 4);
-  l.hist = take(V * 3 * kTopkBins * 4);
+  l.hist = take(V * 2 * kTopkBins * 4);
   l.state = take(V * 8 * 4);
   l.blk = take(V * (size_t)l.nblk * 4);
   l.list = take(V * (size_t)l.nblk * kTopkChunk * 8);

@@ -155,12 +155,12 @@ __global__ __launch_bounds__(256) void topk_hist0_kernel(TopkArgs a) {
       if (valid[i]) atomicAdd(&h[key[i] >> 21], 1u);
   }
   __syncthreads();
-  flush_hist(h, a.hist + ((size_t)b * 3 + 0) * kTopkBins, kTopkBins);
+  flush_hist(h, a.hist + ((size_t)b * 2 + 0) * kTopkBins, kTopkBins);
 }
 
 // pass 1: fix digit 0 from histogram 0 (or the vote kernel's copies of it, whose fold into one took a launch more), histogram
-// the next 11 bits of the keys that carry it; histogram 2, which every workgroup of the last call's emit may have read, is
-// cleared for pass 2
+// the next 11 bits of the keys that carry it; histogram 2, which lies in scratch memory because all of the emit pass' workgroups
+// may read it, so that none can leave it zeroed, is cleared for pass 2
 __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   __shared__ uint32_t h[kTopkBins];
   __shared__ uint32_t lds[8];
@@ -176,19 +176,19 @@ __global__ __launch_bounds__(256) void topk_hist1_kernel(TopkArgs a) {
   const uint32_t k_eff = (uint32_t)min(a.k, N - LO);
   uint32_t d0, krem0;
   if (a.rep_hist != nullptr) find_digit_rep<kTopkBins>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins, k_eff, &d0, &krem0, lds);
-  else find_digit<kTopkBins>(a.hist + ((size_t)b * 3 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
+  else find_digit<kTopkBins>(a.hist + ((size_t)b * 2 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.state[b * 8 + ST_PREFIX0] = d0 << 21; a.state[b * 8 + ST_KREM0] = krem0; a.state[b * 8 + ST_KEFF] = k_eff;
   }
   if (blockIdx.x == 0) {
-    uint32_t* g2 = a.hist + ((size_t)b * 3 + 2) * kTopkBins;
+    uint32_t* g2 = a.hist2 + (size_t)b * 1024;
     for (int i = threadIdx.x; i < 1024; i += 256) g2[i] = 0u;
   }
 #pragma unroll
   for (int i = 0; i < kTopkChunk / 256; ++i)
     if (valid[i] && (key[i] >> 21) == d0) atomicAdd(&h[(key[i] >> 10) & 2047u], 1u);
   __syncthreads();
-  flush_hist(h, a.hist + ((size_t)b * 3 + 1) * kTopkBins, kTopkBins);
+  flush_hist(h, a.hist + ((size_t)b * 2 + 1) * kTopkBins, kTopkBins);
 }
 
 // pass 2: fix digit 1, histogram the last 10 bits; histogram 0 is no longer needed and is cleared.  TABLE: also the chunk's
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
   for (int i = threadIdx.x; i < 1024; i += 256) h[i] = 0;
   const uint32_t prefix0 = a.state[b * 8 + ST_PREFIX0], krem0 = a.state[b * 8 + ST_KREM0];
   uint32_t d1, krem1;
-  find_digit<kTopkBins>(a.hist + ((size_t)b * 3 + 1) * kTopkBins, krem0, &d1, &krem1, lds);
+  find_digit<kTopkBins>(a.hist + ((size_t)b * 2 + 1) * kTopkBins, krem0, &d1, &krem1, lds);
   // an empty selection keeps an impossible prefix so that nothing matches below
   const bool none = krem0 == 0;
   const uint32_t prefix1 = prefix0 | ((d1 & 2047u) << 10);
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
       uint4* g0 = reinterpret_cast<uint4*>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);
       for (int i = threadIdx.x; i < kBoundHistCopies * kTopkBins / 4; i += 256) g0[i] = make_uint4(0u, 0u, 0u, 0u);
     } else {
-      uint32_t* g0 = a.hist + ((size_t)b * 3 + 0) * kTopkBins;
+      uint32_t* g0 = a.hist + ((size_t)b * 2 + 0) * kTopkBins;
       for (int i = threadIdx.x; i < kTopkBins; i += 256) g0[i] = 0u;
     }
   }
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void topk_hist2_kernel(TopkArgs a) {
   for (int i = 0; i < kTopkChunk / 256; ++i)
     if (valid[i] && !none && (key[i] >> 10) == (prefix1 >> 10)) atomicAdd(&h[key[i] & 1023u], 1u);
   __syncthreads();
-  flush_hist(h, a.hist + ((size_t)b * 3 + 2) * kTopkBins, 1024);
+  flush_hist(h, a.hist2 + (size_t)b * 1024, 1024);
   if (TABLE) {
     uint32_t gt = 0;
 #pragma unroll
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void topk_count_kernel(TopkArgs a) {
   load_keys(a.votes + (size_t)b * a.max_seq_len, base, LO, N, key, valid);
   const uint32_t prefix1 = a.state[b * 8 + ST_PREFIX1], krem1 = a.state[b * 8 + ST_KREM1];
   uint32_t d2, need_eq;
-  find_digit<1024>(a.hist + ((size_t)b * 3 + 2) * kTopkBins, krem1, &d2, &need_eq, lds);
+  find_digit<1024>(a.hist2 + (size_t)b * 1024, krem1, &d2, &need_eq, lds);
   const bool none = krem1 == 0;
   const uint32_t thr = none ? 0xffffffffu : (prefix1 | (d2 & 1023u));
   if (none) need_eq = 0;
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void topk_count_kernel(TopkArgs a) {
     if (threadIdx.x == 0) {
       a.state[b * 8 + ST_THR] = thr; a.state[b * 8 + ST_NEED_EQ] = need_eq;
     }
-    uint32_t* g1 = a.hist + ((size_t)b * 3 + 1) * kTopkBins;
+    uint32_t* g1 = a.hist + ((size_t)b * 2 + 1) * kTopkBins;
     for (int i = threadIdx.x; i < kTopkBins; i += 256) g1[i] = 0u;
   }
   uint32_t gt = 0, eq = 0;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
       if (threadIdx.x == 0) a.count[b] = k_eff;
     }
     if (TABLE) {
-      uint32_t* g1 = a.hist + ((size_t)b * 3 + 1) * kTopkBins;
+      uint32_t* g1 = a.hist + ((size_t)b * 2 + 1) * kTopkBins;
       for (int i = threadIdx.x; i < kTopkBins; i += 256) g1[i] = 0u;
     }
   }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
   const uint32_t* blk = a.blk + (size_t)b * a.nblk;
   if (TABLE) {
     uint32_t d2;
-    find_digit<1024>(a.hist + ((size_t)b * 3 + 2) * kTopkBins, krem1, &d2, &need_eq, scan_lds);
+    find_digit<1024>(a.hist2 + (size_t)b * 1024, krem1, &d2, &need_eq, scan_lds);
     d2 &= 1023u;
     thr |= d2;
     const uint16_t* row = a.table + (size_t)b * a.nblk * 1024 + d2;
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(TopkArgs a) {
   }
   uint32_t d0, krem0;
   if (a.rep_hist != nullptr) find_digit_rep<kTopkBins>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins, k_eff, &d0, &krem0, lds);
-  else find_digit<kTopkBins>(a.hist + ((size_t)b * 3 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
+  else find_digit<kTopkBins>(a.hist + ((size_t)b * 2 + 0) * kTopkBins, k_eff, &d0, &krem0, lds);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.state[b * 8 + ST_PREFIX0] = d0 << 21; a.state[b * 8 + ST_KREM0] = krem0; a.state[b * 8 + ST_KEFF] = k_eff;
   }
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
     uint4* g0 = reinterpret_cast<uint4*>(a.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);
     for (int i = tid; i < kBoundHistCopies * kTopkBins / 4; i += kFinalThreads) g0[i] = make_uint4(0u, 0u, 0u, 0u);
   } else {     // histogram 0 has been consumed by the compact pass: leave it zeroed for the next call
-    uint32_t* g0 = a.hist + ((size_t)b * 3 + 0) * kTopkBins;
+    uint32_t* g0 = a.hist + ((size_t)b * 2 + 0) * kTopkBins;
     for (int i = tid; i < kTopkBins; i += kFinalThreads) g0[i] = 0u;
   }
   uint32_t total;
@@ -744,7 +744,10 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
   }
 }
 
-hipError_t launch_topk(const TopkArgs& a, int B, hipStream_t s) {
+hipError_t launch_topk(const TopkArgs& args, int B, hipStream_t s) {
+  TopkArgs a = args;
+  // behind the table, in the list's memory: 2 of its 16 KiB a chunk and 4 KiB a sequence
+  a.hist2 = reinterpret_cast<uint32_t*>(a.table + (size_t)B * a.nblk * 1024);
   dim3 grid(a.nblk, B);
   const bool short_path = a.list != nullptr && a.nblk <= kFinalMaxBlk;
   static_assert(kTopkOneWg == kFinalThreads * 8, "8 votes per thread");

@@ -85,7 +85,7 @@ inline int eval_workgroups(int batch, int max_seq_len, int k) {
 
 // ---------------------------------------------------------------- workspace layout (host + device)
 struct WsLayout {
-  size_t topk_hist;        // uint32 [B][3][kTopkBins] : one histogram per radix pass (must start zeroed)
+  size_t topk_hist;        // uint32 [B][2][kTopkBins] : histograms of the first two radix passes (must start zeroed)
   size_t bound_hist;       // uint32 [B][kBoundHistCopies][kTopkBins] : compact selection, histogram of the vote lower bounds
                            // (must start zeroed too; decode only)
   size_t topk_state;       // uint32 [B][8] : digits and remaining ranks fixed so far
@@ -164,7 +164,7 @@ inline WsLayout ws_layout(const ts_problem* p, int k) {
   w.attn_nsplit = (k + p->num_initial + p->num_local + kAttnChunk - 1) / kAttnChunk;   // forced tokens join the list
   if (w.attn_nsplit < 1) w.attn_nsplit = 1;
   // the histograms come first: they are the part that must start (and is left) zeroed
-  w.topk_hist = take(B * 3 * kTopkBins * 4);
+  w.topk_hist = take(B * 2 * kTopkBins * 4);
   if (p->chunk == 1) w.bound_hist = take(B * kBoundHistCopies * kTopkBins * 4);
   w.topk_state = take(B * 8 * 4);
   w.hdr = take(B * 8 * 4);

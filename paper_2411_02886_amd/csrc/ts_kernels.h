@@ -78,11 +78,12 @@ struct TopkArgs {
   const uint8_t* skip;
   int32_t* idx;
   int32_t* count;
-  uint32_t* hist;       // [B][3][kTopkBins]
+  uint32_t* hist;       // [B][2][kTopkBins]: zero when the call starts and when it ends
   uint32_t* state;      // [B][8]
   uint32_t* blk;        // [B][nblk]
   uint2* list;          // [B][nblk][kTopkChunk] (key, token) entries of the short path; nullptr = the form that passes over all votes
   uint16_t* table;      // [B][nblk][1024] of that form, in the list's memory
+  uint32_t* hist2;      // [B][1024] of that form, behind the table: its third histogram (set by launch_topk)
   int k, max_seq_len, nblk;
   int one_wg;           // sequences that fit one workgroup's registers may be ranked by it alone (0: a tuning knob asks for the passes)
   int heads;            // virtual sequences per real one (Eq. 4: one per head over transposed scores); 1 = plain

@@ -25,6 +25,7 @@ def rules():
         L = ctypes.CDLL(so)
     L.rule_attn_streams.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     L.rule_stream_span.argtypes = [ctypes.c_long, ctypes.c_int]
+    L.rule_zeroed_bytes.restype = ctypes.c_long
     return L
 
 

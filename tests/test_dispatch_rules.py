@@ -76,3 +76,9 @@ def test_every_streamed_call_has_room_for_its_splits():
         span = L.rule_stream_span(pairs, total)
         assert 32 <= span <= 3584 and span % 32 == 0, (pairs, total, span)
         assert (total + span - 1) // span <= (total + 63) // 64, (pairs, total, span)
+
+
+def test_flat_votes_scratch_fits_the_lists_memory():
+    for batch in (1, 2, 7, 300, 65535):
+        for n in (1, 2048, 2049, 8193, 1048576, 1048577):
+            assert rules().rule_topk_scratch_fits(batch, n), (batch, n)

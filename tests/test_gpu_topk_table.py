@@ -84,6 +84,21 @@ def test_lengths_on_both_sides_of_the_line_share_a_workspace():
             _check(layer, [n], 500, [_votes(kind, n, rng)])
 
 
+@pytest.mark.parametrize("lens", [[20000, 0, 9000], [1048576], [1048577, 5]])
+def test_histograms_are_zero_again_after_the_call(lens):
+    """All of the workspace up to its state words: a call for a smaller batch has other histograms there."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from rules_util import rules
+    print("zero again", lens, flush=True)
+    rng = np.random.default_rng(11)
+    layer = _layer(lens, 300)
+    for kind in KINDS:
+        _check(layer, lens, 300, [_votes(kind, n, rng) if n else np.zeros(0, np.float32) for n in lens])
+        zeroed = layer.ws[:rules().rule_zeroed_bytes(len(lens), max(lens)) // 4]
+        assert zeroed.numel() >= len(lens) * 10 * 2048 and not zeroed.any(), kind
+
+
 @pytest.mark.parametrize("n,H,H_kv", [(8256, 32, 8), (8257, 32, 8), (8257, 16, 8), (20001, 28, 4)])
 def test_mean_query_selection_with_and_without_the_vote_launch_histogram(n, H, H_kv):
     """select_mean_query on either side of its line, twice in a row, against the plain pair of calls on the same scores."""
