@@ -42,9 +42,10 @@ inline int stream_span(long pairs, int total) {
 // bf16: whether the attention streams long runs (sparse_attn_stream.hip) instead of taking 64-token chunks, `wgs` of them
 // (sparse_attn_decode.hip).  The more query heads a KV head has, the more the vector kernel has to do per row, and the
 // earlier the line.  Three heads and more: a list that is one run needs no merge, and streaming it is the faster way whatever
-// the rest (73 shapes of 1 to 21 sequences, 2 to 2016 chunks: 1.12 to 2.24 times; us, chunks and streamed: H 8/2, D 64, 1 x 256
-// tokens 9.2 and 5.9; H 24/8, D 64, 15 x 287 10.0 and 6.9; H 64/8, D 128, 21 x 748 33.6 and 15.0); fewer than eight pairs of lists
-// beyond 256 entries are left to the chunks all the same, whose behaviour at the ends of the number range is checked there.  With splits it starts later and merges, which short calls feel
+// the rest (73 shapes of 1 to 21 sequences, 2 to 2016 chunks: 1.12 to 2.24 times, 54 of one to seven pairs and 257 to 300 entries:
+// 1.09 to 1.26; us, chunks and streamed: H 8/2, D 64, 1 x 256 tokens 9.2 and 5.9, 3 x 300 7.3 and 5.8; H 16/4, D 128, 1 x 300 8.1 and
+// 7.3; H 24/8, D 64, 15 x 287 10.0 and 6.9; H 64/8, D 128, 21 x 748 33.6 and 15.0; the log-sum-exp's error against 64 bits 1.3 to
+// 1.9e-7 instead of 1.9 to 3.1e-7, the output's own rounding in both).  With splits it starts later and merges, which short calls feel
 // (74 shapes; us, just below and above the lines): H 64/8, D 128, 1 x 1429 9.7 and 10.0, 3 x 915 11.8 and 10.0; H 28/4, D 128, 2 x
 // 2228 11.2 and 12.1, 10 x 679 12.4 and 10.4; H 40/8, D 128, 1 x 3072 10.3 and 12.1, 6 x 1565 16.3 and 13.2; H 32/8, D 128, 2 x
 // 1291 9.6 and 11.0, 3 x 3385 15.8 and 14.1; D 64, 3 x 3055 11.6 and 11.8, 2 x 5637 13.3 and 11.6; H 24/8, D 64, 3 x 3636 10.8 and
@@ -55,7 +56,7 @@ inline int stream_span(long pairs, int total) {
 // also fill the rounds (H 16/16, D 128, 700 tokens: 480 pairs 35 and 33, 528 pairs in their three rounds 39 and 44).
 inline bool attn_streams(int G, int D, long pairs, int total) {
   const long wgs = (total + kAttnChunk - 1) / kAttnChunk * pairs;
-  if (G >= 3) return (stream_span(pairs, total) >= total && (total <= 256 || pairs >= 8)) || wgs >= (G >= 7 ? 352 : G >= 5 ? 768 : G == 3 ? 1536 : D == 128 ? 1152 : 1280);
+  if (G >= 3) return stream_span(pairs, total) >= total || wgs >= (G >= 7 ? 352 : G >= 5 ? 768 : G == 3 ? 1536 : D == 128 ? 1152 : 1280);
   if (wgs < 4096) return false;
   if (wgs >= (D == 128 ? 10240 : 22528)) return true;
   if (total > (G == 2 ? 1536 : 1024) || stream_span(pairs, total) < total) return false;

@@ -59,9 +59,9 @@ def test_candidates_are_evaluated_by_a_full_chip_whatever_k(batch, k):
 
 @pytest.mark.parametrize("G,D,pairs,total,streamed", [
     # three heads and more, us in chunks and streamed: lists of one run ...
-    (4, 64, 2, 256, 1), (4, 64, 2, 300, 0), (6, 128, 2, 16, 1), (8, 128, 168, 748, 1), (3, 64, 120, 287, 1), (4, 128, 64, 277, 1),
+    (4, 64, 2, 256, 1), (4, 64, 2, 300, 1), (3, 64, 1, 257, 1), (6, 128, 2, 16, 1), (8, 128, 168, 748, 1), (3, 64, 120, 287, 1), (4, 128, 64, 277, 1),
     # ... and the two sides of the lines with splits
-    (8, 128, 8, 1429, 0), (8, 128, 24, 915, 1), (7, 128, 8, 2228, 0), (7, 128, 40, 679, 1), (5, 128, 8, 3072, 0), (5, 128, 48, 1565, 1),
+    (4, 64, 2, 352, 0), (8, 128, 1, 352, 0), (8, 128, 8, 1429, 0), (8, 128, 24, 915, 1), (7, 128, 8, 2228, 0), (7, 128, 40, 679, 1), (5, 128, 8, 3072, 0), (5, 128, 48, 1565, 1),
     (4, 128, 16, 1291, 0), (4, 128, 24, 3385, 1), (4, 64, 24, 3055, 0), (4, 64, 16, 5637, 1), (3, 64, 24, 3636, 0), (3, 64, 104, 960, 1)])
 def test_short_calls_stream_from_their_own_lines_on(G, D, pairs, total, streamed):
     assert rules().rule_attn_streams(G, D, pairs, total) == streamed

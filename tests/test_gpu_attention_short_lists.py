@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("H,H_kv,D,lens,k,ni,nl,streamed", [
     (8, 2, 64, [5], 1, 0, 0, True), (8, 2, 64, [900], 31, 0, 0, True), (12, 2, 128, [900], 32, 0, 0, True),
     (28, 4, 128, [900], 33, 0, 0, True), (32, 8, 128, [900, 40], 96, 4, 29, True), (24, 8, 64, [700, 0, 17], 128, 0, 0, True),
-    (8, 2, 64, [900], 256, 0, 0, True), (8, 2, 64, [900], 257, 0, 0, False), (64, 8, 128, [900], 257, 0, 0, True),
+    (8, 2, 64, [900], 256, 0, 0, True), (8, 2, 64, [900], 257, 0, 0, True), (3, 1, 64, [900, 300, 0], 300, 0, 0, True), (28, 4, 128, [900], 320, 0, 0, True),
+    (8, 2, 64, [900], 352, 0, 0, False), (64, 8, 128, [900], 257, 0, 0, True),
     (64, 8, 128, [2000] * 3, 1000, 0, 0, True), (28, 4, 128, [2500] * 10, 679, 0, 0, True), (40, 8, 128, [1800] * 6, 1565, 0, 0, True)])
 def test_short_lists(H, H_kv, D, lens, k, ni, nl, streamed):
     if not torch.cuda.is_available():
