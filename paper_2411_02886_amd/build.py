@@ -31,6 +31,7 @@ FILE_FLAGS = {"sparse_attn_chunk_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 def _deps():
     hs = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
     hs.append(os.path.join(ROOT, "include", "tokenselect.h"))
+    hs.append(os.path.abspath(__file__))                     # the flags
     return hs
 
 
