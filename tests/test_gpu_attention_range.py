@@ -94,20 +94,21 @@ def test_large_logits(gpu, form, exponent, sign):
     assert np.abs(lse - ref_lse[:, None]).max() <= 2.0 ** -22 * np.abs(ref_lse).max()
 
 
-# exponent of V's elements: weights of at most 1 over 300 to 4096 keys fit a float.  The chunk form lets a weight grow to 2^16
-# before it raises its reference, so the 2^19 of the test do not stand, and neither do the values come closer than that
-LARGE_VALUES = {"chunks": 118, "streamed-one-run": 118, "streamed": 118, "streamed-splits": 115, "chunk-form": 108, "chunk-form-splits": 108}
+# Exponent of V's elements: weights of at most 1 over 300 to 4096 keys fit a float.  The chunk forms raise their reference at a weight of
+# 2, so that weights below that over 274 keys (2^(1 + 8.1 + 118)), and over the 1048 keys of the other (2^(1 + 10.1 + 116)), fit too.
+LARGE_VALUES = {"chunks": 118, "streamed-one-run": 118, "streamed": 118, "streamed-splits": 115, "chunk-form": 118, "chunk-form-splits": 116}
 
 
 @pytest.mark.parametrize("form", list(FORMS))
-def test_large_values_under_rising_logits(gpu, form):
-    """Every other stretch of 128 keys has logits 19 octaves above the rest: less than a float holds, so that a kernel may
+@pytest.mark.parametrize("rise", [13.25, 10.5, 5.75])
+def test_large_values_under_rising_logits(gpu, form, rise):
+    """Every other stretch of 128 keys has logits 19, 15 or 8 octaves above the rest: less than a float holds, so that a kernel may
     leave its reference where it was, but then its weights must not outgrow the room above the values."""
     n, D = rows(form)
-    print("large values", form, flush=True)
+    print("large values", form, rise, flush=True)
     K, q = np.zeros((n, D), np.float32), np.zeros(D, np.float32)
     q[0] = 1.0
-    K[:, 0] = np.where(np.arange(n) // 128 % 2 == 1, 13.25, 0.0)
+    K[:, 0] = np.where(np.arange(n) // 128 % 2 == 1, rise, 0.0)
     V = np.ldexp(1 + np.abs(bf16_values(np.random.default_rng(3), (n, D))) % 1.0, LARGE_VALUES[form] - 1)
     V = W.as_f32(W.store(V.astype(np.float32), W.BF16), W.BF16)
     out, lse, ref, ref_lse = attend(form, K, q, V, 1.0)

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(W.F32, 16, 4, 64, [8449, 8448, 8447]), (W.F32, 20, 4, 64, [8449, 8448, 255, 257]),
-                                   (W.BF16, 24, 8, 64, [65536]), (W.BF16, 24, 8, 64, [65537]), (W.BF16, 40, 8, 64, [8705, 3]),
+                                   (W.BF16, 24, 8, 64, [65536]), (W.BF16, 24, 8, 64, [65537]),
+                                   (W.BF16, 24, 8, 64, [131072]), (W.BF16, 24, 8, 64, [131073]), (W.BF16, 40, 8, 64, [8705, 3]),
                                    (W.BF16, 128, 16, 64, [8704, 256])], ids=lambda s: "dt%d_H%d_%d_D%d_%s" % s)
 def test_workgroup_edges(gpu, shape):
     check(gpu, shape, (0, 0))
