@@ -10,7 +10,7 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
 static int g_score_variant = 2;   // 0 = fma, 1 = packed bf16 dot2, 2 = matrix cores where the shape allows, else 1 (tuning knob, see ts_debug_set_score_variant)
 static int g_score_wg = 0;        // 0 = automatic
 static int g_score_rr = 0;        // tiles per staged run; 0 = automatic
-static int g_topk_five_pass = 0;  // 1 = force the five-pass radix select (tuning knob)
+static int g_topk_five_pass = 0;  // 1 = force the radix select by passes over all votes (tuning knob)
 static int g_codes_mfma = 1;      // 1 = the compact score pass runs on the matrix cores where the shape allows
 static int g_codes_rr = 0;        // tiles per run of the matrix-core compact score pass; 0 = automatic
 
@@ -495,7 +495,7 @@ int32_t ts_topk(const ts_problem* p, const float* votes, int32_t k, int32_t* idx
   a.blk = (uint32_t*)((uint8_t*)ws + w.topk_blk);
   // The short path finishes on one workgroup per sequence: right when few votes share the k-th vote's
   // quarter-octave (decode votes are peaked), slow when most do.  Votes summed over a chunk's queries are flat,
-  // so chunk problems (and callers that say so) take the five-pass form, whose cost does not depend on the
+  // so chunk problems (and callers that say so) take the passes over all votes, whose cost does not depend on the
   // distribution.
   a.table = (uint16_t*)((uint8_t*)ws + w.topk_list);
   a.list = (g_topk_five_pass || p->chunk > 1 || (flags & TS_TOPK_FLAT_VOTES)) ? nullptr : (uint2*)a.table;

@@ -3,7 +3,7 @@
 //   Eq. 3 (I_topk)       votes[t] = sum_h S[t][h]                 raw dot products summed over heads
 //   Eq. 4 (I_head-vote)  votes[t] = #{h : t in TopK_k(S[:, h])}   every head takes its own top-k
 // Eq. 4 runs the radix select of topk.hip once per (sequence, head) over a transposed copy of the score
-// matrix (contiguous per head, so that the five passes stream it), and its emit pass counts winners per token
+// matrix (contiguous per head, so that the passes stream it), and its emit pass counts winners per token
 // with float atomics (integers up to H: exact and order-independent) instead of listing them.
 #include "ts_kernels.h"
 

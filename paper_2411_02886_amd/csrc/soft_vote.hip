@@ -152,10 +152,14 @@ constexpr int kMergeInVote = 1024;   // partials x heads
 constexpr int kMergeParts = 64;      // partials per head: two per thread
 // T: 512 where eight lanes share a token (from 17 heads on: a round of four passes), 1024 for narrower rows.  Smaller workgroups
 // fill the rounds of the machine better and start and end beside each other; each flushes a histogram of its own, though, which is
-// what counts for narrow rows (statistics merge and vote, 1024 and 512 threads: 4 x 20011 to 40009 tokens of 64 heads 18.6 and 14.7
-// us, 32 x 1031 to 16001 of 32 heads 20.7 and 19.6, 30000 of 28 heads 9.1 and 8.4, 131072 of 32 heads 10.5 and 10.5; 5 x
-// 20000 to 60000 of 12 heads 9.4 and 9.8).  Up to 32 heads, one large workgroup for each of most CUs is as fast, and its 256
-// histograms take the compaction less (a step of 131072 tokens 81.2 and 81.7).
+// what counts for narrow rows (statistics merge and vote, 1024 and 512 threads, us: 4 x 20011 to 40009 tokens of 64 heads 18.6 and
+// 14.7; 5 x 20000 to 60000 of 12 heads 9.4 and 9.8).  Up to 32 heads, between half a round and a round of large workgroups (129 to
+// 256), 1024: each has a CU to itself, and there are half as many histograms for the compaction.  Inside (12 shapes; vote, then the step):
+// 66000 x 1 of 28 heads 10.3 and 10.6, 51.0 and 51.5; 80000 x 1 of 32 10.5 and 11.1, 65.8 and 67.3; 131072 x 1 of 32 11.2 and 11.3,
+// 86.2 and 86.9; 65536 x 2 of 28 10.8 and 11.3, 64.0 and 64.5; 20000 x 4 of 32 10.0 and 10.4; 16000 x 8 of 32 10.3 and 10.7, steps the
+// same.  Outside: 65000 x 1 of 32 10.0 and 9.8, steps the same; 30000 x 2 of 32 9.9 and 9.4; 20000 x 1 of 32 9.6 and 8.8, 43.0 and 42.2;
+// 131500 x 1 of 32 13.6 and 12.1, 87.7 and 87.1; 17000 x 8 of 32 12.7 and 11.9, 99.7 and 98.6; 180000 x 1 of 28 13.2 and 12.5;
+// 262144 x 1 of 32 14.7 and 15.1, but 132.0 and 129.8.
 
 template <int T, int CPL, bool VEC, bool MERGE>
 __global__ __launch_bounds__(T) void soft_vote_ranked_kernel(VoteArgs a, int lpt_shift) {

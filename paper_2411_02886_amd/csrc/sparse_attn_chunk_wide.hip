@@ -15,10 +15,10 @@
 //   * A list entry becomes a row on the way (token id, page id, place, a tile apart); it passes through LDS, fetched like
 //     the rows, because a register's load would be waited for together with all rows behind it.
 //   * Tiles that every row sees in full have a loop of their own without masks.
-// Measured, 512 queries of H 32/8, 4096 selected + 512 own keys: 58.6 -> 50.3 us a call (launch, list, start, end and merge are 20 of them
+// Measured, 512 queries of H 32/8, 4096 selected + 512 own keys: 58.9 -> 51.3 us a call (launch, list, start, end and merge are 20 of them
 // in both); 3 x 777 queries of H 28/4, 1666 + 640 + 777 keys 184 -> 148; 3 x 300 of H 40/8 85 -> 68; with 64 to 512 keys the
-// same to 1.1 times as fast (35 shapes, 0.98 at the worst).  Of its cycles the matrix
-// core is busy 37 %, the vector ALU 38 %; a tile of 64 keys takes a wave 4000 cycles, 2200 of them products.  Tried on the way: the eight waves' two
+// same to 1.1 times as fast (35 shapes, 0.98 at the worst).  Of a wave's cycles the matrix
+// core is busy 40 %, the vector ALU 43 %; a tile of 64 keys takes a wave 3900 cycles, 2180 of them products.  Tried on the way: the eight waves' two
 // key groups taking turns, one at the products, one at the weights, 51.8 us; reads further ahead no faster; four-key look-ups
 // by ds_bpermute 1.5 us slower.
 #include "ts_kernels.h"
@@ -225,7 +225,6 @@ __global__ __launch_bounds__(kCwThreads, 1) void chunk_attn_wide_kernel(ChunkAtt
   // matrix cores form the scores of block j + 1 and add the output of block j - 1: one piece of straight-line code.
   f32x16_t s[2][2];                                             // [block parity][row block] S^T: key 8 * (e / 4) + 4 * half + e % 4
   uint32_t pk[2][2][8];                                         // the weights, rounded to bf16
-  // fragment of step t: K rows (t < KS) for the scores of block HN of tile itn, V^T for the output of block HP of tile itp
   auto round_logits = [&](f32x16_t (&x)[2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int rb2 = 0; rb2 < 2; ++rb2)
@@ -257,7 +256,7 @@ __global__ __launch_bounds__(kCwThreads, 1) void chunk_attn_wide_kernel(ChunkAtt
     const uint32_t vt = va0 + (uint32_t)((k_slot((it + CUR + 1) & 1) + 1) * TILE_B + NXT * 32 * RBYTES);
     constexpr int NS = KS + 2 * NBO, T0 = SC ? 0 : KS, T1 = OUT ? NS : KS; // steps: scores, then output; two MFMAs each
     constexpr bool CIN = CUR == 0 && OUT;                       // this block's first fragments were read at the end of the one before
-    bf16x8_t frag[NS];
+    bf16x8_t frag[NS];                                          // of step t: K rows of the next block (t < KS), V^T of the last one
     auto fetch = [&](int t) __attribute__((always_inline)) {
       if (t < KS) { frag[t] = *(lds_bf16x8*)(kt ^ (uint32_t)(t * 32)); return; }
       const int k2 = (t - KS) / NBO, nb = (t - KS) % NBO;       // k-step k2 takes keys 16 * k2 + 4 * half + {0..3, 8..11}, the keys of x[8 * k2 ..]

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void topk_emit_kernel(TopkArgs a) {
 // Short path (3 launches): after pass 0 every chunk compacts, in token order, the keys that fall in or above
 // the bin of the k-th key (the winners for sure plus the few candidates that share its bin; typically k plus a
 // few hundred entries in all), and one workgroup per sequence finishes the job on that list: two more radix
-// digits over the candidates in LDS histograms, then the ordered emit.  Same result as the five-pass form.
+// digits over the candidates in LDS histograms, then the ordered emit.  Same result as the passes over all votes.
 
 constexpr int kFinalThreads = 1024;        // many threads, few entries each: the per-entry chain of a thread is the latency
                                            // that counts (256 threads x 32 entries measured 1.7x slower)
@@ -752,7 +752,7 @@ hipError_t launch_topk(const TopkArgs& args, int B, hipStream_t s) {
   const bool short_path = a.list != nullptr && a.nblk <= kFinalMaxBlk;
   static_assert(kTopkOneWg == kFinalThreads * 8, "8 votes per thread");
   if (a.one_wg && a.max_seq_len <= kTopkOneWg) {
-    // the whole sequence fits one workgroup's registers: one launch instead of two, three or (flat votes) five, whatever
+    // the whole sequence fits one workgroup's registers: one launch instead of two, three or (flat votes) four, whatever
     // the distribution.  4096 tokens, k 256: 4.6 + 5.1 -> 5.5 us (and no histogram in the vote kernel).  The line lies at
     // 8 votes per thread: a decode step of 8000 tokens 42 -> 37 us; with 16 votes per thread 16000 tokens took 45 us
     // instead of 43, and five sequences of them 72 instead of 68

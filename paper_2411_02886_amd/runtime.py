@@ -147,7 +147,7 @@ class DecodeLayer:
         five-call, five-call with the ranked vote, compact, k 2048 but for the last: 32 heads over 8, head size 128, 18 MiB 96, 93,
         102; 19.5 MiB 103, 100, 104; 20 MiB 113, 110, 108; 23 MiB 120, 116, 111; 32 over 4, 18 MiB 72, 69, 71; 20 MiB 79, 77, 73;
         12 over 2, 18 MiB 83, 79, 85; 20 MiB 89, 85, 87; 64 over 8, 17 MiB 76, 75, 82; 23.9 MiB 81, 80, 85; 40 over 8, k 1024, 20 MiB
-        91, 89, 95; 23.9 MiB 102, 100, 100).  Above 24 MiB the line does not follow the faster form of each shape: the compact form
+        91, 89, 95; 23.9 MiB 102, 100, 100; float rows, 32 over 8, 20 MiB 164, 159, 153).  Above 24 MiB the line does not follow the faster form of each shape: the compact form
         ranks the candidates by votes of double-precision products, the five-call form by votes of float scores, and no call is to
         lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k 2048: 206.5 five-call, 221.8
         compact).  A caller who prefers the time passes compact=False."""
