@@ -50,6 +50,11 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   constexpr int U = 4;                 // wave steps per block: 32 rows = 8 KiB (D = 128)
   constexpr int NBLK = STEPS / U;      // blocks per tile: 4 or 8
   constexpr int TB = U * TPS;          // tokens per block: 8 or 4
+  // Five to eight heads: every matrix product starts from zero and the sums are added up by vector additions.  Handed from product
+  // to product they are aligned to the running sum and cut off: root mean square error of the scores against 64 bits, D 128,
+  // 6.8e-7 (two by two 5.7e-7), this way 5.4e-7, the vector kernel's 5.5e-7.  Three and four heads: one chain, as a sum of
+  // four would be taken out of four times as many values (32/8, 32 x 1031 to 16001 tokens 112 -> 113.5 us).
+  constexpr int NC = CP == 8 ? KS : 1;
   constexpr int UPL = 4 / KB;          // scores per lane and MFMA: 2 or 1
   constexpr int ROWP = RB + 16;        // LDS row pitch: 16 rows land in 16 different bank groups
   typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -159,19 +164,34 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   auto multiply = [&](float (&res)[2][UPL]) {
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
-      mfma_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+      mfma_f32x4_t part[NC];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const uint4 av = *reinterpret_cast<const uint4*>(ktile + arow[cb] + ks * 64);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mfma_bf16x8_t, av),
-                                                      __builtin_bit_cast(mfma_bf16x8_t, bq[cb][ks]), acc, 0, 0, 0);
+      for (int c = 0; c < NC; ++c) {
+        part[c] = mfma_f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = c * (KS / NC); ks < (c + 1) * (KS / NC); ++ks) {
+          const uint4 av = *reinterpret_cast<const uint4*>(ktile + arow[cb] + ks * 64);
+          part[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mfma_bf16x8_t, av),
+                                                            __builtin_bit_cast(mfma_bf16x8_t, bq[cb][ks]), part[c], 0, 0, 0);
+        }
       }
       // result rows of this lane: kg * 4 + ii; the row's KV head inside the block is (kg * 4 + ii) % KB = ii % KB
-      if (KB == 2) {
-        res[cb][0] = kvo ? acc[1] : acc[0];
-        res[cb][UPL - 1] = kvo ? acc[3] : acc[2];
-      } else {
-        res[cb][0] = kvo == 0 ? acc[0] : kvo == 1 ? acc[1] : kvo == 2 ? acc[2] : acc[3];
+      float own[NC][UPL];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const mfma_f32x4_t acc = part[c];
+        if (KB == 2) {
+          own[c][0] = kvo ? acc[1] : acc[0];
+          own[c][UPL - 1] = kvo ? acc[3] : acc[2];
+        } else {
+          own[c][0] = kvo == 0 ? acc[0] : kvo == 1 ? acc[1] : kvo == 2 ? acc[2] : acc[3];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < UPL; ++e) {
+        res[cb][e] = NC > 1 ? own[0][e] + own[NC > 1 ? 1 : 0][e] : own[0][e];
+        if (NC == 4) res[cb][e] += own[NC - 2][e] + own[NC - 1][e];
+        if (NC > 1) asm volatile("" : "+v"(res[cb][e]));   // formed here: left to itself the compiler carries the parts of all blocks to the tile's end (G 8: 216 registers, 144 this way)
       }
     }
   };
@@ -370,11 +390,14 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
 static hipEvent_t g_codes_time_start = nullptr, g_codes_time_stop = nullptr;
 void set_codes_timing_events(hipEvent_t start, hipEvent_t stop) { g_codes_time_start = start; g_codes_time_stop = stop; }
 
-// shapes the matrix-core form covers: bf16, two column blocks per wave tile
+// Shapes the matrix-core form covers: bf16, two column blocks per wave tile.  Wave tiles of 8 KV heads (G 3 and 4) or of 4 (G 5
+// to 8), and no more of them side by side than a workgroup has waves (five to eight heads over 8 or 16 KV heads, score pass, us, vector
+// kernel and this one: 64/8, 4 x 20011 to 40009 tokens 63.0 and 46.4, 6000 18.4 and 8.6, 200000 93.5 and 77.6; 40/8, 2500 tokens
+// 14.5 and 7.6, 100000 45.5 and 45.5).
 bool score_codes_mfma_supported(int dtype, int D, int G, int H_kv) {
   if (dtype != TS_BF16 || (D != 64 && D != 128)) return false;
-  if (G >= 3 && G <= 4) return H_kv >= 8;                 // wave tile of 8 KV heads
-  if (G >= 5 && G <= 8) return H_kv == 4;                 // wave tile of 4 KV heads
+  if (G >= 3 && G <= 4) return H_kv >= 8;
+  if (G >= 5 && G <= 8) return H_kv >= 4 && H_kv <= 16;
   return false;
 }
 
