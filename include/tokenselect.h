@@ -189,8 +189,9 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
  *                      vote_lo[b][t] <= votes[b][t] <= vote_hi[b][t], vote_hi / vote_lo about 2^(1/4); both 0
  *                      outside the ranked range.  Must follow ts_paged_qk_codes with the same problem, workspace
  *                      and score_scale.
- *                      (The last bits of row_stats depend on how the score pass was split over workgroups: on
- *                      max_seq_len, and for batches of four and more on whether a skip mask or a cache test was given.)
+ *                      (The last bits of row_stats, here and from ts_soft_vote, depend on how the score pass was split over
+ *                      workgroups: on max_seq_len and, for a batch, on whether a skip mask or a cache test was given; without
+ *                      either the sequences of a batch share the workgroups, and the other lengths count too.)
  * ts_topk_exact        The TopK of Eq. 5.  Every token whose upper bound reaches the k-th largest lower bound
  *                      (a superset of the k largest votes; usually 1.1-1.5 k tokens) has its scores recomputed
  *                      from K (exact products, double accumulation: closer to Eq. 5 than the float scores of the score

@@ -256,16 +256,33 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, bool whole
     // for the score matrix's rows, four times as many bytes (the 32: 118.8 -> 147.5).
     if (!dense && whole_batch && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
   }
+  // A batch that no mask or cache test can thin out shares a grid of two workgroups per CU (shared_share) from more work on than a
+  // tile for each wave of such a grid: up to there every wave of the other grid has its tile at once, and the sharing out costs
+  // a microsecond (16 sequences of 683 to 2048 tokens, H 32/8, 12.9 and 13.5 us; 16 of 1533 to 4600 25.6 and 20.6).  Three
+  // workgroups per CU are slower (32 of 1031 to 16001 tokens 97.6 and 105 us); the runs are as long as a wave's tiles can be, while
+  // two workgroups' LDS allows.
+  const bool flat = whole_batch && p->batch >= 2 && p->batch <= kScoreFlatMaxBatch && g_codes_rr <= 0 && g_score_wg <= 0 &&
+                    wgs_of(1) * p->batch > kScoreFlatWg;
+  if (flat) {
+    const long most = (p->batch * ntt / (kScoreFlatWg - p->batch) * NU + 3) / 4 + 1;   // tiles of a wave
+    rr = dense ? 2 : 8;
+    if (rr > most) rr = (int)most;
+  }
   if (rr > 8) rr = 8;
   while (rr > 1 && score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) > 163840) --rr;
   a->RR = rr;
   long wgl = wgs_of(rr);
   if (g_score_wg > 0) wgl = g_score_wg;
+  if (flat) { a->flat_batch = p->batch; wgl = kScoreFlatWg; }
   *wg_out = wgl;
 }
 
-// Partials per sequence that a score launch of this shape leaves (workgroups it runs with): what the statistics merge
-// loads before it has seen the count in the workspace.
+static dim3 mfma_grid(const ts_problem* p, const ScoreArgs& a, long wgl) {
+  return a.flat_batch > 0 ? dim3((unsigned)wgl) : dim3((unsigned)wgl, p->batch);
+}
+
+// Partials per sequence that a score launch of this shape leaves (workgroups it runs with; at most, where a batch shares them):
+// what the statistics merge loads before it has seen the count in the workspace.
 static int expected_parts(const ts_problem* p, bool dense, bool whole_batch) {
   const int G = p->num_q_heads / p->num_kv_heads;
   if ((dense ? g_score_variant == 2 : true) && g_codes_mfma && (p->num_q_heads % 4) == 0 &&
@@ -273,7 +290,8 @@ static int expected_parts(const ts_problem* p, bool dense, bool whole_batch) {
     ScoreArgs a{};
     long wgl = 0;
     mfma_launch_shape(p, G, dense, whole_batch, &a, &wgl);
-    return (int)wgl;
+    const long most = ((long)(p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens * a.NU + 3) / 4;   // a tile per wave at least
+    return (int)(a.flat_batch > 0 && most < wgl ? most : wgl);
   }
   return score_workgroups(p);
 }
@@ -312,8 +330,8 @@ static int32_t paged_qk_scores_impl(const ts_problem* p, const void* q, const ts
   if (g_score_variant == 2 && g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)scores & 3) == 0) &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, true, false, &a, &wgl);
-    const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, dim3((unsigned)wgl, p->batch),
+    mfma_launch_shape(p, G, true, skip == nullptr && sc == nullptr, &a, &wgl);
+    const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, mfma_grid(p, a, wgl),
                                                  score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, true), (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
@@ -359,7 +377,7 @@ static int32_t paged_qk_codes_impl(const ts_problem* p, const void* q, const ts_
     // L2 is the cheaper way (measured, H 28/4: 524288 tokens 89.2 us cached / 90.2 streamed, 786432 tokens 142.0 / 135.7,
     // 1048576 tokens 184.5 / 176.1; H 32/8: 524288 tokens 167.4 / 168.7, 786432 tokens 267.4 / 254.4)
     a.nt_codes = (double)p->batch * p->max_seq_len * p->num_q_heads * 1.125 > 20.0 * 1048576.0;
-    const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, dim3((unsigned)wgl, p->batch),
+    const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, mfma_grid(p, a, wgl),
                                                  score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, false), (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
@@ -455,7 +473,7 @@ int32_t ts_soft_vote(const ts_problem* p, const float* scores, float score_scale
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, false);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip == nullptr);
   return launch_soft_vote(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -472,7 +490,7 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, false);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip == nullptr);
   a.rank_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_soft_vote_ranked(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }

@@ -31,9 +31,57 @@ namespace ts {
 typedef __attribute__((ext_vector_type(8))) __bf16 mfma_bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float mfma_f32x4_t;
 
+// What a wave scans: run n of its tiles starts at tile base + n * stride of sequence b, whose x-th of n workgroups this is.
+struct ScoreShare { int b, x, n, N, indptr, base, stride, tiles; };
+
+// A call that scans every sequence of its batch hands the workgroups of a one-dimensional grid out here, where the lengths are
+// known: each takes tpw consecutive tiles of one sequence (its waves equal parts of them), tpw the fewest with which the grid serves
+// all.  In a grid of (workgroups of the longest, sequences) those with work are the first of each row, which is the first XCDs' part of
+// it: they read on when the others have finished, and every XCD can take only its share of the memory's rate.  (32 sequences of
+// 1031 to 16001 tokens, H 32/8: 112 -> 98 us; 32 of 12500 146 -> 130; 2 of 66667 to 200000 102 -> 90; H 28/4, 5 of 26667 to 80000
+// 57 -> 50.)
+// Every sequence gets a workgroup, an empty one too: its statistics are those of no score.  False: nothing left for this one.
+__device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, ScoreShare& s) {
+  const int lane = threadIdx.x & 63, B = a.flat_batch;
+  const int len_any = a.seq_lens[min(lane, B - 1)], ptr = a.page_indptr[min(lane, B - 1)];
+  const int len = lane < B ? min(max(len_any, 0), a.max_seq_len) : 0;
+  const uint32_t ntt = (uint32_t)(len + kScoreTileTokens - 1) / kScoreTileTokens;
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(ntt), 63);
+  const uint32_t groups = 4 / a.NU;                        // waves that share a tile range
+  const uint32_t slots = gridDim.x - (uint32_t)B;          // the sequences' counts are rounded up
+  const uint32_t tpw = max((total + slots - 1) / slots, groups);
+  const uint32_t cnt = lane < B ? max((ntt + tpw - 1) / tpw, 1u) : 0u;
+  const uint32_t incl = wave_inclusive_scan(cnt);
+  const int b = __popcll(__builtin_amdgcn_ballot_w64(incl <= blockIdx.x));
+  if (b >= B) return false;
+  s.b = b;
+  s.n = __builtin_amdgcn_readlane((int)cnt, b);
+  s.x = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, b) - s.n);
+  s.N = __builtin_amdgcn_readlane(len, b);
+  s.indptr = __builtin_amdgcn_readlane(ptr, b);
+  const int t0 = s.x * (int)tpw, have = min((int)tpw, __builtin_amdgcn_readlane((int)ntt, b) - t0);
+  const int part = wave / a.NU, lo = have * part / (int)groups, hi = have * (part + 1) / (int)groups;
+  s.base = t0 + lo; s.stride = a.RR; s.tiles = hi - lo;
+  return true;
+}
+
+// The other calls: the grid's second dimension is the sequence.  Its runs go round its waves; the tiles that exist form a prefix of a wave's.
+__device__ __forceinline__ void own_tiles(const ScoreArgs& a, int wave, ScoreShare& s) {
+  const int ntt = (s.N + kScoreTileTokens - 1) / kScoreTileTokens, nrun = (ntt + a.RR - 1) / a.RR;
+  const int run_first = (blockIdx.x * 4 + wave) / a.NU, run_step = (gridDim.x * 4) / a.NU;
+  s.base = run_first * a.RR; s.stride = run_step * a.RR; s.tiles = 0;
+  if (run_first < nrun) {
+    const int my_runs = (nrun - run_first + run_step - 1) / run_step;
+    const int last_run = run_first + (my_runs - 1) * run_step;
+    s.tiles = (my_runs - 1) * a.RR + min(a.RR, ntt - last_run * a.RR);
+  }
+}
+
 // G in 3..4: CP = 4, column block = 4 KV heads, wave tile = 8 KV heads.  G in 5..8: CP = 8, 2 and 4.
 // DENSE: Algorithm 2's score matrix itself leaves the chip (fp32 rows, ts_paged_qk_scores) instead of the bytes.
-template <int D, int G, bool DENSE>
+// SHARED: the sequences share a one-dimensional grid (shared_share).
+// SUMS: how the products along D are added up; taken for the shapes with five to eight heads that have more than one wave tile side by side.
+template <int D, int G, bool DENSE, bool SHARED, bool SUMS>
 __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   constexpr int RB = D * 2;            // bytes per K row
   constexpr int L = RB / 128;          // 16-byte loads per lane per row
@@ -50,11 +98,11 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   constexpr int U = 4;                 // wave steps per block: 32 rows = 8 KiB (D = 128)
   constexpr int NBLK = STEPS / U;      // blocks per tile: 4 or 8
   constexpr int TB = U * TPS;          // tokens per block: 8 or 4
-  // Five to eight heads: every matrix product starts from zero and the sums are added up by vector additions.  Handed from product
-  // to product they are aligned to the running sum and cut off: root mean square error of the scores against 64 bits, D 128,
-  // 6.8e-7 (two by two 5.7e-7), this way 5.4e-7, the vector kernel's 5.5e-7.  Three and four heads: one chain, as a sum of
-  // four would be taken out of four times as many values (32/8, 32 x 1031 to 16001 tokens 112 -> 113.5 us).
-  constexpr int NC = CP == 8 ? KS : 1;
+  // SUMS: every matrix product starts from zero and the sums are added up by vector additions.  Handed from product to product
+  // they are aligned to the running sum and cut off: root mean square error of the scores against 64 bits, D 128, 6.8e-7
+  // (two by two 5.7e-7), this way 5.4e-7, the vector kernel's 5.5e-7.  It costs 24 vector instructions a block, 0.7 us of a
+  // call in which a wave has one tile (4000 tokens of H 32/4: 7.1 and 7.8 us).
+  constexpr int NC = SUMS ? KS : 1;
   constexpr int UPL = 4 / KB;          // scores per lane and MFMA: 2 or 1
   constexpr int ROWP = RB + 16;        // LDS row pitch: 16 rows land in 16 different bank groups
   typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -63,13 +111,19 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 7, r = lane >> 3;
   const int mrow = lane & 15, kg = lane >> 4;            // MFMA row / column and k-group of this lane
-  const int b = blockIdx.y;
-  const int N = min(max(a.seq_lens[b], 0), a.max_seq_len);
-  const int indptr = a.page_indptr[b];
+  ScoreShare sh;
+  if (SHARED) {
+    if (!shared_share(a, wave, sh)) return;
+  } else {
+    sh.b = blockIdx.y; sh.x = blockIdx.x; sh.n = gridDim.x;
+    sh.N = min(max(a.seq_lens[sh.b], 0), a.max_seq_len);
+    sh.indptr = a.page_indptr[sh.b];
+  }
+  const int b = sh.b, N = sh.N, indptr = sh.indptr;
   // Algorithm 1's test inside this launch: the vectors' loads and partial sums go first, the decision is taken below,
   // once the first page ids are on their way (the same sums in the same order in every workgroup of the sequence).
   // The reduction uses the head of the dynamic LDS, which nothing else touches before the decision.
-  const bool sc_on = a.sc_cached_q != nullptr;
+  const bool sc_on = !SHARED && a.sc_cached_q != nullptr;
   double (*sc_red)[4] = reinterpret_cast<double (*)[4]>(smem8);
   int sc_first0 = 0;
   if (sc_on) {
@@ -77,7 +131,7 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
     sc_first0 = a.sc_first[b];
     selcache_sums<TS_BF16>(reinterpret_cast<const uint4*>(a.q + (size_t)b * a.H * RB),
                       reinterpret_cast<const uint4*>(a.sc_cached_q + (size_t)b * a.H * RB), a.H * RB / 16, sc_red, qkeep);
-  } else if (a.skip != nullptr && a.skip[b] != 0) {
+  } else if (!SHARED && a.skip != nullptr && a.skip[b] != 0) {
     return;
   }
   const int H = a.H;
@@ -96,7 +150,6 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   const int kvh = u * HB + kvh_l;
   const int h_base = u * HBG;
   const int ntt = (N + TT - 1) / TT;
-  const int tt_step = (gridDim.x * 4) / a.NU;
   const int npages = (N + a.P - 1) >> a.p_shift;
   const float c2 = a.c2;
   const int r_lo = min(a.n_init, N), r_hi = max(r_lo, N - a.n_local);
@@ -121,16 +174,10 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
     arow[cb] = ((tb >> TPS_SHIFT) * 8 + (tb & (TPS - 1)) * HB + kv) * ROWP + kg * 16;
   }
 
-  const int nrun = (ntt + RR - 1) / RR;
-  const int run_first = (blockIdx.x * 4 + wave) / a.NU, run_step = tt_step;
-  int my_tiles = 0;
-  if (run_first < nrun) {
-    const int my_runs = (nrun - run_first + run_step - 1) / run_step;
-    const int last_run = run_first + (my_runs - 1) * run_step;
-    my_tiles = (my_runs - 1) * RR + min(RR, ntt - last_run * RR);
-  }
+  if (!SHARED) own_tiles(a, wave, sh);
+  const int my_tiles = sh.tiles;
   const int total_blocks = my_tiles * NBLK;
-  auto tile_of = [&](int n, int rr) -> int { return (run_first + n * run_step) * RR + rr; };
+  auto tile_of = [&](int n, int rr) -> int { return sh.base + n * sh.stride + rr; };
   auto load_pids = [&](int tt) -> int {
     const int pg = (tt * TT + (lane & 31)) >> a.p_shift;
     return a.page_indices[indptr + min(pg, npages - 1)];
@@ -327,7 +374,7 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   }
   if (sc_on) {
     const int reselect = selcache_decide(sc_red, reinterpret_cast<int*>(sc_red + 3), sc_first0, a.sc_theta);
-    if (blockIdx.x == 0) {                                // the state after the step: C_Q <- Q on a miss, kept on a hit
+    if (sh.x == 0) {                                      // the state after the step: C_Q <- Q on a miss, kept on a hit
       const int npieces = a.H * RB / 16;
       const uint4* qv = reinterpret_cast<const uint4*>(a.q + (size_t)b * a.H * RB);
       const uint4* cv = reinterpret_cast<const uint4*>(a.sc_cached_q + (size_t)b * a.H * RB);
@@ -378,11 +425,11 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
       const float2 e = wv[w * HBG + hl];
       l += (e.x == -INFINITY) ? 0.f : e.y * __builtin_amdgcn_exp2f(c2 * (e.x - m));
     }
-    float* pp = a.partials + (((size_t)b * kScoreMaxWg + blockIdx.x) * H + h) * 2;
+    float* pp = a.partials + (((size_t)b * kScoreMaxWg + sh.x) * H + h) * 2;
     pp[0] = m; pp[1] = l;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.hdr[b * 8 + 0] = gridDim.x;                          // statistics partials of this launch
+  if (sh.x == 0 && threadIdx.x == 0) {
+    a.hdr[b * 8 + 0] = sh.n;                               // statistics partials of this launch
     a.hdr[b * 8 + 2] = __float_as_uint(a.scale);
   }
 }
@@ -409,26 +456,37 @@ size_t score_codes_mfma_lds_bytes(int D, int G, int RR, bool dense) {
   return 4 * per_wave;
 }
 
-template <int D, int G, bool DENSE>
+template <int D, int G, bool DENSE, bool SHARED, bool SUMS>
 static hipError_t launch_cm(const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
+  const auto kernel = &score_codes_mfma_kernel<D, G, DENSE, SHARED, SUMS>;
   if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_codes_mfma_kernel<D, G, DENSE>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   if (g_codes_time_start != nullptr && g_codes_time_stop != nullptr)
-    hipExtLaunchKernelGGL((score_codes_mfma_kernel<D, G, DENSE>), grid, dim3(256), (uint32_t)lds, s, g_codes_time_start, g_codes_time_stop, 0u, a);
+    hipExtLaunchKernelGGL(kernel, grid, dim3(256), (uint32_t)lds, s, g_codes_time_start, g_codes_time_stop, 0u, a);
   else
-    hipLaunchKernelGGL((score_codes_mfma_kernel<D, G, DENSE>), grid, dim3(256), lds, s, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, a);
   return hipGetLastError();
+}
+
+template <int D, int G, bool SUMS>
+static hipError_t launch_cm_form(const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
+  const bool shared = a.flat_batch > 0;
+  if (a.codes == nullptr) return shared ? launch_cm<D, G, true, true, SUMS>(a, grid, lds, s) : launch_cm<D, G, true, false, SUMS>(a, grid, lds, s);
+  return shared ? launch_cm<D, G, false, true, SUMS>(a, grid, lds, s) : launch_cm<D, G, false, false, SUMS>(a, grid, lds, s);
+}
+
+template <int G>
+static hipError_t launch_cm_shape(int D, const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
+  constexpr bool WIDE = G >= 5;
+  if (WIDE && a.NU > 1) return D == 64 ? launch_cm_form<64, G, WIDE>(a, grid, lds, s) : launch_cm_form<128, G, WIDE>(a, grid, lds, s);
+  return D == 64 ? launch_cm_form<64, G, false>(a, grid, lds, s) : launch_cm_form<128, G, false>(a, grid, lds, s);
 }
 
 // a.codes != nullptr: the compact form; else a.scores receives the fp32 score matrix
 hipError_t launch_score_codes_mfma(int D, int G, const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-  const bool dense = a.codes == nullptr;
-#define TS_CM(GG) case GG: \
-    if (dense) return D == 64 ? launch_cm<64, GG, true>(a, grid, lds, s) : launch_cm<128, GG, true>(a, grid, lds, s); \
-    return D == 64 ? launch_cm<64, GG, false>(a, grid, lds, s) : launch_cm<128, GG, false>(a, grid, lds, s);
+#define TS_CM(GG) case GG: return launch_cm_shape<GG>(D, a, grid, lds, s);
   switch (G) { TS_CM(3) TS_CM(4) TS_CM(5) TS_CM(6) TS_CM(7) TS_CM(8) }
 #undef TS_CM
   return hipErrorInvalidValue;
