@@ -164,16 +164,20 @@ hipError_t launch_vote_bounds(const BoundArgs& a, int B, hipStream_t s) {
 // The candidates (listed per 2048-token chunk by topk_compact_kernel over the upper bounds) re-evaluated from K.
 //
 // What bounds it: for one sequence the chain of dependent loads (chunk counts -> token -> page id -> K row).  For a batch
-// no single thing: 32 sequences of 1031 to 16001 tokens, H 32/8, are about 70 thousand candidates and 140 MB of gathered K
-// rows in 47 us; by count the double-precision products need about 10 of them, and conversions, reduction and row loads
-// follow one after another at two waves per SIMD.  Hence the split: the candidates of a sequence are
-// numbered through and every workgroup takes an equal share of them, whatever chunk they come from.  (When the
-// workgroup that had compacted a chunk also evaluated it, a short sequence -- all of its tokens candidates, in one
-// or two chunks -- was one workgroup's serial tail: 32 sequences of 1031 to 16001 tokens, H 32/8, k 2048 took 277 us,
-// compaction and this kernel take 54 us.)
-// Eight or sixteen lanes share a K row, so that a wave can keep the query heads of its KV heads as doubles in registers
-// for its whole life (up to 128 of them) instead of converting them again for every candidate.  The scores of up to CB candidates meet in LDS, where the softmax weights
-// are formed with every lane at work.
+// the gather of the rows, with the chain before it and the votes behind it, which all workgroups pass through at the same time: 32
+// sequences of 1031 to 16001 tokens, H 32/8, are about 70 thousand candidates and 140 MB of K rows, 24 us at the rate of a
+// gather, in 35 us.  The candidates of a sequence are numbered through and every workgroup takes an equal share of them,
+// whatever chunk they come from.  (When the workgroup that had compacted a chunk also evaluated it, a short sequence -- all
+// of its tokens candidates, in one or two chunks -- was one workgroup's serial tail: 277 us for the 32 sequences.)
+// The products run on v_mfma_f64_4x4x4 (four blocks of 4 candidates x 4 query heads, one KV head each, 4 elements a step).  The
+// double-precision matrix instructions are no faster than v_fma_f64, and both occupy the vector ALU; what goes is everything
+// around the products: a lane converts its quarter of a row once for four heads, no sums travel across lanes, and the query
+// takes 64 registers, so that the next step's loads leave as the current pieces are converted.  (A row on eight lanes, products by
+// v_fma_f64, sums by DPP: the 32 sequences 45.5 us; 32 of 4000 to 12500, H 28/4, k 4000 80.6, now 51.  Eight waves
+// instead of four a workgroup: the same for batches, 0.5 to 1 us more for one sequence; where a wave of four has two units to go
+// through, 4 x 20000 to 40000, H 64/32, D 64, k 2000, 18.2 and
+// 14.5, 16.0 before.)
+// The scores of up to CB candidates meet in LDS, where the softmax weights are formed with every lane at work.
 
 // exp(c * d) as ts_soft_vote forms it: argument reduced in double, 2^fraction from the float hardware exponential
 __device__ __forceinline__ float refine_vote_exp(double d, double c2) {
@@ -190,76 +194,30 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor4 = 0x124, kDppRor8 = 0x128;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
 
-// Sums v[g] over the LPR lanes of a row and leaves head g = (lane % GP) of the sums in each lane (GP = G rounded up to
-// a power of two; LPR = 8 or 16).  Where two lanes meet, each takes over half of the heads that both still carry, so
-// the number of additions halves from step to step.
-template <int GP, int LPR>
-__device__ __forceinline__ double row_reduce(double (&v)[GP], int lane) {
-  if (GP == 8) {
-    const bool b = (lane & 4) != 0;        // the half mirror flips bits 0 to 2: done first, when all lanes carry all heads
+// the elements of a 16-byte piece as doubles
+template <int DT>
+__device__ __forceinline__ void unpack_f64(uint4 w, double* f) {
+  const uint32_t x[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int g = 0; g < GP / 2; ++g) {
-      const double keep = b ? v[g + GP / 2] : v[g], give = b ? v[g] : v[g + GP / 2];
-      v[g] = keep + dpp_f64<kDppHalfMirror>(give);
-    }
-  } else {
-#pragma unroll
-    for (int g = 0; g < GP; ++g) v[g] += (LPR == 16) ? dpp_f64<kDppRor4>(v[g]) : dpp_f64<kDppHalfMirror>(v[g]);
-  }
-  if (GP >= 4) {
-    const bool b = (lane & 2) != 0;
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      if (g + 2 < GP) {
-        const double keep = b ? v[g + 2] : v[g], give = b ? v[g] : v[g + 2];
-        v[g] = keep + dpp_f64<kDppXor2>(give);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int g = 0; g < GP; ++g) v[g] += dpp_f64<kDppXor2>(v[g]);
-  }
-  if (GP >= 2) {
-    const bool b = (lane & 1) != 0;
-    const double keep = b ? v[GP > 1 ? 1 : 0] : v[0], give = b ? v[0] : v[GP > 1 ? 1 : 0];
-    v[0] = keep + dpp_f64<kDppXor1>(give);
-  } else {
-    v[0] += dpp_f64<kDppXor1>(v[0]);
-  }
-  if (LPR == 16) v[0] += dpp_f64<kDppRor8>(v[0]);
-  return v[0];
-}
-
-// the elements of NW 16-byte pieces as doubles
-template <int DT, int NW>
-__device__ __forceinline__ void unpack_f64(const uint4 (&w)[NW], double* f) {
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const uint32_t x[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (DT == TS_BF16) { f[i * 8 + 2 * c] = (double)bf16_lo(x[c]); f[i * 8 + 2 * c + 1] = (double)bf16_hi(x[c]); }
-      else f[i * 4 + c] = (double)__uint_as_float(x[c]);
-    }
+  for (int c = 0; c < 4; ++c) {
+    if (DT == TS_BF16) { f[2 * c] = (double)bf16_lo(x[c]); f[2 * c + 1] = (double)bf16_hi(x[c]); }
+    else f[c] = (double)__uint_as_float(x[c]);
   }
 }
 
-constexpr int kEvalThreads = 256;
-constexpr int kEvalMaxBatch = 128;        // candidates whose scores a workgroup holds in LDS at a time, at most
+constexpr int kEvalMaxBatch = 256;        // candidates whose scores a workgroup holds in LDS at a time, at most
 
-template <int DT, int D, int G>
-__global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a, int cb) {
+// CS: sets of four query heads of a KV head.  WAVES: eight where that many (set, four KV heads) pairs are, else four.
+template <int DT, int D, int CS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void topk_eval_kernel(RefineArgs a, int cb) {
+  constexpr int T = 64 * WAVES;
   constexpr int ES = Elt<DT>::size;
   constexpr int RB = D * ES;
-  constexpr int EPL = (D == 128 && G <= 4) ? 16 : 8;   // elements of a row per lane: the query then takes 128 registers at most
-  constexpr int LPR = D / EPL;            // lanes per K row: 8 or 16
-  constexpr int RPS = 64 / LPR;           // rows of a wave step
-  constexpr int NW = ES * EPL / 16;       // 16-byte pieces of a lane's elements, LPR pieces apart
-  constexpr int GP = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : 8;
-  constexpr int UB = NW == 1 ? 4 : 2;     // wave steps of a round
-  __shared__ uint32_t wave_sum[kEvalThreads / 64];
+  constexpr int EPP = 16 / ES;            // elements of a 16-byte piece
+  constexpr int NP = RB / 64;             // pieces per lane: four lanes share a K row
+  __shared__ uint32_t wave_sum[WAVES];
   __shared__ int ctok[kEvalMaxBatch];
   __shared__ long long cslot[kEvalMaxBatch];
   __shared__ double s_m[128];
@@ -267,38 +225,38 @@ __global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a
   extern __shared__ double sc[];          // [cb][H] scores of the batch, then uint32 [nblk + 1] prefix of the chunk counts
   const TopkArgs& ta = a.t;
   const int b = blockIdx.y;
-  const int H = a.H;
+  const int H = a.H, G = H / a.H_kv;
   uint32_t* off = reinterpret_cast<uint32_t*>(sc + (size_t)cb * H);
   const int skip_flag = ta.skip != nullptr ? (int)ta.skip[b] : 0;
   const int Nb = min(max(ta.seq_lens[b], 0), ta.max_seq_len);
   const int indptr = a.page_indptr[b];
   if (skip_flag != 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // a wave owns one slice of the KV heads (every nuw-th, where there are more slices than waves) and every 4 / nuw-th step
-  const int j = lane % LPR, r = lane / LPR;
-  const int HB = min(a.H_kv, RPS);                    // KV heads of a wave step
-  const int hb_shift = 31 - __clz(HB);
-  const int NU = a.H_kv >> hb_shift;                  // slices
-  const int nuw = min(NU, 4);
-  const int kvh_l = r & (HB - 1), tis = r >> hb_shift;
-  const int tps = RPS >> hb_shift;                    // candidates of a wave step
-  const int wsub = wave / nuw, wstep = 4 / nuw;
-  double qd[G][EPL];
-  auto load_q = [&](int u) {
+  // Operand lanes: row (query head) c of block bl, elements of pieces kk, kk + 4, ...; result lanes: row kk, column c of block bl.
+  // A block is four candidates and one KV head; with fewer than four KV heads the blocks are different candidates.
+  const int c = lane & 3, bl = (lane >> 2) & 3, kk = lane >> 4;
+  const int HB = min(a.H_kv, 4), hb_shift = 31 - __clz(HB);
+  const int NU = a.H_kv >> hb_shift;                  // groups of HB KV heads
+  const int tps = 16 >> hb_shift;                     // candidates of a wave step
+  const int units = NU * CS;                          // 1, 2, 4 or, with eight waves, 8: a wave stays with one
+  const int unit = wave & (units - 1), wsub = wave / units, wstep = WAVES / units;
+  const int kvh = (unit & (NU - 1)) * HB + (bl & (HB - 1));
+  const int g = unit / NU * 4 + c;                    // this lane's query head of the KV head
+  const int cand = (bl >> hb_shift) * 4;              // first candidate of the block in a step
+  double qd[NP * EPP];
+  {
+    const uint8_t* qp = a.q + ((size_t)b * H + (size_t)kvh * G + min(g, G - 1)) * RB + kk * 16;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      uint4 w[NW];
-      const uint8_t* qp = a.q + ((size_t)b * H + (size_t)(u * HB + kvh_l) * G + g) * RB + j * 16;
-#pragma unroll
-      for (int i = 0; i < NW; ++i) w[i] = *reinterpret_cast<const uint4*>(qp + i * (LPR * 16));
-      unpack_f64<DT, NW>(w, qd[g]);
+    for (int i = 0; i < NP; ++i) {
+      uint4 w = *reinterpret_cast<const uint4*>(qp + i * 64);
+      if (g >= G) w = make_uint4(0u, 0u, 0u, 0u);
+      unpack_f64<DT>(w, qd + i * EPP);
     }
-  };
-  load_q(wave % nuw);
+  }
   // the lower bounds' histogram has been consumed by the compaction: leave it zeroed, a share per workgroup
   {
     uint4* g0 = reinterpret_cast<uint4*>(ta.rep_hist + (size_t)b * kBoundHistCopies * kTopkBins);   // 256-byte aligned section
-    for (int i = (int)(blockIdx.x * kEvalThreads + threadIdx.x); i < kBoundHistCopies * kTopkBins / 4; i += (int)gridDim.x * kEvalThreads)
+    for (int i = (int)(blockIdx.x * T + threadIdx.x); i < kBoundHistCopies * kTopkBins / 4; i += (int)gridDim.x * T)
       g0[i] = make_uint4(0u, 0u, 0u, 0u);
   }
   if (threadIdx.x < H) {
@@ -306,26 +264,26 @@ __global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a
     s_m[threadIdx.x] = (double)st.x; s_inv[threadIdx.x] = 1.0 / (double)st.y;
   }
   // ---- prefix of the chunks' candidate counts
-  constexpr int CPT = 4;                              // consecutive chunks per thread and round: 1024 chunks at a time
+  constexpr int CPT = 4;                              // consecutive chunks per thread and round: 2048 chunks at a time
   uint32_t carry = 0;
-  for (int c0 = 0; c0 < ta.nblk; c0 += kEvalThreads * CPT) {
-    const int c = c0 + (int)threadIdx.x * CPT;
+  for (int c0 = 0; c0 < ta.nblk; c0 += T * CPT) {
+    const int ch = c0 + (int)threadIdx.x * CPT;
     uint32_t cnt[CPT], sum = 0;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) { cnt[i] = c + i < ta.nblk ? ta.blk[(size_t)b * ta.nblk + c + i] : 0u; sum += cnt[i]; }
+    for (int i = 0; i < CPT; ++i) { cnt[i] = ch + i < ta.nblk ? ta.blk[(size_t)b * ta.nblk + ch + i] : 0u; sum += cnt[i]; }
     const uint32_t incl = wave_inclusive_scan(sum);
     __syncthreads();
     if (lane == 63) wave_sum[wave] = incl;
     __syncthreads();
     uint32_t base = carry + incl - sum;
 #pragma unroll
-    for (int w = 0; w < kEvalThreads / 64; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       const uint32_t x = wave_sum[w];
       if (w < wave) base += x;
       carry += x;
     }
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) { if (c + i < ta.nblk) off[c + i] = base; base += cnt[i]; }
+    for (int i = 0; i < CPT; ++i) { if (ch + i < ta.nblk) off[ch + i] = base; base += cnt[i]; }
   }
   if (threadIdx.x == 0) off[ta.nblk] = carry;
   const uint32_t total = carry;
@@ -351,54 +309,40 @@ __global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a
     }
     __syncthreads();
     const int nsteps = (n + tps - 1) / tps;
-    for (int u = wave % nuw; u < NU; u += nuw) {
-      if (NU > nuw) load_q(u);
-      const int kvh = u * HB + kvh_l;
-      // steps of this wave and slice: wsub, wsub + wstep, ...; the next round's rows are in flight during a round
-      uint4 cur[UB][NW], nxt[UB][NW];
-      auto issue = [&](int s0, uint4 (&kr)[UB][NW]) {
+    // steps of this wave: wsub, wsub + wstep, ...; a piece of the next step's rows is asked for as soon as one has been converted
+    auto row_of = [&](int st) -> const uint8_t* {
+      return a.k_pool + ((size_t)cslot[min(st * tps + cand + c, n - 1)] * a.H_kv + kvh) * RB + kk * 16;
+    };
+    uint4 buf[NP];
+    auto step = [&](int st, bool more) {
+      const uint8_t* kn = more ? row_of(st + wstep) : nullptr;
+      double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll
-        for (int uu = 0; uu < UB; ++uu) {
-          const int st = s0 + uu * wstep;
-          if (st >= nsteps) continue;                                   // the same for the whole wave
-          const long long slot = cslot[min(st * tps + tis, n - 1)];
-          const uint8_t* kp = a.k_pool + ((size_t)slot * a.H_kv + kvh) * RB + j * 16;
+      for (int i = 0; i < NP; ++i) {
+        double kd[EPP];
+        unpack_f64<DT>(buf[i], kd);
+        if (more) buf[i] = *reinterpret_cast<const uint4*>(kn + i * 64);
+        // products of two floats are exact in double
 #pragma unroll
-          for (int i = 0; i < NW; ++i) kr[uu][i] = *reinterpret_cast<const uint4*>(kp + i * (LPR * 16));
+        for (int e = 0; e < EPP; e += 2) {
+          acc0 = __builtin_amdgcn_mfma_f64_4x4x4f64(kd[e], qd[i * EPP + e], acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f64_4x4x4f64(kd[e + 1], qd[i * EPP + e + 1], acc1, 0, 0, 0);
         }
-      };
-      if (wsub < nsteps) issue(wsub, cur);
-      for (int s0 = wsub; s0 < nsteps; s0 += wstep * UB) {
-        issue(s0 + wstep * UB, nxt);
-#pragma unroll
-        for (int uu = 0; uu < UB; ++uu) {
-          const int st = s0 + uu * wstep;
-          if (st >= nsteps) continue;
-          double kd[EPL];
-          unpack_f64<DT, NW>(cur[uu], kd);
-          double v[GP];
-#pragma unroll
-          for (int g = 0; g < GP; ++g) {
-            v[g] = 0.0;
-            if (g < G) {
-              // products of two floats are exact in double
-#pragma unroll
-              for (int e = 0; e < EPL; ++e) v[g] = fma(kd[e], qd[g < G ? g : 0][e], v[g]);
-            }
-          }
-          const double s = row_reduce<GP, LPR>(v, lane);
-          const int ci = st * tps + tis, g = j & (GP - 1);
-          if (ci < n && j < GP && g < G) sc[(size_t)ci * H + kvh * G + g] = s;
-        }
-#pragma unroll
-        for (int uu = 0; uu < UB; ++uu)
-#pragma unroll
-          for (int i = 0; i < NW; ++i) cur[uu][i] = nxt[uu][i];
       }
+      const int ci = st * tps + cand + kk;
+      if (ci < n && g < G) sc[(size_t)ci * H + kvh * G + g] = acc0 + acc1;
+    };
+    int st = wsub;
+    if (st < nsteps) {
+      const uint8_t* kp = row_of(st);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) buf[i] = *reinterpret_cast<const uint4*>(kp + i * 64);
+      for (; st + wstep < nsteps; st += wstep) step(st, true);
+      step(st, false);
     }
     __syncthreads();
     // ---- votes: 16 lanes per candidate
-    for (int ci = (int)threadIdx.x >> 4; ci < ((n + 15) & ~15); ci += kEvalThreads / 16) {
+    for (int ci = (int)threadIdx.x >> 4; ci < ((n + 15) & ~15); ci += T / 16) {
       const int cc = min(ci, n - 1);
       double vote = 0.0;
       for (int h = (int)threadIdx.x & 15; h < H; h += 16)
@@ -415,15 +359,16 @@ __global__ __launch_bounds__(kEvalThreads, 2) void topk_eval_kernel(RefineArgs a
 
 template <int DT, int D>
 static hipError_t eval_g(int G, const RefineArgs& a, dim3 grid, hipStream_t s) {
-  int cb = 3072 / a.H;                                // the scores of a batch and the prefix of 8192 chunks fit 64 KiB
+  // the scores of a batch and the prefix of the chunk counts (8192 at most) fit 64 KiB beside 6 KiB of static LDS
+  const size_t off_bytes = (size_t)(a.t.nblk + 1) * sizeof(uint32_t);
+  int cb = (int)((59392 - off_bytes) / ((size_t)a.H * sizeof(double)));
   if (cb > kEvalMaxBatch) cb = kEvalMaxBatch;
-  const size_t lds = (size_t)cb * a.H * sizeof(double) + (size_t)(a.t.nblk + 1) * sizeof(uint32_t);
-  switch (G) {
-#define TS_CASE(GG) case GG: hipLaunchKernelGGL((topk_eval_kernel<DT, D, GG>), grid, dim3(kEvalThreads), lds, s, a, cb); break;
-    TS_CASE(1) TS_CASE(2) TS_CASE(3) TS_CASE(4) TS_CASE(5) TS_CASE(6) TS_CASE(7) TS_CASE(8)
-#undef TS_CASE
-    default: return hipErrorInvalidValue;
-  }
+  const size_t lds = (size_t)cb * a.H * sizeof(double) + off_bytes;
+  const int units = (a.H_kv + 3) / 4 * (G > 4 ? 2 : 1);
+#define TS_EVAL(CS, WAVES) hipLaunchKernelGGL((topk_eval_kernel<DT, D, CS, WAVES>), grid, dim3(64 * WAVES), lds, s, a, cb)
+  if (G > 4) { if (units > 4) TS_EVAL(2, 8); else TS_EVAL(2, 4); }
+  else { if (units > 4) TS_EVAL(1, 8); else TS_EVAL(1, 4); }
+#undef TS_EVAL
   return hipGetLastError();
 }
 

@@ -65,8 +65,8 @@ inline bool attn_streams(int G, int D, long pairs, int total) {
   return G == 2 || 5 * pairs >= 4 * ((pairs + 255) / 256 * 256);
 }
 
-// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (their
-// registers allow no more).  How many candidates there are is known on the device only -- a little more than k when votes
+// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (what the
+// LDS for their scores allows).  How many candidates there are is known on the device only -- a little more than k when votes
 // are peaked, every token when they are flat, whatever k is -- so the number does not fall with k (k 64 of 1048576 flat
 // votes: 12.9 ms with k / 4 workgroups, 1.7 ms with 512); those that would get fewer than kEvalMinShare candidates leave at once.
 // Large batches: 512 / batch may leave a good part of the round empty; more rounds of smaller shares do not, and a round

@@ -35,3 +35,30 @@ def test_equal_votes_around_the_cut(gpu, copies, k):
     rows[slots[order[-copies:]]] = rows[slots[order[k - 1]]]
     layer, q = make_layer(w)
     check_compact(w, layer, q, label="ties %d k %d" % (copies, k))
+
+
+@pytest.mark.parametrize("dtype,H,H_kv,D", [(W.BF16, 1, 1, 128), (W.BF16, 5, 1, 64), (W.F32, 4, 1, 128), (W.BF16, 6, 2, 128), (W.F32, 16, 2, 64),
+                                            (W.BF16, 12, 4, 64), (W.F32, 28, 4, 128), (W.BF16, 64, 8, 128), (W.BF16, 64, 16, 64),
+                                            (W.F32, 64, 32, 64), (W.BF16, 128, 16, 128), (W.BF16, 128, 32, 128)])
+def test_votes_of_the_candidates_against_64_bits(gpu, dtype, H, H_kv, D):
+    """Every number of KV heads and head sets that a wave step is laid out for, with fewer candidates than a step, a step's and
+    more: sel_votes against Eq. 5 in 64 bits from the GPU's own statistics.  The products are exact in both; a weight's power of
+    two comes from the float exponential (1 ulp, 1.2e-7) of an argument rounded to float (0.5 * 6e-8 * ln 2), the vote is
+    rounded once (6e-8): below 3e-7, 5e-7 asserted."""
+    from paper_2411_02886_amd.runtime import to_host
+    lens, scale = [1, 3, 17, 70, 2500], 0.5
+    w = W.make_workload("sel_votes", dtype=dtype, B=len(lens), H=H, H_kv=H_kv, D=D, seq_lens=lens, k=300, beta=2.5, planted_per_head=0, seed=93)
+    layer, q = make_layer(w)
+    print("candidates' votes", dtype, H, H_kv, D, flush=True)
+    layer.select_compact(q, scale, None)
+    torch.cuda.synchronize()
+    idx, cnt, st, got = (to_host(x) for x in (layer.idx, layer.count, layer.row_stats, layer.sel_votes))
+    qf = W.as_f32(w.q, dtype).astype(np.float64)
+    rows = W.as_f32(w.k_pool.reshape(-1, H_kv, D), dtype).astype(np.float64)
+    for b, n in enumerate(lens):
+        m = int(cnt[b])
+        assert m == min(n, 300)
+        k = rows[w.slots_of(b)[idx[b, :m]]]                                  # [m][H_kv][D]
+        s = np.einsum("mhd,hd->mh", np.repeat(k, H // H_kv, axis=1), qf[b, 0])
+        ref = (np.exp(float(np.float32(scale)) * (s - st[b, :, 0].astype(np.float64))) / st[b, :, 1].astype(np.float64)).sum(axis=1)
+        np.testing.assert_allclose(got[b, :m], ref, rtol=5e-7, err_msg="b %d" % b)
