@@ -221,8 +221,10 @@ static size_t score_lds_bytes(const ScoreArgs& a, int G) {
 // Launch shape of the matrix-core score kernel (both forms): fills the wave-tile fields and a.RR, returns the
 // workgroups per sequence.  A wave owns one run of consecutive tiles where the sequence is short enough, so that
 // its output leaves in one burst at the end of its life; about 2048 waves per sequence (measured on MI355X:
-// 131072 tokens 49 us with one tile per wave, 45.7 us with two).  whole_batch: no sequence can be skipped.
-static void mfma_launch_shape(const ts_problem* p, int G, bool dense, bool whole_batch, ScoreArgs* a, long* wg_out) {
+// 131072 tokens 49 us with one tile per wave, 45.7 us with two).
+enum Scan { kScanTested, kScanMasked, kScanWhole };   // the cache test runs in the launch; a skip mask; every sequence
+static void mfma_launch_shape(const ts_problem* p, int G, bool dense, Scan scan, ScoreArgs* a, long* wg_out) {
+  const bool whole_batch = scan == kScanWhole;
   a->HB = G <= 4 ? 8 : 4; a->hb_shift = ilog2(a->HB); a->NU = p->num_kv_heads / a->HB;
   a->uniform_page = p->page_size >= (8 / a->HB);
   const long ntt = (p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens;
@@ -256,24 +258,45 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, bool whole
     // for the score matrix's rows, four times as many bytes (the 32: 118.8 -> 147.5).
     if (!dense && whole_batch && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
   }
-  // A batch that no mask or cache test can thin out shares a grid of two workgroups per CU (shared_share) from more work on than a
-  // tile for each wave of such a grid: up to there every wave of the other grid has its tile at once, and the sharing out costs
-  // a microsecond (16 sequences of 683 to 2048 tokens, H 32/8, 12.9 and 13.5 us; 16 of 1533 to 4600 25.6 and 20.6).  Three
-  // workgroups per CU are slower (32 of 1031 to 16001 tokens 97.6 and 105 us); the runs are as long as a wave's tiles can be, while
-  // two workgroups' LDS allows.
-  const bool flat = whole_batch && p->batch >= 2 && p->batch <= kScoreFlatMaxBatch && g_codes_rr <= 0 && g_score_wg <= 0 &&
-                    wgs_of(1) * p->batch > kScoreFlatWg;
-  if (flat) {
-    const long most = (p->batch * ntt / (kScoreFlatWg - p->batch) * NU + 3) / 4 + 1;   // tiles of a wave
-    rr = dense ? 2 : 8;
-    if (rr > most) rr = (int)most;
+  // A batch whose lengths and mask are known when the launch starts shares one grid (shared_share) from more work on than a tile for
+  // each wave of two workgroups per CU: up to there every wave of the other grid has its tile at once, and the sharing out
+  // costs half a microsecond (16 sequences of 683 to 2048 tokens, H 32/8, 12.9 and 13.5 us; 16 of 1533 to 4600 25.6 and 20.6).
+  // Beyond one round of a tile per wave two workgroups per CU share the work, at head size 64, with its rows of half the length,
+  // three (32 of 1031 to 16001 tokens of 32/8, D 128, 97.6 us, with three per CU 105; D 64, 112 batches of 3 to 32 sequences
+  // 1.05 times as fast as in a grid of their own, 1.01 with two per CU; D 128, 56 batches 1.06).  The staged runs are as long as
+  // a wave's tiles can be, while two workgroups' LDS allows.  With a mask the statistics keep the runs found above (of none of
+  // the sequences 1.08, of half of them 1.05 to 1.1 times as fast).
+  const int groups = 4 / NU;
+  const long slots = kScoreFlatWg - p->batch, sr = rr;
+  a->SR = rr;
+  bool shares = scan != kScanTested && p->batch >= 2 && p->batch <= kScoreFlatMaxBatch && g_codes_rr <= 0 && g_score_wg <= 0 &&
+                wgs_of(1) * p->batch > kScoreFlatWg;
+  if (shares && scan == kScanMasked) {
+    const long units = (p->batch * ((ntt + groups * sr - 1) / (groups * sr)) + slots - 1) / slots;   // of a workgroup, at most
+    a->run_stat_bytes = (int)(units * groups * p->num_q_heads * sizeof(float2));
+    shares = wgs_of(rr) < kScoreMaxWg && units <= 64 && a->run_stat_bytes <= 16384;   // one run per wave of a call of its own
+    if (shares) rr = (int)(units * sr < 8 ? units * sr : 8);
+    else a->run_stat_bytes = 0;
+  } else if (shares) {
+    const long most = (p->batch * ntt / slots * NU + 3) / 4 + 1;   // tiles of a wave
+    rr = (int)(most < 8 ? most : 8);
+  }
+  if (shares) {
+    if (dense) rr = rr >= 4 ? 2 : 1;                       // rows of floats: four times the LDS
+    while (rr > 1 && score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) + a->run_stat_bytes > 81920) --rr;
   }
   if (rr > 8) rr = 8;
   while (rr > 1 && score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) > 163840) --rr;
   a->RR = rr;
   long wgl = wgs_of(rr);
   if (g_score_wg > 0) wgl = g_score_wg;
-  if (flat) { a->flat_batch = p->batch; wgl = kScoreFlatWg; }
+  if (shares) {
+    const long lds = (long)score_codes_mfma_lds_bytes(p->head_dim, G, rr, dense) + a->run_stat_bytes;
+    long per_cu = 163840 / lds, most = p->head_dim == 64 ? 4 : 3;            // registers
+    if (per_cu > most) per_cu = most;
+    a->flat_batch = p->batch; wgl = 256 * per_cu;
+    a->flat_wgs = p->head_dim == 64 && wgl > 512 ? 768 : kScoreFlatWg;
+  }
   *wg_out = wgl;
 }
 
@@ -283,15 +306,16 @@ static dim3 mfma_grid(const ts_problem* p, const ScoreArgs& a, long wgl) {
 
 // Partials per sequence that a score launch of this shape leaves (workgroups it runs with; at most, where a batch shares them):
 // what the statistics merge loads before it has seen the count in the workspace.
-static int expected_parts(const ts_problem* p, bool dense, bool whole_batch) {
+static int expected_parts(const ts_problem* p, bool dense, const uint8_t* skip) {
   const int G = p->num_q_heads / p->num_kv_heads;
   if ((dense ? g_score_variant == 2 : true) && g_codes_mfma && (p->num_q_heads % 4) == 0 &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     ScoreArgs a{};
     long wgl = 0;
-    mfma_launch_shape(p, G, dense, whole_batch, &a, &wgl);
-    const long most = ((long)(p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens * a.NU + 3) / 4;   // a tile per wave at least
-    return (int)(a.flat_batch > 0 && most < wgl ? most : wgl);
+    mfma_launch_shape(p, G, dense, skip == nullptr ? kScanWhole : kScanMasked, &a, &wgl);
+    const long ntt = (p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens, grain = skip == nullptr ? 1 : a.SR;
+    const long most = ((ntt + grain - 1) / grain * a.NU + 3) / 4;   // units, or workgroups of a tile per wave
+    return (int)(a.flat_batch > 0 && (skip != nullptr || most < wgl) ? most : wgl);
   }
   return score_workgroups(p);
 }
@@ -330,9 +354,9 @@ static int32_t paged_qk_scores_impl(const ts_problem* p, const void* q, const ts
   if (g_score_variant == 2 && g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)scores & 3) == 0) &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, true, skip == nullptr && sc == nullptr, &a, &wgl);
+    mfma_launch_shape(p, G, true, sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole, &a, &wgl);
     const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, mfma_grid(p, a, wgl),
-                                                 score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, true), (hipStream_t)stream);
+                                                 score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, true) + a.run_stat_bytes, (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
   a.vec_store = (p->num_q_heads % 4 == 0) && ((a.HB * G) % 4 == 0) && (((uintptr_t)scores & 15) == 0);
@@ -371,14 +395,14 @@ static int32_t paged_qk_codes_impl(const ts_problem* p, const void* q, const ts_
   if (g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)codes & 3) == 0) &&
       score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, false, skip == nullptr && sc == nullptr, &a, &wgl);
+    mfma_launch_shape(p, G, false, sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole, &a, &wgl);
     // Bytes and block maxima that fit the chip's L2 (eight XCDs x 4 MiB) with room to spare stay there as dirty lines
     // until the kernel ends and cost the read stream nothing; more than that thrashes it, and streaming them past the
     // L2 is the cheaper way (measured, H 28/4: 524288 tokens 89.2 us cached / 90.2 streamed, 786432 tokens 142.0 / 135.7,
     // 1048576 tokens 184.5 / 176.1; H 32/8: 524288 tokens 167.4 / 168.7, 786432 tokens 267.4 / 254.4)
     a.nt_codes = (double)p->batch * p->max_seq_len * p->num_q_heads * 1.125 > 20.0 * 1048576.0;
     const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, mfma_grid(p, a, wgl),
-                                                 score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, false), (hipStream_t)stream);
+                                                 score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, false) + a.run_stat_bytes, (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
   a.vec_store = (p->num_q_heads % 4 == 0) && ((a.HB * G) % 4 == 0) && (((uintptr_t)codes & 3) == 0);
@@ -420,7 +444,7 @@ int32_t ts_soft_vote_bounds(const ts_problem* p, const uint8_t* codes, float sco
   a.scale = score_scale;
   VoteArgs m{};
   m.partials = (const float*)((uint8_t*)ws + w.score_partials); m.hdr = a.hdr;
-  m.row_stats_out = row_stats; m.skip = skip; m.parts_hint = expected_parts(p, false, skip == nullptr); m.H = p->num_q_heads; m.scale = score_scale;
+  m.row_stats_out = row_stats; m.skip = skip; m.parts_hint = expected_parts(p, false, skip); m.H = p->num_q_heads; m.scale = score_scale;
   if (launch_stats_merge(m, p->batch, (hipStream_t)stream) != hipSuccess) return TS_ERR_HIP;
   return launch_vote_bounds(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
@@ -473,7 +497,7 @@ int32_t ts_soft_vote(const ts_problem* p, const float* scores, float score_scale
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip == nullptr);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip);
   return launch_soft_vote(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
@@ -490,7 +514,7 @@ int32_t ts_soft_vote_ranked(const ts_problem* p, const float* scores, float scor
   a.partials = (const float*)((uint8_t*)ws + w.score_partials); a.hdr = (const uint32_t*)((uint8_t*)ws + w.hdr);
   a.scores = scores; a.row_stats = row_stats; a.row_stats_out = row_stats; a.votes = votes; a.seq_lens = p->seq_lens; a.skip = skip;
   a.H = p->num_q_heads; a.max_seq_len = p->max_seq_len; a.scale = score_scale;
-  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip == nullptr);
+  a.n_init = p->num_initial; a.n_local = p->num_local; a.parts_hint = expected_parts(p, true, skip);
   a.rank_hist = (uint32_t*)((uint8_t*)ws + w.bound_hist);
   return launch_soft_vote_ranked(a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
 }

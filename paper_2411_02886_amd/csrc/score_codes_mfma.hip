@@ -32,25 +32,38 @@ typedef __attribute__((ext_vector_type(8))) __bf16 mfma_bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float mfma_f32x4_t;
 
 // What a wave scans: run n of its tiles starts at tile base + n * stride of sequence b, whose x-th of n workgroups this is.
-struct ScoreShare { int b, x, n, N, indptr, base, stride, tiles; };
+// uw: units of a workgroup, whose statistics leave one by one (masked calls).
+struct ScoreShare { int b, x, n, N, indptr, base, stride, tiles, uw; };
 
-// A call that scans every sequence of its batch hands the workgroups of a one-dimensional grid out here, where the lengths are
-// known: each takes tpw consecutive tiles of one sequence (its waves equal parts of them), tpw the fewest with which the grid serves
-// all.  In a grid of (workgroups of the longest, sequences) those with work are the first of each row, which is the first XCDs' part of
-// it: they read on when the others have finished, and every XCD can take only its share of the memory's rate.  (32 sequences of
-// 1031 to 16001 tokens, H 32/8: 112 -> 98 us; 32 of 12500 146 -> 130; 2 of 66667 to 200000 102 -> 90; H 28/4, 5 of 26667 to 80000
-// 57 -> 50.)
+// The workgroups of a one-dimensional grid are handed out here, where the lengths are known: each takes upw consecutive units of one
+// sequence (a unit is a tile; its waves take equal parts), upw the fewest that serve all.  In a grid of (workgroups of the
+// longest, sequences) those with work are the first of each row, which is the first XCDs' part of it: they read on when the
+// others have finished, and every XCD can take only its share of the memory's rate.  (32 sequences of 1031 to 16001 tokens, H 32/8:
+// 112 -> 98 us; 32 of 12500 146 -> 130; 2 of 66667 to 200000 102 -> 90; H 28/4, 5 of 26667 to 80000 57 -> 50.)
 // Every sequence gets a workgroup, an empty one too: its statistics are those of no score.  False: nothing left for this one.
+// MASKED: a skip mask leaves sequences out.  What a sequence's statistics are to the last bit must not depend on the others then, so
+// they are formed as in a call of its own: in units of one run of a.SR tiles per wave of such a call's workgroups.  A workgroup
+// takes uw whole units, its waves uw consecutive runs each, and every unit leaves its partial.  (8 sequences of 24000 to 32000 tokens, H
+// 32/8: all of them 82 -> 72 us, five 52 -> 50, one 13.9 -> 14.7; H 64/8, 12000 to 37000: 104 -> 80, 68 -> 52, 22 -> 11.)
+template <bool MASKED>
 __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, ScoreShare& s) {
   const int lane = threadIdx.x & 63, B = a.flat_batch;
   const int len_any = a.seq_lens[min(lane, B - 1)], ptr = a.page_indptr[min(lane, B - 1)];
-  const int len = lane < B ? min(max(len_any, 0), a.max_seq_len) : 0;
+  const bool scanned = lane < B && !(MASKED && a.skip[min(lane, B - 1)] != 0);
+  const int len = scanned ? min(max(len_any, 0), a.max_seq_len) : 0;
   const uint32_t ntt = (uint32_t)(len + kScoreTileTokens - 1) / kScoreTileTokens;
-  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(ntt), 63);
   const uint32_t groups = 4 / a.NU;                        // waves that share a tile range
-  const uint32_t slots = gridDim.x - (uint32_t)B;          // the sequences' counts are rounded up
-  const uint32_t tpw = max((total + slots - 1) / slots, groups);
-  const uint32_t cnt = lane < B ? max((ntt + tpw - 1) / tpw, 1u) : 0u;
+  const uint32_t grain = MASKED ? groups * (uint32_t)a.SR : 1u;   // tiles of a unit
+  const uint32_t units = (ntt + grain - 1) / grain;
+  // The grid is what the chip holds at a time.  If that is enough for a tile (a run) per wave, so be it; else two workgroups per CU
+  // share the work, the rest of the grid leaves.
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(units), 63);
+  const uint32_t least = MASKED ? 1u : groups;
+  const uint32_t wgs = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(scanned ? max((units + least - 1) / least, 1u) : 0u), 63);
+  const uint32_t slots = (uint32_t)a.flat_wgs - (uint32_t)B;   // the sequences' counts are rounded up
+  const uint32_t share = (total + slots - 1) / slots;
+  const uint32_t upw = wgs <= gridDim.x ? least : max((share + least - 1) / least * least, least);   // the waves' parts are equal
+  const uint32_t cnt = scanned ? max((units + upw - 1) / upw, 1u) : 0u;
   const uint32_t incl = wave_inclusive_scan(cnt);
   const int b = __popcll(__builtin_amdgcn_ballot_w64(incl <= blockIdx.x));
   if (b >= B) return false;
@@ -59,9 +72,17 @@ __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, Score
   s.x = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, b) - s.n);
   s.N = __builtin_amdgcn_readlane(len, b);
   s.indptr = __builtin_amdgcn_readlane(ptr, b);
-  const int t0 = s.x * (int)tpw, have = min((int)tpw, __builtin_amdgcn_readlane((int)ntt, b) - t0);
-  const int part = wave / a.NU, lo = have * part / (int)groups, hi = have * (part + 1) / (int)groups;
-  s.base = t0 + lo; s.stride = a.RR; s.tiles = hi - lo;
+  const int ntt_b = __builtin_amdgcn_readlane((int)ntt, b), part = wave / a.NU;
+  s.stride = a.RR; s.uw = (int)upw;
+  if (MASKED) {
+    const int per = (int)upw * a.SR;                       // tiles of a wave
+    s.base = s.x * (int)(upw * grain) + part * per;
+    s.tiles = min(max(ntt_b - s.base, 0), per);
+  } else {
+    const int t0 = s.x * (int)upw, have = min((int)upw, ntt_b - t0);
+    const int lo = have * part / (int)groups, hi = have * (part + 1) / (int)groups;
+    s.base = t0 + lo; s.tiles = hi - lo;
+  }
   return true;
 }
 
@@ -79,9 +100,9 @@ __device__ __forceinline__ void own_tiles(const ScoreArgs& a, int wave, ScoreSha
 
 // G in 3..4: CP = 4, column block = 4 KV heads, wave tile = 8 KV heads.  G in 5..8: CP = 8, 2 and 4.
 // DENSE: Algorithm 2's score matrix itself leaves the chip (fp32 rows, ts_paged_qk_scores) instead of the bytes.
-// SHARED: the sequences share a one-dimensional grid (shared_share).
+// SHARE: 0 a grid of (workgroups, sequences), 1 and 2 the sequences share a one-dimensional grid, 2 with a skip mask (shared_share).
 // SUMS: how the products along D are added up; taken for the shapes with five to eight heads that have more than one wave tile side by side.
-template <int D, int G, bool DENSE, bool SHARED, bool SUMS>
+template <int D, int G, bool DENSE, int SHARE, bool SUMS>
 __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   constexpr int RB = D * 2;            // bytes per K row
   constexpr int L = RB / 128;          // 16-byte loads per lane per row
@@ -112,8 +133,9 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   const int j = lane & 7, r = lane >> 3;
   const int mrow = lane & 15, kg = lane >> 4;            // MFMA row / column and k-group of this lane
   ScoreShare sh;
+  constexpr bool SHARED = SHARE != 0, MASKED = SHARE == 2;
   if (SHARED) {
-    if (!shared_share(a, wave, sh)) return;
+    if (!shared_share<MASKED>(a, wave, sh)) return;
   } else {
     sh.b = blockIdx.y; sh.x = blockIdx.x; sh.n = gridDim.x;
     sh.N = min(max(a.seq_lens[sh.b], 0), a.max_seq_len);
@@ -391,6 +413,8 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
   // One register buffer is enough: once a block sits in LDS its registers are free, and the next block's loads go
   // out before the matrix cores touch the current one.
   int issued = 1;
+  float2* run_stat = reinterpret_cast<float2*>(smem8 + (size_t)4 * wave_bytes);   // masked: [run of the workgroup][H]
+  int c_s = 0, c_run = (wave / a.NU) * sh.uw;                   // tiles of the run that is being summed, its place
   for (int tile = 0; tile < my_tiles; ++tile) {
 #pragma unroll
     for (int bb = 0; bb < NBLK; ++bb) {
@@ -401,12 +425,44 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
       wave_lds_sync();
     }
     finish_tile(c_r, tile_of(c_n, c_r) * TT);
+    if (MASKED && (++c_s == a.SR || tile + 1 == my_tiles)) {
+      if (kg == 0 && col_ok) {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) run_stat[c_run * H + h_base + (cb * KB + kvo) * G + gq] = make_float2(wm[cb], wl[cb]);
+      }
+      wm[0] = wm[1] = -INFINITY; wl[0] = wl[1] = 0.f;
+      c_s = 0; ++c_run;
+    }
     if (c_r + 1 == RR || tile + 1 == my_tiles) {
       flush_run(tile_of(c_n, 0), c_r + 1);
       c_r = 0; ++c_n;
     } else {
       ++c_r;
     }
+  }
+  if (MASKED) {
+    // ---- one partial per unit and head, merged as the waves of a workgroup of its own merge theirs below
+    __syncthreads();
+    const int groups = 4 / a.NU, ntt_runs = (ntt + a.SR - 1) / a.SR, unit0 = sh.x * sh.uw;
+    const int nunit = (ntt_runs + groups - 1) / groups;         // of the sequence
+    for (int i = threadIdx.x; i < sh.uw * H; i += 256) {
+      const int un = i / H, h = i - un * H, r0 = (unit0 + un) * groups;
+      if (r0 >= ntt_runs && unit0 + un > 0) continue;           // an empty sequence leaves one partial of no score
+      const int nr = min(groups, ntt_runs - r0);
+      float m = -INFINITY, l = 0.f;
+      for (int w = 0; w < nr; ++w) m = fmaxf(m, run_stat[(un * groups + w) * H + h].x);
+      for (int w = 0; w < nr; ++w) {
+        const float2 e = run_stat[(un * groups + w) * H + h];
+        l += (e.x == -INFINITY) ? 0.f : e.y * __builtin_amdgcn_exp2f(c2 * (e.x - m));
+      }
+      float* pp = a.partials + (((size_t)b * kScoreMaxWg + unit0 + un) * H + h) * 2;
+      pp[0] = m; pp[1] = l;
+    }
+    if (sh.x == 0 && threadIdx.x == 0) {
+      a.hdr[b * 8 + 0] = max(nunit, 1);
+      a.hdr[b * 8 + 2] = __float_as_uint(a.scale);
+    }
+    return;
   }
   // ---- one (max, sum-exp) partial per workgroup and head, as the vector kernels leave it
   __syncthreads();                                        // every wave is done with its LDS region
@@ -456,9 +512,9 @@ size_t score_codes_mfma_lds_bytes(int D, int G, int RR, bool dense) {
   return 4 * per_wave;
 }
 
-template <int D, int G, bool DENSE, bool SHARED, bool SUMS>
+template <int D, int G, bool DENSE, int SHARE, bool SUMS>
 static hipError_t launch_cm(const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-  const auto kernel = &score_codes_mfma_kernel<D, G, DENSE, SHARED, SUMS>;
+  const auto kernel = &score_codes_mfma_kernel<D, G, DENSE, SHARE, SUMS>;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -472,9 +528,11 @@ static hipError_t launch_cm(const ScoreArgs& a, dim3 grid, size_t lds, hipStream
 
 template <int D, int G, bool SUMS>
 static hipError_t launch_cm_form(const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-  const bool shared = a.flat_batch > 0;
-  if (a.codes == nullptr) return shared ? launch_cm<D, G, true, true, SUMS>(a, grid, lds, s) : launch_cm<D, G, true, false, SUMS>(a, grid, lds, s);
-  return shared ? launch_cm<D, G, false, true, SUMS>(a, grid, lds, s) : launch_cm<D, G, false, false, SUMS>(a, grid, lds, s);
+  const int share = a.flat_batch == 0 ? 0 : a.skip == nullptr ? 1 : 2;
+#define TS_SHARE(DENSE) return share == 0 ? launch_cm<D, G, DENSE, 0, SUMS>(a, grid, lds, s) : share == 1 ? launch_cm<D, G, DENSE, 1, SUMS>(a, grid, lds, s) : launch_cm<D, G, DENSE, 2, SUMS>(a, grid, lds, s)
+  if (a.codes == nullptr) TS_SHARE(true);
+  TS_SHARE(false);
+#undef TS_SHARE
 }
 
 template <int G>

@@ -11,7 +11,7 @@ constexpr int kWave = 64;
 constexpr int kScoreTileTokens = 32;   // tokens per wave tile in the score pass
 constexpr int kScoreLdsStride = 36;    // floats per head row of the staged score tile (16 B aligned)
 constexpr int kScoreMaxWg = 1024;      // upper bound on workgroups per sequence in the score pass
-constexpr int kScoreFlatWg = 512;      // workgroups that the sequences of a batch share in the score pass: two per CU
+constexpr int kScoreFlatWg = 512;      // two workgroups per CU: from more one-tile work on the sequences of a batch share a grid in the score pass
 constexpr int kScoreFlatMaxBatch = 64; // ... that is, so many sequences: one per lane
 constexpr int kTopkBins = 2048;        // 11-bit radix digit
 constexpr int kTopkChunk = 2048;       // keys per workgroup in the top-k passes

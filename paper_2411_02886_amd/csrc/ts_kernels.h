@@ -18,6 +18,9 @@ struct ScoreArgs {
   int uniform_page;       // every step of a wave reads one page (P >= tokens per step)
   int vec_store;          // score rows can be written as 16-byte pieces
   int RR;                 // consecutive tiles a wave stages in LDS and writes out as one run (1, 2 or 4)
+  int SR;                 // ... shared by a batch with a skip mask: tiles of a run whose statistics a call of the sequence alone would keep together
+  int flat_wgs;           // workgroups that a batch shares where a tile per wave would be more than one round of them
+  int run_stat_bytes;     // LDS for the statistics of such runs, behind the waves' regions
   int flat_batch;         // matrix-core kernel: > 0 the batch, whose sequences share a one-dimensional grid; 0: grid.y is the sequence
   int n_init, n_local;    // forced tokens: the statistics cover [min(n_init, N), max(that, N - n_local)) only
   float scale, c2;        // score_scale and score_scale * log2(e)

@@ -57,3 +57,40 @@ def test_batches_that_share_the_grid(gpu, H, H_kv, D, P, lens, k):
         layer, q = make_layer(w, num_initial=ni, num_local=nl)
         print("shared score grid", H, H_kv, D, P, len(lens), max(lens), ni, nl, flush=True)
         check_compact(w, layer, q, score_scale=1.0, label="shared %dx%d" % (len(lens), max(lens)))
+
+
+@pytest.mark.parametrize("compact", [False, True], ids=["five-call", "compact"])
+@pytest.mark.parametrize("H,H_kv,D,P,lens,max_len", [
+    (32, 8, 64, 16, [12000, 0, 9000, 1, 31, 12100, 127, 5000], 12100), (28, 4, 64, 16, [7000] * 9 + [129, 6999], 7000),
+    (64, 8, 64, 1, [9000, 40, 8000, 33, 64, 1], 9000), (64, 16, 64, 16, [4200, 65, 4100, 63], 4200),
+    # runs of several tiles: the length that the sequences may have decides
+    (32, 8, 64, 16, [9000, 257, 0, 700], 150000), (40, 8, 128, 16, [5000, 2049, 31], 70000), (24, 8, 128, 16, [3000, 100], 300000)])
+def test_masked_batches_leave_the_statistics_of_each_sequence_alone(gpu, compact, H, H_kv, D, P, lens, max_len):
+    """A skip mask or a batch around it changes nothing of a sequence: statistics, index set and count are those of a call of its
+    own, bit for bit, and the skipped ones keep theirs."""
+    from paper_2411_02886_amd.runtime import to_host
+    from paper_2411_02886_amd.runtime import DecodeLayer
+    w = W.make_workload("masked", dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=P, B=len(lens), seq_lens=lens, k=60, beta=2.5, planted_per_head=0, seed=len(lens) + H)
+    layer, q = make_layer(w, max_seq_len=max_len)
+
+    def select(L, q, skip):
+        L.idx.fill_(-7); L.count.fill_(-7); L.row_stats.fill_(-3.0)
+        (L.select_compact if compact else L.select)(q, 1.0, skip)
+        torch.cuda.synchronize()
+        return [to_host(x).copy() for x in (L.row_stats, L.idx, L.count)]
+    alone = []
+    for b in range(len(lens)):
+        one = DecodeLayer(dtype=w.dtype, H=H, H_kv=H_kv, D=D, P=P, k=w.k, k_pool=w.k_pool, v_pool=w.v_pool, page_indptr=np.array([0, len(w.pages_of(b))], np.int32),
+                          page_indices=w.pages_of(b) if lens[b] else np.zeros(1, np.int32), seq_lens=[lens[b]], max_seq_len=max_len)
+        alone.append(select(one, q[b:b + 1].contiguous(), None))
+    rng = np.random.default_rng(7)
+    masks = [[0] * len(lens)] + [list(rng.integers(0, 2, len(lens))) for _ in range(3)] + [[1] * len(lens)]
+    for mask in masks:
+        print("masked", H, H_kv, D, mask, flush=True)
+        got = select(layer, q, torch.tensor(mask, dtype=torch.uint8, device=q.device))
+        for b in range(len(lens)):
+            if mask[b]:
+                assert (got[0][b] == -3.0).all() and (got[1][b] == -7).all() and got[2][b] == -7, (mask, b)
+            else:
+                for x, y in zip(got, alone[b]):
+                    assert np.array_equal(x[b], y[0], equal_nan=True), (mask, b)
