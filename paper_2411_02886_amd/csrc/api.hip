@@ -750,6 +750,10 @@ int32_t ts_sparse_paged_attn(const ts_problem* p, const void* q, const int32_t* 
     a.nsplit = (total + a.span - 1) / a.span;
     return launch_sparse_attn_stream(p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
   }
+  if (attn_whole(p->dtype, p->head_dim, G, pairs, total)) {
+    a.whole = 1; a.span = kAttnWhole; a.nsplit = 1; a.nch = 1;
+    return launch_sparse_attn_decode(p->dtype, p->head_dim, G, a, p->batch, (hipStream_t)stream) == hipSuccess ? TS_OK : TS_ERR_HIP;
+  }
   // chunks per workgroup: one while the chunks alone are few workgroups (a latency problem), four when there are many
   // thousands (the next chunk's rows are in flight while a chunk is worked on)
   a.nch = w.attn_nsplit * pairs >= 8192 ? kAttnMaxRun : 1;

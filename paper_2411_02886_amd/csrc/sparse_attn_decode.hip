@@ -28,28 +28,54 @@ template <> __device__ __forceinline__ void unpack16<TS_BF16>(uint4 w, float* f)
   f[4] = bf16_lo(w.z); f[5] = bf16_hi(w.z); f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
 }
 
+template <int DT> __device__ __forceinline__ void store_out(uint8_t* out, size_t i, float v) {
+  if (DT == TS_BF16) reinterpret_cast<uint16_t*>(out)[i] = (uint16_t)f32_to_bf16_bits(v);
+  else reinterpret_cast<float*>(out)[i] = v;
+}
+
+// sum over the lanes of a wave whose numbers differ in the bits from LPR on, by the swaps of half and quarter waves
+template <int LPR>
+__device__ __forceinline__ float row_group_sum(float v) {
+  if (LPR <= 8) v += __shfl_xor(v, 8);
+  if (LPR <= 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if (LPR <= 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  return v;
+}
+
 // MULTI: a workgroup takes up to kAttnMaxRun consecutive chunks of 64 tokens (a.nch of them) and folds them into one
 // partial with a running (max, sum): the next chunk's K and V rows are in flight while the current chunk is worked
 // on.  For batches whose splits alone give thousands of workgroups the step is a throughput problem, and a workgroup
 // that loads, then computes, then leaves keeps the memory system busy about half of its life; a plain random gather
 // of 256-byte pieces from the same pools runs at 5.9 TB/s.  With few workgroups (one sequence) the single-chunk form
 // stays: there the chain of one workgroup is the latency that counts.
-template <int DT, int D, int G, bool MULTI>
-__global__ __launch_bounds__(256) void sparse_attn_decode_kernel(AttnArgs a) {
+// WAVES 16: the whole list of a pair, 256 entries at most, by one workgroup, which writes the output itself: no partials, no merge
+// launch.  One sequence of 256 tokens, fp32 H 8/2, D 64: 4.6 + 4.2 -> 6.2 us; up to 256 pairs, one per CU, 16 to 256 entries:
+// 1.02 to 2 times as fast over 380 shapes, with more pairs slower (2048 of H 16/16, D 64, 64 entries 13.6 and 26.0).
+template <int DT, int D, int G, bool MULTI, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void sparse_attn_decode_kernel(AttnArgs a) {
+  constexpr int T = 64 * WAVES;
+  constexpr bool WHOLE = WAVES == 16;
   constexpr int ES = AElt<DT>::size;
   constexpr int RB = D * ES;
   constexpr int L = RB / 128;          // 16-byte K loads per lane per row (eight lanes per row)
   constexpr int EPL = 16 / ES;         // elements per 16-byte piece
   constexpr int LPR = RB / 16;         // lanes per V row
   constexpr int RPL = 64 / LPR;        // V rows per wave load
-  constexpr int CH = kAttnChunk;       // selected tokens per chunk
-  constexpr int WT = CH / 4;           // tokens per wave and chunk
+  constexpr int CH = 16 * WAVES;       // selected tokens per chunk: kAttnChunk, or the whole list
+  constexpr int WT = CH / WAVES;       // tokens per wave and chunk
   constexpr int KS = WT / 8;           // K steps per wave (eight rows each)
   constexpr int VS = WT / RPL;         // V loads per lane
   constexpr int NSL = MULTI ? kAttnMaxRun * CH : CH;
   __shared__ long long s_slot[NSL];
   __shared__ float s_p[G][CH];
-  __shared__ __attribute__((aligned(16))) float s_red[4 * (64 / (D * AElt<DT>::size / 16))][G][D];   // [wave x row group][head][d]
+  constexpr int RPW = WHOLE ? 1 : RPL; // partial rows a wave leaves: of all its row groups, or their sum
+  __shared__ __attribute__((aligned(16))) float s_red[WAVES * RPW][G][D];   // [wave x row group][head][d]
   __shared__ float s_ml[G][3];         // running max, running sum, factor that rescales what was summed before this chunk
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -64,7 +90,10 @@ __global__ __launch_bounds__(256) void sparse_attn_decode_kernel(AttnArgs a) {
   const int j0 = split * span;
   const int nj = min(max(total - j0, 0), span);
   if (nj <= 0) {                       // nothing attended in this split: publish an empty partial
-    if (threadIdx.x < G) {
+    if (WHOLE) {
+      for (int i = threadIdx.x; i < G * D; i += T) store_out<DT>(a.out, ((size_t)b * H + kvh * G) * D + i, 0.f);
+      if (threadIdx.x < G && a.lse != nullptr) a.lse[(size_t)b * H + kvh * G + threadIdx.x] = -INFINITY;
+    } else if (threadIdx.x < G) {
       float* ml = a.part_ml + (((size_t)b * H + kvh * G + threadIdx.x) * a.nsplit + split) * 2;
       ml[0] = -INFINITY; ml[1] = 0.f;
     }
@@ -168,7 +197,28 @@ __global__ __launch_bounds__(256) void sparse_attn_decode_kernel(AttnArgs a) {
 
     // ---- softmax of the chunk against the running maximum: eight lanes per head, eight tokens per lane, the lanes of
     // a head meet through DPP
-    if (threadIdx.x < G * 8) {
+    if (WHOLE) {
+      // a wave per head, CH / 64 tokens per lane
+      constexpr int TPL = CH / 64 > 0 ? CH / 64 : 1;
+      if (wave < G) {
+        float x[TPL];
+        float m = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < TPL; ++e) { x[e] = s_p[wave][lane + 64 * e]; m = fmaxf(m, x[e]); }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+        float l = 0.f;
+#pragma unroll
+        for (int e = 0; e < TPL; ++e) {
+          const float p = (x[e] == -INFINITY) ? 0.f : expf(x[e] - m);
+          s_p[wave][lane + 64 * e] = p;
+          l += p;
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) l += __shfl_xor(l, o);
+        if (lane == 0) { s_ml[wave][0] = m; s_ml[wave][1] = l; }
+      }
+    } else if (threadIdx.x < G * 8) {
       constexpr int TPL = CH / 8;                  // tokens per lane
       const int g = threadIdx.x >> 3, part = threadIdx.x & 7;
       float x[TPL];
@@ -205,6 +255,10 @@ __global__ __launch_bounds__(256) void sparse_attn_decode_kernel(AttnArgs a) {
       const int jl = wave * WT + it * RPL + rsub;
       float vf[EPL];
       unpack16<DT>(cur.v[it], vf);
+      if (WHOLE && s_slot[jl] < 0) {                 // most of a short list is padding: its first row, which may hold an infinity
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) vf[e] = 0.f;
+      }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float p = s_p[g][jl];        // 0 for padding rows
@@ -216,24 +270,40 @@ __global__ __launch_bounds__(256) void sparse_attn_decode_kernel(AttnArgs a) {
   }
   // lanes with the same piece but different rsub hold partial sums of the same outputs: all of them go to LDS (16-byte
   // stores) and meet there -- a cross-lane exchange of the G * EPL accumulators costs more LDS operations than that,
-  // and one strip per wave filled by the row groups in turn (a quarter of the LDS) costs 1-2 us of latency
+  // and one strip per wave filled by the row groups in turn (a quarter of the LDS) costs 1-2 us of latency.  Sixteen waves' strips
+  // would not fit beside each other: they exchange.
+  if (WHOLE) {
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int e4 = 0; e4 < EPL / 4; ++e4)
-      *reinterpret_cast<float4*>(&s_red[wave * RPL + rsub][g][piece * EPL + e4 * 4]) =
-          make_float4(acc[g][e4 * 4], acc[g][e4 * 4 + 1], acc[g][e4 * 4 + 2], acc[g][e4 * 4 + 3]);
+      for (int e = 0; e < EPL; ++e) acc[g][e] = row_group_sum<LPR>(acc[g][e]);
+  }
+  if (!WHOLE || rsub == 0) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e4 = 0; e4 < EPL / 4; ++e4)
+        *reinterpret_cast<float4*>(&s_red[wave * RPW + (WHOLE ? 0 : rsub)][g][piece * EPL + e4 * 4]) =
+            make_float4(acc[g][e4 * 4], acc[g][e4 * 4 + 1], acc[g][e4 * 4 + 2], acc[g][e4 * 4 + 3]);
+  }
   __syncthreads();
-  for (int i = threadIdx.x; i < G * D; i += 256) {
+  const size_t hb0 = (size_t)b * H + kvh * G;
+  for (int i = threadIdx.x; i < G * D; i += T) {
     const int g = i / D, d = i % D;
     float o = 0.f;
 #pragma unroll
-    for (int r4 = 0; r4 < 4 * RPL; ++r4) o += s_red[r4][g][d];
-    a.part_out[(((size_t)b * H + kvh * G + g) * a.nsplit + split) * D + d] = o;
+    for (int r4 = 0; r4 < WAVES * RPW; ++r4) o += s_red[r4][g][d];
+    if (WHOLE) store_out<DT>(a.out, hb0 * D + i, s_ml[g][1] > 0.f ? o / s_ml[g][1] : 0.f);
+    else a.part_out[((hb0 + g) * a.nsplit + split) * D + d] = o;
   }
   if (threadIdx.x < G) {
-    float* ml = a.part_ml + (((size_t)b * H + kvh * G + threadIdx.x) * a.nsplit + split) * 2;
-    ml[0] = s_ml[threadIdx.x][0]; ml[1] = s_ml[threadIdx.x][1];
+    const float m = s_ml[threadIdx.x][0], l = s_ml[threadIdx.x][1];
+    if (WHOLE) {
+      if (a.lse != nullptr) a.lse[hb0 + threadIdx.x] = l > 0.f ? m + logf(l) : -INFINITY;
+    } else {
+      float* ml = a.part_ml + ((hb0 + threadIdx.x) * a.nsplit + split) * 2;
+      ml[0] = m; ml[1] = l;
+    }
   }
 }
 
@@ -298,21 +368,24 @@ __global__ __launch_bounds__(D * kMergeGroups) void sparse_attn_merge_kernel(Att
 #pragma unroll
   for (int gg = 0; gg < kMergeGroups; ++gg) o += s_o[gg][d];
   const float res = Lsum > 0.f ? o / Lsum : 0.f;
-  if (DT == TS_BF16) reinterpret_cast<uint16_t*>(a.out)[hb * D + d] = (uint16_t)f32_to_bf16_bits(res);
-  else reinterpret_cast<float*>(a.out)[hb * D + d] = res;
+  store_out<DT>(a.out, hb * D + d, res);
   if (d == 0 && a.lse != nullptr) a.lse[hb] = Lsum > 0.f ? M + logf(Lsum) : -INFINITY;
 }
 
 template <int DT, int D>
 static hipError_t attn_launch_g(int G, const AttnArgs& a, dim3 grid, hipStream_t s) {
-#define TS_CASE(g) case g: if (a.nch > 1) hipLaunchKernelGGL((sparse_attn_decode_kernel<DT, D, g, true>), grid, dim3(256), 0, s, a); \
-                   else hipLaunchKernelGGL((sparse_attn_decode_kernel<DT, D, g, false>), grid, dim3(256), 0, s, a); break;
+  const bool whole = a.whole != 0;
+  if (whole && (!attn_whole_supported(DT, D, G) || a.nsplit != 1 || a.span != kAttnWhole)) return hipErrorInvalidValue;
+#define TS_ATTN(g, MULTI, WAVES) hipLaunchKernelGGL((sparse_attn_decode_kernel<DT, D, g, MULTI, WAVES>), grid, dim3(64 * WAVES), 0, s, a)
+#define TS_CASE(g) case g: if (whole) TS_ATTN(g, false, (attn_whole_supported(DT, D, g) ? 16 : 4)); \
+                   else if (a.nch > 1) TS_ATTN(g, true, 4); else TS_ATTN(g, false, 4); break;
   switch (G) {
     TS_CASE(1) TS_CASE(2) TS_CASE(3) TS_CASE(4) TS_CASE(5) TS_CASE(6) TS_CASE(7) TS_CASE(8)
     default: return hipErrorInvalidValue;
   }
 #undef TS_CASE
-  hipLaunchKernelGGL((sparse_attn_merge_kernel<DT, D>), dim3(a.H, grid.z), dim3(D * kMergeGroups), 0, s, a);
+#undef TS_ATTN
+  if (!whole) hipLaunchKernelGGL((sparse_attn_merge_kernel<DT, D>), dim3(a.H, grid.z), dim3(D * kMergeGroups), 0, s, a);
   return hipGetLastError();
 }
 

@@ -17,6 +17,7 @@ constexpr int kTopkBins = 2048;        // 11-bit radix digit
 constexpr int kTopkChunk = 2048;       // keys per workgroup in the top-k passes
 constexpr int kBoundHistCopies = 8;    // replicas of the lower-bound histogram (same-address atomics are what its flush costs)
 constexpr int kAttnChunk = 64;         // selected tokens per workgroup in sparse attention
+constexpr int kAttnWhole = 256;        // list entries that one workgroup of sixteen waves attends by itself
 constexpr int kAttnMaxRun = 4;        // chunks one attention workgroup folds into its partial, at most (256 list entries: one per thread)
 constexpr int kAttnMaxSplit = 512;     // splits the merge kernel can stage (k <= 32768)
 
@@ -63,6 +64,14 @@ inline bool attn_streams(int G, int D, long pairs, int total) {
   if (wgs >= (D == 128 ? 10240 : 22528)) return true;
   if (total > (G == 2 ? 1536 : 1024) || stream_span(pairs, total) < total) return false;
   return G == 2 || 5 * pairs >= 4 * ((pairs + 255) / 256 * 256);
+}
+
+// Whether one workgroup of sixteen waves attends a pair's whole list: up to kAttnWhole entries, a pair per CU, head counts that the waves
+// have registers and LDS for.  (fp32, D 64, eight heads: 8 pairs of 64 entries 8.1 us in chunks, 8.5 so; 128 pairs 9.4 and 8.7.
+// bf16 lists of three and more heads stream.)
+constexpr bool attn_whole_supported(int dtype, int D, int G) { return dtype == TS_F32 ? (D == 64 || G <= 3) : G < 3; }
+inline bool attn_whole(int dtype, int D, int G, long pairs, int total) {
+  return attn_whole_supported(dtype, D, G) && total <= kAttnWhole && pairs <= 256 && (dtype != TS_F32 || G < 8 || pairs >= 64);
 }
 
 // Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (what the

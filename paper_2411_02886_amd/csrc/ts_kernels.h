@@ -137,6 +137,7 @@ struct AttnArgs {
   int H, H_kv, P, p_shift, idx_stride, nsplit, max_seq_len;
   int n_init, n_local;  // forced tokens attended before / after the selected ones
   int span;             // list entries per split
+  int whole;            // lists of up to kAttnWhole entries: one workgroup of sixteen waves per pair, no merge (nsplit 1)
   int nch;              // chunks of kAttnChunk tokens per workgroup (1 .. kAttnMaxRun); nsplit counts workgroups
   float sm_scale;
 };
