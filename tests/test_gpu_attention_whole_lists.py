@@ -18,6 +18,13 @@ def test_whole_lists(dtype, H, H_kv, D, B, longest, k, ni, nl):
     check_batch(dtype, B, H, H_kv, D, 16, longest, k, ni, nl, None)
 
 
+@pytest.mark.parametrize("dtype,H,H_kv,D,B,longest,k,ni,nl", [(W.F32, 8, 2, 64, 6, 240, 60, 100, 20), (W.F32, 8, 2, 64, 9, 600, 200, 150, 45),
+                                                              (W.F32, 7, 1, 128, 70, 700, 300, 200, 61), (W.BF16, 28, 4, 128, 3, 400, 260, 390, 0)])
+def test_fewer_tokens_than_forced_ones(dtype, H, H_kv, D, B, longest, k, ni, nl):
+    """The list is loaded as if all forced tokens were there; sequences shorter than that (whole list, splits, runs of chunks)."""
+    check_batch(dtype, B, H, H_kv, D, 16, longest, k, ni, nl, None)
+
+
 @pytest.mark.parametrize("dtype,H,H_kv,D", [(W.F32, 8, 2, 64), (W.BF16, 4, 2, 128)])
 def test_an_infinite_value_in_a_short_list(dtype, H, H_kv, D):
     """The list's first row stands in for the padding: an infinity there comes out infinite, and only in its own place."""
