@@ -67,6 +67,32 @@ def test_ranked_pair_agrees_with_the_plain_pair_and_restores_the_workspace(gpu, 
     assert np.array_equal(to_host(layer.idx), idx_c)
 
 
+@pytest.mark.parametrize("k", [1, 2000, 8999, 20000])
+def test_votes_of_zero_are_the_last_bin_of_the_upper_half(gpu, k):
+    """With a large score scale most votes underflow to zero, whose key opens the upper half of the first histogram's bins: a k-th
+    vote of zero, and a k of all tokens, are found there, as by the passes over all votes."""
+    from paper_2411_02886_amd.runtime import to_host
+    lens = [9000, 20000, 300]
+    w = W.make_workload("zero", dtype=W.BF16, B=3, H=32, H_kv=8, D=128, P=16, seq_lens=lens, k=k, planted_per_head=2, seed=k)
+    layer, q = make_layer(w)
+    layer.select(q, 300.0, None); torch.cuda.synchronize()
+    idx, count, votes = to_host(layer.idx).copy(), to_host(layer.count).copy(), to_host(layer.votes).copy()
+    if k >= 2000:
+        assert all((votes[b, idx[b, :count[b]]] == 0).any() for b in range(3))
+    for ranked in (True, False):
+        layer.idx.fill_(-9); layer.count.fill_(-9)
+        layer.select(q, 300.0, None, ranked_vote=True) if ranked else layer.select_compact(q, 300.0, None)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(layer.count), count)
+        for b in range(3):
+            got = to_host(layer.idx)[b, :count[b]]
+            if ranked:
+                assert np.array_equal(got, idx[b, :count[b]]), b
+            else:                            # its votes are those of double-precision products: those clear of zero come first
+                clear = np.flatnonzero(votes[b, :lens[b]] > 1e-30)
+                assert set(clear) <= set(got) if len(clear) <= count[b] else set(got) <= set(clear), b
+
+
 @pytest.mark.parametrize("lens", [[9000, 3333, 0, 17], [30000]], ids=["9000-ragged", "30000"])
 @pytest.mark.parametrize("scale", [1.0, 0.01], ids=["peaked", "flat"])
 def test_the_vote_launch_histogram_in_the_five_launch_form(gpu, lens, scale):
