@@ -239,9 +239,13 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, Scan scan,
     // rounds best: the CU holds floor(160 KiB / LDS) workgroups, three at most (registers), and a last round
     // that is half empty costs as much as a full one (786432 tokens of H 28/4: 8-tile runs 151 us, 6-tile runs
     // two full rounds).
+    // The score matrix of several wave tiles side by side leaves in pieces of rows, which long runs do not join, and their LDS
+    // costs workgroups: two tiles at most (H 64/8, D 128, 80000 tokens 37 us with one or two, 50 with four), one for
+    // eight heads at head size 64 (131000 tokens 32.1, 35.0 with two, 44.9 with four; 300000 68.6, 73.1, 105.6).
+    const int longest = dense && G >= 5 && NU > 1 ? (p->head_dim == 64 && G == 8 ? 1 : 2) : 8;
     rr = 1;
     double best = -1.0;
-    for (int r = 8; r >= 1; r -= (r > 2 ? 2 : 1)) {     // 8, 6, 4, 2, 1: odd run lengths measured slower throughout
+    for (int r = longest; r >= 1; r -= (r > 2 ? 2 : 1)) {     // 8, 6, 4, 2, 1: odd run lengths measured slower throughout
       const long n = wgs_of(r);
       if (r > 1 && n < 512) continue;
       long per_cu = (long)(163840 / score_codes_mfma_lds_bytes(p->head_dim, G, r, dense));
@@ -304,15 +308,33 @@ static dim3 mfma_grid(const ts_problem* p, const ScoreArgs& a, long wgl) {
   return a.flat_batch > 0 ? dim3((unsigned)wgl) : dim3((unsigned)wgl, p->batch);
 }
 
+// Whether the score pass runs on the matrix cores (out: what it writes to, for its alignment).
+// Five to seven heads over 8 and 16 KV heads: a wave's piece of a row of the score matrix is 80 to 112 bytes, not whole lines, and from
+// about 100 MB of K on the vector kernel, whose workgroups write whole rows, is the faster one.  Score matrix, us, vector and
+// matrix cores: 40/8, D 128, 40000 tokens (82 MB) 24.0 and 20.4, 2 x 30000 (123 MB) 24.8 and 27.1, 80000 34.4 and 37.9, 300000
+// 115 and 133; 56/8 27.3 and 21.7, 28.3 and 28.7, 37.2 and 40.3, 128 and 138; 80/16, D 64, 40000 (82 MB) 25.5 and 20.3, 80000
+// 38.1 and 40.7.  Eight heads' pieces are lines (64/8, D 128, 300000 138 and 122, D 64 83 and 69), and the compact form's bytes stay
+// in the L2 (40/8, D 128, 300000 115 and 107; D 64 80 and 57).  With a mask or a test a sequence's scores are those of a call of
+// its own, and so its own length counts.
+static bool score_on_matrix_cores(const ts_problem* p, bool dense, Scan scan, const void* out) {
+  const int G = p->num_q_heads / p->num_kv_heads;
+  if (!g_codes_mfma || (dense && g_score_variant != 2) || (p->num_q_heads % 4) != 0 || ((uintptr_t)out & 3) != 0 ||
+      !score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads))
+    return false;
+  if (!dense || G < 5 || G == 8 || p->num_kv_heads == 4) return true;
+  const double k_bytes = (double)p->max_seq_len * p->num_kv_heads * p->head_dim * 2 * (scan == kScanWhole ? p->batch : 1);
+  return k_bytes <= 96.0 * 1048576.0;
+}
+
 // Partials per sequence that a score launch of this shape leaves (workgroups it runs with; at most, where a batch shares them):
 // what the statistics merge loads before it has seen the count in the workspace.
 static int expected_parts(const ts_problem* p, bool dense, const uint8_t* skip) {
   const int G = p->num_q_heads / p->num_kv_heads;
-  if ((dense ? g_score_variant == 2 : true) && g_codes_mfma && (p->num_q_heads % 4) == 0 &&
-      score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
+  const Scan scan = skip == nullptr ? kScanWhole : kScanMasked;
+  if (score_on_matrix_cores(p, dense, scan, nullptr)) {
     ScoreArgs a{};
     long wgl = 0;
-    mfma_launch_shape(p, G, dense, skip == nullptr ? kScanWhole : kScanMasked, &a, &wgl);
+    mfma_launch_shape(p, G, dense, scan, &a, &wgl);
     const long ntt = (p->max_seq_len + kScoreTileTokens - 1) / kScoreTileTokens, grain = skip == nullptr ? 1 : a.SR;
     const long most = ((ntt + grain - 1) / grain * a.NU + 3) / 4;   // units, or workgroups of a tile per wave
     return (int)(a.flat_batch > 0 && (skip != nullptr || most < wgl) ? most : wgl);
@@ -351,10 +373,10 @@ static int32_t paged_qk_scores_impl(const ts_problem* p, const void* q, const ts
   if (sc != nullptr && (st = fill_selcache(p, q, sc, &a)) != TS_OK) return st;
   const int G = p->num_q_heads / p->num_kv_heads;
   a.scores = scores;
-  if (g_score_variant == 2 && g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)scores & 3) == 0) &&
-      score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
+  const Scan scan = sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole;
+  if (score_on_matrix_cores(p, true, scan, scores)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, true, sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole, &a, &wgl);
+    mfma_launch_shape(p, G, true, scan, &a, &wgl);
     const hipError_t e = launch_score_codes_mfma(p->head_dim, G, a, mfma_grid(p, a, wgl),
                                                  score_codes_mfma_lds_bytes(p->head_dim, G, a.RR, true) + a.run_stat_bytes, (hipStream_t)stream);
     return e == hipSuccess ? TS_OK : TS_ERR_HIP;
@@ -392,10 +414,10 @@ static int32_t paged_qk_codes_impl(const ts_problem* p, const void* q, const ts_
   const int G = p->num_q_heads / p->num_kv_heads;
   a.codes = codes;
   a.blk_max = (float*)((uint8_t*)ws + w.blk_max); a.nblk = w.score_nblk;
-  if (g_codes_mfma && (p->num_q_heads % 4) == 0 && (((uintptr_t)codes & 3) == 0) &&
-      score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) {
+  const Scan scan = sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole;
+  if (score_on_matrix_cores(p, false, scan, codes)) {
     long wgl = 0;
-    mfma_launch_shape(p, G, false, sc != nullptr ? kScanTested : skip != nullptr ? kScanMasked : kScanWhole, &a, &wgl);
+    mfma_launch_shape(p, G, false, scan, &a, &wgl);
     // Bytes and block maxima that fit the chip's L2 (eight XCDs x 4 MiB) with room to spare stay there as dirty lines
     // until the kernel ends and cost the read stream nothing; more than that thrashes it, and streaming them past the
     // L2 is the cheaper way (measured, H 28/4: 524288 tokens 89.2 us cached / 90.2 streamed, 786432 tokens 142.0 / 135.7,

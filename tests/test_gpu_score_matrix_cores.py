@@ -45,6 +45,39 @@ def test_scores_are_as_close_to_64_bits_as_the_vector_kernels(gpu, H, H_kv, D):
     assert rms[1] <= 1.02 * rms[0]
 
 
+@pytest.mark.parametrize("H,H_kv,D,B,max_len,masked,vector", [
+    (40, 8, 128, 1, 49152, False, False), (40, 8, 128, 1, 49153, False, True), (56, 8, 64, 2, 49152, False, False), (56, 8, 64, 2, 49153, False, True),
+    (48, 8, 128, 3, 49152, True, False), (48, 8, 128, 3, 49153, True, True), (80, 16, 64, 1, 49153, False, True), (64, 8, 128, 1, 49153, False, False),
+    (64, 8, 64, 1, 140000, False, False), (28, 4, 128, 1, 98305, False, False)])
+def test_the_score_matrix_on_both_sides_of_its_line(gpu, H, H_kv, D, B, max_len, masked, vector):
+    """Five to seven heads over 8 and 16 KV heads take the vector kernel from 96 MiB of K that a call (with a mask: a sequence) may have on.
+    Both sides against 64 bits: products are exact, and D - 1 additions of float lose at most 2^-24 of the sum of the absolute
+    products each, twice that where they are cut off."""
+    from paper_2411_02886_amd.runtime import to_host
+    lens = [2049, 33, 700][:B]
+    w = W.make_workload("line", dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=16, B=B, seq_lens=lens, k=64, beta=2.5, planted_per_head=0, seed=H + B)
+    layer, q = make_layer(w, max_seq_len=max_len)
+    skip = torch.zeros(B, dtype=torch.uint8, device=q.device) if masked else None
+    got = []
+    try:
+        for mfma in (1, 0):
+            gpu.ts_debug_set_codes_path(mfma, 0)
+            print("score matrix line", H, H_kv, D, B, max_len, masked, mfma, flush=True)
+            layer.select(q, 1.0, skip)
+            torch.cuda.synchronize()
+            got.append([to_host(layer.scores)[b, :n].copy() for b, n in enumerate(lens)])
+    finally:
+        gpu.ts_debug_set_codes_path(1, 0)
+    assert all(np.array_equal(x, y) for x, y in zip(*got)) == vector
+    qf = W.as_f32(w.q, w.dtype).astype(np.float64)
+    rows = W.as_f32(w.k_pool.reshape(-1, H_kv, D), w.dtype).astype(np.float64)
+    for b in range(B):
+        k = np.repeat(rows[w.slots_of(b)], H // H_kv, axis=1)
+        exact, size = np.einsum("nhd,hd->nh", k, qf[b, 0]), np.einsum("nhd,hd->nh", np.abs(k), np.abs(qf[b, 0]))
+        for x in got:
+            assert (np.abs(x[b] - exact) <= 2.0 ** -23 * (D - 1) * size).all()
+
+
 @pytest.mark.parametrize("H,H_kv,D,P,lens,k", [
     # 513 workgroups of one-tile waves and more: the sequences share the grid
     (32, 8, 64, 16, [33000, 32700], 200), (24, 8, 128, 1, [0, 21001, 1, 32, 33, 20000, 129], 300), (28, 4, 64, 16, [40000, 7] + [31] * 14, 64),
