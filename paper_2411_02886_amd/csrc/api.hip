@@ -234,18 +234,23 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, Scan scan,
     return n > kScoreMaxWg ? (long)kScoreMaxWg : n;
   };
   int rr = g_codes_rr;
-  if (rr <= 0) {
+  if (rr <= 0 && dense && G >= 5 && NU > 1) {
+    // The score matrix of several wave tiles side by side leaves in pieces of rows, which long runs do not join, and the LDS of
+    // four tiles costs workgroups (H 64/8, D 64, 300000 tokens 69 us with one, 73 with two, 105 with four).  One tile per wave
+    // up to one round of three workgroups per CU; then a second one that is nearly empty takes longer than two tiles per
+    // wave in the first (D 128, 50000 tokens 26.7 and 22.6, 65000 31.2 and 27.9; D 64 16.6 and 15.9).  Between the most
+    // workgroups of a launch and two full rounds D 128 has the shorter runs again (80000 37.7 and 38.8, 90000 39.2 and
+    // 42.3, D 64 23.5 and 22.5), beyond it the longer ones and D 64 the shorter (120000 53.8 and 50.3, D 64 30.3 and 33.3).
+    const long one = (ntt * NU + 3) / 4;               // workgroups of one tile per wave
+    rr = one <= 768 ? 1 : one > 1536 ? (p->head_dim == 64 ? 1 : 2) : one <= kScoreMaxWg || p->head_dim == 64 ? 2 : 1;
+  } else if (rr <= 0) {
     // Longest run that still gives every CU two workgroups, among those the one whose workgroups fill the
     // rounds best: the CU holds floor(160 KiB / LDS) workgroups, three at most (registers), and a last round
     // that is half empty costs as much as a full one (786432 tokens of H 28/4: 8-tile runs 151 us, 6-tile runs
     // two full rounds).
-    // The score matrix of several wave tiles side by side leaves in pieces of rows, which long runs do not join, and their LDS
-    // costs workgroups: two tiles at most (H 64/8, D 128, 80000 tokens 37 us with one or two, 50 with four), one for
-    // eight heads at head size 64 (131000 tokens 32.1, 35.0 with two, 44.9 with four; 300000 68.6, 73.1, 105.6).
-    const int longest = dense && G >= 5 && NU > 1 ? (p->head_dim == 64 && G == 8 ? 1 : 2) : 8;
     rr = 1;
     double best = -1.0;
-    for (int r = longest; r >= 1; r -= (r > 2 ? 2 : 1)) {     // 8, 6, 4, 2, 1: odd run lengths measured slower throughout
+    for (int r = 8; r >= 1; r -= (r > 2 ? 2 : 1)) {     // 8, 6, 4, 2, 1: odd run lengths measured slower throughout
       const long n = wgs_of(r);
       if (r > 1 && n < 512) continue;
       long per_cu = (long)(163840 / score_codes_mfma_lds_bytes(p->head_dim, G, r, dense));

@@ -48,7 +48,7 @@ def test_scores_are_as_close_to_64_bits_as_the_vector_kernels(gpu, H, H_kv, D):
 @pytest.mark.parametrize("H,H_kv,D,B,max_len,masked,vector", [
     (40, 8, 128, 1, 49152, False, False), (40, 8, 128, 1, 49153, False, True), (56, 8, 64, 2, 49152, False, False), (56, 8, 64, 2, 49153, False, True),
     (48, 8, 128, 3, 49152, True, False), (48, 8, 128, 3, 49153, True, True), (80, 16, 64, 1, 49153, False, True), (64, 8, 128, 1, 49153, False, False),
-    (64, 8, 64, 1, 140000, False, False), (28, 4, 128, 1, 98305, False, False)])
+    (64, 8, 64, 1, 98305, False, False), (64, 8, 128, 2, 65600, True, False), (64, 8, 128, 1, 98305, False, False), (28, 4, 128, 1, 98305, False, False)])
 def test_the_score_matrix_on_both_sides_of_its_line(gpu, H, H_kv, D, B, max_len, masked, vector):
     """Five to seven heads over 8 and 16 KV heads take the vector kernel from 96 MiB of K that a call (with a mask: a sequence) may have on.
     Both sides against 64 bits: products are exact, and D - 1 additions of float lose at most 2^-24 of the sum of the absolute
