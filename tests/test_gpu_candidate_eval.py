@@ -62,3 +62,15 @@ def test_votes_of_the_candidates_against_64_bits(gpu, dtype, H, H_kv, D):
         s = np.einsum("mhd,hd->mh", np.repeat(k, H // H_kv, axis=1), qf[b, 0])
         ref = (np.exp(float(np.float32(scale)) * (s - st[b, :, 0].astype(np.float64))) / st[b, :, 1].astype(np.float64)).sum(axis=1)
         np.testing.assert_allclose(got[b, :m], ref, rtol=5e-7, err_msg="b %d" % b)
+
+
+@pytest.mark.parametrize("lens,k", [([200000], 64), ([3, 0, 9000], 2048), ([2500] * 70, 300)])
+def test_the_histogram_is_left_zeroed(gpu, lens, k):
+    """Every workgroup clears its share of the lower bounds' histogram, with candidates (behind the loads of their rows) or without."""
+    from rules_util import rules
+    w = W.make_workload("cleared", dtype=W.BF16, B=len(lens), H=8, H_kv=2, D=64, seq_lens=lens, k=k, beta=2.5, planted_per_head=2, seed=94)
+    layer, q = make_layer(w)
+    for _ in range(2):
+        layer.select_compact(q, 1.0, None)
+        torch.cuda.synchronize()
+        assert not layer.ws[:rules().rule_zeroed_bytes(len(lens), max(lens)) // 4].any()
