@@ -177,6 +177,11 @@ hipError_t launch_vote_bounds(const BoundArgs& a, int B, hipStream_t s) {
 // instead of four a workgroup: the same for batches, 0.5 to 1 us more for one sequence; where a wave of four has two units to go
 // through, 4 x 20000 to 40000, H 64/32, D 64, k 2000, 18.2 and
 // 14.5, 16.0 before.)
+// One query head per KV head (ONE) would use a quarter of the matrix instruction's columns: v_fma_f64, and the sums of the four lanes of a row
+// by the swaps of half and quarter waves (one sequence of 200000 tokens, k 2048: H 8/8, D 128, 6.7 -> 6.1 us, fp32 7.6 ->
+// 7.0; 16/16, D 64, 6.7 -> 6.2; 32 of 1031 to 16001, H 1/1, D 128, 37.4 -> 34.2).  Two heads the same way: 4/2, D 128, 6.6 -> 6.8, fp32
+// 6.8 -> 7.0, for want of registers.  (Eight lanes to a row are still faster there for a single sequence: 16/8, D 128, 6.6, with
+// four 6.9; fp32 7.2 and 7.9; batches 35.6 and 33.6.)
 // The scores of up to CB candidates meet in LDS, where the softmax weights are formed with every lane at work.
 
 // exp(c * d) as ts_soft_vote forms it: argument reduced in double, 2^fraction from the float hardware exponential
@@ -196,6 +201,17 @@ __device__ __forceinline__ double dpp_f64(double v) {
 }
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
 
+// sum over the four lanes of a wave that are 16 apart
+__device__ __forceinline__ double quarter_sum_f64(double v) {
+  auto sum = [](auto lo, auto hi) {
+    return __longlong_as_double(((long long)hi[0] << 32) | (unsigned int)lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | (unsigned int)lo[1]);
+  };
+  unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  v = sum(__builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false), __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false));
+  u = (unsigned long long)__double_as_longlong(v);
+  return sum(__builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false), __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false));
+}
+
 // the elements of a 16-byte piece as doubles
 template <int DT>
 __device__ __forceinline__ void unpack_f64(uint4 w, double* f) {
@@ -209,8 +225,8 @@ __device__ __forceinline__ void unpack_f64(uint4 w, double* f) {
 
 constexpr int kEvalMaxBatch = 256;        // candidates whose scores a workgroup holds in LDS at a time, at most
 
-// CS: sets of four query heads of a KV head.  WAVES: eight where that many (set, four KV heads) pairs are, else four.
-template <int DT, int D, int CS, int WAVES>
+// CS: sets of four query heads of a KV head.  ONE: one query head per KV head.  WAVES: eight where that many (set, four KV heads) pairs are, else four.
+template <int DT, int D, int CS, int WAVES, bool ONE>
 __global__ __launch_bounds__(64 * WAVES, 2) void topk_eval_kernel(RefineArgs a, int cb) {
   constexpr int T = 64 * WAVES;
   constexpr int ES = Elt<DT>::size;
@@ -262,14 +278,14 @@ __global__ __launch_bounds__(64 * WAVES, 2) void topk_eval_kernel(RefineArgs a, 
   uint4 qw[NP];
   double qd[NP * EPP];
   {
-    const uint8_t* qp = a.q + ((size_t)b * H + (size_t)kvh * G + min(g, G - 1)) * RB + kk * 16;
+    const uint8_t* qp = a.q + ((size_t)b * H + (size_t)kvh * G + (ONE ? 0 : min(g, G - 1))) * RB + kk * 16;
 #pragma unroll
     for (int i = 0; i < NP; ++i) qw[i] = *reinterpret_cast<const uint4*>(qp + i * 64);
   }
   auto convert_q = [&]() {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-      if (g >= G) qw[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (!ONE && g >= G) qw[i] = make_uint4(0u, 0u, 0u, 0u);
       unpack_f64<DT>(qw[i], qd + i * EPP);
     }
   };
@@ -333,7 +349,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void topk_eval_kernel(RefineArgs a, 
     uint4 buf[NP];
     auto step = [&](int st, bool more) {
       const uint8_t* kn = more ? row_of(st + wstep) : nullptr;
-      double acc0 = 0.0, acc1 = 0.0;
+      double acc[2] = {0.0, 0.0};
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         double kd[EPP];
@@ -341,13 +357,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void topk_eval_kernel(RefineArgs a, 
         if (more) buf[i] = *reinterpret_cast<const uint4*>(kn + i * 64);
         // products of two floats are exact in double
 #pragma unroll
-        for (int e = 0; e < EPP; e += 2) {
-          acc0 = __builtin_amdgcn_mfma_f64_4x4x4f64(kd[e], qd[i * EPP + e], acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f64_4x4x4f64(kd[e + 1], qd[i * EPP + e + 1], acc1, 0, 0, 0);
-        }
+        for (int e = 0; e < EPP; ++e)
+          acc[e & 1] = ONE ? fma(kd[e], qd[i * EPP + e], acc[e & 1]) : __builtin_amdgcn_mfma_f64_4x4x4f64(kd[e], qd[i * EPP + e], acc[e & 1], 0, 0, 0);
       }
-      const int ci = st * tps + cand + kk;
-      if (ci < n && g < G) sc[(size_t)ci * H + kvh * G + g] = acc0 + acc1;
+      const double sum = ONE ? quarter_sum_f64(acc[0] + acc[1]) : acc[0] + acc[1];
+      const int ci = st * tps + cand + (ONE ? c : kk);
+      if (ci < n && (ONE ? kk == 0 : g < G)) sc[(size_t)ci * H + (ONE ? kvh : kvh * G + g)] = sum;
     };
     int st = wsub;
     if (st < nsteps) {
@@ -385,9 +400,10 @@ static hipError_t eval_g(int G, const RefineArgs& a, dim3 grid, hipStream_t s) {
   if (cb > kEvalMaxBatch) cb = kEvalMaxBatch;
   const size_t lds = (size_t)cb * a.H * sizeof(double) + off_bytes;
   const int units = (a.H_kv + 3) / 4 * (G > 4 ? 2 : 1);
-#define TS_EVAL(CS, WAVES) hipLaunchKernelGGL((topk_eval_kernel<DT, D, CS, WAVES>), grid, dim3(64 * WAVES), lds, s, a, cb)
-  if (G > 4) { if (units > 4) TS_EVAL(2, 8); else TS_EVAL(2, 4); }
-  else { if (units > 4) TS_EVAL(1, 8); else TS_EVAL(1, 4); }
+#define TS_EVAL(CS, WAVES, ONE) hipLaunchKernelGGL((topk_eval_kernel<DT, D, CS, WAVES, ONE>), grid, dim3(64 * WAVES), lds, s, a, cb)
+  if (G > 4) { if (units > 4) TS_EVAL(2, 8, false); else TS_EVAL(2, 4, false); }
+  else if (G > 1) { if (units > 4) TS_EVAL(1, 8, false); else TS_EVAL(1, 4, false); }
+  else { if (units > 4) TS_EVAL(1, 8, true); else TS_EVAL(1, 4, true); }
 #undef TS_EVAL
   return hipGetLastError();
 }

@@ -74,3 +74,10 @@ def test_the_histogram_is_left_zeroed(gpu, lens, k):
         layer.select_compact(q, 1.0, None)
         torch.cuda.synchronize()
         assert not layer.ws[:rules().rule_zeroed_bytes(len(lens), max(lens)) // 4].any()
+
+
+@pytest.mark.parametrize("dtype,H_kv,D", [(W.BF16, 1, 64), (W.F32, 2, 64), (W.F32, 4, 128), (W.BF16, 8, 128), (W.F32, 8, 128), (W.BF16, 16, 64),
+                                          (W.F32, 32, 64), (W.BF16, 32, 128)])
+def test_one_query_head_per_kv_head(gpu, dtype, H_kv, D):
+    """Products by vector instructions: every number of KV heads, four and eight waves."""
+    test_votes_of_the_candidates_against_64_bits(gpu, dtype, H_kv, H_kv, D)
