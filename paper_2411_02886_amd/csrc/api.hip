@@ -268,8 +268,9 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, Scan scan,
     if (!dense && whole_batch && rr < 4 && p->batch >= 4 && wgs_of(4) * p->batch >= 512) rr = 4;
   }
   // A batch whose lengths and mask are known when the launch starts shares one grid (shared_share) from more work on than a tile for
-  // each wave of two workgroups per CU: up to there every wave of the other grid has its tile at once, and the sharing out
-  // costs half a microsecond (16 sequences of 683 to 2048 tokens, H 32/8, 12.9 and 13.5 us; 16 of 1533 to 4600 25.6 and 20.6).
+  // each wave of two workgroups per CU: up to there every wave of the other grid has its tile at once, and sharing costs up
+  // to a microsecond (score matrix, us, the other grid and shared: 8 sequences of 3000 to 6000 tokens, H 32/8, 18.6 and 19.5; 4 of 5000
+  // to 10000 18.5 and 19.3; 16 of 683 to 2048 13.4 and 13.3; beyond the line 16 of 1533 to 4600 25.5 and 20.3).
   // Beyond one round of a tile per wave two workgroups per CU share the work, at head size 64, with its rows of half the length,
   // three (32 of 1031 to 16001 tokens of 32/8, D 128, 97.6 us, with three per CU 105; D 64, 112 batches of 3 to 32 sequences
   // 1.05 times as fast as in a grid of their own, 1.01 with two per CU; D 128, 56 batches 1.06).  The staged runs are as long as
@@ -304,6 +305,7 @@ static void mfma_launch_shape(const ts_problem* p, int G, bool dense, Scan scan,
     long per_cu = 163840 / lds, most = p->head_dim == 64 ? 4 : 3;            // registers
     if (per_cu > most) per_cu = most;
     a->flat_batch = p->batch; wgl = 256 * per_cu;
+    a->flat_grid = (int)wgl; a->nu_shift = ilog2(NU); a->grain_mul = score_unit_mul((uint32_t)(groups * a->SR));
     a->flat_wgs = p->head_dim == 64 && wgl > 512 ? 768 : kScoreFlatWg;
   }
   *wg_out = wgl;

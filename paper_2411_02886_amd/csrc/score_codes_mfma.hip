@@ -43,28 +43,37 @@ struct ScoreShare { int b, x, n, N, indptr, base, stride, tiles, uw; };
 // Every sequence gets a workgroup, an empty one too: its statistics are those of no score.  False: nothing left for this one.
 // MASKED: a skip mask leaves sequences out.  What a sequence's statistics are to the last bit must not depend on the others then, so
 // they are formed as in a call of its own: in units of one run of a.SR tiles per wave of such a call's workgroups.  A workgroup
-// takes uw whole units, its waves uw consecutive runs each, and every unit leaves its partial.  (8 sequences of 24000 to 32000 tokens, H
-// 32/8: all of them 82 -> 72 us, five 52 -> 50, one 13.9 -> 14.7; H 64/8, 12000 to 37000: 104 -> 80, 68 -> 52, 22 -> 11.)
+// takes uw whole units, its waves uw consecutive runs each, and every unit leaves its partial.  (Bytes, us in a grid of (workgroups,
+// sequences) and shared: 8 sequences of 24000 to 32000 tokens, H 32/8, all of them 86 and 75, four 47 and 40, one 24 and 15; H 28/4,
+// 16 of 4000 to 16000, 38 and 33, 23 and 21, 10.2 and 9.7; H 64/8, 12000 to 37000, 94 and 80, 56 and 48, 18.4 and 19.3; H
+// 32/4, 8000 to 24000, 31.6 and 28.7, 18.7 and 19.1, 9.9 and 9.5.)
 template <bool MASKED>
 __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, ScoreShare& s) {
-  const int lane = threadIdx.x & 63, B = a.flat_batch;
-  const int len_any = a.seq_lens[min(lane, B - 1)], ptr = a.page_indptr[min(lane, B - 1)];
-  const bool scanned = lane < B && !(MASKED && a.skip[min(lane, B - 1)] != 0);
+  const int lane = threadIdx.x & 63, B = a.flat_batch, at = min(lane, B - 1);
+  const int len_any = a.seq_lens[at], ptr = a.page_indptr[at], left_out = MASKED ? (int)a.skip[at] : 0;
+  wave = __builtin_amdgcn_readfirstlane(wave);
+  const int groups_shift = 2 - a.nu_shift, groups = 1 << groups_shift;   // waves that share a tile range
+  const bool scanned = lane < B && left_out == 0;
   const int len = scanned ? min(max(len_any, 0), a.max_seq_len) : 0;
   const uint32_t ntt = (uint32_t)(len + kScoreTileTokens - 1) / kScoreTileTokens;
-  const uint32_t groups = 4 / a.NU;                        // waves that share a tile range
-  const uint32_t grain = MASKED ? groups * (uint32_t)a.SR : 1u;   // tiles of a unit
-  const uint32_t units = (ntt + grain - 1) / grain;
-  // The grid is what the chip holds at a time.  If that is enough for a tile (a run) per wave, so be it; else two workgroups per CU
-  // share the work, the rest of the grid leaves.
-  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(units), 63);
-  const uint32_t least = MASKED ? 1u : groups;
-  const uint32_t wgs = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(scanned ? max((units + least - 1) / least, 1u) : 0u), 63);
-  const uint32_t slots = (uint32_t)a.flat_wgs - (uint32_t)B;   // the sequences' counts are rounded up
-  const uint32_t share = (total + slots - 1) / slots;
-  const uint32_t upw = wgs <= gridDim.x ? least : max((share + least - 1) / least * least, least);   // the waves' parts are equal
-  const uint32_t cnt = scanned ? max((units + upw - 1) / upw, 1u) : 0u;
-  const uint32_t incl = wave_inclusive_scan(cnt);
+  const uint32_t grain = MASKED ? (uint32_t)(groups * a.SR) : 1u;        // tiles of a unit
+  const uint32_t units = MASKED ? score_unit_div(ntt + grain - 1, a.grain_mul) : ntt;
+  // The grid is what the chip holds at a time.  If that is enough for a tile (a run) per wave, so be it: one scan and no division stand
+  // before the first loads then.  (With three scans and four divisions in either case a call of which little is scanned had lost 0.3 to 0.9
+  // us against a grid of its own: one of 16 sequences of 4000 to 16000, H 28/4, 9.9 us, 9.6 now; of 64 of 500 to 4000, H 32/8,
+  // 12.9 and 12.3; none of them 2.3 and 1.9.)
+  const uint32_t least = MASKED ? 1u : (uint32_t)groups;
+  uint32_t upw = least, cnt = scanned ? max(MASKED ? units : (units + least - 1) >> groups_shift, 1u) : 0u;
+  uint32_t incl = wave_inclusive_scan(cnt);
+  if ((uint32_t)__builtin_amdgcn_readlane((int)incl, 63) > (uint32_t)a.flat_grid) {
+    // else two (three) workgroups per CU share the work, the rest of the grid leaves
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(units), 63);
+    const uint32_t slots = (uint32_t)a.flat_wgs - (uint32_t)B;   // the sequences' counts are rounded up
+    const uint32_t share = (total + slots - 1) / slots;
+    upw = max((share + least - 1) & ~(least - 1), least);        // the waves' parts are equal
+    cnt = scanned ? max((units + upw - 1) / upw, 1u) : 0u;
+    incl = wave_inclusive_scan(cnt);
+  }
   const int b = __popcll(__builtin_amdgcn_ballot_w64(incl <= blockIdx.x));
   if (b >= B) return false;
   s.b = b;
@@ -72,7 +81,7 @@ __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, Score
   s.x = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, b) - s.n);
   s.N = __builtin_amdgcn_readlane(len, b);
   s.indptr = __builtin_amdgcn_readlane(ptr, b);
-  const int ntt_b = __builtin_amdgcn_readlane((int)ntt, b), part = wave / a.NU;
+  const int ntt_b = __builtin_amdgcn_readlane((int)ntt, b), part = wave >> a.nu_shift;
   s.stride = a.RR; s.uw = (int)upw;
   if (MASKED) {
     const int per = (int)upw * a.SR;                       // tiles of a wave
@@ -80,7 +89,7 @@ __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, Score
     s.tiles = min(max(ntt_b - s.base, 0), per);
   } else {
     const int t0 = s.x * (int)upw, have = min((int)upw, ntt_b - t0);
-    const int lo = have * part / (int)groups, hi = have * (part + 1) / (int)groups;
+    const int lo = (have * part) >> groups_shift, hi = (have * (part + 1)) >> groups_shift;
     s.base = t0 + lo; s.tiles = hi - lo;
   }
   return true;

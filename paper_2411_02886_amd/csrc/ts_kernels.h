@@ -22,6 +22,9 @@ struct ScoreArgs {
   int flat_wgs;           // workgroups that a batch shares where a tile per wave would be more than one round of them
   int run_stat_bytes;     // LDS for the statistics of such runs, behind the waves' regions
   int flat_batch;         // matrix-core kernel: > 0 the batch, whose sequences share a one-dimensional grid; 0: grid.y is the sequence
+  int flat_grid;          // ... its workgroups
+  int nu_shift;           // ... log2 of NU
+  uint32_t grain_mul;     // ... with a skip mask: score_unit_mul of the tiles of a unit
   int n_init, n_local;    // forced tokens: the statistics cover [min(n_init, N), max(that, N - n_local)) only
   float scale, c2;        // score_scale and score_scale * log2(e)
   uint32_t* hdr;          // [B][8] what later calls must know about this launch (partials / block size, score_scale)

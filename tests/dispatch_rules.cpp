@@ -20,5 +20,6 @@ int rule_topk_scratch_fits(int batch, int max_seq_len) {   // the table and the 
   const ts::WsLayout w = ts::ws_layout(&p, 1);
   return (size_t)batch * w.topk_nblk * 1024 * 2 + (size_t)batch * 1024 * 4 <= w.topk_dense - w.topk_list ? 1 : 0;
 }
+unsigned rule_unit_div(unsigned x, unsigned d) { return ts::score_unit_div(x, ts::score_unit_mul(d)); }
 int rule_stream_span(long pairs, int total) { return ts::stream_span(pairs, total); }
 }

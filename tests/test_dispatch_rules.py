@@ -82,3 +82,14 @@ def test_flat_votes_scratch_fits_the_lists_memory():
     for batch in (1, 2, 7, 300, 65535):
         for n in (1, 2048, 2049, 8193, 1048576, 1048577):
             assert rules().rule_topk_scratch_fits(batch, n), (batch, n)
+
+
+def test_units_of_the_shared_score_grid_are_divided_exactly():
+    """Runs of 1, 2, 4, 6 and 8 tiles for one, two and four waves; tiles of up to 2^31 tokens."""
+    L, rng = rules(), random.Random(3)
+    for d in sorted({g * r for g in (1, 2, 4) for r in (1, 2, 4, 6, 8)}):
+        most = 2**26 + d
+        xs = list(range(0, 5 * d)) + [rng.randrange(most) for _ in range(2000)] + [most - i for i in range(3 * d)]
+        xs += [q * d + e for q in (rng.randrange(most // d) for _ in range(500)) for e in (0, d - 1)]
+        for x in xs:
+            assert L.rule_unit_div(x, d) == x // d, (x, d)
