@@ -21,7 +21,7 @@
 // ts_paged_qk_codes).  Bytes and statistics are collected in LDS for a run of consecutive tiles and leave as
 // one contiguous burst at the end of the run: on this memory system small writes sprinkled into the read
 // stream cost many times their bytes, a burst at the end of a wave's life costs about its own time.
-#include "ts_kernels.h"
+#include "ts_score_shape.h"
 #include "selcache_device.h"
 #include "ts_score_math.h"
 #include <hip/hip_ext.h>
@@ -30,10 +30,6 @@ namespace ts {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 mfma_bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float mfma_f32x4_t;
-
-// What a wave scans: run n of its tiles starts at tile base + n * stride of sequence b, whose x-th of n workgroups this is.
-// uw: units of a workgroup, whose statistics leave one by one (masked calls).
-struct ScoreShare { int b, x, n, N, indptr, base, stride, tiles, uw; };
 
 // The workgroups of a one-dimensional grid are handed out here, where the lengths are known: each takes upw consecutive units of one
 // sequence (a unit is a tile; its waves take equal parts), upw the fewest that serve all.  In a grid of (workgroups of the
@@ -52,26 +48,21 @@ __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, Score
   const int lane = threadIdx.x & 63, B = a.flat_batch, at = min(lane, B - 1);
   const int len_any = a.seq_lens[at], ptr = a.page_indptr[at], left_out = MASKED ? (int)a.skip[at] : 0;
   wave = __builtin_amdgcn_readfirstlane(wave);
-  const int groups_shift = 2 - a.nu_shift, groups = 1 << groups_shift;   // waves that share a tile range
   const bool scanned = lane < B && left_out == 0;
   const int len = scanned ? min(max(len_any, 0), a.max_seq_len) : 0;
-  const uint32_t ntt = (uint32_t)(len + kScoreTileTokens - 1) / kScoreTileTokens;
-  const uint32_t grain = MASKED ? (uint32_t)(groups * a.SR) : 1u;        // tiles of a unit
-  const uint32_t units = MASKED ? score_unit_div(ntt + grain - 1, a.grain_mul) : ntt;
+  const int ntt = (int)((uint32_t)(len + kScoreTileTokens - 1) / kScoreTileTokens);
+  const uint32_t units = score_share_units(a, MASKED, ntt);
   // The grid is what the chip holds at a time.  If that is enough for a tile (a run) per wave, so be it: one scan and no division stand
   // before the first loads then.  (With three scans and four divisions in either case a call of which little is scanned had lost 0.3 to 0.9
   // us against a grid of its own: one of 16 sequences of 4000 to 16000, H 28/4, 9.9 us, 9.6 now; of 64 of 500 to 4000, H 32/8,
   // 12.9 and 12.3; none of them 2.3 and 1.9.)
-  const uint32_t least = MASKED ? 1u : (uint32_t)groups;
-  uint32_t upw = least, cnt = scanned ? max(MASKED ? units : (units + least - 1) >> groups_shift, 1u) : 0u;
+  uint32_t upw = score_share_least(a, MASKED);
+  uint32_t cnt = scanned ? score_share_least_count(a, MASKED, units) : 0u;
   uint32_t incl = wave_inclusive_scan(cnt);
   if ((uint32_t)__builtin_amdgcn_readlane((int)incl, 63) > (uint32_t)a.flat_grid) {
     // else two (three) workgroups per CU share the work, the rest of the grid leaves
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(units), 63);
-    const uint32_t slots = (uint32_t)a.flat_wgs - (uint32_t)B;   // the sequences' counts are rounded up
-    const uint32_t share = (total + slots - 1) / slots;
-    upw = max((share + least - 1) & ~(least - 1), least);        // the waves' parts are equal
-    cnt = scanned ? max((units + upw - 1) / upw, 1u) : 0u;
+    upw = score_share_upw(a, MASKED, (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(units), 63));
+    cnt = scanned ? score_share_count(units, upw) : 0u;
     incl = wave_inclusive_scan(cnt);
   }
   const int b = __popcll(__builtin_amdgcn_ballot_w64(incl <= blockIdx.x));
@@ -81,17 +72,7 @@ __device__ __forceinline__ bool shared_share(const ScoreArgs& a, int wave, Score
   s.x = (int)blockIdx.x - (__builtin_amdgcn_readlane((int)incl, b) - s.n);
   s.N = __builtin_amdgcn_readlane(len, b);
   s.indptr = __builtin_amdgcn_readlane(ptr, b);
-  const int ntt_b = __builtin_amdgcn_readlane((int)ntt, b), part = wave >> a.nu_shift;
-  s.stride = a.RR; s.uw = (int)upw;
-  if (MASKED) {
-    const int per = (int)upw * a.SR;                       // tiles of a wave
-    s.base = s.x * (int)(upw * grain) + part * per;
-    s.tiles = min(max(ntt_b - s.base, 0), per);
-  } else {
-    const int t0 = s.x * (int)upw, have = min((int)upw, ntt_b - t0);
-    const int lo = (have * part) >> groups_shift, hi = (have * (part + 1)) >> groups_shift;
-    s.base = t0 + lo; s.tiles = hi - lo;
-  }
+  score_share_tiles(a, MASKED, wave, (int)upw, __builtin_amdgcn_readlane(ntt, b), s);
   return true;
 }
 
@@ -501,25 +482,6 @@ __global__ __launch_bounds__(256) void score_codes_mfma_kernel(ScoreArgs a) {
 
 static hipEvent_t g_codes_time_start = nullptr, g_codes_time_stop = nullptr;
 void set_codes_timing_events(hipEvent_t start, hipEvent_t stop) { g_codes_time_start = start; g_codes_time_stop = stop; }
-
-// Shapes the matrix-core form covers: bf16, two column blocks per wave tile.  Wave tiles of 8 KV heads (G 3 and 4) or of 4 (G 5
-// to 8), and no more of them side by side than a workgroup has waves (five to eight heads over 8 or 16 KV heads, score pass, us, vector
-// kernel and this one: 64/8, 4 x 20011 to 40009 tokens 63.0 and 46.4, 6000 18.4 and 8.6, 200000 93.5 and 77.6; 40/8, 2500 tokens
-// 14.5 and 7.6, 100000 45.5 and 45.5).
-bool score_codes_mfma_supported(int dtype, int D, int G, int H_kv) {
-  if (dtype != TS_BF16 || (D != 64 && D != 128)) return false;
-  if (G >= 3 && G <= 4) return H_kv >= 8;
-  if (G >= 5 && G <= 8) return H_kv >= 4 && H_kv <= 16;
-  return false;
-}
-
-// dense: the run's fp32 rows are staged instead of its bytes
-size_t score_codes_mfma_lds_bytes(int D, int G, int RR, bool dense) {
-  const int HB = G <= 4 ? 8 : 4;
-  const size_t per_wave = (size_t)32 * (D * 2 + 16) + (size_t)RR * kScoreTileTokens * HB * G * (dense ? 4 : 1) +
-                          (size_t)RR * HB * G * 4;
-  return 4 * per_wave;
-}
 
 template <int D, int G, bool DENSE, int SHARE, bool SUMS>
 static hipError_t launch_cm(const ScoreArgs& a, dim3 grid, size_t lds, hipStream_t s) {

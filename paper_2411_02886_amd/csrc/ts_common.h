@@ -121,14 +121,7 @@ struct WsLayout {
   int attn_nsplit;
 };
 
-// x / d of the score pass's shared grid, x up to 2^26 tiles and d the tiles of a unit: powers of two and 6, 12 and 24, where the
-// rounded-up factor is off by 16 / 2^31 at most, exact to 2^27.
-inline uint32_t score_unit_mul(uint32_t d) { return (uint32_t)((((uint64_t)1 << 31) + d - 1) / d); }
-#ifdef __HIPCC__
-__host__ __device__
-#endif
-inline uint32_t score_unit_div(uint32_t x, uint32_t mul) { return (uint32_t)(((uint64_t)x * mul) >> 31); }
-
+inline int ilog2(int x) { int s = 0; while ((1 << s) < x) ++s; return s; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Key-list splits of the chunk-form attention: a workgroup owns 128 rows and fills a CU, so the key list

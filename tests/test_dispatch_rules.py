@@ -1,9 +1,10 @@
 """Host rules that choose between kernels and split their work, checked without a GPU."""
 import random
 
+import numpy as np
 import pytest
 
-from rules_util import rules
+from rules_util import MASKED, WHOLE, rules, score_shape, score_share
 
 
 def test_streaming_attention_splits_are_legal_and_fit_the_workspace():
@@ -93,3 +94,73 @@ def test_units_of_the_shared_score_grid_are_divided_exactly():
         xs += [q * d + e for q in (rng.randrange(most // d) for _ in range(500)) for e in (0, d - 1)]
         for x in xs:
             assert L.rule_unit_div(x, d) == x // d, (x, d)
+
+
+def check_share(B, H, H_kv, D, max_len, dense, lens, skip):
+    """Every tile of every scanned sequence belongs to one wave of each slice of the KV heads, the workgroups fit the grid and the
+    partials' section, the runs of a masked call their LDS; returns the units of a workgroup over the fewest it could take."""
+    case = (B, H, H_kv, D, max_len, dense, lens, skip)
+    shape = score_shape(B, H, H_kv, D, max_len, dense, WHOLE if skip is None else MASKED)
+    groups = 4 // shape.NU
+    assert shape.lds <= 163840 and shape.lds * (shape.grid // 256) <= 163840, case
+    rows = score_share(B, H, H_kv, D, max_len, dense, lens, skip)
+    wg, wave, b, x, n, base, tiles, uw = rows.T
+    for s in range(B):
+        mine = b == s
+        if skip is not None and skip[s]:
+            assert not mine.any(), case
+            continue
+        ntt = (lens[s] + 31) // 32
+        cnt = int(n[mine][0])
+        assert sorted(set(wg[mine])) == list(range(wg[mine].min(), wg[mine].min() + cnt)), case      # none cut off by the grid
+        assert sorted(set(x[mine])) == list(range(cnt)) and cnt <= 1024, case
+        for u in range(shape.NU):
+            sel = mine & (wave % shape.NU == u)
+            edges = sorted((f, f + t) for f, t in zip(base[sel], tiles[sel]) if t > 0)
+            assert [f for f, _ in edges] == [0] * bool(edges) + [e for _, e in edges[:-1]] and (edges[-1][1] if edges else 0) == ntt, case
+        if skip is not None:
+            runs = -(-ntt // shape.SR)
+            assert max(1, -(-runs // groups)) <= 1024 and uw.max() * groups * H * 8 <= shape.run_stat_bytes, case
+            part = wave[mine] // shape.NU
+            live = tiles[mine] > 0
+            assert (base[mine][live] == ((x[mine] * uw[mine] * groups + part * uw[mine]) * shape.SR)[live]).all(), case
+            assert (tiles[mine] <= uw[mine] * shape.SR).all(), case
+    return int(uw[0]) // (groups if skip is None else 1)
+
+
+_SCORE_HEADS = [(24, 8), (32, 8), (28, 4), (32, 4), (40, 8), (64, 8), (48, 16), (64, 16), (96, 32), (128, 32), (80, 16), (128, 16)]
+
+
+def test_a_shared_score_grid_covers_every_tile_once():
+    rng, seen = random.Random(4), set()
+    for i in range(700):
+        (H, H_kv), D, dense, masked = rng.choice(_SCORE_HEADS), rng.choice([64, 128]), rng.random() < 0.5, rng.random() < 0.5
+        B = rng.choice([2, 3, 5, 8, 16, 33, 63, 64])
+        longest = int(2 ** rng.uniform(6, 19 - np.log2(B) / 2))
+        lens = [rng.choice([rng.randint(0, longest), longest, rng.randint(0, 70), rng.randint(longest // 2, longest)]) for _ in range(B)]
+        lens = [min(n, longest) for n in lens]
+        shape = score_shape(B, H, H_kv, D, longest, dense, MASKED if masked else WHOLE)
+        if shape is None or not shape.shared:
+            continue
+        skip = [int(rng.random() < 0.4) for _ in range(B)] if masked else None
+        if masked and all(skip):
+            skip[0] = 0
+        units = check_share(B, H, H_kv, D, longest, dense, lens, skip)
+        seen.add((masked, shape.NU, units > 1))
+    assert seen == {(m, nu, more) for m in (False, True) for nu in (1, 2, 4) for more in (False, True)}
+
+
+def test_the_runs_of_a_masked_score_grid_are_those_of_a_call_alone():
+    """The bits of a sequence's statistics: one run of SR tiles per wave, as a launch of the sequence by itself has them."""
+    rng, n = random.Random(5), 0
+    for _ in range(3000):
+        (H, H_kv), D, dense = rng.choice(_SCORE_HEADS), rng.choice([64, 128]), rng.random() < 0.5
+        B, longest = rng.randint(2, 64), int(2 ** rng.uniform(8, 19))
+        shape = score_shape(B, H, H_kv, D, longest, dense, MASKED)
+        if shape is None or not shape.shared:
+            continue
+        alone = score_shape(1, H, H_kv, D, longest, dense, WHOLE)
+        assert alone is not None and not alone.shared and alone.RR == shape.SR, (B, H, H_kv, D, longest, dense)
+        assert alone.grid < 1024 and alone.grid * 4 >= -(-((longest + 31) // 32) // alone.RR) * alone.NU      # one run per wave
+        n += 1
+    assert n > 300

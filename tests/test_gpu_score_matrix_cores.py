@@ -79,7 +79,7 @@ def test_the_score_matrix_on_both_sides_of_its_line(gpu, H, H_kv, D, B, max_len,
 
 
 @pytest.mark.parametrize("H,H_kv,D,P,lens,k", [
-    # 513 workgroups of one-tile waves and more: the sequences share the grid
+    # 513 workgroups of one-tile waves and more: the sequences share the grid (but for the three of 64/16, too few)
     (32, 8, 64, 16, [33000, 32700], 200), (24, 8, 128, 1, [0, 21001, 1, 32, 33, 20000, 129], 300), (28, 4, 64, 16, [40000, 7] + [31] * 14, 64),
     (64, 8, 64, 16, [9000, 12, 17000], 100), (64, 16, 64, 16, [4200, 4097, 4000], 64), (32, 8, 64, 16, list(range(1, 1400, 22)), 40),
     # one sequence too many, and one workgroup too few: each sequence has workgroups of its own
@@ -127,3 +127,66 @@ def test_masked_batches_leave_the_statistics_of_each_sequence_alone(gpu, compact
             else:
                 for x, y in zip(got, alone[b]):
                     assert np.array_equal(x[b], y[0], equal_nan=True), (mask, b)
+
+
+# more work than a tile (a run) per wave of the workgroups that the chip holds: one, two and four wave tiles side by side
+_FULL_GRIDS = [(32, 8, 64, [60000, 0, 58123, 33, 41007]), (32, 8, 128, [44000, 45001, 31, 30017]), (28, 4, 128, [52000, 129, 51999, 20000]),
+               (64, 8, 64, [30000, 29333, 1, 27041]), (64, 8, 128, [20021, 19000, 21001]), (128, 16, 64, [14000, 13999, 64, 13500]), (96, 32, 64, [14000, 13500, 12777]),
+               (40, 8, 64, [23000, 22000, 23456])]
+
+
+@pytest.mark.parametrize("H,H_kv,D,lens", _FULL_GRIDS)
+def test_batches_whose_workgroups_take_several_tiles_per_wave(gpu, H, H_kv, D, lens):
+    from rules_util import score_units
+    for dense in (False, True):
+        assert score_units(len(lens), H, H_kv, D, max(lens), dense, lens, None) > 1
+    w = W.make_workload("full", dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=16, B=len(lens), seq_lens=lens, k=150, beta=2.5, planted_per_head=0, seed=H + D)
+    layer, q = make_layer(w, num_initial=4, num_local=61)
+    print("full shared score grid", H, H_kv, D, lens, flush=True)
+    check_compact(w, layer, q, score_scale=1.0, label="full %d/%d" % (H, H_kv))
+
+
+@pytest.mark.parametrize("compact", [False, True], ids=["five-call", "compact"])
+@pytest.mark.parametrize("H,H_kv,D,lens,max_len", [c + (max(c[3]),) for c in _FULL_GRIDS] + [(32, 8, 64, [66000, 65000, 45001], 150000)])   # runs of two tiles
+def test_masked_batches_of_several_units_per_workgroup(gpu, compact, H, H_kv, D, lens, max_len):
+    """The statistics are those of each sequence alone, bit for bit, also where a workgroup forms several units' of them."""
+    from rules_util import MASKED, score_shape, score_units
+    some = [int(b == 1) for b in range(len(lens))]
+    assert score_shape(len(lens), H, H_kv, D, max_len, not compact, MASKED).shared
+    assert score_units(len(lens), H, H_kv, D, max_len, not compact, lens, [0] * len(lens)) > 1
+    for mask, (got, alone) in masked_and_alone(H, H_kv, D, 16, lens, max_len, compact, [[0] * len(lens), some]):
+        for b in range(len(lens)):
+            for x, y in zip(got, alone[b]):
+                assert np.array_equal(x[b], np.full_like(x[b], -7 if x.dtype == np.int32 else -3) if mask[b] else y[0], equal_nan=True), (mask, b)
+
+
+def masked_and_alone(H, H_kv, D, P, lens, max_len, compact, masks):
+    from paper_2411_02886_amd.runtime import DecodeLayer, to_host
+    w = W.make_workload("masked", dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=P, B=len(lens), seq_lens=lens, k=60, beta=2.5, planted_per_head=0, seed=len(lens) + H)
+    layer, q = make_layer(w, max_seq_len=max_len)
+
+    def select(L, q, skip):
+        L.idx.fill_(-7); L.count.fill_(-7); L.row_stats.fill_(-3.0)
+        (L.select_compact if compact else L.select)(q, 1.0, skip)
+        torch.cuda.synchronize()
+        return [to_host(x).copy() for x in (L.row_stats, L.idx, L.count)]
+    alone = []
+    for b in range(len(lens)):
+        one = DecodeLayer(dtype=w.dtype, H=H, H_kv=H_kv, D=D, P=P, k=w.k, k_pool=layer.k_pool, v_pool=layer.v_pool, page_indptr=np.array([0, len(w.pages_of(b))], np.int32),
+                          page_indices=w.pages_of(b) if lens[b] else np.zeros(1, np.int32), seq_lens=[lens[b]], max_seq_len=max_len)
+        alone.append(select(one, q[b:b + 1].contiguous(), None))
+    for mask in masks:
+        print("masked, full grid", H, H_kv, D, mask, flush=True)
+        yield mask, (select(layer, q, torch.tensor(mask, dtype=torch.uint8, device=q.device)), alone)
+
+
+def test_which_batches_share_the_grid():      # no GPU in it, but here stand the lists
+    """The launch forms that the lists above stand for."""
+    from rules_util import MASKED, WHOLE, score_shape
+    for H, H_kv, D, longest, B, shared in [(32, 8, 64, 33000, 2, 1), (24, 8, 128, 21001, 7, 1), (28, 4, 64, 40000, 16, 1), (64, 8, 64, 17000, 3, 1), (64, 16, 64, 4200, 3, 0),
+                                           (32, 8, 64, 1387, 64, 1), (32, 8, 64, 1400, 66, 0), (32, 8, 64, 32768, 2, 0)]:
+        assert score_shape(B, H, H_kv, D, longest, False, WHOLE).shared == shared, (H, H_kv, D, longest, B)
+    for H, H_kv, D, longest, B, dense, shared in [(32, 8, 64, 12100, 8, True, 1), (28, 4, 64, 7000, 11, True, 1), (64, 8, 64, 9000, 6, True, 1), (64, 16, 64, 4200, 4, True, 0),
+                                                  (32, 8, 64, 150000, 4, True, 1), (40, 8, 128, 70000, 3, False, 1), (24, 8, 128, 300000, 2, False, 1), (24, 8, 128, 300000, 2, True, 0)]:
+        assert score_shape(B, H, H_kv, D, longest, dense, MASKED).shared == shared, (H, H_kv, D, longest, B, dense)
+    assert score_shape(3, 40, 8, 128, 70000, True, MASKED) is None                     # the vector kernel
