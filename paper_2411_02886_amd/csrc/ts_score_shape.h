@@ -109,12 +109,16 @@ inline void score_codes_mfma_shape(const ts_problem* p, int G, bool dense, Scan 
   // Beyond one round of a tile per wave two workgroups per CU share the work, at head size 64, with its rows of half the length,
   // three (32 of 1031 to 16001 tokens of 32/8, D 128, 97.6 us, with three per CU 105; D 64, 112 batches of 3 to 32 sequences
   // 1.05 times as fast as in a grid of their own, 1.01 with two per CU; D 128, 56 batches 1.06).  The staged runs are as long as
-  // a wave's tiles can be, while two workgroups' LDS allows.  With a mask the statistics keep the runs found above (of none of
-  // the sequences 1.08, of half of them 1.05 to 1.1 times as fast).
+  // a wave's tiles can be, while two workgroups' LDS allows.  With a mask the statistics keep the runs found above.  Not with a mask for the
+  // score matrix of five to seven heads with several wave tiles side by side: its rows leave in pieces, and several tiles per
+  // workgroup at a time make it worse (us, shared and in a grid of its own: 40/8, D 64, 8 x 40960 tokens, all of them 88 and 76,
+  // half 43.8 and 41.9, one 12.9 and 14.1; 56/8, D 64, 103 and 84, 52 and 46, 16.1 and 15.0; D 128, 8 x 10240, 41.8 and
+  // 38.1, 22.5 and 21.9, 10.7 and 10.1).
   const int groups = 4 / NU;
   const long slots = kScoreFlatWg - p->batch, sr = rr;
   a->SR = rr;
-  bool shares = scan != kScanTested && p->batch >= 2 && p->batch <= kScoreFlatMaxBatch && forced_rr <= 0 && forced_wg <= 0 &&
+  const bool in_pieces = dense && G >= 5 && G <= 7 && NU > 1;
+  bool shares = scan != kScanTested && !(scan == kScanMasked && in_pieces) && p->batch >= 2 && p->batch <= kScoreFlatMaxBatch && forced_rr <= 0 && forced_wg <= 0 &&
                 wgs_of(1) * p->batch > kScoreFlatWg;
   if (shares && scan == kScanMasked) {
     const long units = (p->batch * ((ntt + groups * sr - 1) / (groups * sr)) + slots - 1) / slots;   // of a workgroup, at most

@@ -164,3 +164,13 @@ def test_the_runs_of_a_masked_score_grid_are_those_of_a_call_alone():
         assert alone.grid < 1024 and alone.grid * 4 >= -(-((longest + 31) // 32) // alone.RR) * alone.NU      # one run per wave
         n += 1
     assert n > 300
+
+
+@pytest.mark.parametrize("H,H_kv", [(40, 8), (48, 8), (56, 8), (80, 16), (112, 16)])
+def test_masked_score_matrices_that_leave_in_pieces_do_not_share_the_grid(H, H_kv):
+    """40/8, D 64, 8 x 40960 tokens, all of them: 88 us shared, 76 in a grid of their own; their bytes 58 and 70."""
+    for D in (64, 128):
+        longest = 40960 * 8 * 64 // (H_kv * D)
+        assert not score_shape(8, H, H_kv, D, longest, True, MASKED).shared
+        assert score_shape(8, H, H_kv, D, longest, False, MASKED).shared
+    assert score_shape(8, 28, 4, 128, 10240, True, MASKED).shared and score_shape(8, 64, 8, 64, 20480, True, MASKED).shared
