@@ -497,10 +497,10 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
   uint32_t d0 = MODE != FINAL_LIST ? 0u : a.state[b * 8 + ST_PREFIX0] >> 21, krem0 = MODE != FINAL_LIST ? 0u : a.state[b * 8 + ST_KREM0];
   const int k_eff = SHORT ? min(a.k, N - LO) : (int)a.state[b * 8 + ST_KEFF];
   // What the list's loads can be given before the lengths, the counts and the state are known leaves beside those: of the
-  // candidates the first batch (the section holds a.nblk * kTopkChunk of them), of the chunks their counts.  The clearing
-  // stores below stand behind them: a load waits for the stores before it.  (With the same in the decode attention and its
-  // merge a step of 131072 tokens, H 32/8, k 2048, takes 79.9 us instead of 80.8; 1048576 of 28/4, k 4096, 226.5 instead of
-  // 227.4; this kernel's part 0.3 us.)
+  // candidates the first 1 1/8 k, which are there as a rule (the section holds a.nblk * kTopkChunk; the others follow when their
+  // number is known), of the chunks their counts.  The clearing stores below stand behind them: a load waits for the stores
+  // before it.  (This kernel, compact form, us, before and so: 131072 tokens, H 32/8, k 2048, 5.4 and 5.2; 1048576 of 28/4, k 4096, 7.6 and
+  // 7.3; 32 of 1031 to 16001 7.0 and 6.2.  A whole batch of places loaded early is more than the list: k 4096 7.9; k places 7.5.)
   uint2 e[kFinalPer];
   const uint2* dense = FULL ? a.dense + (size_t)b * a.nblk * kTopkChunk : nullptr;
   auto load_dense = [&](uint32_t p0) {
@@ -512,7 +512,8 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
       e[i + 1] = make_uint2(w.z, w.w);
     }
   };
-  if (FULL) load_dense((uint32_t)tid * kFinalPer);
+  const uint32_t early = (uint32_t)a.k + (uint32_t)a.k / 8;
+  if (FULL && (uint32_t)tid * kFinalPer < early) load_dense((uint32_t)tid * kFinalPer);
   const uint32_t n_first = MODE == FINAL_LIST && tid < a.nblk ? a.blk[(size_t)b * a.nblk + tid] : 0u;
   if (skip_flag != 0) return;
   if (SHORT) {                               // the votes' loads go out first
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(kFinalThreads) void topk_final_kernel(TopkArgs a) {
   auto load_batch = [&](uint32_t base) {
     const uint32_t p0 = base + (uint32_t)tid * kFinalPer;
     if (FULL) {
-      if (base != 0u || !single) load_dense(p0);
+      if (base != 0u || !single || (p0 >= early && p0 < total)) load_dense(p0);
 #pragma unroll
       for (int i = 0; i < kFinalPer; ++i)
         if (p0 + i >= total) e[i] = make_uint2(0u, 0xffffffffu);

@@ -81,3 +81,16 @@ def test_the_histogram_is_left_zeroed(gpu, lens, k):
 def test_one_query_head_per_kv_head(gpu, dtype, H_kv, D):
     """Products by vector instructions: every number of KV heads, four and eight waves."""
     test_votes_of_the_candidates_against_64_bits(gpu, dtype, H_kv, H_kv, D)
+
+
+@pytest.mark.parametrize("k,copies", [(1, 1), (7, 5), (1000, 110), (1000, 126), (1000, 400), (4096, 512), (4096, 2500)])
+def test_candidates_beyond_those_that_are_loaded_early(gpu, k, copies):
+    """The finish asks for k + k / 8 candidates before it knows how many there are: with as many equal votes at the cut there are fewer,
+    just as many, and more."""
+    w = W.make_workload("early", dtype=W.BF16, H=8, H_kv=2, D=64, seq_lens=[9000], k=k, beta=2.5, planted_per_head=20, seed=95)
+    ora = oracle_decode(w, 0)
+    order = np.argsort(-ora["votes"], kind="stable")
+    slots, rows = w.slots_of(0), w.k_pool.reshape(-1, w.H_kv, w.D)
+    rows[slots[order[k - 1:k - 1 + copies]]] = rows[slots[order[k - 1]]]
+    layer, q = make_layer(w)
+    check_compact(w, layer, q, label="early k %d copies %d" % (k, copies))
