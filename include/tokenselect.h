@@ -113,6 +113,12 @@ int32_t ts_workspace_init(void* ws, size_t ws_bytes, void* stream);
  * exp(score_scale * (score - max)) per head) are left in the workspace for ts_soft_vote.
  * q [device] [B][C][H][D]; scores [device] float [B][max_seq_len][H] (rows t >= N_b untouched);
  * score_scale >= 0 (Eq. 5 as printed uses 1).  One kernel launch.
+ * The products are exact and summed in float; the order of the sums, and with it the last bits of a score, is that of the kernel
+ * which is the faster one: by dtype, heads and head_dim, and for bf16 with five to seven query heads per KV head over 8 or 16 KV
+ * heads also by max_seq_len and, without a skip mask, by batch.  (ts_paged_qk_codes: not by the last two.)
+ * A call is therefore not invariant to its batch in the last bits of scores, row_stats and votes, and a tie within them at
+ * the cut of the TopK may fall either way.  With a skip mask, all zeros too, or a cache test it is: every sequence gets
+ * the scores and row_stats of a call with it alone, with the same max_seq_len, bit for bit.
  * Decode only: chunk must be 1 (TS_ERR_UNSUPPORTED otherwise). */
 int32_t ts_paged_qk_scores(const ts_problem* p, const void* q, float* scores, float score_scale,
                            const uint8_t* skip /* [device] [B] or NULL */, void* ws, size_t ws_bytes, void* stream);
@@ -191,7 +197,8 @@ int32_t ts_topk_noalloc(const ts_problem* p, const float* votes, int32_t k, int3
  *                      and score_scale.
  *                      (The last bits of row_stats, here and from ts_soft_vote, depend on how the score pass was split over
  *                      workgroups: on max_seq_len and, for a batch, on whether a skip mask or a cache test was given; without
- *                      either the sequences of a batch share the workgroups, and the other lengths count too.)
+ *                      either the sequences of a batch share the workgroups, and the other lengths count too.  See
+ *                      ts_paged_qk_scores.)
  * ts_topk_exact        The TopK of Eq. 5.  Every token whose upper bound reaches the k-th largest lower bound
  *                      (a superset of the k largest votes; usually 1.1-1.5 k tokens) has its scores recomputed
  *                      from K (exact products, double accumulation: closer to Eq. 5 than the float scores of the score

@@ -66,9 +66,9 @@ __device__ __forceinline__ void find_digit(const uint32_t* gh, uint32_t k_rem, u
 
 // find_digit over a histogram kept as kBoundHistCopies replicas (the vote kernel's flush spreads its atomics
 // over them): the copies are summed on the way in.  Votes are not negative, their keys lie in the upper half of the bins: the
-// lower half is only read where that does not hold k_rem entries.  (Every workgroup reads the copies, 32 KiB instead of 64: 32
-// sequences of 1031 to 16001 tokens, H 32/8, k 2048, a step of 204.4 us takes 203.0; 131072 x 1 80.1 and 79.6, the selection and
-// attention of a chunk's mean query over as many 141.7 and 141.1.)
+// lower half is only read where that does not hold k_rem entries.  (Every workgroup reads the copies, 32 KiB instead of 64:
+// topk_compact_kernel, us, compact form, 1048576 tokens of H 28/4, k 4096, 5.6 and 4.8; 32 sequences of 1031 to 16001, 32/8, k 2048, 6.6 and
+// 5.7, five-call form 6.4 and 5.3; 131072 4.8 and 4.4.  A whole step gains less than two runs of it differ.)
 template <int NB>
 __device__ __forceinline__ void find_digit_rep(const uint32_t* gh, uint32_t k_rem, uint32_t* digit, uint32_t* k_next,
                                                uint32_t* lds /* >= 8 words */) {

@@ -74,8 +74,9 @@ inline bool attn_whole(int dtype, int D, int G, long pairs, int total) {
   return attn_whole_supported(dtype, D, G) && total <= kAttnWhole && pairs <= 256 && (dtype != TS_F32 || G < 8 || pairs >= 64);
 }
 
-// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (what the
-// LDS for their scores allows).  How many candidates there are is known on the device only -- a little more than k when votes
+// Workgroups per sequence that re-evaluate the candidates of the compact selection: two per CU over the batch (what the LDS for the scores of
+// 256 candidates, up to 58 KiB, allows from 29 heads on, and the registers of float rows at head size 128; narrower layers would
+// hold more, but a candidate's chain of loads bounds the kernel and not the work of a CU).  How many candidates there are is known on the device only -- a little more than k when votes
 // are peaked, every token when they are flat, whatever k is -- so the number does not fall with k (k 64 of 1048576 flat
 // votes: 12.9 ms with k / 4 workgroups, 1.7 ms with 512); those that would get fewer than kEvalMinShare candidates leave at once.
 // Large batches: 512 / batch may leave a good part of the round empty; more rounds of smaller shares do not, and a round

@@ -25,13 +25,15 @@ inline bool score_codes_mfma_supported(int dtype, int D, int G, int H_kv) {
 }
 
 // Whether the matrix-core kernel covers a call and is the faster one.
-// Five to seven heads over 8 and 16 KV heads: a wave's piece of a row of the score matrix is 80 to 112 bytes, not whole lines, and from
-// about 100 MB of K on the vector kernel, whose workgroups write whole rows, is the faster one.  Score matrix, us, vector and
-// matrix cores: 40/8, D 128, 40000 tokens (82 MB) 24.0 and 20.4, 2 x 30000 (123 MB) 24.8 and 27.1, 80000 34.4 and 37.9, 300000
-// 115 and 133; 56/8 27.3 and 21.7, 28.3 and 28.7, 37.2 and 40.3, 128 and 138; 80/16, D 64, 40000 (82 MB) 25.5 and 20.3, 80000
-// 38.1 and 40.7.  Eight heads' pieces are lines (64/8, D 128, 300000 138 and 122, D 64 83 and 69), and the compact form's bytes stay
+// Five to seven heads over 8 and 16 KV heads: a wave's piece of a row of the score matrix is 80 to 112 bytes, not whole lines, and the
+// vector kernel, whose workgroups write whole rows, is the faster one for large matrices.  Over 150 shapes the two cross between 104 and
+// 130 MiB of K; the line lies where no shape is slower by it: up to 96 MiB the matrix cores take 0.76 to 0.92 of the vector kernel's time.  us,
+// vector and matrix cores: 40/8, D 128, 49152 tokens (96 MiB) 24.5 and 22.4, 57344 25.4 and 25.1, 81920 35.3 and 37.1; 8 x 7168 (112
+// MiB) 24.6 and 25.7; 56/8 28.1 and 23.9, 28.4 and 26.2, 37.4 and 39.3; 28.2 and 27.1; 80/16, D 64, 49152 (96 MiB) 27.4 and 22.7, 81920
+// 39.0 and 40.1.  Eight heads' pieces are lines (64/8, D 128, 300000 138 and 122, D 64 83 and 69), and the compact form's bytes stay
 // in the L2 (40/8, D 128, 300000 115 and 107; D 64 80 and 57).  With a mask or a test a sequence's scores are those of a call of
-// its own, and so its own length counts.
+// its own, and so its own length counts, however many are scanned: of batches of 100 to 350 MiB together all scanned take 0.83 to 1.17
+// of the vector kernel's time (median 1.01; 40/8, D 64, 2 x 81920, the worst), half of them 0.64 to 1.10, one 0.50 to 0.92.
 inline bool score_takes_matrix_cores(const ts_problem* p, bool dense, Scan scan) {
   const int G = p->num_q_heads / p->num_kv_heads;
   if ((p->num_q_heads % 4) != 0 || !score_codes_mfma_supported(p->dtype, p->head_dim, G, p->num_kv_heads)) return false;

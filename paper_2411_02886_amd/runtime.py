@@ -144,13 +144,15 @@ class DecodeLayer:
     def compact_form_pays(self) -> bool:
         """Which form of the Eq. 5 selection compact=None takes: compact, which never writes the fp32 score matrix, where the
         matrices of the batch are larger than 24 MiB together, and for one sequence of up to 32 heads from 20 MiB on (us on MI355X,
-        five-call, five-call with the ranked vote, compact, k 2048 but for the last: 32 heads over 8, head size 128, 18 MiB 96, 93,
-        102; 19.5 MiB 103, 100, 104; 20 MiB 113, 110, 108; 23 MiB 120, 116, 111; 32 over 4, 18 MiB 72, 69, 71; 20 MiB 79, 77, 73;
-        12 over 2, 18 MiB 83, 79, 85; 20 MiB 89, 85, 87; 64 over 8, 17 MiB 76, 75, 82; 23.9 MiB 81, 80, 85; 40 over 8, k 1024, 20 MiB
-        91, 89, 95; 23.9 MiB 102, 100, 100; float rows, 32 over 8, 20 MiB 164, 159, 153).  Above 24 MiB the line does not follow the faster form of each shape: the compact form
+        five-call, five-call with the ranked vote, compact, k 2048 but for the last: 32 heads over 8, head size 128, 18 MiB 95, 92,
+        95; 19.5 MiB 102, 99, 97; 20 MiB 107, 104, 97; 23 MiB 112, 109, 103; 32 over 4, 18 MiB 71, 68, 70; 20 MiB 77, 73, 71;
+        12 over 2, 18 MiB 82, 77, 83; 20 MiB 89, 84, 85; 64 over 8, 17 MiB 68, 68, 72; 23.9 MiB 83, 82, 77; 40 over 8, k 1024, 16 MiB
+        84, 81, 76; 20 MiB 89, 87, 80; 23.9 MiB 100, 98, 95; float rows, 32 over 8, 20 MiB 155, 152, 151).  The line was laid when the
+        compact form was slower; up to 7 % is left just below it (40 over 8, 28 over 4), and it stays because the votes that rank a call
+        change with the form.  Above 24 MiB it does not follow the faster form of each shape either: the compact form
         ranks the candidates by votes of double-precision products, the five-call form by votes of float scores, and no call is to
-        lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k 2048: 206.5 five-call, 221.8
-        compact).  A caller who prefers the time passes compact=False."""
+        lose the closer ones to a few per cent of time (32 sequences of up to 16001 tokens, k 2048: 197 five-call, 200
+        compact; 64 over 8, 32 of 4000 to 8180: 169 and 193).  A caller who prefers the time passes compact=False."""
         mib = self.B * self.max_seq_len * self.H * 4 / 2**20
         return mib > 24 or (self.B == 1 and self.H <= 32 and mib > 19.75)
 
