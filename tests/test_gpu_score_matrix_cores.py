@@ -191,3 +191,24 @@ def test_which_batches_share_the_grid():      # no GPU in it, but here stand the
                                                   (32, 8, 64, 150000, 4, True, 1), (40, 8, 128, 70000, 3, False, 1), (24, 8, 128, 300000, 2, False, 1), (24, 8, 128, 300000, 2, True, 0)]:
         assert score_shape(B, H, H_kv, D, longest, dense, MASKED).shared == shared, (H, H_kv, D, longest, B, dense)
     assert score_shape(3, 40, 8, 128, 70000, True, MASKED) is None                     # the vector kernel
+
+
+@pytest.mark.parametrize("compact", [False, True], ids=["five-call", "compact"])
+@pytest.mark.parametrize("H,H_kv,D,lens,max_len", [(40, 8, 128, [15000, 14001, 65], 30000), (56, 8, 64, [15000, 33, 9001], 99000), (32, 8, 64, [40000, 39001, 1], 40000),
+                                                   (128, 16, 64, [3000, 2999], 20000)])
+def test_the_cache_test_leaves_the_statistics_of_each_sequence_alone(gpu, compact, H, H_kv, D, lens, max_len):
+    """All sequences miss: what the checked call and the vote leave are those of each sequence alone, bit for bit (both sides of the
+    line between the kernels)."""
+    from paper_2411_02886_amd.runtime import DecodeLayer, to_host
+    w = W.make_workload("tested", dtype=W.BF16, H=H, H_kv=H_kv, D=D, P=16, B=len(lens), seq_lens=lens, k=60, beta=2.5, planted_per_head=0, seed=H)
+    layer, q = make_layer(w, max_seq_len=max_len)
+    layer.first.fill_(1)
+    (layer.select_compact if compact else layer.select)(q, 1.0, check_theta=0.9)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        one = DecodeLayer(dtype=w.dtype, H=H, H_kv=H_kv, D=D, P=16, k=w.k, k_pool=layer.k_pool, v_pool=layer.v_pool, page_indptr=np.array([0, len(w.pages_of(b))], np.int32),
+                          page_indices=w.pages_of(b), seq_lens=[n], max_seq_len=max_len)
+        (one.select_compact if compact else one.select)(q[b:b + 1].contiguous(), 1.0)
+        torch.cuda.synchronize()
+        for x, y in ((layer.row_stats, one.row_stats), (layer.idx, one.idx), (layer.count, one.count)) + (() if compact else ((layer.scores[:, :n], one.scores[:, :n]),)):
+            assert np.array_equal(to_host(x)[b], to_host(y)[0]), b
